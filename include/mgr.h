@@ -20,9 +20,10 @@
  *    coarse nodes.  The full decomposition stops when the shortest level grid
  *    has 3 nodes (L = min_d ceil(log2(n_d - 1)) - 1), and 0..L+1 level steps
  *    are accepted.  A node's class is L minus the finest level k <= L whose
- *    grid holds it in every dimension.  These shapes run per-stage kernels
- *    (no per-plane addressing limit); the other entry points refuse them with
- *    MGR_ERR_SHAPE.
+ *    grid holds it in every dimension.  (4-D shapes and planes of 2 GiB or
+ *    more run per-stage kernels without the per-plane addressing limit, the
+ *    others the fused kernels of the 2^k + 1 grids.)  The other entry points
+ *    refuse these shapes with MGR_ERR_SHAPE.
  *  - `coords` describes node positions (nonuniform structured grids,
  *    Sec. II-A): NULL, or coords[d] == NULL, means uniform spacing along d;
  *    otherwise coords[d] is a HOST array of shape[d] strictly increasing

@@ -1,4 +1,7 @@
-// General tensor grids: 1 to 4 dimensions of any size >= 3 per dimension.
+// General tensor grids: 1 to 4 dimensions of any size >= 3 per dimension, one
+// stage per kernel.  Runs the 4-D shapes and those past the fused kernels'
+// 32-bit offsets; other any-length grids of 1 to 3 dimensions run the fused
+// kernels (View3 in mgr_internal.h).
 //
 // The paper's grids have 2^k + 1 nodes per dimension; for other sizes the
 // nested level grids keep, along each dimension, the nodes at multiples of

@@ -12,9 +12,22 @@ namespace mgr {
 // Strided 3-D view: element (j0, j1, j2) lives at j0*s[0] + j1*s[1] + j2*s[2].
 // Problems of fewer dimensions are padded with leading size-1 dimensions
 // that never coarsen ("inactive").
+//
+// Level grids of any length.  A level grid of m nodes keeps its even
+// positions and its last one as coarse nodes, so an even m has no fine node
+// in its last interval.  The fused kernels see such a dimension as one of
+// m + 1 nodes, always odd: a phantom fine node (index m - 1, a null node: it
+// reads zero, has zero weights, is never stored) before the last node, which
+// is then an even index like every other coarse node.  n counts these nodes
+// (2 mc - 1 for mc coarse nodes); the offset of index j along d is
+// min(j s[d], last[d]), which puts the last node of a strided level grid
+// (not at a multiple of the stride unless the size is 2^k + 1) and of a
+// packed one in place.  For 2^k + 1 sizes last[d] = (n[d] - 1) s[d] and there
+// are no phantoms, so kernels compiled without kGen ignore both.
 struct View3 {
     int64_t n[3];
     int64_t s[3];
+    int64_t last[3];
 };
 
 // Per-dimension device tables of one level step, in the working precision.
@@ -54,6 +67,8 @@ struct StreamArgs {
     View3 fv;
     DimTables<T> tb;
     int write_coarse;  // also write u at coarse positions of C
+    int gen;           // any-length level grid: offsets through View3::last, phantoms
+    int ph[3];         // index of the phantom node of A (and C) along each dimension, or -1
     int chunk, nt1, nt2, nch;  // filled in by the launcher
 };
 
@@ -117,6 +132,7 @@ constexpr int kTailTabElems = 3200;
 template <typename T>
 struct TailLevel {
     int m[3], mc[3];  // level grid and coarse sizes (1 for inactive dims)
+    int act[3], ph[3];  // any-length level grids: nodes without the phantom, its index (or -1)
     DimTables<T> tb;  // interpolation weights and stencils
     const T* lf[3];   // plain Thomas factors of M_{l-1}: multipliers,
     const T* ip[3];   // inverse pivots
@@ -129,6 +145,8 @@ struct TailArgs {
     TailLevel<T> lv[kMaxTail];  // index k - k0
     int k0, nlev;
     int64_t st[3];  // element strides of the user arrays
+    int64_t last[3];  // offset of their last node along each dimension
+    int gen;          // any-length level grids (View3)
     const T* src;   // user input
     T* dst;         // user output
     const T* Z0;    // decomposition: correction added to the level-k0 input (or null)
@@ -380,9 +398,12 @@ enum KernelClass {
     KC_COUNT
 };
 
+// ph: the phantom index per dimension of an any-length level grid, or null.
 template <typename T>
 hipError_t launch_coef_decompose(const T* A, View3 av, T* C, View3 cv, T* W, View3 wv,
-                                 DimTables<T> tb, hipStream_t st);
+                                 DimTables<T> tb, const int* ph, hipStream_t st);
+// Offsets of either view through View3::last, so a strided level grid of any
+// length is copied whole.
 template <typename T>
 hipError_t launch_copy_view(const T* X, const T* Z, View3 xv, T* Y, View3 yv, hipStream_t st);
 

@@ -25,6 +25,12 @@ __device__ __forceinline__ int64_t at(const View3& v, int64_t j0, int64_t j1, in
     return j0 * v.s[0] + j1 * v.s[1] + j2 * v.s[2];
 }
 
+// The same through View3::last (level grids of any length).
+__device__ __forceinline__ int64_t at_last(const View3& v, int64_t j0, int64_t j1, int64_t j2)
+{
+    return min(j0 * v.s[0], v.last[0]) + min(j1 * v.s[1], v.last[1]) + min(j2 * v.s[2], v.last[2]);
+}
+
 inline unsigned grid_for(int64_t total)
 {
     int64_t b = (total + kBlock - 1) / kBlock;
@@ -64,10 +70,11 @@ __device__ __forceinline__ void corners(const int64_t* j, const DimTables<T>& tb
 // Multilinear interpolation from the coarse corners, evaluated separably
 // (along dim 2, then 1, then 0).  `half` maps level-grid corner indices to
 // a packed coarse array (index / 2) when set.
-template <typename T, bool kHalf>
+template <typename T, bool kHalf, bool kGen = false>
 __device__ __forceinline__ T interp_corners(const T* __restrict__ A, const View3& av,
                                             const Corners<T>& c)
 {
+    auto pos = [&](int64_t x, int64_t y, int64_t z) { return kGen ? at_last(av, x, y, z) : at(av, x, y, z); };
     T r0[2];
 #pragma unroll
     for (int a = 0; a < 2; a++) {
@@ -78,8 +85,8 @@ __device__ __forceinline__ T interp_corners(const T* __restrict__ A, const View3
             int64_t i1 = b ? c.hi[1] : c.lo[1];
             int64_t l2 = c.lo[2], h2 = c.hi[2];
             int64_t q0 = kHalf ? i0 >> 1 : i0, q1 = kHalf ? i1 >> 1 : i1;
-            T vlo = A[at(av, q0, q1, kHalf ? l2 >> 1 : l2)];
-            T vhi = (h2 != l2) ? A[at(av, q0, q1, kHalf ? h2 >> 1 : h2)] : T(0);
+            T vlo = A[pos(q0, q1, kHalf ? l2 >> 1 : l2)];
+            T vhi = (h2 != l2) ? A[pos(q0, q1, kHalf ? h2 >> 1 : h2)] : T(0);
             r1[b] = lerp2(c.wl[2], vlo, c.wh[2], vhi);
             if (c.hi[1] == c.lo[1]) { r1[1] = T(0); break; }
         }
@@ -91,23 +98,28 @@ __device__ __forceinline__ T interp_corners(const T* __restrict__ A, const View3
 
 // Coefficients (Sec. II-A.1) of one level step: c(p) = u(p) - Pi u(p) at
 // fine-only nodes, written to C; coarse values copied packed to W.
-template <typename T>
+struct Phantoms {
+    int64_t j[3];
+};
+template <typename T, bool kGen>
 __global__ void __launch_bounds__(kBlock)
 k_coef_decompose(const T* A, View3 av, T* C, View3 cv,  // A and C may alias (in place)
-                 T* __restrict__ W, View3 wv, DimTables<T> tb, int64_t total)
+                 T* __restrict__ W, View3 wv, DimTables<T> tb, Phantoms ph, int64_t total)
 {
     for (int64_t idx = (int64_t)blockIdx.x * kBlock + threadIdx.x; idx < total;
          idx += (int64_t)gridDim.x * kBlock) {
         int64_t j[3];
         decode3(idx, av.n, j);
-        T u = A[at(av, j[0], j[1], j[2])];
+        if (kGen && (j[0] == ph.j[0] || j[1] == ph.j[1] || j[2] == ph.j[2])) continue;
+        T u = A[kGen ? at_last(av, j[0], j[1], j[2]) : at(av, j[0], j[1], j[2])];
         if (((j[0] | j[1] | j[2]) & 1) == 0) {
             W[at(wv, j[0] >> 1, j[1] >> 1, j[2] >> 1)] = u;
             continue;
         }
         Corners<T> c;
         corners(j, tb, c);
-        C[at(cv, j[0], j[1], j[2])] = u - interp_corners<T, false>(A, av, c);
+        C[kGen ? at_last(cv, j[0], j[1], j[2]) : at(cv, j[0], j[1], j[2])] =
+            u - interp_corners<T, false, kGen>(A, av, c);
     }
 }
 
@@ -122,8 +134,8 @@ k_copy_view(const T* __restrict__ X, const T* __restrict__ Z, View3 xv, T* __res
          idx += (int64_t)gridDim.x * kBlock) {
         int64_t j[3];
         decode3(idx, yv.n, j);
-        const int64_t xo = at(xv, j[0], j[1], j[2]);
-        Y[at(yv, j[0], j[1], j[2])] = Z ? X[xo] + Z[xo] : X[xo];
+        const int64_t xo = at_last(xv, j[0], j[1], j[2]);
+        Y[at_last(yv, j[0], j[1], j[2])] = Z ? X[xo] + Z[xo] : X[xo];
     }
 }
 
@@ -155,11 +167,17 @@ inline int64_t vol(const View3& v) { return v.n[0] * v.n[1] * v.n[2]; }
 
 template <typename T>
 hipError_t launch_coef_decompose(const T* A, View3 av, T* C, View3 cv, T* W, View3 wv,
-                                 DimTables<T> tb, hipStream_t st)
+                                 DimTables<T> tb, const int* ph, hipStream_t st)
 {
     int64_t total = vol(av);
-    hipLaunchKernelGGL(k_coef_decompose<T>, dim3(grid_for(total)), dim3(kBlock), 0, st, A, av,
-                       C, cv, W, wv, tb, total);
+    Phantoms p{{-1, -1, -1}};
+    for (int d = 0; ph && d < 3; d++) p.j[d] = ph[d];
+    if (ph)
+        hipLaunchKernelGGL((k_coef_decompose<T, true>), dim3(grid_for(total)), dim3(kBlock), 0, st, A, av, C, cv, W, wv,
+                           tb, p, total);
+    else
+        hipLaunchKernelGGL((k_coef_decompose<T, false>), dim3(grid_for(total)), dim3(kBlock), 0, st, A, av, C, cv, W, wv,
+                           tb, p, total);
     return hipGetLastError();
 }
 
@@ -190,7 +208,7 @@ hipError_t launch_bench_copy(const void* src, void* dst, size_t nbytes, hipStrea
 
 #define MGR_INSTANTIATE(T)                                                                      \
     template hipError_t launch_coef_decompose<T>(const T*, View3, T*, View3, T*, View3,         \
-                                                 DimTables<T>, hipStream_t);                    \
+                                                 DimTables<T>, const int*, hipStream_t);        \
     template hipError_t launch_copy_view<T>(const T*, const T*, View3, T*, View3, hipStream_t);      \
     template hipError_t launch_add_split<T>(const T*, View3, const T*, T*, T*, hipStream_t);
 

@@ -36,7 +36,8 @@ struct ReconGeom {
     static_assert(64 * CW == 2 * kT2, "one lane per fine column");
 };
 
-template <typename T, bool kAct0, bool kAct1>
+// kGen: level grids of any length (View3: clamped offsets, phantom nodes).
+template <typename T, bool kAct0, bool kAct1, bool kGen>
 __global__ void __launch_bounds__(kThreads) k_stream_recon(StreamArgs<T> a)
 {
     using G = ReconGeom<kAct1>;
@@ -72,8 +73,9 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon(StreamArgs<T> a)
     // ---- this lane's fine column and the wave's fine rows
     const int c = (wave % G::CW) * 64 + lane;
     const int gc = 2 * I2 + c;
-    const bool cin = gc < m2;
+    const bool cin = gc < m2 && (!kGen || gc != a.ph[2]);
     const bool ceven = !(c & 1);
+    auto clamped = [](int off, int64_t last) { return kGen ? min(off, (int)last) : off; };
     const int ucl = c >> 1, ucr = (c >> 1) + (c & 1);  // coarse tile columns
     T wcl = T(1), wch = T(0);
     if (cin && (c & 1)) {
@@ -84,6 +86,7 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon(StreamArgs<T> a)
     const int as1 = (int)a.av.s[1], as2 = (int)a.av.s[2];
     const int cs1 = (int)a.cv.s[1], cs2 = (int)a.cv.s[2];
     const int R0 = kAct1 ? 2 * I1 : 0;
+    const int rbA = clamped(R0 * as1, a.av.last[1]), rbC = clamped(R0 * cs1, a.cv.last[1]);
     // byte offsets from the tile's first fine row; coarse positions of even
     // planes (vAe) and everything outside the grid read zero
     unsigned vAe[NRW], vAo[NRW], vC[NRW];
@@ -91,17 +94,23 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon(StreamArgs<T> a)
 #pragma unroll
     for (int k = 0; k < NRW; k++) {
         const int r = rg + RW * k, gr = R0 + r;
-        const bool in = cin && gr < m1;
-        const unsigned oa = (unsigned)((gr - R0) * as1 + gc * as2) * S;
+        const bool in = cin && gr < m1 && (!kGen || !kAct1 || gr != a.ph[1]);
+        const unsigned oa =
+            (unsigned)(clamped(gr * as1, a.av.last[1]) - rbA + clamped(gc * as2, a.av.last[2])) * S;
         vAo[k] = in ? oa : kOut;
         vAe[k] = (in && !((r & 1) == 0 && ceven)) ? oa : kOut;
-        vC[k] = in ? (unsigned)((gr - R0) * cs1 + gc * cs2) * S : kOut;
+        vC[k] = in ? (unsigned)(clamped(gr * cs1, a.cv.last[1]) - rbC + clamped(gc * cs2, a.cv.last[2])) * S
+                   : kOut;
         const bool rodd = kAct1 && (r & 1) && gr < m1;
         wrl[k] = rodd ? uni(a.tb.w[1][2 * gr]) : T(1);
         wrh[k] = rodd ? uni(a.tb.w[1][2 * gr + 1]) : T(0);
     }
-    const unsigned spanA = (unsigned)((min(R0 + G::FR, m1) - R0 - 1) * as1 + m2 * as2) * S;
-    const unsigned spanC = (unsigned)((min(R0 + G::FR, m1) - R0 - 1) * cs1 + m2 * cs2) * S;
+    const unsigned spanA =
+        (unsigned)(clamped((min(R0 + G::FR, m1) - 1) * as1, a.av.last[1]) - rbA +
+                   (kGen ? (int)a.av.last[2] + 1 : m2 * as2)) * S;
+    const unsigned spanC =
+        (unsigned)(clamped((min(R0 + G::FR, m1) - 1) * cs1, a.cv.last[1]) - rbC +
+                   (kGen ? (int)a.cv.last[2] + 1 : m2 * cs2)) * S;
     // coarse tile slots: (I1 + idx / CC, I2 + idx % CC)
     const int ws1 = (int)a.wv.s[1], ws2 = (int)a.wv.s[2];
     unsigned vW[NCT];
@@ -116,6 +125,10 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon(StreamArgs<T> a)
 
     const unsigned as0 = (unsigned)a.av.s[0], cs0 = (unsigned)a.cv.s[0], ws0 = (unsigned)a.wv.s[0];
     auto mul64 = [](int i, unsigned st) { return (int64_t)((uint64_t)(unsigned)i * st); };
+    auto plane_off = [&](int i, unsigned st, int64_t last) {
+        const int64_t o = mul64(i, st);
+        return kGen ? min(o, last) : o;
+    };
     const int64_t wrow = (int64_t)I1 * ws1;
     auto load_tile = [&](int ac, T (&w)[NCT], T (&z)[NCT]) {
         const int64_t o = mul64(ac, ws0) + wrow;
@@ -129,13 +142,15 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon(StreamArgs<T> a)
     };
     // fine plane f, clamped into [0, m0), of the coefficients
     auto load_fine = [&](int f, bool even, T (&v)[NRW]) {
-        const __amdgpu_buffer_rsrc_t r =
-            make_rsrc(a.A + mul64(max(min(f, m0 - 1), 0), as0) + (int64_t)R0 * as1, spanA);
+        const __amdgpu_buffer_rsrc_t r = make_rsrc(
+            a.A + plane_off(max(min(f, m0 - 1), 0), as0, a.av.last[0]) + rbA, spanA);
 #pragma unroll
         for (int k = 0; k < NRW; k++) v[k] = buf_load<T>(r, even ? vAe[k] : vAo[k]);
     };
     auto store_fine = [&](int f, bool own, const T (&v)[NRW]) {
-        const __amdgpu_buffer_rsrc_t r = make_rsrc(a.C + mul64(f, cs0) + (int64_t)R0 * cs1, own ? spanC : 0u);
+        const bool st = own && (!kGen || !kAct0 || f != a.ph[0]);
+        const __amdgpu_buffer_rsrc_t r =
+            make_rsrc(a.C + plane_off(f, cs0, a.cv.last[0]) + rbC, st ? spanC : 0u);
 #pragma unroll
         for (int k = 0; k < NRW; k++) buf_store(v[k], r, vC[k]);
     };
@@ -216,7 +231,7 @@ struct AlignedRecon {
     static constexpr int NCT = (CR * CC + kThreads - 1) / kThreads;
 };
 
-template <typename T, bool kAct0>
+template <typename T, bool kAct0, bool kGen>
 __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
 {
     using G = AlignedRecon<T>;
@@ -240,7 +255,7 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
     const int P0 = ch * a.chunk, P1 = min(P0 + a.chunk, c0);
     const int A1 = min(P1, c0 - 1);
     const int R0 = 2 * I1, C0 = 2 * I2;
-    const bool first = t2 == 0, last = t2 == nt2 - 1;
+    const bool first = t2 == 0;
 
     // dim-0 and column weights, staged once the first loads are issued
     auto stage_tables = [&] {
@@ -296,23 +311,32 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
     // Element offset of C's column C0 in row gr of plane f, modulo a line.
     const unsigned cs0 = (unsigned)a.cv.s[0], cs1 = (unsigned)a.cv.s[1];
     const unsigned cbase = (unsigned)(((uintptr_t)a.C / S) & (LE - 1));
+    const unsigned lA1 = (unsigned)a.av.last[1], lA2 = (unsigned)a.av.last[2];
+    const unsigned lC1 = (unsigned)a.cv.last[1], lC2 = (unsigned)a.cv.last[2];
+    auto clamped = [](unsigned off, unsigned last) { return kGen ? min(off, last) : off; };
+    auto plane_off = [&](int i, unsigned st, int64_t last) {
+        const int64_t o = mul64(i, st);
+        return kGen ? min(o, last) : o;
+    };
     auto col_of = [&](int f, int gr, bool& ok) {
-        const int sh = (int)((cbase + (unsigned)f * cs0 + (unsigned)gr * cs1 + (unsigned)C0) & (unsigned)(LE - 1));
+        // (modulo 2^32, hence modulo a line)
+        const unsigned po = kGen ? (unsigned)plane_off(f, cs0, a.cv.last[0]) : (unsigned)f * cs0;
+        const int sh = (int)((cbase + po + clamped((unsigned)gr * cs1, lC1) + (unsigned)C0) & (unsigned)(LE - 1));
         const int olo = first ? 0 : -sh;
-        const int ohi = last ? m2 - C0 : TW - sh;
+        const int ohi = min(m2 - C0, TW - sh);  // the last tile ends with the row
         const int x = olo + lane;
-        ok = x < ohi && gr < m1;
+        ok = x < ohi && gr < m1 && (!kGen || (gr != a.ph[1] && C0 + x != a.ph[2]));
         return x;
     };
     const unsigned as0 = (unsigned)a.av.s[0], as1 = (unsigned)a.av.s[1], as2 = (unsigned)a.av.s[2];
-    const unsigned spanA = (unsigned)((m1 - 1) * as1 + (m2 - 1) * as2 + 1) * S;
-    const unsigned spanC = (unsigned)((m1 - 1) * cs1 + (m2 - 1) + 1) * S;
+    const unsigned spanA = (clamped((unsigned)(m1 - 1) * as1, lA1) + clamped((unsigned)(m2 - 1) * as2, lA2) + 1) * S;
+    const unsigned spanC = (clamped((unsigned)(m1 - 1) * cs1, lC1) + clamped((unsigned)(m2 - 1), lC2) + 1) * S;
     // coefficients of fine plane f (clamped into the grid) at this lane's
     // nodes; coarse positions of even planes and columns the tile does not
     // own read zero
     auto load_fine = [&](int f, T (&v)[NRW]) {
         f = max(min(f, m0 - 1), 0);
-        const __amdgpu_buffer_rsrc_t r = make_rsrc(a.A + mul64(f, as0), spanA);
+        const __amdgpu_buffer_rsrc_t r = make_rsrc(a.A + plane_off(f, as0, a.av.last[0]), spanA);
 #pragma unroll
         for (int k = 0; k < NRW; k++) {
             const int gr = R0 + rg + 4 * k;
@@ -320,7 +344,8 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
             const int x = col_of(f, gr, ok);
             const int gc = C0 + x;
             const bool coarse = !(f & 1) && !(gr & 1) && !(gc & 1);
-            v[k] = buf_load<T>(r, (ok && !coarse) ? (unsigned)gr * as1 * S + (unsigned)gc * as2 * S : kOut);
+            v[k] = buf_load<T>(r, (ok && !coarse) ? (clamped((unsigned)gr * as1, lA1) + clamped((unsigned)gc * as2, lA2)) * S
+                                                  : kOut);
         }
     };
     // 2-D prolongation of the corrected coarse tile b at (row r, column gc)
@@ -341,7 +366,7 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
         bool ok;
         const int x = col_of(f, gr, ok);
         // the user's output, in whole lines, read by nothing after
-        buf_store_nt(v, r, ok ? ((unsigned)gr * cs1 + (unsigned)(C0 + x)) * S : kOut);
+        buf_store_nt(v, r, ok ? (clamped((unsigned)gr * cs1, lC1) + clamped((unsigned)(C0 + x), lC2)) * S : kOut);
     };
 
     T pW[NCT], pZ[NCT], fo[NRW], fe[NRW];
@@ -363,7 +388,8 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
             // fine plane 2ac - 1 between the prolongations of ac - 1 and ac
             const int f = 2 * ac - 1;
             const T wl = sW0[2 * (2 * (ac - P0) - 1)], wh = sW0[2 * (2 * (ac - P0) - 1) + 1];
-            const __amdgpu_buffer_rsrc_t r = make_rsrc(a.C + mul64(f, cs0), spanC);
+            const unsigned sp = (kGen && f == a.ph[0]) ? 0u : spanC;
+            const __amdgpu_buffer_rsrc_t r = make_rsrc(a.C + plane_off(f, cs0, a.cv.last[0]), sp);
 #pragma unroll
             for (int k = 0; k < NRW; k++) {
                 bool ok;
@@ -375,7 +401,7 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
         {
             // fine plane 2ac (coarse positions read 0 from the coefficients)
             const int f = 2 * ac;
-            const __amdgpu_buffer_rsrc_t r = make_rsrc(a.C + mul64(f, cs0), ac < P1 ? spanC : 0u);
+            const __amdgpu_buffer_rsrc_t r = make_rsrc(a.C + plane_off(f, cs0, a.cv.last[0]), ac < P1 ? spanC : 0u);
 #pragma unroll
             for (int k = 0; k < NRW; k++) {
                 bool ok;
@@ -389,7 +415,7 @@ __global__ void __launch_bounds__(kThreads) k_stream_recon_al(StreamArgs<T> a)
     }
 }
 
-template <typename T, bool kAct0, bool kAct1>
+template <typename T, bool kAct0, bool kAct1, bool kGen>
 hipError_t launch_recon_cfg(StreamArgs<T> a, hipStream_t st)
 {
     using G = ReconGeom<kAct1>;
@@ -397,7 +423,7 @@ hipError_t launch_recon_cfg(StreamArgs<T> a, hipStream_t st)
     a.nt1 = kAct1 ? (c1 + G::kT1 - 1) / G::kT1 : 1;
     a.nt2 = (c2 + G::kT2 - 1) / G::kT2;
     const int tiles = a.nt1 * a.nt2;
-    auto kern = k_stream_recon<T, kAct0, kAct1>;
+    auto kern = k_stream_recon<T, kAct0, kAct1, kGen>;
     int chunk = c0;
     if (kAct0) {
         static int occ = 0;
@@ -412,14 +438,16 @@ hipError_t launch_recon_cfg(StreamArgs<T> a, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T>
+template <typename T, bool kGen>
 hipError_t launch_recon_al(StreamArgs<T> a, hipStream_t st)
 {
     using G = AlignedRecon<T>;
     const int c0 = (int)a.wv.n[0], c1 = (int)a.wv.n[1];
     const int m2 = (int)a.av.n[2];
     a.nt1 = (c1 + G::kT1 - 1) / G::kT1;
-    a.nt2 = (m2 + G::TW - 1) / G::TW;
+    // a tile's range starts up to LE - 1 columns before its nominal one, so
+    // with this count the last tile of a row never owns more than its 64 lanes
+    a.nt2 = (m2 + G::LE - 1 + G::TW - 1) / G::TW;
     const int tiles = a.nt1 * a.nt2;
     // Chunks of at most 8 coarse planes: on large grids that is several
     // rounds of workgroups, and the tiles of a plane region then stream it
@@ -427,27 +455,25 @@ hipError_t launch_recon_al(StreamArgs<T> a, hipStream_t st)
     // memory (measured: 8 planes per chunk ran 12% faster than one long
     // round); small grids keep the one-round split, whose chunks are shorter.
     static int occ = 0;
-    const int slots = resident_per_cu(k_stream_recon_al<T, true>, occ) * device_cu_count();
+    const int slots = resident_per_cu(k_stream_recon_al<T, true, kGen>, occ) * device_cu_count();
     const int nch = std::max(1, slots / tiles);
     const int chunk = std::min(std::max((c0 + nch - 1) / nch, 2), 8);
     a.chunk = chunk;
     a.nch = (c0 + chunk - 1) / chunk;
-    hipLaunchKernelGGL((k_stream_recon_al<T, true>), dim3((unsigned)(tiles * a.nch)), dim3(kThreads), 0, st, a);
+    hipLaunchKernelGGL((k_stream_recon_al<T, true, kGen>), dim3((unsigned)(tiles * a.nch)), dim3(kThreads), 0, st, a);
     return hipGetLastError();
 }
 
 // The line-aligned form takes 3-D grids whose coefficients and output both
 // have unit column stride (the finest level step: on coarser steps the
-// coefficients are strided and the per-lane kernel measured faster) and rows
-// short enough that the last tile of a row owns at most 64 columns
-// (m2 = 64 q + 1, or m2 <= 33), with offsets below 2^31 bytes.
+// coefficients are strided and the per-lane kernel measured faster), with
+// offsets below 2^31 bytes.
 template <typename T>
 bool recon_al_ok(const StreamArgs<T>& a)
 {
     if (a.av.n[0] < 2 || a.av.n[1] < 2 || a.av.s[2] != 1 || a.cv.s[2] != 1 || ((uintptr_t)a.C % sizeof(T)) != 0)
         return false;
     const int64_t m2 = a.av.n[2];
-    if (!((m2 - 1) % 64 == 0 || m2 <= 33)) return false;
     const int64_t span = std::max((a.av.n[1] - 1) * a.av.s[1] + (m2 - 1) * a.av.s[2] + 1,
                                   (a.cv.n[1] - 1) * a.cv.s[1] + m2);
     return span * (int64_t)sizeof(T) < ((int64_t)1 << 31);
@@ -458,11 +484,11 @@ bool recon_al_ok(const StreamArgs<T>& a)
 template <typename T>
 hipError_t launch_stream_recon(StreamArgs<T> a, hipStream_t st)
 {
-    if (recon_al_ok(a)) return launch_recon_al(a, st);
+    if (recon_al_ok(a)) return a.gen ? launch_recon_al<T, true>(a, st) : launch_recon_al<T, false>(a, st);
     const bool act0 = a.av.n[0] > 1, act1 = a.av.n[1] > 1;
-    if (act0 && act1) return launch_recon_cfg<T, true, true>(a, st);
-    if (act0) return launch_recon_cfg<T, true, false>(a, st);
-    if (!act1) return launch_recon_cfg<T, false, false>(a, st);
+    if (act0 && act1) return a.gen ? launch_recon_cfg<T, true, true, true>(a, st) : launch_recon_cfg<T, true, true, false>(a, st);
+    if (act0) return a.gen ? launch_recon_cfg<T, true, false, true>(a, st) : launch_recon_cfg<T, true, false, false>(a, st);
+    if (!act1) return a.gen ? launch_recon_cfg<T, false, false, true>(a, st) : launch_recon_cfg<T, false, false, false>(a, st);
     return hipErrorInvalidValue;
 }
 

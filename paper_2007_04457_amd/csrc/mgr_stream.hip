@@ -32,17 +32,17 @@
 namespace mgr {
 namespace {
 
-template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU>
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(stream_min_waves<T, kDec, kZ>(), 8)))
 k_stream_level(StreamArgs<T> a)
 {
     __shared__ LevelSmem<T, kAct0, kAct1, kDec> sm;
-    stream_level_tile<T, kAct0, kAct1, kDec, kZ, kU>(a, remap_xcd((int)blockIdx.x, (int)gridDim.x), sm);
+    stream_level_tile<T, kAct0, kAct1, kDec, kZ, kU, wide_tile<T, kDec>(), kGen>(a, remap_xcd((int)blockIdx.x, (int)gridDim.x), sm);
 }
 
 // Tiles and plane chunks of one level step (filled into a); returns its
 // workgroup count.
-template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU>
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen>
 int level_cfg(StreamArgs<T>& a)
 {
     using G = LevelGeom<kAct1, cols_per_lane<T>(), wide_tile<T, kDec>()>;
@@ -55,7 +55,7 @@ int level_cfg(StreamArgs<T>& a)
         // One round of resident workgroups: a second, partial round would
         // run latency-bound on a mostly idle chip.
         static int occ = 0;
-        const int slots = resident_per_cu(k_stream_level<T, kAct0, kAct1, kDec, kZ, kU>, occ) * device_cu_count();
+        const int slots = resident_per_cu(k_stream_level<T, kAct0, kAct1, kDec, kZ, kU, kGen>, occ) * device_cu_count();
         const int nch = std::max(1, slots / tiles);
         chunk = (c0 + nch - 1) / nch;
         chunk = std::min(std::max(chunk, 2), kMaxChunk);
@@ -65,11 +65,11 @@ int level_cfg(StreamArgs<T>& a)
     return tiles * a.nch;
 }
 
-template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU>
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen>
 hipError_t launch_level_cfg(StreamArgs<T> a, hipStream_t st)
 {
-    const int blocks = level_cfg<T, kAct0, kAct1, kDec, kZ, kU>(a);
-    hipLaunchKernelGGL((k_stream_level<T, kAct0, kAct1, kDec, kZ, kU>), dim3((unsigned)blocks), dim3(kThreads), 0,
+    const int blocks = level_cfg<T, kAct0, kAct1, kDec, kZ, kU, kGen>(a);
+    hipLaunchKernelGGL((k_stream_level<T, kAct0, kAct1, kDec, kZ, kU, kGen>), dim3((unsigned)blocks), dim3(kThreads), 0,
                        st, a);
     return hipGetLastError();
 }
@@ -85,17 +85,17 @@ struct MultiStream {
 };
 static_assert(sizeof(MultiStream<double>) <= 4096, "fits the kernel argument segment");
 
-template <typename T, bool kAct0, bool kAct1>
+template <typename T, bool kAct0, bool kAct1, bool kGen>
 __global__ void __launch_bounds__(kThreads) k_stream_load_multi(MultiStream<T> m)
 {
     __shared__ LevelSmem<T, kAct0, kAct1, false> sm;
     const int b = remap_xcd((int)blockIdx.x, (int)gridDim.x);
     int l = 0;
     for (int i = 1; i < m.n; i++) l += (b >= m.start[i]) ? 1 : 0;
-    stream_level_tile<T, kAct0, kAct1, false, false, false>(m.a[l], b - m.start[l], sm);
+    stream_level_tile<T, kAct0, kAct1, false, false, false, wide_tile<T, false>(), kGen>(m.a[l], b - m.start[l], sm);
 }
 
-template <typename T, bool kAct0, bool kAct1>
+template <typename T, bool kAct0, bool kAct1, bool kGen>
 hipError_t launch_load_multi_cfg(const StreamArgs<T>* a, int n, hipStream_t st)
 {
     MultiStream<T> m;
@@ -105,30 +105,38 @@ hipError_t launch_load_multi_cfg(const StreamArgs<T>* a, int n, hipStream_t st)
     for (int i = 0; i < n; i++) {
         m.a[i] = a[i];
         m.start[i] = tot;
-        tot += level_cfg<T, kAct0, kAct1, false, false, false>(m.a[i]);
+        tot += level_cfg<T, kAct0, kAct1, false, false, false, kGen>(m.a[i]);
     }
     for (int i = n; i <= kMultiLevels; i++) m.start[i] = tot;
-    hipLaunchKernelGGL((k_stream_load_multi<T, kAct0, kAct1>), dim3((unsigned)tot), dim3(kThreads), 0, st, m);
+    hipLaunchKernelGGL((k_stream_load_multi<T, kAct0, kAct1, kGen>), dim3((unsigned)tot), dim3(kThreads), 0, st, m);
     return hipGetLastError();
 }
 
-template <typename T, bool kAct0, bool kAct1, bool kU>
+template <typename T, bool kAct0, bool kAct1, bool kU, bool kGen>
 hipError_t launch_cfg_u(StreamArgs<T> a, bool dec, hipStream_t st)
 {
-    if (dec && a.Z) return launch_level_cfg<T, kAct0, kAct1, true, true, kU>(a, st);
-    if (dec) return launch_level_cfg<T, kAct0, kAct1, true, false, kU>(a, st);
-    return launch_level_cfg<T, kAct0, kAct1, false, false, kU>(a, st);
+    if (dec && a.Z) return launch_level_cfg<T, kAct0, kAct1, true, true, kU, kGen>(a, st);
+    if (dec) return launch_level_cfg<T, kAct0, kAct1, true, false, kU, kGen>(a, st);
+    return launch_level_cfg<T, kAct0, kAct1, false, false, kU, kGen>(a, st);
 }
 
 template <typename T, bool kAct0, bool kAct1>
 hipError_t launch_cfg(StreamArgs<T> a, bool dec, hipStream_t st)
 {
+    if (a.gen) return launch_cfg_u<T, kAct0, kAct1, false, true>(a, dec, st);
     // unit column stride of the input and (decomposing) of the coefficients:
     // FP32 column pairs then move in single 8-byte accesses
     const bool unit = a.av.s[2] == 1 && (!dec || a.cv.s[2] == 1);
     if constexpr (cols_per_lane<T>() == 2)
-        if (unit) return launch_cfg_u<T, kAct0, kAct1, true>(a, dec, st);
-    return launch_cfg_u<T, kAct0, kAct1, false>(a, dec, st);
+        if (unit) return launch_cfg_u<T, kAct0, kAct1, true, false>(a, dec, st);
+    return launch_cfg_u<T, kAct0, kAct1, false, false>(a, dec, st);
+}
+
+template <typename T, bool kAct0, bool kAct1>
+hipError_t launch_load_multi(const StreamArgs<T>* a, int n, hipStream_t st)
+{
+    return a[0].gen ? launch_load_multi_cfg<T, kAct0, kAct1, true>(a, n, st)
+                    : launch_load_multi_cfg<T, kAct0, kAct1, false>(a, n, st);
 }
 
 }  // namespace
@@ -166,10 +174,11 @@ hipError_t launch_stream_load_multi(const StreamArgs<T>* a, int n, hipStream_t s
     if (n < 1 || n > kMultiLevels) return hipErrorInvalidValue;
     const bool act0 = a[0].av.n[0] > 1, act1 = a[0].av.n[1] > 1;
     for (int i = 1; i < n; i++)
-        if ((a[i].av.n[0] > 1) != act0 || (a[i].av.n[1] > 1) != act1) return hipErrorInvalidValue;
-    if (act0 && act1) return launch_load_multi_cfg<T, true, true>(a, n, st);
-    if (act0) return launch_load_multi_cfg<T, true, false>(a, n, st);
-    if (!act1) return launch_load_multi_cfg<T, false, false>(a, n, st);
+        if ((a[i].av.n[0] > 1) != act0 || (a[i].av.n[1] > 1) != act1 || a[i].gen != a[0].gen)
+            return hipErrorInvalidValue;
+    if (act0 && act1) return launch_load_multi<T, true, true>(a, n, st);
+    if (act0) return launch_load_multi<T, true, false>(a, n, st);
+    if (!act1) return launch_load_multi<T, false, false>(a, n, st);
     return hipErrorInvalidValue;
 }
 

@@ -165,7 +165,9 @@ struct alignas(16) LevelSmem {
 // columns move in one access.
 // kWide: the tile geometry (defaults to the per-level launch's; the batch
 // chooses it per plan).
-template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kWide = wide_tile<T, kDec>()>
+// kGen: level grids of any length (View3: clamped offsets, phantom nodes).
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kWide = wide_tile<T, kDec>(),
+          bool kGen = false>
 __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bid,
                                                   LevelSmem<T, kAct0, kAct1, kDec, kWide>& sm)
 {
@@ -220,7 +222,10 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
     const int gc = C0 + cb;  // global column of cb
     constexpr int RC = 2 * kT2 + 3;  // region columns
     // column j of the lane: in the region and the grid / owned by the tile
-    auto col_in = [&](int j) { return cb + j < RC && gc + j >= 0 && gc + j < m2; };
+    auto col_in = [&](int j) {
+        return cb + j < RC && gc + j >= 0 && gc + j < m2 && (!kGen || gc + j != a.ph[2]);
+    };
+    static_assert(!kGen || CPL == 1, "clamped columns move one by one");
     auto col_own = [&](int j) { return col_in(j) && gc + j >= 2 * I2 && gc + j < min(2 * (I2 + kT2), m2); };
     // Interpolation weights per column: zero outside the grid, so outside
     // nodes get a zero coefficient (their loads return zero); (1, 0) at even
@@ -256,8 +261,10 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
     // cb is even; in FP64 only at even lanes)
     constexpr int jw = 0;
     const bool w_own = col_own(jw) && !((cb + jw) & 1);
-    const unsigned cA = any_in ? (unsigned)(gc * as2) * S : kOut;
-    const unsigned cC = any_own ? (unsigned)(gc * cs2) * S : kOut;
+    // offset of index i: a clamp to the last node for any-length level grids
+    auto clamped = [](int off, int64_t last) { return kGen ? min(off, (int)last) : off; };
+    const unsigned cA = any_in ? (unsigned)clamped(gc * as2, a.av.last[2]) * S : kOut;
+    const unsigned cC = any_own ? (unsigned)clamped(gc * cs2, a.cv.last[2]) * S : kOut;
     const unsigned cW = w_own ? (unsigned)(((gc + jw) >> 1) * ws2) * S : kOut;
     const unsigned stepA = (unsigned)as2 * S, stepC = (unsigned)cs2 * S;
 
@@ -273,8 +280,10 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
     // kernel).  A row outside the grid loads a grid row instead and its
     // values are replaced by zero where they are used (rin), so the loads
     // stay unconditional and need no per-row lane offsets.
-    const unsigned spanA = (unsigned)((m1 - 1) * as1 + (m2 - 1) * as2 + 1) * S;
-    const unsigned spanC = (unsigned)((m1 - 1) * cs1 + (m2 - 1) * cs2 + 1) * S;
+    const unsigned spanA =
+        (unsigned)(clamped((m1 - 1) * as1, a.av.last[1]) + clamped((m2 - 1) * as2, a.av.last[2]) + 1) * S;
+    const unsigned spanC =
+        (unsigned)(clamped((m1 - 1) * cs1, a.cv.last[1]) + clamped((m2 - 1) * cs2, a.cv.last[2]) + 1) * S;
     const unsigned spanW = (unsigned)(((m1 - 1) / 2) * ws1 + ((m2 - 1) / 2) * ws2 + 1) * S;
     int gr[NRW];               // grid row (uniform)
     bool rin[NRW], rown[NRW];  // in the grid / owned (uniform)
@@ -284,14 +293,14 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
     for (int k = 0; k < NRW; k++) {
         const int r = rg + RW * k;
         gr[k] = R0 + r;
-        rin[k] = r < NR && gr[k] >= 0 && gr[k] < m1;
+        rin[k] = r < NR && gr[k] >= 0 && gr[k] < m1 && (!kGen || !kAct1 || gr[k] != a.ph[1]);
         rown[k] = rin[k] && gr[k] >= oR0 && gr[k] < oR1;
         // a row past the staged region re-reads this wave's previous row (the
         // same lines: no further memory traffic), a row outside the grid the
         // nearest grid row
         const int grc = min(max(r < NR ? gr[k] : gr[k] - RW, 0), m1 - 1);
-        soA[k] = (unsigned)uni((int)((unsigned)(grc * as1) * S));
-        soC[k] = (unsigned)uni((int)((unsigned)(grc * cs1) * S));
+        soA[k] = (unsigned)uni((int)((unsigned)clamped(grc * as1, a.av.last[1]) * S));
+        soC[k] = (unsigned)uni((int)((unsigned)clamped(grc * cs1, a.cv.last[1]) * S));
         soW[k] = (unsigned)uni((int)((unsigned)((grc >> 1) * ws1) * S));
         wrl[k] = T(0);
         wrh[k] = T(0);
@@ -335,13 +344,18 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
     const unsigned as0 = (unsigned)a.av.s[0], cs0 = (unsigned)a.cv.s[0], ws0 = (unsigned)a.wv.s[0],
                    fs0 = (unsigned)a.fv.s[0];
     auto mul64 = [](int i, unsigned st) { return (int64_t)((uint64_t)(unsigned)i * st); };
+    auto plane_off = [&](int i, unsigned st, int64_t last) {
+        const int64_t o = mul64(i, st);
+        return kGen ? min(o, last) : o;
+    };
     // all loads are unconditional: a load under a branch makes the compiler
     // wait for every outstanding load where the paths join
     using Cols = T[CPL];
     auto load_plane = [&](int f, Cols (&v)[NRW], Cols (&vz)[NRW]) {
-        const int64_t po = mul64(f, as0);
-        const __amdgpu_buffer_rsrc_t rA = make_rsrc(a.A + po, spanA);
-        const __amdgpu_buffer_rsrc_t rZ = make_rsrc(kZ ? a.Z + po : a.A, kZ ? spanA : 0u);
+        const int64_t po = plane_off(f, as0, a.av.last[0]);
+        const unsigned sp = (kGen && kAct0 && f == a.ph[0]) ? 0u : spanA;  // a phantom plane reads zero
+        const __amdgpu_buffer_rsrc_t rA = make_rsrc(a.A + po, sp);
+        const __amdgpu_buffer_rsrc_t rZ = make_rsrc(kZ ? a.Z + po : a.A, kZ ? sp : 0u);
 #pragma unroll
         for (int k = 0; k < NRW; k++) {
             buf_load_cols<kU>(rA, cA, soA[k], stepA, v[k]);
@@ -381,8 +395,8 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
             lds_barrier();
             return;
         }
-        const bool fown = f >= oF0 && f < oF1;
-        const int64_t pc = mul64(f, cs0);
+        const bool fown = f >= oF0 && f < oF1 && (!kGen || !kAct0 || f != a.ph[0]);
+        const int64_t pc = plane_off(f, cs0, a.cv.last[0]);
         const __amdgpu_buffer_rsrc_t rC = make_rsrc(a.C + pc, spanC);
         Cols cv[NRW];
         if (even) {

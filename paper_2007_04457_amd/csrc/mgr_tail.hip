@@ -126,6 +126,47 @@ __device__ __forceinline__ T tail_interp(const T* A, const TailShape& s, const L
     return a0 * lo + b0 * hi;
 }
 
+// The interpolant of an any-length grid: a sum over the coarse corners, the
+// neighbours along dim 0 first and along dim 2 last, each weighted by the
+// product of its one-dimensional weights.
+template <typename T, bool kHalf>
+__device__ __forceinline__ T tail_interp_corners(const T* A, const TailShape& s, const LdsTab<T>& t, int j0, int j1,
+                                                 int j2)
+{
+    const int n1 = kHalf ? s.mc[1] : s.m[1], n2 = kHalf ? s.mc[2] : s.m[2];
+    const int j[3] = {j0, j1, j2};
+    T acc = T(0);
+    for (int mask = 0; mask < 8; mask++) {
+        int q[3];
+        T w = T(1);
+        bool skip = false;
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            const bool up = (mask >> d) & 1, odd = j[d] & 1;
+            skip = skip || (up && !odd);
+            q[d] = odd ? (up ? j[d] + 1 : j[d] - 1) : j[d];
+            if (odd) w *= t.w[d][2 * j[d] + (up ? 1 : 0)];
+        }
+        if (skip) continue;
+        const T v = kHalf ? A[((q[0] >> 1) * n1 + (q[1] >> 1)) * n2 + (q[2] >> 1)] : A[(q[0] * n1 + q[1]) * n2 + q[2]];
+        acc = fma(w, v, acc);
+    }
+    return acc;
+}
+
+// Node (j0, j1, j2) of an any-length level grid: a phantom, and its place in
+// the packed grid (without phantoms).
+template <typename T>
+__device__ __forceinline__ bool tail_phantom(const TailLevel<T>& L, int j0, int j1, int j2)
+{
+    return j0 == L.ph[0] || j1 == L.ph[1] || j2 == L.ph[2];
+}
+template <typename T>
+__device__ __forceinline__ int tail_packed(const TailLevel<T>& L, int j0, int j1, int j2)
+{
+    return (min(j0, L.act[0] - 1) * L.act[1] + min(j1, L.act[1] - 1)) * L.act[2] + min(j2, L.act[2] - 1);
+}
+
 // f = R M vec(U) with U's coarse nodes read as zero; passes last dim first.
 template <typename T>
 __device__ void lds_load_vector(const T* U, T* P1, T* P2, T* F, const TailShape& s,
@@ -235,11 +276,19 @@ __device__ Regions<T> carve(T* sbuf, const TailLevel<T>& L0)
     return r;
 }
 
-template <typename T, bool kDec>
+// kGen: level grids of any length.  Their LDS arrays hold the phantom nodes
+// (zero); the user's arrays are reached through clamped offsets and the packed
+// grids in the workspace and in R.W have no phantoms.
+template <typename T, bool kDec, bool kGen>
 __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* sbuf, T* stab)
 {
     const Regions<T> R = carve(sbuf, a.lv[0]);
     const int64_t* st = a.st;
+    // offset in the user's arrays of node j of level grid k
+    auto user = [&](int k, int j0, int j1, int j2) {
+        const int64_t o0 = j0 * (st[0] << k), o1 = j1 * (st[1] << k), o2 = j2 * (st[2] << k);
+        return kGen ? min(o0, a.last[0]) + min(o1, a.last[1]) + min(o2, a.last[2]) : o0 + o1 + o2;
+    };
 
     if (kDec) {
         // input level grid k0: the caller's array (k0 == 0) or workspace
@@ -254,8 +303,9 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
                     const int idx = min(b0 + q * kT + (int)threadIdx.x, s.V - 1);
                     int j0, j1, j2;
                     dec3(idx, s.m, j0, j1, j2);
-                    tmp[q] = (a.k0 == 0) ? src[j0 * st[0] + j1 * st[1] + j2 * st[2]]
-                                         : L.Wk[idx] + (a.Z0 ? a.Z0[idx] : T(0));
+                    const int pk = kGen ? tail_packed(L, j0, j1, j2) : idx;
+                    tmp[q] = (a.k0 == 0) ? src[user(0, j0, j1, j2)] : L.Wk[pk] + (a.Z0 ? a.Z0[pk] : T(0));
+                    if (kGen && tail_phantom(L, j0, j1, j2)) tmp[q] = T(0);
                 }
 #pragma unroll
                 for (int q = 0; q < kTB; q++)
@@ -269,31 +319,40 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
             const LdsTab<T> t = stage_tables(L, stab);
             __syncthreads();
             // coefficients in place (only coarse nodes are read by others)
-            const int64_t v0 = st[0] << k, v1 = st[1] << k, v2 = st[2] << k;
             for (int idx = threadIdx.x; idx < s.V; idx += kT) {
                 int j0, j1, j2;
                 dec3(idx, s.m, j0, j1, j2);
+                if (kGen && tail_phantom(L, j0, j1, j2)) continue;
                 if (((j0 | j1 | j2) & 1) == 0) {
                     R.W[((j0 >> 1) * s.mc[1] + (j1 >> 1)) * s.mc[2] + (j2 >> 1)] = R.U[idx];
                 } else {
-                    const T c = R.U[idx] - tail_interp<T, false>(R.U, s, t, j0, j1, j2);
+                    const T c = R.U[idx] - (kGen ? tail_interp_corners<T, false>(R.U, s, t, j0, j1, j2)
+                                                 : tail_interp<T, false>(R.U, s, t, j0, j1, j2));
                     R.U[idx] = c;
-                    dst[j0 * v0 + j1 * v1 + j2 * v2] = c;
+                    dst[user(k, j0, j1, j2)] = c;
                 }
             }
             __syncthreads();
             lds_load_vector(R.U, R.P1, R.P2, R.F, s, t);
             lds_solve_apply(R.F, R.W, T(1), s, t);
             if (l + 1 < a.nlev) {
-                for (int q = threadIdx.x; q < s.Vc; q += kT) R.U[q] = R.W[q];
+                if (kGen) {
+                    const TailLevel<T>& N = a.lv[l + 1];
+                    for (int q = threadIdx.x; q < N.m[0] * N.m[1] * N.m[2]; q += kT) {
+                        int j0, j1, j2;
+                        dec3(q, N.m, j0, j1, j2);
+                        R.U[q] = tail_phantom(N, j0, j1, j2) ? T(0) : R.W[tail_packed(N, j0, j1, j2)];
+                    }
+                } else {
+                    for (int q = threadIdx.x; q < s.Vc; q += kT) R.U[q] = R.W[q];
+                }
                 __syncthreads();
             } else {
                 // coarsest values to their nodes
-                const int64_t c0 = st[0] << (k + 1), c1 = st[1] << (k + 1), c2 = st[2] << (k + 1);
                 for (int idx = threadIdx.x; idx < s.Vc; idx += kT) {
                     int j0, j1, j2;
                     dec3(idx, s.mc, j0, j1, j2);
-                    dst[j0 * c0 + j1 * c1 + j2 * c2] = R.W[idx];
+                    dst[user(k + 1, j0, j1, j2)] = R.W[idx];
                 }
             }
         }
@@ -302,11 +361,10 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
             const TailLevel<T>& Lc = a.lv[a.nlev - 1];
             const TailShape s = shape_of(Lc.m, Lc.mc);
             const int L = a.k0 + a.nlev;
-            const int64_t c0 = st[0] << L, c1 = st[1] << L, c2 = st[2] << L;
             for (int idx = threadIdx.x; idx < s.Vc; idx += kT) {
                 int j0, j1, j2;
                 dec3(idx, s.mc, j0, j1, j2);
-                R.W[idx] = src[j0 * c0 + j1 * c1 + j2 * c2];
+                R.W[idx] = src[user(L, j0, j1, j2)];
             }
         }
         for (int l = a.nlev - 1; l >= 0; l--) {
@@ -314,7 +372,6 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
             const int k = a.k0 + l;
             const TailShape s = shape_of(L.m, L.mc);
             const LdsTab<T> t = stage_tables(L, stab);
-            const int64_t v0 = st[0] << k, v1 = st[1] << k, v2 = st[2] << k;
             for (int b0 = 0; b0 < s.V; b0 += kTB * kT) {
                 T tmp[kTB];
 #pragma unroll
@@ -322,7 +379,9 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
                     const int idx = min(b0 + q * kT + (int)threadIdx.x, s.V - 1);
                     int j0, j1, j2;
                     dec3(idx, s.m, j0, j1, j2);
-                    tmp[q] = (((j0 | j1 | j2) & 1) == 0) ? T(0) : src[j0 * v0 + j1 * v1 + j2 * v2];
+                    tmp[q] = (((j0 | j1 | j2) & 1) == 0 || (kGen && tail_phantom(L, j0, j1, j2)))
+                                 ? T(0)
+                                 : src[user(k, j0, j1, j2)];
                 }
 #pragma unroll
                 for (int q = 0; q < kTB; q++)
@@ -336,12 +395,22 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
                 dec3(idx, s.m, j0, j1, j2);
                 if (((j0 | j1 | j2) & 1) == 0)
                     R.U[idx] = R.W[((j0 >> 1) * s.mc[1] + (j1 >> 1)) * s.mc[2] + (j2 >> 1)];
-                else
+                else if (!kGen)
                     R.U[idx] += tail_interp<T, true>(R.W, s, t, j0, j1, j2);
+                else if (!tail_phantom(L, j0, j1, j2))
+                    R.U[idx] += tail_interp_corners<T, true>(R.W, s, t, j0, j1, j2);
             }
             __syncthreads();
             if (l > 0) {
-                for (int q = threadIdx.x; q < s.V; q += kT) R.W[q] = R.U[q];
+                if (kGen) {
+                    for (int q = threadIdx.x; q < s.V; q += kT) {
+                        int j0, j1, j2;
+                        dec3(q, s.m, j0, j1, j2);
+                        if (!tail_phantom(L, j0, j1, j2)) R.W[tail_packed(L, j0, j1, j2)] = R.U[q];
+                    }
+                } else {
+                    for (int q = threadIdx.x; q < s.V; q += kT) R.W[q] = R.U[q];
+                }
                 __syncthreads();
             }
         }
@@ -351,20 +420,21 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
         for (int idx = threadIdx.x; idx < s.V; idx += kT) {
             int j0, j1, j2;
             dec3(idx, s.m, j0, j1, j2);
+            if (kGen && tail_phantom(L, j0, j1, j2)) continue;
             if (a.k0 == 0)
-                dst[j0 * st[0] + j1 * st[1] + j2 * st[2]] = R.U[idx];
+                dst[user(0, j0, j1, j2)] = R.U[idx];
             else
-                L.Wk[idx] = R.U[idx];
+                L.Wk[kGen ? tail_packed(L, j0, j1, j2) : idx] = R.U[idx];
         }
     }
 }
 
-template <typename T, bool kDec>
+template <typename T, bool kDec, bool kGen>
 __global__ void __launch_bounds__(kT) k_tail(TailArgs<T> a)
 {
     __shared__ T sbuf[kTailDataElems];
     __shared__ T stab[kTailTabElems];
-    tail_body<T, kDec>(a, a.src, a.dst, sbuf, stab);
+    tail_body<T, kDec, kGen>(a, a.src, a.dst, sbuf, stab);
 }
 
 // One workgroup per entry of a batch; arguments in device memory.
@@ -375,7 +445,7 @@ __global__ void __launch_bounds__(kT) k_tail_batch(const TailArgs<T>* __restrict
     __shared__ T sbuf[kTailDataElems];
     __shared__ T stab[kTailTabElems];
     const int f = field[blockIdx.x];
-    tail_body<T, kDec>(args[blockIdx.x], src[f], dst[f], sbuf, stab);
+    tail_body<T, kDec, false>(args[blockIdx.x], src[f], dst[f], sbuf, stab);
 }
 
 }  // namespace
@@ -400,10 +470,16 @@ template hipError_t launch_tail_batch<double>(const TailArgs<double>*, const int
 template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st)
 {
-    if (decompose)
-        hipLaunchKernelGGL((k_tail<T, true>), dim3(1), dim3(kT), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_tail<T, false>), dim3(1), dim3(kT), 0, st, a);
+    if (a.gen) {
+        if (decompose)
+            hipLaunchKernelGGL((k_tail<T, true, true>), dim3(1), dim3(kT), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_tail<T, false, true>), dim3(1), dim3(kT), 0, st, a);
+    } else if (decompose) {
+        hipLaunchKernelGGL((k_tail<T, true, false>), dim3(1), dim3(kT), 0, st, a);
+    } else {
+        hipLaunchKernelGGL((k_tail<T, false, false>), dim3(1), dim3(kT), 0, st, a);
+    }
     return hipGetLastError();
 }
 
