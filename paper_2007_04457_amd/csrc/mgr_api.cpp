@@ -173,15 +173,18 @@ int validate(int dtype, int ndim, const int64_t* shape, const double* const* coo
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- FP64 geometry tables (Sec. III-A.2 readings) --------------------------
-// Node positions along a dimension, scaled so the mean finest spacing is 1
-// (only ratios of spacings enter the method).
+// Node positions along a dimension, scaled so the mean finest spacing is near
+// 1 (only ratios of spacings enter the method).  The factor is a power of two:
+// any other rounds the positions, and on a graded mesh the smallest spacings
+// then carry that rounding (2e-4 in an interpolation weight where spacings
+// span eleven decades).
 std::vector<double> axis_positions(int64_t n, const double* x)
 {
     std::vector<double> X((size_t)n);
     if (!x) {
         for (int64_t i = 0; i < n; i++) X[(size_t)i] = (double)i;
     } else {
-        double sc = (double)(n - 1) / (x[n - 1] - x[0]);
+        const double sc = std::exp2(std::round(std::log2((double)(n - 1) / (x[n - 1] - x[0]))));
         for (int64_t i = 0; i < n; i++) X[(size_t)i] = (x[i] - x[0]) * sc;
     }
     return X;
