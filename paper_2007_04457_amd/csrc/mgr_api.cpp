@@ -54,8 +54,15 @@ struct LevelLayout {
     size_t PT[3];  // P^T as a 5-point row per coarse node (transposed interpolation)
     size_t sup[3];  // plain super-diagonal of M_{l-1}
     size_t L[3], U[3], IP[3], A[3], B[3], ssub[3], ssup[3], sl[3], sip[3], su[3];
-    int S[3];
+    int S[3], dec[3];
 };
+
+// Separators of a solve do not couple in the working precision
+// (SolveTables::dec).
+int separators_apart(double couple, size_t esize)
+{
+    return couple <= (esize == 8 ? 0x1p-57 : 0x1p-28) ? 1 : 0;
+}
 
 struct Plan {
     int device = 0, dtype = 0, ndim = 0, nlevels = 0;
@@ -325,6 +332,7 @@ struct SolveTab {
     std::vector<double> L, U, IP, A, B;            // padded, S * kSlot
     std::vector<double> ssub, ssup, sl, sip, su;   // per separator, length S
     int S = 1;
+    double couple = 0.0;  // largest share of a separator's neighbours in its row (SolveTables::dec)
 };
 
 // Partitioned-Thomas tables of the coarse mass matrix on positions yc
@@ -417,6 +425,10 @@ SolveTab build_solve(const std::vector<double>& yc)
             t.sl[(size_t)s] = Lc / den;
             den = D - t.sl[(size_t)s] * t.su[(size_t)(s - 1)];
         }
+        // (the first segment's row 0, 32 rows away, is left out of the sums
+        // over the rows around a separator: its response counts here too)
+        const double far = (s == 1) ? std::fabs(beta[0]) : 0.0;
+        t.couple = std::max(t.couple, (std::fabs(Lc) + std::fabs(Uc)) / std::fabs(D) + far);
         t.su[(size_t)s] = Uc;
         t.sip[(size_t)s] = 1.0 / den;
     }
@@ -480,7 +492,7 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             ly.w[d] = ly.K[d] = ly.lf[d] = ly.ip[d] = ly.PT[d] = 0;
             ly.sup[d] = ly.L[d] = ly.U[d] = ly.IP[d] = ly.A[d] = ly.B[d] = 0;
             ly.ssub[d] = ly.ssup[d] = ly.sl[d] = ly.sip[d] = ly.su[d] = 0;
-            ly.S[d] = 1;
+            ly.S[d] = ly.dec[d] = 1;
             if (!p.active[d]) continue;
             std::vector<double> y((size_t)act);
             for (int64_t j = 0; j < act; j++) y[(size_t)j] = X[d][(size_t)std::min(j << k, p.n[d] - 1)];
@@ -510,6 +522,7 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
                 push_table(host, ip, &ly.ip[d]);
             }
             ly.S[d] = sv.S;
+            ly.dec[d] = separators_apart(sv.couple, sizeof(T));
             push_table(host, sv.sup, &ly.sup[d]);
             push_table(host, sv.L, &ly.L[d]);
             push_table(host, sv.U, &ly.U[d]);
@@ -752,6 +765,7 @@ SolveTables<T> solve_tables_of(const Plan& p, int k, int d)
     t.sip = base + ly.sip[d];
     t.su = base + ly.su[d];
     t.S = ly.S[d];
+    t.dec = ly.dec[d];
     return t;
 }
 
@@ -1398,7 +1412,7 @@ struct GenLevelHost {
     int64_t m[kGenMaxDim], mc[kGenMaxDim];
     size_t wl[kGenMaxDim], wh[kGenMaxDim], K[kGenMaxDim];
     size_t solve[kGenMaxDim][10];  // L, U, IP, A, B, ssub, ssup, sl, sip, su
-    int S[kGenMaxDim];
+    int S[kGenMaxDim], dec[kGenMaxDim];
 };
 
 struct GenPlan {
@@ -1445,6 +1459,7 @@ int build_gen_plan(GenPlan& p, const double* const* coords)
             push_table(host, t.K, &ly.K[d]);
             SolveTab sv = build_solve(yc);
             ly.S[d] = sv.S;
+            ly.dec[d] = separators_apart(sv.couple, sizeof(T));
             const std::vector<double>* parts[10] = {&sv.L, &sv.U, &sv.IP, &sv.A, &sv.B,
                                                     &sv.ssub, &sv.ssup, &sv.sl, &sv.sip, &sv.su};
             for (int q = 0; q < 10; q++) push_table(host, *parts[q], &ly.solve[d][q]);
@@ -1593,6 +1608,7 @@ int gen_correction(const GenPlan& p, int k, const T* y, hipStream_t st, T** zout
         const T** f[10] = {&t.L, &t.U, &t.IP, &t.A, &t.B, &t.ssub, &t.ssup, &t.sl, &t.sip, &t.su};
         for (int q = 0; q < 10; q++) *f[q] = tb + ly.solve[d][q];
         t.S = ly.S[d];
+        t.dec = ly.dec[d];
         MGR_TRY(timed(KC_SOLVE, k, st,
                       [&] { return launch_solve_fibres<T>(out, ly.mc[d], inner, outer, t, ws + p.Yb, st); }),
                 "solve launch");
@@ -1926,7 +1942,28 @@ int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
                 bs.Yb = ws + p.Yb;
                 const int S = bs.tb.S;
                 const int vidx = (int)out.solves.size();
-                if (bs.inner == 1 && S <= kThreadsBatch && bs.n <= kBatchRowSpan) {
+                const int ns = solve_chunk_segs(S, bs.inner, bs.nfib);
+                if (bs.tb.dec && ns < S) {
+                    const int nch = (S + ns - 1) / ns;
+                    std::vector<BatchItem> s1, s2;
+                    if (bs.inner > 1) {
+                        for (int y = 0; y < nch - 1; y++)
+                            for (int64_t x = 0; x < cdiv(bs.nfib, kThreadsBatch); x++)
+                                s1.push_back(BatchItem{BI_SEP_BOUNDS, vidx, (int)x, y, f});
+                        for (int y = 0; y < nch; y++)
+                            for (int64_t x = 0; x < cdiv(bs.nfib, 16); x++)
+                                s2.push_back(BatchItem{BI_CHUNK_STRIDED, vidx, (int)x, y, f});
+                    } else {
+                        for (int64_t x = 0; x < cdiv(bs.nfib * (nch - 1), kThreadsBatch / 64); x++)
+                            s1.push_back(BatchItem{BI_SEP_BOUNDS, vidx, (int)x, 0, f});
+                        bs.rows = (int)std::max<int64_t>(1, std::min<int64_t>(kThreadsBatch / ns, kBatchRowSpan / (ns * kSeg)));
+                        for (int y = 0; y < nch; y++)
+                            for (int64_t x = 0; x < cdiv(bs.nfib, bs.rows); x++)
+                                s2.push_back(BatchItem{BI_CHUNK_ROWS, vidx, (int)x, y, f});
+                    }
+                    stages.push_back(std::move(s1));
+                    stages.push_back(std::move(s2));
+                } else if (bs.inner == 1 && S <= kThreadsBatch && bs.n <= kBatchRowSpan) {
                     bs.rows = (int)std::max<int64_t>(1, std::min<int64_t>(kThreadsBatch / S, kBatchRowSpan / bs.n));
                     std::vector<BatchItem> sg;
                     for (int64_t x = 0; x < cdiv(bs.nfib, bs.rows); x++) sg.push_back(BatchItem{BI_ROWS, vidx, (int)x, 0, f});

@@ -25,6 +25,8 @@ union BatchSmem {
     StridedSmem<T> str;
     RowsSmem<T, kBatchRowSpan, true> rows_t;
     RowsSmem<T, kBatchRowSpan, false> rows_g;
+    ChunkSmem<T, kBatchRowSpan + 64, true> chunk_t;
+    ChunkSmem<T, kBatchRowSpan + 64, false> chunk_g;
 };
 
 // The kernel's LDS (dynamic, sized to BatchSmem<T> at launch).  Each item
@@ -110,7 +112,53 @@ __device__ __attribute__((noinline)) void exec_strided(const BatchKernelArgs<T>*
     const BatchSolve<T> b = load_uniform(A->solves + it.args);
     const int tid = threadIdx.x;
     solve_strided_tile<T, 16, false>(b.F, fibre_map(b), b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads,
-                                     tid, *reinterpret_cast<StridedSmem<T>*>(batch_lds));
+                                     tid, *reinterpret_cast<StridedSmem<T>*>(batch_lds), 0, b.tb.S, nullptr);
+}
+
+// Long fibres whose separators do not couple: the separators between chunks,
+// and the chunks.
+template <typename T>
+__device__ __attribute__((noinline)) void exec_sep_bounds(const BatchKernelArgs<T>* A, const BatchItem* itp)
+{
+    const BatchItem it = load_uniform(itp);
+    const BatchSolve<T> b = load_uniform(A->solves + it.args);
+    const FibreMap m = fibre_map(b);
+    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib);
+    if (m.inner > 1)
+        sep_bounds_strided(b.F, b.Yb, m, b.tb, ns, it.bx, it.by);
+    else
+        sep_bounds_rows(b.F, b.Yb, m, b.tb, ns, (int64_t)it.bx * (kBlk / 64) + (threadIdx.x >> 6));
+}
+
+template <typename T>
+__device__ __attribute__((noinline)) void exec_chunk_rows(const BatchKernelArgs<T>* A, const BatchItem* itp)
+{
+    const BatchItem it = load_uniform(itp);
+    const BatchSolve<T> b = load_uniform(A->solves + it.args);
+    const FibreMap m = fibre_map(b);
+    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib), s0 = it.by * ns, nsc = min(ns, m.S - s0);
+    const int64_t row0 = (int64_t)it.bx * b.rows;
+    const int nrows = (int)min((int64_t)b.rows, m.nfib - row0);
+    const T* zb = b.Yb + ((int64_t)it.by - 1) * m.nfib;
+    if (ns <= kMaxSegWG)
+        solve_chunk_rows<T, kBatchRowSpan + 64, true>(
+            b.F, m, b.tb, row0, nrows, s0, nsc, zb, *reinterpret_cast<ChunkSmem<T, kBatchRowSpan + 64, true>*>(batch_lds));
+    else
+        solve_chunk_rows<T, kBatchRowSpan + 64, false>(
+            b.F, m, b.tb, row0, nrows, s0, nsc, zb, *reinterpret_cast<ChunkSmem<T, kBatchRowSpan + 64, false>*>(batch_lds));
+}
+
+template <typename T>
+__device__ __attribute__((noinline)) void exec_chunk_strided(const BatchKernelArgs<T>* A, const BatchItem* itp)
+{
+    const BatchItem it = load_uniform(itp);
+    const BatchSolve<T> b = load_uniform(A->solves + it.args);
+    const FibreMap m = fibre_map(b);
+    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib), s0 = it.by * ns;
+    const int tid = threadIdx.x;
+    solve_strided_tile<T, 16, false>(b.F, m, b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads, tid,
+                                     *reinterpret_cast<StridedSmem<T>*>(batch_lds), s0, min(ns, m.S - s0),
+                                     b.Yb + ((int64_t)it.by - 1) * m.nfib);
 }
 
 template <typename T>
@@ -152,6 +200,9 @@ k_batch(const BatchKernelArgs<T>* __restrict__ A, int first)
         case BI_ROWS: exec_rows<T>(A, itp); break;
         case BI_STRIDED: exec_strided<T>(A, itp); break;
         case BI_SCATTER: exec_scatter<T>(A, itp); break;
+        case BI_SEP_BOUNDS: exec_sep_bounds<T>(A, itp); break;
+        case BI_CHUNK_ROWS: exec_chunk_rows<T>(A, itp); break;
+        case BI_CHUNK_STRIDED: exec_chunk_strided<T>(A, itp); break;
         default: exec_phase<T>(A, itp); break;
     }
 }
@@ -212,6 +263,9 @@ __device__ __forceinline__ void run_item(const BatchKernelArgs<T>* A, const Batc
         case BI_ROWS: exec_rows<T>(A, itp); break;
         case BI_STRIDED: exec_strided<T>(A, itp); break;
         case BI_SCATTER: exec_scatter<T>(A, itp); break;
+        case BI_SEP_BOUNDS: exec_sep_bounds<T>(A, itp); break;
+        case BI_CHUNK_ROWS: exec_chunk_rows<T>(A, itp); break;
+        case BI_CHUNK_STRIDED: exec_chunk_strided<T>(A, itp); break;
         default: exec_phase<T>(A, itp); break;
     }
 }

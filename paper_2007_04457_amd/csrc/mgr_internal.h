@@ -83,6 +83,16 @@ constexpr int kSlot = kSeg + 1;
 // separator responses A (left) and B (right); per separator k = 1..S-1 the
 // matrix entries coupling it to its neighbours (ssub, ssup) and the Thomas
 // factors of the separator system (sl, sip, su).
+// dec: the separators do not couple within the working precision.  Two
+// neighbouring separators see each other through the 31 rows between them,
+// and the inverse of a mass matrix decays by about 0.27 a row, so in the
+// separator system the off-diagonals are some 2^-60 of the diagonal (largest
+// over uniform, randomly spaced and moderately graded meshes); the host sets
+// dec where both off-diagonals of every separator together stay below 2^-57
+// (FP64) or 2^-28 (FP32) of it.  Each separator is then sip times its own
+// right-hand side: no serial sweep, and long fibres split anywhere
+// (solve_chunk_segs).  Strongly graded meshes that miss the bound keep the
+// elimination along the separators.
 template <typename T>
 struct SolveTables {
     const T* L;
@@ -96,7 +106,20 @@ struct SolveTables {
     const T* sip;
     const T* su;
     int S;
+    int dec;
 };
+
+// Segments per workgroup of a fibre of S segments (nfib fibres, contiguous or
+// strided) whose separators do not couple; S: the fibre is not split.  Up to
+// 16 segments share a workgroup's LDS tables; a longer fibre is cut into
+// chunks of 16, or of 128 where there are too few contiguous fibres to fill a
+// workgroup with 16-segment pieces (1-D problems).
+__host__ __device__ inline int solve_chunk_segs(int S, int64_t inner, int64_t nfib)
+{
+    if (S <= 16) return S;
+    if (inner == 1 && nfib < 16) return S < 128 ? S : 128;
+    return 16;
+}
 
 // In-place correction solve of F along dimension d.
 template <typename T>
@@ -320,6 +343,9 @@ enum BatchItemType {
     BI_SEG_FINAL,
     BI_SCATTER,      // coarsest values W_L + z_{L-1} to their nodes (fields without a tail)
     BI_STREAM3W,     // streaming level tile, 3-D problem, wide tile geometry
+    BI_SEP_BOUNDS,   // long fibres whose separators do not couple, two waves:
+    BI_CHUNK_ROWS,   // the separators between chunks, then the chunks (by: chunk)
+    BI_CHUNK_STRIDED,
     BI_COUNT
 };
 

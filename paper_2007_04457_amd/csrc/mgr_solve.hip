@@ -22,8 +22,10 @@
 // 64 neighbouring fibres (coalesced), wave s solving segment s; along the
 // contiguous dimension a workgroup stages whole rows through LDS and lanes
 // take (row, segment) pairs.  Separators are solved in LDS by one lane per
-// fibre.  Longer fibres fall back to three launches (segment ends,
-// separators, final) through global memory.
+// fibre, or, where they do not couple (SolveTables::dec), each by the lanes
+// that need it.  Longer fibres are cut into chunks there; on meshes where
+// separators couple they take three launches (segment ends, separators,
+// final) through global memory.
 #include <algorithm>
 #include <cstring>
 
@@ -42,7 +44,54 @@ k_solve_strided_wg(T* __restrict__ F, FibreMap m, SolveTables<T> tb)
     // write: keep them on one XCD (one L2)
     const int bx = remap_xcd((int)blockIdx.x, (int)gridDim.x);
     solve_strided_tile<T, 64, true>(F, m, tb, (int64_t)bx * 64, s, (int)threadIdx.x, 64 * m.S,
-                              (int)(threadIdx.y * 64 + threadIdx.x), sm);
+                                    (int)(threadIdx.y * 64 + threadIdx.x), sm, 0, m.S, nullptr);
+}
+
+// One chunk (ns segments, the last chunk fewer) of 64 fibres, the nfb groups of
+// fibres fastest; waves past the last chunk's segments idle through the
+// barriers.
+template <typename T>
+__global__ void __launch_bounds__(64 * kMaxSegWG)
+k_solve_strided_chunk(T* __restrict__ F, const T* __restrict__ zb, FibreMap m, SolveTables<T> tb, int ns, int nfb)
+{
+    __shared__ StridedSmem<T> sm;
+    const int s = __builtin_amdgcn_readfirstlane(threadIdx.y);
+    const int b = remap_xcd((int)blockIdx.x, (int)gridDim.x);
+    const int c = b / nfb, bx = b - c * nfb, s0 = c * ns;
+    solve_strided_tile<T, 64, false>(F, m, tb, (int64_t)bx * 64, s, (int)threadIdx.x, 64 * (int)blockDim.y,
+                                     (int)(threadIdx.y * 64 + threadIdx.x), sm, s0, min(ns, m.S - s0),
+                                     zb + ((int64_t)c - 1) * m.nfib);
+}
+
+// Elements a chunk-rows workgroup stages: 32 KB of either type.
+template <typename T>
+constexpr int chunk_span()
+{
+    return 8192 * 4 / (int)sizeof(T);
+}
+template <typename T, bool kLdsTab>
+__global__ void __launch_bounds__(kBlk)
+k_solve_rows_chunk(T* __restrict__ F, const T* __restrict__ zb, FibreMap m, SolveTables<T> tb, int ns, int rpb, int nrb)
+{
+    __shared__ ChunkSmem<T, chunk_span<T>() + 64, kLdsTab> sm;
+    const int c = (int)blockIdx.x / nrb, s0 = c * ns;
+    const int64_t row0 = (int64_t)((int)blockIdx.x - c * nrb) * rpb;
+    solve_chunk_rows<T, chunk_span<T>() + 64, kLdsTab>(F, m, tb, row0, (int)min((int64_t)rpb, m.nfib - row0), s0,
+                                                       min(ns, m.S - s0), zb + ((int64_t)c - 1) * m.nfib, sm);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kBlk)
+k_sep_bounds_strided(const T* __restrict__ F, T* __restrict__ zb, FibreMap m, SolveTables<T> tb, int ns)
+{
+    const int nfb = (int)((m.nfib + kBlk - 1) / kBlk);
+    sep_bounds_strided(F, zb, m, tb, ns, (int)blockIdx.x % nfb, (int)blockIdx.x / nfb);
+}
+template <typename T>
+__global__ void __launch_bounds__(kBlk)
+k_sep_bounds_rows(const T* __restrict__ F, T* __restrict__ zb, FibreMap m, SolveTables<T> tb, int ns)
+{
+    sep_bounds_rows(F, zb, m, tb, ns, (int64_t)blockIdx.x * (kBlk / 64) + (threadIdx.x >> 6));
 }
 
 
@@ -209,7 +258,7 @@ struct PlaneSolveArgs {
 
 template <typename T>
 __device__ __forceinline__ void plane_dim(T* P, T* end0, T* end1, const T* tab, const T* septab, int n, int S,
-                                          int nf, int sd, int sf, int tid)
+                                          int nf, int sd, int sf, int tid, int dec)
 {
     // task tid: segment s of fibre f; fibre f starts at P[f sf], node i of it
     // is at P[f sf + i sd]
@@ -231,6 +280,25 @@ __device__ __forceinline__ void plane_dim(T* P, T* end0, T* end1, const T* tab, 
         end1[s * nf + f] = ylast;
     }
     __syncthreads();
+    if (dec) {
+        auto sep = [&](int k) {
+            return sep_alone(p[(k * kSeg) * sd], septab[0 * kMaxSegWG + k], end1[(k - 1) * nf + f],
+                             septab[1 * kMaxSegWG + k], end0[k * nf + f], septab[3 * kMaxSegWG + k]);
+        };
+        const T zl = (s > 0) ? sep(s) : T(0);
+        const T zr = (s < S - 1) ? sep(s + 1) : T(0);
+        __syncthreads();  // every task has read its separators
+        if (active) {
+            const T* ta = tab + 3 * kMaxSegWG * kSlot + s * kSlot;
+            const T* tb = tab + 4 * kMaxSegWG * kSlot + s * kSlot;
+#pragma unroll
+            for (int q = 0; q < kSlot; q++)
+                if (q < len) p[(lo + q) * sd] = seg_final(v[q], ta[q], zl, tb[q], zr);
+            if (s > 0) p[(s * kSeg) * sd] = zl;
+        }
+        __syncthreads();
+        return;
+    }
     if (active && s == 0 && S > 1)
         sep_solve(S, p, (int64_t)kSeg * sd, end0 + f, end1 + f, nf, septab + 0 * kMaxSegWG,
                   septab + 1 * kMaxSegWG, septab + 2 * kMaxSegWG, septab + 3 * kMaxSegWG, septab + 4 * kMaxSegWG);
@@ -293,9 +361,9 @@ __global__ void __launch_bounds__(kPlaneThreads) k_solve_plane(PlaneSolveArgs<T>
     }
     __syncthreads();
     // rows (dimension 2): fibre f = row, node i at f n2 + i
-    plane_dim(P, end, end + kPlaneThreads, tab, septab, n2, a.tb[0].S, n1, 1, n2, tid);
+    plane_dim(P, end, end + kPlaneThreads, tab, septab, n2, a.tb[0].S, n1, 1, n2, tid, a.tb[0].dec);
     // columns (dimension 1): fibre f = column, node i at i n2 + f
-    plane_dim(P, end, end + kPlaneThreads, tab + TAB, septab + SEP, n1, a.tb[1].S, n2, n2, 1, tid);
+    plane_dim(P, end, end + kPlaneThreads, tab + TAB, septab + SEP, n1, a.tb[1].S, n2, n2, 1, tid, a.tb[1].dec);
     for (int e = tid; e < V; e += nthr) F[e] = P[e];
 }
 
@@ -345,7 +413,8 @@ __global__ void __launch_bounds__(kMaxThr) k_solve_strided_multi(MultiSolve<T> a
     const int l = multi_entry(a, b);
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.y);
     solve_strided_tile<T, 64, false>(a.F[l], a.m[l], a.tb[l], (int64_t)(b - a.start[l]) * 64, s, (int)threadIdx.x,
-                                     (int)(64 * blockDim.y), (int)(threadIdx.y * 64 + threadIdx.x), sm);
+                                     (int)(64 * blockDim.y), (int)(threadIdx.y * 64 + threadIdx.x), sm, 0, a.m[l].S,
+                                     nullptr);
 }
 
 }  // namespace
@@ -435,6 +504,36 @@ hipError_t launch_solve_fibres(T* F, int64_t n, int64_t inner, int64_t outer, So
     m.outer = outer;
     m.nfib = m.inner * m.outer;
     m.S = tb.S;
+    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib);
+    if (tb.dec && ns < m.S) {
+        // chunks of ns segments: the separators between them first, from the
+        // rows around each, then every chunk by itself in one pass.  4097 x
+        // 4097 FP64 nodes (134 MB): rows 112 us, against 266 us with a whole
+        // row per workgroup (a serial sweep over 127 separators, segment
+        // tables read from global memory); the strided dimension 84 us,
+        // against 184 us in three phases (two passes and a serial sweep
+        // through global memory).  Bound by memory: 3.2 TB/s.
+        const int nch = (m.S + ns - 1) / ns;
+        if (m.inner > 1) {
+            hipLaunchKernelGGL(k_sep_bounds_strided<T>, dim3(blocks(m.nfib) * (unsigned)(nch - 1)), dim3(kBlk), 0, st, F,
+                               Yb, m, tb, ns);
+            const int nfb = (int)((m.nfib + 63) / 64);
+            hipLaunchKernelGGL(k_solve_strided_chunk<T>, dim3((unsigned)(nfb * nch)), dim3(64, (unsigned)ns), 0, st, F,
+                               Yb, m, tb, ns, nfb);
+        } else {
+            const int64_t units = m.nfib * (nch - 1);
+            hipLaunchKernelGGL(k_sep_bounds_rows<T>, dim3((unsigned)((units + 3) / 4)), dim3(kBlk), 0, st, F, Yb, m, tb,
+                               ns);
+            const int rpb = (int)std::max<int64_t>(1, std::min<int64_t>(kBlk / ns, chunk_span<T>() / (ns * kSeg)));
+            const int nrb = (int)((m.nfib + rpb - 1) / rpb);
+            const dim3 grid((unsigned)(nrb * nch));
+            if (ns <= kMaxSegWG)
+                hipLaunchKernelGGL((k_solve_rows_chunk<T, true>), grid, dim3(kBlk), 0, st, F, Yb, m, tb, ns, rpb, nrb);
+            else
+                hipLaunchKernelGGL((k_solve_rows_chunk<T, false>), grid, dim3(kBlk), 0, st, F, Yb, m, tb, ns, rpb, nrb);
+        }
+        return hipGetLastError();
+    }
     if (m.inner == 1 && m.S <= kBlk && m.n <= rows_span<T>()) {
         return launch_rows<T, rows_span<T>()>(F, m, tb, st);
     }

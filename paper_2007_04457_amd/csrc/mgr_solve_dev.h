@@ -10,6 +10,9 @@ namespace {
 constexpr int kBlk = 256;
 constexpr int kMaxSegWG = 16;  // strided single-launch form: S <= 16
 
+// LDS position of staged element e: one pad element per 32
+__device__ __forceinline__ int padded(int e) { return e + (e >> 5); }
+
 struct FibreMap {
     int64_t n, inner, outer, nfib;
     int S;
@@ -108,42 +111,60 @@ struct StridedSmem {
     T sep[kMaxSegWG * 64];        // f, then z, at each separator [s][j]
 };
 
-template <typename T, int FB, bool kAllSeg>  // kAllSeg: every s < S
+// A separator whose neighbours' terms are below the working precision
+// (SolveTables::dec).
+template <typename T>
+__device__ __forceinline__ T sep_alone(T f, T sub, T ylast, T sup, T yfirst, T ip)
+{
+    return sep_rhs(f, sub, ylast, sup, yfirst) * ip;
+}
+
+// s: the lane's segment within the workgroup, of the ns segments s0 .. s0 +
+// ns - 1 (a whole fibre, or a chunk of one whose separators do not couple:
+// its two outer separators are then in zb, the chunk's own at zb[fib], the
+// next one's at zb[nfib + fib]).  kAllSeg: every s < ns.
+template <typename T, int FB, bool kAllSeg>
 __device__ __forceinline__ void solve_strided_tile(T* __restrict__ F, const FibreMap& m,
                                                    const SolveTables<T>& tb, int64_t fib0, int s,
-                                                   int j, int nthr, int tid, StridedSmem<T>& sm)
+                                                   int j, int nthr, int tid, StridedSmem<T>& sm,
+                                                   int s0, int ns, const T* __restrict__ zb)
 {
     const int S = m.S;
-    const bool inseg = kAllSeg || s < S;
-    const int sc = kAllSeg ? s : (inseg ? s : S - 1);
+    const bool inseg = kAllSeg || s < ns;
+    const int sc = kAllSeg ? s : (inseg ? s : ns - 1);
     const int64_t fib = fib0 + j;
     const bool active = inseg && fib < m.nfib;
     const int64_t fc = fib < m.nfib ? fib : m.nfib - 1;  // idle lanes read a valid fibre
     const int64_t base = (fc / m.inner) * m.n * m.inner + fc % m.inner;
+    const bool outer_l = s == 0 && s0 > 0, outer_r = s == ns - 1 && s0 + ns < S;
     int lo, len;
-    seg_range(m, sc, lo, len);
+    seg_range(m, s0 + sc, lo, len);
     // the fibre loads are issued first and the tables' after them, so that
     // one memory latency covers both (staging the tables first would wait
     // for their loads before the fibre loads were issued)
     T v[kSlot];
 #pragma unroll
     for (int q = 0; q < kSlot; q++) v[q] = F[base + (int64_t)(lo + min(q, len - 1)) * m.inner];
-    const T fsep = F[base + (int64_t)(sc * kSeg) * m.inner];  // f at the segment's left separator
-    for (int e = tid; e < S * kSlot; e += nthr) {
-        sm.tab[0][e] = tb.L[e];
-        sm.tab[1][e] = tb.U[e];
-        sm.tab[2][e] = tb.IP[e];
-        sm.tab[3][e] = tb.A[e];
-        sm.tab[4][e] = tb.B[e];
+    const T fsep = F[base + (int64_t)((s0 + sc) * kSeg) * m.inner];  // f at the segment's left separator
+    T zol = T(0), zor = T(0);
+    if (outer_l) zol = zb[fc];
+    if (outer_r) zor = zb[m.nfib + fc];
+    for (int e = tid; e < ns * kSlot; e += nthr) {
+        const int g = s0 * kSlot + e;
+        sm.tab[0][e] = tb.L[g];
+        sm.tab[1][e] = tb.U[g];
+        sm.tab[2][e] = tb.IP[g];
+        sm.tab[3][e] = tb.A[g];
+        sm.tab[4][e] = tb.B[g];
     }
-    for (int e = tid; e < S; e += nthr) {
-        sm.septab[0][e] = tb.ssub[e];
-        sm.septab[1][e] = tb.ssup[e];
-        sm.septab[2][e] = tb.sl[e];
-        sm.septab[3][e] = tb.sip[e];
-        sm.septab[4][e] = tb.su[e];
+    for (int e = tid; e < ns; e += nthr) {
+        sm.septab[0][e] = tb.ssub[s0 + e];
+        sm.septab[1][e] = tb.ssup[s0 + e];
+        sm.septab[2][e] = tb.sl[s0 + e];
+        sm.septab[3][e] = tb.sip[s0 + e];
+        sm.septab[4][e] = tb.su[s0 + e];
     }
-    if (inseg) sm.sep[s * FB + j] = (s > 0) ? fsep : T(0);
+    if (inseg) sm.sep[s * FB + j] = (s0 + s > 0) ? fsep : T(0);
     __syncthreads();  // tables staged
     const T ylast = seg_solve(v, &sm.tab[0][sc * kSlot], &sm.tab[1][sc * kSlot], &sm.tab[2][sc * kSlot]);
     if (inseg) {
@@ -151,19 +172,168 @@ __device__ __forceinline__ void solve_strided_tile(T* __restrict__ F, const Fibr
         sm.end[1][s * FB + j] = ylast;
     }
     __syncthreads();
-    if (s == 0 && S > 1)
-        sep_solve(S, &sm.sep[j], FB, &sm.end[0][j], &sm.end[1][j], FB, sm.septab[0], sm.septab[1],
-                  sm.septab[2], sm.septab[3], sm.septab[4]);
-    __syncthreads();
-    if (!active) return;
-    const T zl = (s > 0) ? sm.sep[s * FB + j] : T(0);
-    const T zr = (s < S - 1) ? sm.sep[(s + 1) * FB + j] : T(0);
+    T zl, zr;
+    if (tb.dec) {
+        auto sep = [&](int k) {
+            return sep_alone(sm.sep[k * FB + j], sm.septab[0][k], sm.end[1][(k - 1) * FB + j], sm.septab[1][k],
+                             sm.end[0][k * FB + j], sm.septab[3][k]);
+        };
+        if (!active) return;
+        zl = (s > 0) ? sep(s) : zol;
+        zr = (s < ns - 1) ? sep(s + 1) : zor;
+    } else {
+        if (s == 0 && S > 1)
+            sep_solve(S, &sm.sep[j], FB, &sm.end[0][j], &sm.end[1][j], FB, sm.septab[0], sm.septab[1],
+                      sm.septab[2], sm.septab[3], sm.septab[4]);
+        __syncthreads();
+        if (!active) return;
+        zl = (s > 0) ? sm.sep[s * FB + j] : T(0);
+        zr = (s < S - 1) ? sm.sep[(s + 1) * FB + j] : T(0);
+    }
     const T* ta = &sm.tab[3][s * kSlot];
     const T* tbt = &sm.tab[4][s * kSlot];
 #pragma unroll
     for (int q = 0; q < kSlot; q++)
         if (q < len) F[base + (int64_t)(lo + q) * m.inner] = seg_final(v[q], ta[q], zl, tbt[q], zr);
-    if (s > 0) F[base + (int64_t)(s * kSeg) * m.inner] = zl;
+    if (s0 + s > 0) F[base + (int64_t)((s0 + s) * kSeg) * m.inner] = zl;
+}
+
+// ---- long fibres whose separators do not couple ----------------------------
+// The separators between chunks (every ns-th of a fibre), each from the 31
+// rows on either side of it: with alpha and beta the segments' responses to
+// it, z = sip (f + sum beta f over the segment before + sum alpha f over the
+// segment after), which is the separator's row with the segments' end values
+// written out as the inner products they are.  zb[(b - 1) * nfib + fib] for
+// b = 1 .. chunks - 1.
+__device__ __forceinline__ int chunk_bounds(const FibreMap& m, int ns) { return (m.S + ns - 1) / ns - 1; }
+
+// Weight of row p - 31 + j around separator s at row p (1 at the separator).
+template <typename T>
+__device__ __forceinline__ T sep_weight(const SolveTables<T>& tb, int s, int j)
+{
+    if (j < 31) return tb.B[(s - 1) * kSlot + 1 + j - (s > 1 ? 1 : 0)];
+    if (j == 31) return T(1);
+    return tb.A[s * kSlot + j - 32];
+}
+
+// One separator of one fibre per lane (strided dimensions).
+template <typename T>
+__device__ __forceinline__ void sep_bounds_strided(const T* __restrict__ F, T* __restrict__ zb, const FibreMap& m,
+                                                   const SolveTables<T>& tb, int ns, int bx, int b)
+{
+    const int64_t fib = (int64_t)bx * kBlk + threadIdx.x;
+    if (fib >= m.nfib) return;
+    const int64_t base = (fib / m.inner) * m.n * m.inner + fib % m.inner;
+    const int s = (b + 1) * ns, p = s * kSeg;
+    T acc = T(0);
+    for (int j0 = 0; j0 < 63; j0 += 21) {
+        T v[21];
+#pragma unroll
+        for (int q = 0; q < 21; q++) v[q] = F[base + (int64_t)min(p - 31 + j0 + q, (int)m.n - 1) * m.inner];
+#pragma unroll
+        for (int q = 0; q < 21; q++) acc = fma(sep_weight(tb, s, j0 + q), v[q], acc);
+    }
+    zb[(int64_t)b * m.nfib + fib] = acc * tb.sip[s];
+}
+
+// One separator of one contiguous fibre per wave: lane j takes row
+// p - 31 + j, and the wave sums.  u: separator of the launch, fibres fastest.
+template <typename T>
+__device__ __forceinline__ void sep_bounds_rows(const T* __restrict__ F, T* __restrict__ zb, const FibreMap& m,
+                                                const SolveTables<T>& tb, int ns, int64_t u)
+{
+    if (u >= m.nfib * chunk_bounds(m, ns)) return;
+    const int b = (int)(u / m.nfib);
+    const int64_t fib = u - b * m.nfib;
+    const int s = (b + 1) * ns, p = s * kSeg, j = threadIdx.x & 63;
+    T acc = T(0);
+    if (j < 63) acc = sep_weight(tb, s, j) * F[fib * m.n + min(p - 31 + j, (int)m.n - 1)];
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) acc += __shfl_xor(acc, w);
+    if (j == 0) zb[(int64_t)b * m.nfib + fib] = acc * tb.sip[s];
+}
+
+// Rows [row0, row0 + nrows) x segments [s0, s0 + ns) (nrows * ns <= kBlk,
+// nrows * (ns * kSeg + 1) <= kSpan): the chunk's columns, from its own left
+// separator on, are staged through LDS, solved and written back.
+template <typename T, int kSpan, bool kLdsTab>
+struct ChunkSmem {
+    T f[kSpan + kSpan / 32 + 1];
+    T end[2][kBlk];
+    T tab[5][kLdsTab ? kMaxSegWG * kSlot : 1];
+};
+template <typename T, int kSpan, bool kLdsTab>
+__device__ __forceinline__ void solve_chunk_rows(T* __restrict__ F, const FibreMap& m, const SolveTables<T>& tb,
+                                                 int64_t row0, int nrows, int s0, int ns, const T* __restrict__ zb,
+                                                 ChunkSmem<T, kSpan, kLdsTab>& sm)
+{
+    const int tid = threadIdx.x, n = (int)m.n;
+    const int c0 = s0 * kSeg;                                   // the chunk's first column
+    const int c1 = (s0 + ns >= m.S) ? n : (s0 + ns) * kSeg;     // one past its last
+    const int w = c1 - c0, span = nrows * w;
+    // (row, segment) of the lane; segment fastest
+    const int r = tid / ns, s = tid - r * ns;
+    const bool active = r < nrows;
+    const int rr = active ? r : 0;
+    constexpr int NQ = (kSpan + kBlk - 1) / kBlk;
+    T tmp[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; q++) {
+        const int e = min(q * kBlk + tid, span - 1);
+        const int er = e / w;
+        tmp[q] = F[(row0 + er) * n + c0 + (e - er * w)];
+    }
+    T zl = T(0), zr = T(0);
+    const int64_t fib = row0 + rr;
+    if (s == 0 && s0 > 0) zl = zb[fib];
+    if (s == ns - 1 && s0 + ns < m.S) zr = zb[m.nfib + fib];
+    if (kLdsTab)
+        for (int e = tid; e < ns * kSlot; e += kBlk) {
+            const int g = s0 * kSlot + e;
+            sm.tab[0][e] = tb.L[g];
+            sm.tab[1][e] = tb.U[g];
+            sm.tab[2][e] = tb.IP[g];
+            sm.tab[3][e] = tb.A[g];
+            sm.tab[4][e] = tb.B[g];
+        }
+#pragma unroll
+    for (int q = 0; q < NQ; q++)
+        if (q * kBlk + tid < span) sm.f[padded(q * kBlk + tid)] = tmp[q];
+    __syncthreads();
+    const int so = kLdsTab ? s * kSlot : (s0 + s) * kSlot;
+    const T* const tA = kLdsTab ? &sm.tab[3][so] : tb.A + so;
+    const T* const tB = kLdsTab ? &sm.tab[4][so] : tb.B + so;
+    int lo, len;
+    seg_range(m, s0 + s, lo, len);
+    const int e0 = rr * w - c0;  // staged index of column c is e0 + c
+    T v[kSlot];
+#pragma unroll
+    for (int q = 0; q < kSlot; q++) v[q] = sm.f[padded(e0 + lo + min(q, len - 1))];
+    const T ylast = seg_solve(v, kLdsTab ? &sm.tab[0][so] : tb.L + so, kLdsTab ? &sm.tab[1][so] : tb.U + so,
+                              kLdsTab ? &sm.tab[2][so] : tb.IP + so);
+    sm.end[0][tid] = v[0];
+    sm.end[1][tid] = ylast;
+    __syncthreads();
+    auto sep = [&](int k, int t) {  // separator left of local segment k, lane t holding that segment
+        return sep_alone(sm.f[padded(e0 + (s0 + k) * kSeg)], tb.ssub[s0 + k], sm.end[1][t - 1], tb.ssup[s0 + k],
+                         sm.end[0][t], tb.sip[s0 + k]);
+    };
+    if (active && s > 0) zl = sep(s, tid);
+    if (active && s < ns - 1) zr = sep(s + 1, tid + 1);
+    __syncthreads();  // every lane has read its separators
+    if (active) {
+#pragma unroll
+        for (int q = 0; q < kSlot; q++)
+            if (q < len) sm.f[padded(e0 + lo + q)] = seg_final(v[q], tA[q], zl, tB[q], zr);
+        if (s0 + s > 0) sm.f[padded(e0 + (s0 + s) * kSeg)] = zl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NQ; q++) {
+        const int e = q * kBlk + tid;
+        const int er = e / w;
+        if (e < span) F[(row0 + er) * n + c0 + (e - er * w)] = sm.f[padded(e)];
+    }
 }
 
 // ---- contiguous dimension, one launch --------------------------------------
@@ -176,7 +346,6 @@ constexpr int rows_span()
 {
     return kSpanMax * 4 / (int)sizeof(T);
 }
-__device__ __forceinline__ int padded(int e) { return e + (e >> 5); }
 
 template <typename T, int kSpan, bool kLdsTab>
 struct RowsSmem {
@@ -268,6 +437,24 @@ __device__ __forceinline__ void rows_solve_lds(const FibreMap& m, const SolveTab
     sm.end[0][tid] = v[0];
     sm.end[1][tid] = ylast;
     bar();
+    T zl = T(0), zr = T(0);
+    if (tb.dec) {
+        auto sep = [&](int k, int t) {
+            return sep_alone(sm.f[padded(rr * n + k * kSeg)], sm.septab[0][k], sm.end[1][t - 1], sm.septab[1][k],
+                             sm.end[0][t], sm.septab[3][k]);
+        };
+        if (active && s > 0) zl = sep(s, tid);
+        if (active && s < m.S - 1) zr = sep(s + 1, tid + 1);
+        bar();  // every lane has read its separators
+        if (active) {
+#pragma unroll
+            for (int q = 0; q < kSlot; q++)
+                if (q < len) sm.f[padded(r * n + lo + q)] = seg_final(v[q], tA[q], zl, tB[q], zr);
+            if (s > 0) sm.f[padded(r * n + s * kSeg)] = zl;
+        }
+        bar();
+        return;
+    }
     if (active && s == 0 && m.S > 1) {
         // row r's separators live in sm.f at r*n + k*kSeg
         const int t0 = tid;
@@ -286,8 +473,8 @@ __device__ __forceinline__ void rows_solve_lds(const FibreMap& m, const SolveTab
         }
     }
     bar();
-    const T zl = (s > 0) ? sm.f[padded(rr * n + s * kSeg)] : T(0);
-    const T zr = (s < m.S - 1) ? sm.f[padded(rr * n + (s + 1) * kSeg)] : T(0);
+    zl = (s > 0) ? sm.f[padded(rr * n + s * kSeg)] : T(0);
+    zr = (s < m.S - 1) ? sm.f[padded(rr * n + (s + 1) * kSeg)] : T(0);
     bar();  // every lane has read its separators
     if (active) {
 #pragma unroll
