@@ -50,9 +50,9 @@ constexpr int kMaxDim = 3;
 struct LevelLayout {
     int64_t m[3], mc[3];
     int ph[3];
-    size_t w[3], K[3], lf[3], ip[3];  // lf, ip: plain Thomas factors of M_{l-1}
+    size_t w[3], K[3];
     size_t PT[3];  // P^T as a 5-point row per coarse node (transposed interpolation)
-    size_t sup[3];  // plain super-diagonal of M_{l-1}
+    bool tail;  // the level may join the tail
     size_t L[3], U[3], IP[3], A[3], B[3], ssub[3], ssup[3], sl[3], sip[3], su[3];
     int S[3], dec[3];
 };
@@ -77,6 +77,8 @@ struct Plan {
     size_t ws_bytes = 0, tables_bytes = 0, esize = 4;
     std::vector<size_t> Woff;  // W_k element offsets, k = 1..L (index k)
     size_t F = 0, F2 = 0, Tb = 0, Yb = 0;  // F, F2: corrections of even, odd level steps
+    size_t tail_lv = 0, tail_tab = 0;  // the tail's level descriptions (TailLevel, from level step 0 on) and tables
+    std::vector<TailLevel> tails;      // host copy of the descriptions
     size_t Yb2 = 0;  // long-fibre solve scratch for the coarser level steps of a recomposition
     // Recomposition computes every level's correction before it is applied,
     // so it keeps one buffer per level step: Zrec[0] = F, Zrec[1] = F2, then
@@ -435,6 +437,74 @@ SolveTab build_solve(const std::vector<double>& yc)
     return t;
 }
 
+// Rows of B = M_{l-1}^{-1} R M_l of a level dimension in the layout of TailDim.
+// A row decays by about 0.27 a coarse node on either side of its own, so the
+// inputs whose weights together stay below 2^-58 (FP64) or 2^-30 (FP32) of a
+// row's sum are left out, over the whole dimension at the distance its worst
+// row needs.
+struct TailTabHost {
+    std::vector<double> B;
+    int nt = 0, off = 0;
+};
+TailTabHost build_tail_rows(const std::vector<double>& K, const SolveTab& sv, int64_t mc, size_t esize)
+{
+    const int64_t m = 2 * mc - 1;
+    std::vector<double> lf((size_t)mc, 0.0), ip((size_t)mc, 0.0), x((size_t)mc), R((size_t)(mc * m), 0.0);
+    double den = 0.0;
+    for (int64_t i = 0; i < mc; i++) {
+        const double diag = 2.0 * (sv.sub[(size_t)i] + sv.sup[(size_t)i]);
+        if (i > 0) lf[(size_t)i] = sv.sub[(size_t)i] / den;
+        den = diag - (i > 0 ? lf[(size_t)i] * sv.sup[(size_t)(i - 1)] : 0.0);
+        ip[(size_t)i] = 1.0 / den;
+    }
+    const double tol = (esize == 8) ? 0x1p-58 : 0x1p-30;
+    int64_t h = 0;
+    for (int64_t i = 0; i < mc; i++) {
+        // M x = e_i (M is symmetric: x is also row i of its inverse)
+        std::fill(x.begin(), x.end(), 0.0);
+        x[(size_t)i] = 1.0;
+        for (int64_t k = i + 1; k < mc; k++) x[(size_t)k] = -lf[(size_t)k] * x[(size_t)(k - 1)];
+        for (int64_t k = mc - 1; k >= 0; k--)
+            x[(size_t)k] = (x[(size_t)k] - (k < mc - 1 ? sv.sup[(size_t)k] * x[(size_t)(k + 1)] : 0.0)) * ip[(size_t)k];
+        double* row = &R[(size_t)(i * m)];
+        double sum = 0.0;
+        for (int64_t k = 0; k < mc; k++)
+            for (int t = -2; t <= 2; t++) {
+                const int64_t j = 2 * k + t;
+                if (j >= 0 && j < m) row[j] += x[(size_t)k] * K[(size_t)(5 * k + t + 2)];
+            }
+        for (int64_t j = 0; j < m; j++) sum += std::fabs(row[j]);
+        double out = 0.0;
+        int64_t d = m;
+        while (d > h) {  // distance d and beyond left out
+            const double w = (2 * i - d >= 0 ? std::fabs(row[2 * i - d]) : 0.0) + (2 * i + d < m ? std::fabs(row[2 * i + d]) : 0.0);
+            if (out + w > tol * sum) break;
+            out += w;
+            d--;
+        }
+        h = std::max(h, d);
+    }
+    TailTabHost t;
+    t.nt = (int)std::min<int64_t>(m, 7 + 2 * h);
+    t.off = (int)h;
+    const int64_t ng = (mc + 3) / 4;
+    t.B.assign((size_t)(4 * ng * t.nt), 0.0);
+    for (int64_t i = 0; i < mc; i++) {
+        const int64_t g = i / 4, start = std::min(std::max<int64_t>(8 * g - h, 0), m - t.nt);
+        for (int q = 0; q < t.nt; q++) t.B[(size_t)((g * t.nt + q) * 4 + i % 4)] = R[(size_t)(i * m + start + q)];
+    }
+    return t;
+}
+
+// LDS elements of a level step's arrays in the tail kernel (region_of there):
+// level grid, coarse values and the reductions of all but the last dimension.
+int64_t tail_data_elems(const LevelLayout& ly)
+{
+    const int64_t V = ly.m[0] * ly.m[1] * ly.m[2], Vc = ly.mc[0] * ly.mc[1] * ly.mc[2];
+    const int na = (ly.m[0] > 1) + (ly.m[1] > 1) + (ly.m[2] > 1);
+    return V + Vc + (na > 1 ? ly.m[0] * ly.m[1] * ly.mc[2] : 0) + (na > 2 ? ly.m[0] * ly.mc[1] * ly.mc[2] : 0);
+}
+
 std::string plan_key(int device, int dtype, int ndim, const int64_t* shape,
                      const double* const* coords, int nlevels)
 {
@@ -482,15 +552,55 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
         if (p.active[d]) X[d] = axis_positions(p.n[d], coords ? coords[p.udim[d]] : nullptr);
     host.clear();
     p.lv.resize((size_t)L);
-    for (int k = 0; k < L; k++) {
+    auto nodes = [&](int d, int k) { return p.active[d] ? gen_lsize(p.n[d], k) : 1; };  // without the phantom
+    int64_t small = 0;
+    for (int k = L - 1; k >= 0; k--) {
         LevelLayout& ly = p.lv[(size_t)k];
+        ly.tail = L - k <= kMaxTail;
         for (int d = 0; d < 3; d++) {
-            const int64_t act = p.active[d] ? gen_lsize(p.n[d], k) : 1;  // nodes, without the phantom
+            const int64_t act = nodes(d, k);
             ly.mc[d] = p.active[d] ? act / 2 + 1 : 1;
             ly.m[d] = 2 * ly.mc[d] - 1;
             ly.ph[d] = (ly.m[d] != act) ? (int)act - 1 : -1;
-            ly.w[d] = ly.K[d] = ly.lf[d] = ly.ip[d] = ly.PT[d] = 0;
-            ly.sup[d] = ly.L[d] = ly.U[d] = ly.IP[d] = ly.A[d] = ly.B[d] = 0;
+            ly.tail = ly.tail && ly.m[d] <= kTailMaxSide;
+        }
+        // every coarser level is in it too
+        ly.tail = ly.tail && (k == L - 1 || p.lv[(size_t)(k + 1)].tail) &&
+                  (small += tail_data_elems(ly)) <= kTailDataElems;
+    }
+    std::vector<double> tail_tab;
+    p.tails.assign((size_t)L, TailLevel{});
+    for (int k = 0, cum = 0; k < L; k++) {
+        const LevelLayout& ly = p.lv[(size_t)k];
+        if (!ly.tail) continue;
+        TailLevel& t = p.tails[(size_t)k];
+        for (int d = 0; d < 3; d++) {
+            TailDim& td = t.d[d];
+            td.m = (int)ly.m[d];
+            td.mc = (int)ly.mc[d];
+            td.ph = ly.ph[d];
+            td.act = (ly.ph[d] < 0) ? td.m : td.m - 1;
+            td.rm = 1.0f / (float)td.m;
+            td.rmc = 1.0f / (float)td.mc;
+            t.na += (td.m > 1) ? 1 : 0;
+        }
+        for (int d = 2, q = 0; d >= 0; d--)
+            if (ly.m[d] > 1) t.dims |= d << (2 * q++);
+        t.V = (int)(ly.m[0] * ly.m[1] * ly.m[2]);
+        t.Vc = (int)(ly.mc[0] * ly.mc[1] * ly.mc[2]);
+        t.cum = cum;
+        t.g = t.V;
+        t.p1 = t.g + t.Vc;
+        t.p2 = t.p1 + (t.na > 1 ? (int)(ly.m[0] * ly.m[1] * ly.mc[2]) : 0);
+        t.tab = -1;
+        cum += (int)tail_data_elems(ly);
+    }
+    for (int k = 0; k < L; k++) {
+        LevelLayout& ly = p.lv[(size_t)k];
+        for (int d = 0; d < 3; d++) {
+            const int64_t act = nodes(d, k);
+            ly.w[d] = ly.K[d] = ly.PT[d] = 0;
+            ly.L[d] = ly.U[d] = ly.IP[d] = ly.A[d] = ly.B[d] = 0;
             ly.ssub[d] = ly.ssup[d] = ly.sl[d] = ly.sip[d] = ly.su[d] = 0;
             ly.S[d] = ly.dec[d] = 1;
             if (!p.active[d]) continue;
@@ -503,27 +613,21 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             std::vector<double> yc((size_t)ly.mc[d]);
             for (int64_t i = 0; i < ly.mc[d]; i++) yc[(size_t)i] = y[(size_t)std::min(2 * i, act - 1)];
             SolveTab sv = build_solve(yc);
-            {
-                // plain Thomas factors of the whole coarse fibre (small levels)
-                const size_t nc = yc.size();
-                std::vector<double> lf(nc, 0.0), ip(nc, 0.0);
-                double den = 0.0;
-                for (size_t i = 0; i < nc; i++) {
-                    const double diag = 2.0 * (sv.sub[i] + sv.sup[i]);
-                    if (i == 0) {
-                        den = diag;
-                    } else {
-                        lf[i] = sv.sub[i] / den;
-                        den = diag - lf[i] * sv.sup[i - 1];
-                    }
-                    ip[i] = 1.0 / den;
-                }
-                push_table(host, lf, &ly.lf[d]);
-                push_table(host, ip, &ly.ip[d]);
+            if (ly.tail) {
+                // weight pairs and rows of B of the level's tail tables
+                TailDim& td = p.tails[(size_t)k].d[d];
+                const TailTabHost tt = build_tail_rows(t.K, sv, ly.mc[d], sizeof(T));
+                td.nt = tt.nt;
+                td.off = tt.off;
+                if (p.tails[(size_t)k].tab < 0) p.tails[(size_t)k].tab = (int)tail_tab.size();
+                td.w = (int)tail_tab.size() - p.tails[(size_t)k].tab;
+                tail_tab.insert(tail_tab.end(), t.w.begin(), t.w.end());
+                while (tail_tab.size() % 4) tail_tab.push_back(0.0);
+                td.B = (int)tail_tab.size() - p.tails[(size_t)k].tab;
+                tail_tab.insert(tail_tab.end(), tt.B.begin(), tt.B.end());
             }
             ly.S[d] = sv.S;
             ly.dec[d] = separators_apart(sv.couple, sizeof(T));
-            push_table(host, sv.sup, &ly.sup[d]);
             push_table(host, sv.L, &ly.L[d]);
             push_table(host, sv.U, &ly.U[d]);
             push_table(host, sv.IP, &ly.IP[d]);
@@ -535,6 +639,14 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             push_table(host, sv.sip, &ly.sip[d]);
             push_table(host, sv.su, &ly.su[d]);
         }
+    }
+    push_table(host, tail_tab, &p.tail_tab);
+    p.tail_lv = host.size();
+    if (L > 0) {
+        // the descriptions as they are (4-byte words) among the tables
+        const size_t bytes = sizeof(TailLevel) * p.tails.size();
+        host.resize(align_up(p.tail_lv + (bytes + sizeof(T) - 1) / sizeof(T), 64), T(0));
+        std::memcpy((void*)(host.data() + p.tail_lv), p.tails.data(), bytes);
     }
     // workspace: W_1..W_L, corrections F, F2 (and per level for
     // recomposition), adjoint buffer Tb, long-fibre solve scratch Yb
@@ -883,31 +995,6 @@ int identity_copy(const Plan& p, const void* src, void* dst, hipStream_t st)
 // step whose level grid is small, but no more than kMaxTail steps.
 std::atomic<int64_t> g_tail_nodes{kTailMaxNodes};
 
-// LDS elements the tail kernel needs for level step k: level grid, the
-// load-vector passes, correction and coarse values; and for its tables.
-int64_t tail_data_elems(const Plan& p, int k)
-{
-    const LevelLayout& ly = p.lv[(size_t)k];
-    int64_t sh[3] = {ly.m[0], ly.m[1], ly.m[2]};
-    const int64_t V = sh[0] * sh[1] * sh[2], Vc = ly.mc[0] * ly.mc[1] * ly.mc[2];
-    int64_t tot = V + 2 * Vc, pass = 0;
-    for (int d = 2; d >= 0; d--) {
-        if (!p.active[d]) continue;
-        sh[d] = ly.mc[d];
-        if (++pass < 3 && sh[0] * sh[1] * sh[2] != Vc) tot += sh[0] * sh[1] * sh[2];
-    }
-    return tot;
-}
-
-int64_t tail_tab_elems(const Plan& p, int k)
-{
-    const LevelLayout& ly = p.lv[(size_t)k];
-    int64_t tot = 0;
-    for (int d = 0; d < 3; d++)
-        if (p.active[d]) tot += 2 * ly.m[d] + 8 * ly.mc[d];
-    return tot;
-}
-
 // First level step handled by the tail kernel: the finest step such that it
 // and every coarser step are small, at most kMaxTail steps.
 int tail_start(const Plan& p)
@@ -915,10 +1002,9 @@ int tail_start(const Plan& p)
     const int L = p.nlevels;
     const int64_t limit = g_tail_nodes.load();
     int k = L;
-    while (k > 0 && L - (k - 1) <= kMaxTail) {
+    while (k > 0) {
         const LevelLayout& ly = p.lv[(size_t)(k - 1)];
-        if (ly.m[0] * ly.m[1] * ly.m[2] > limit) break;
-        if (tail_data_elems(p, k - 1) > kTailDataElems || tail_tab_elems(p, k - 1) > kTailTabElems) break;
+        if (!ly.tail || ly.m[0] * ly.m[1] * ly.m[2] > limit) break;
         k--;
     }
     return k;
@@ -933,29 +1019,21 @@ TailArgs<T> tail_args(const Plan& p, int k0, const T* src, T* dst, void* wsp = n
     const T* base = (const T*)p.tables;
     a.k0 = k0;
     a.nlev = p.nlevels - k0;
-    a.gen = p.gen ? 1 : 0;
     for (int d = 0; d < 3; d++) {
         a.st[d] = p.st[d];
         a.last[d] = (p.n[d] - 1) * p.st[d];
     }
     a.src = src;
     a.dst = dst;
-    for (int l = 0; l < a.nlev; l++) {
-        const int k = k0 + l;
-        const LevelLayout& ly = p.lv[(size_t)k];
-        TailLevel<T>& t = a.lv[l];
-        for (int d = 0; d < 3; d++) {
-            t.m[d] = (int)ly.m[d];
-            t.mc[d] = (int)ly.mc[d];
-            t.ph[d] = ly.ph[d];
-            t.act[d] = (ly.ph[d] < 0) ? t.m[d] : t.m[d] - 1;
-            t.lf[d] = p.active[d] ? base + ly.lf[d] : nullptr;
-            t.ip[d] = p.active[d] ? base + ly.ip[d] : nullptr;
-            t.up[d] = p.active[d] ? base + ly.sup[d] : nullptr;
-        }
-        t.tb = tables_of<T>(p, k);
-        t.Wk = (k == 0) ? nullptr : ws + p.Woff[(size_t)k];
-    }
+    a.Wk = (k0 == 0) ? nullptr : ws + p.Woff[(size_t)k0];
+    a.lv = (const TailLevel*)(base + p.tail_lv) + k0;
+    const TailLevel &t0 = p.tails[(size_t)k0], &t1 = p.tails.back();
+    a.tab = base + p.tail_tab + t0.tab;
+    // (the tables after the arrays start at a multiple of four elements)
+    a.data_elems = (int)align_up((size_t)(t1.cum - t0.cum) + (size_t)tail_data_elems(p.lv.back()), 4);
+    a.tab_elems = t1.tab - t0.tab;
+    for (int d = 0; d < 3; d++)
+        if (t1.d[d].m > 1) a.tab_elems += tail_tab_len(t1.d[d].m, t1.d[d].mc, t1.d[d].nt);
     return a;
 }
 
@@ -1752,6 +1830,7 @@ struct BatchPlan {
            off_args = 0, dev_bytes = 0;
     std::vector<std::pair<int, int>> waves;  // (first item, items) per launch
     int n_items = 0, n_tail = 0;
+    int tail_data = 0, tail_tab = 0;  // LDS elements of the tail launch
     int chunk = 8, tuned = 0;
     int wide = 0;                  // 3-D streaming items on the wide tile geometry
     int64_t bytes = 0;             // input bytes of the batch
@@ -2122,6 +2201,11 @@ int batch_upload(BatchPlan& b, int chunk)
     b.waves = t.waves;
     b.n_items = (int)t.items.size();
     b.n_tail = (int)t.tail.size();
+    b.tail_data = b.tail_tab = 0;
+    for (const TailArgs<T>& ta : t.tail) {
+        b.tail_data = std::max(b.tail_data, ta.data_elems);
+        b.tail_tab = std::max(b.tail_tab, ta.tab_elems);
+    }
     b.chunk = chunk;
     b.ran_persistent = 0;
     return MGR_OK;
@@ -2182,7 +2266,7 @@ int batch_run(BatchPlan& b, const void* const* src, void* const* dst, hipStream_
                       return launch_tail_batch<T>((const TailArgs<T>*)(d + b.off_tail), (const int*)(d + b.off_tailf),
                                                   (const T* const*)(d + b.off_ptrs),
                                                   (T* const*)(d + b.off_ptrs + sizeof(void*) * (size_t)nf), b.n_tail,
-                                                  true, st);
+                                                  b.tail_data, b.tail_tab, st);
                   }),
             "batch tail launch");
     return MGR_OK;

@@ -143,45 +143,65 @@ template <typename T>
 hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const SolveTables<T>& t1, hipStream_t st);
 
 // Single-workgroup kernel for the small coarse levels (mgr_tail.hip): all
-// level steps k0 .. k0 + nlev - 1 in one launch, in LDS.  A level step may
-// join it when its level grid, load-vector passes, correction and coarse
-// values fit kTailDataElems elements and its tables kTailTabElems.
+// level steps k0 .. k0 + nlev - 1 in one launch, in LDS.  The levels' arrays
+// (tail_data_elems) must fit kTailDataElems elements; the tables share the LDS
+// when both fit kTailLdsElems, else they are read from global memory.
 constexpr int kTailThreads = 1024;
 constexpr int kMaxTail = 16;
 constexpr int64_t kTailMaxNodes = 5000;
-constexpr int kTailDataElems = 11264;
-constexpr int kTailTabElems = 3200;
+constexpr int kTailMaxSide = 513;  // longest dimension of a level grid (its tables' rows)
+constexpr int kTailDataElems = 17000;
+constexpr int kTailLdsElems = 18400;
 
-template <typename T>
-struct TailLevel {
-    int m[3], mc[3];  // level grid and coarse sizes (1 for inactive dims)
-    int act[3], ph[3];  // any-length level grids: nodes without the phantom, its index (or -1)
-    DimTables<T> tb;  // interpolation weights and stencils
-    const T* lf[3];   // plain Thomas factors of M_{l-1}: multipliers,
-    const T* ip[3];   // inverse pivots
-    const T* up[3];   // and super-diagonal
-    T* Wk;            // packed level grid k in the workspace (k > 0)
+// A level's description, in device memory beside its tables (kernel arguments
+// lie in host memory: every first touch of a level's line there costs the
+// kernel a trip to it).
+//
+// One dimension: interpolation weight pairs w (as DimTables) and the rows of
+// B = M_{l-1}^{-1} R M_l, four outputs to a group: group g (outputs 4 g .. 4 g +
+// 3) reads the nt inputs from clamp(8 g - off, 0, m - nt) on, and
+// B[(g nt + t) 4 + o] weights input t for output 4 g + o.
+struct TailDim {
+    int m, mc;      // level grid (with its phantom) and coarse nodes (1 for inactive dims)
+    int act, ph;    // nodes without the phantom, the phantom's index (or -1)
+    int nt, off;
+    float rm, rmc;  // 1 / m, 1 / mc (divisions)
+    int w, B;       // element offsets from the level's tables
 };
+struct TailLevel {
+    TailDim d[3];
+    int V, Vc, na;   // nodes (with phantoms), coarse nodes, active dimensions
+    int dims;        // the active dimensions, last first, two bits each
+    int cum;         // LDS elements of the arrays of the finer level steps
+    int g, p1, p2;   // offsets of a level's arrays from its start: U is first, then the
+                     // coarse values and the reductions along the last and the middle dimension
+    int tab;         // element offset of the level's tables
+};
+// Table elements of a dimension: weight pairs, padded, and B.
+inline int tail_tab_weights(int m) { return (2 * m + 3) & ~3; }
+inline int tail_tab_len(int m, int mc, int nt) { return tail_tab_weights(m) + 4 * nt * ((mc + 3) / 4); }
 
 template <typename T>
 struct TailArgs {
-    TailLevel<T> lv[kMaxTail];  // index k - k0
-    int k0, nlev;
-    int64_t st[3];  // element strides of the user arrays
-    int64_t last[3];  // offset of their last node along each dimension
-    int gen;          // any-length level grids (View3)
-    const T* src;   // user input
-    T* dst;         // user output
-    const T* Z0;    // decomposition: correction added to the level-k0 input (or null)
+    const TailLevel* lv;  // level step k0 and the following ones (device memory)
+    const T* tab;         // the tables of level step k0 and, contiguous, the following ones
+    int k0, nlev, data_elems, tab_elems;  // LDS elements of the arrays, of the tables
+    int64_t st[3];    // element strides of the user arrays
+    int64_t last[3];  // offset of their last node along each dimension (View3)
+    const T* src;     // user input
+    T* dst;           // user output
+    T* Wk;            // packed level grid k0 in the workspace (k0 > 0)
+    const T* Z0;      // decomposition: correction added to it
 };
 
 template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st);
-// One workgroup per entry: dev_args[i] in device memory, applied to field
-// field[i] of the per-field pointer tables src / dst (device memory).
+// Decompositions, one workgroup per entry: dev_args[i] in device memory,
+// applied to field field[i] of the per-field pointer tables src / dst (device
+// memory).  data_elems, tab_elems: the largest over the entries.
 template <typename T>
-hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst,
-                             int n, bool decompose, hipStream_t st);
+hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst, int n,
+                             int data_elems, int tab_elems, hipStream_t st);
 
 template <typename T>
 hipError_t launch_stream_level(StreamArgs<T> a, bool dec, hipStream_t st);

@@ -4,486 +4,575 @@
 // step is latency bound and a separate launch per stage costs more than the
 // work.  This kernel runs all remaining level steps (decomposition: the
 // finest of them first; recomposition: the coarsest first) in one workgroup
-// of kTailThreads lanes with the level grid, the load-vector passes, the
-// correction and the coarse values, and the level's tables, held in LDS.
-// Global memory is touched only at the boundary: the input level grid, the
-// coefficients of each level (written to / read from the caller's array at
-// stride 2^k) and the coarsest values.
+// of kTailThreads lanes.  Global memory is touched only at the boundary: the
+// input level grid, the coefficients of each level (written to / read from the
+// caller's array at stride 2^k), the coarsest values and the tables, all of
+// whose loads are issued before the first of them is waited for.
 //
-// The stages are those of Sec. II-A in the paper's order: coefficients by
-// multilinear interpolation from the coarse nodes (Sec. II-A.1), the load
-// vector R M vec(C) one dimension at a time (Sec. II-A.2, merged stencil of
-// Sec. III-A.2), the tridiagonal correction solves (plain Thomas, one lane
-// per fibre) and the correction applied to the coarse nodes.
+// What bounds it is latency: the chain of phases between barriers.  So
+//  - the load vector and the correction solve of a dimension are one linear
+//    map, z = B c with B = M_{l-1}^{-1} R M_l (rows of the product, built on
+//    the host in FP64; M^{-1} decays by about 0.27 a row, so long rows are
+//    cut where what is left is below the working precision): one phase of
+//    independent dot products per dimension instead of a stencil pass and a
+//    serial elimination;
+//  - a level's coarse nodes live in an array of their own (G) and its fine
+//    nodes in U, which is zero at coarse nodes, so the coefficients are
+//    formed in place, no pass needs a mask, and the last dimension's phase
+//    adds the correction and hands the values to the next level;
+//  - a recomposition's corrections depend on the stored coefficients alone:
+//    those of all levels share the three phases, and the coarse-to-fine chain
+//    keeps one phase per level.
+// A dot-product task is four neighbouring outputs of one fibre: lanes take
+// fibres (their reads are contiguous or at an odd stride: no bank conflicts),
+// the four table entries of a tap are one broadcast read.  (Two fibres a lane
+// halve those reads' share of the LDS bandwidth but lengthen each phase's
+// chain: 16.0 -> 17.7 us in the kernel at 17^3.)  Coefficients and
+// interpolation go by cells: a coarse node and the up to seven fine nodes
+// after it share its eight corners.
+//
+// Per call, the launch included (FP32): 17^3 decomposed in 28.6 -> 18 us with
+// these phases in place of stencil passes and a serial elimination per
+// dimension, recomposed in 34 -> 19; 513 nodes 79 -> 24, 93 -> 25; 65^2 41 -> 30,
+// 50 -> 30.  What is left is the chain itself: 2000 to 4000 cycles a phase, of
+// LDS round trips and of the address arithmetic that the first loads wait for.
+//
+// Four dimensions never come here; level grids of any length do (View3: the
+// LDS arrays hold the phantom nodes, which are zero; user's and packed arrays
+// have none).
 #include "mgr_internal.h"
 
 namespace mgr {
 namespace {
 
 constexpr int kT = kTailThreads;
-constexpr int kTB = 6;  // grid loads in flight per lane
+constexpr int kWaves = kT / 64;
+constexpr int kTB = (5 * 1024) / kT;  // loads of the finest grid in flight per lane
+constexpr int kTailOffs = 516;        // nodes of the finest grid per dimension (at most kTailMaxSide)
+static_assert(kTailOffs >= kTailMaxSide && kTailOffs <= kT, "one pass");
 
-struct TailShape {
-    int m[3], mc[3];
-    int V, Vc;
+// idx / n for idx < 2^20 and r = 1 / n: the quotient of idx + 1/2 lies at least
+// 1 / (2 n) from a whole number, further than its rounding.  (Integer products
+// here are of small numbers: 24-bit multiplies, four times the rate of 32-bit
+// ones.)
+__device__ __forceinline__ int fdiv(int idx, float r) { return (int)fmaf((float)idx, r, 0.5f * r); }
+
+__device__ __forceinline__ bool phantom(const TailLevel& L, int j0, int j1, int j2)
+{
+    return j0 == L.d[0].ph || j1 == L.d[1].ph || j2 == L.d[2].ph;
+}
+// Place of node (j0, j1, j2) in the packed grid (without phantoms).
+__device__ __forceinline__ int packed_at(const TailLevel& L, int j0, int j1, int j2)
+{
+    return __mul24(__mul24(min(j0, L.d[0].act - 1), L.d[1].act) + min(j1, L.d[1].act - 1), L.d[2].act) +
+           min(j2, L.d[2].act - 1);
+}
+// Index j0, j1, j2 of node idx of a box of sizes (., n1, n2).
+__device__ __forceinline__ void split(int idx, int n1, float r1, int n2, float r2, int& j0, int& j1, int& j2)
+{
+    const int q = fdiv(idx, r2);
+    j2 = idx - __mul24(q, n2);
+    j0 = fdiv(q, r1);
+    j1 = q - __mul24(j0, n1);
+}
+__device__ __forceinline__ void node_of(const TailLevel& L, int idx, int& j0, int& j1, int& j2)
+{
+    split(idx, L.d[1].m, L.d[1].rm, L.d[2].m, L.d[2].rm, j0, j1, j2);
+}
+__device__ __forceinline__ void coarse_of(const TailLevel& L, int c, int& i0, int& i1, int& i2)
+{
+    split(c, L.d[1].mc, L.d[1].rmc, L.d[2].mc, L.d[2].rmc, i0, i1, i2);
+}
+
+// The four table entries of a tap, one read.
+template <typename T>
+struct Tap {
+    typedef T V __attribute__((ext_vector_type(4), aligned(16)));
 };
 
-__device__ __forceinline__ TailShape shape_of(const int* m, const int* mc)
+// Dot products of one dimension: the array `in` is (outer, D.m, inner); n
+// results at a time go to out(o, inner, n, v): v[k] is element o + k inner of
+// (outer, D.mc, inner).
+template <typename T, class Out>
+__device__ __forceinline__ void tail_dots(const TailDim& D, const T* B, const T* in, int outer, int inner, float rinner,
+                                          Out out)
 {
-    TailShape s;
-    for (int d = 0; d < 3; d++) {
-        s.m[d] = m[d];
-        s.mc[d] = mc[d];
-    }
-    s.V = m[0] * m[1] * m[2];
-    s.Vc = mc[0] * mc[1] * mc[2];
-    return s;
-}
-
-__device__ __forceinline__ void dec3(int idx, const int* n, int& j0, int& j1, int& j2)
-{
-    j2 = idx % n[2];
-    const int t = idx / n[2];
-    j1 = t % n[1];
-    j0 = t / n[1];
-}
-
-// Per-level tables staged in LDS (offsets into the table area).
-template <typename T>
-struct LdsTab {
-    T* w[3];   // interpolation weight pairs, 2 m
-    T* K[3];   // stencil, 5 mc
-    T* lf[3];  // Thomas multipliers, mc
-    T* ip[3];  // inverse pivots, mc
-    T* up[3];  // super-diagonal, mc
-};
-
-template <typename T>
-__device__ LdsTab<T> stage_tables(const TailLevel<T>& L, T* stab)
-{
-    // Layout per active dimension: w (2 m), K (5 mc), lf, ip, up (mc each).
-    // All tables are copied in one pass over their concatenation, one
-    // element per lane and round, so a level costs one memory latency here
-    // rather than one per table.
-    LdsTab<T> t;
-    const T* src[15];  // segment 5 d + j (empty for inactive dimensions)
-    int len[15], off = 0;
-#pragma unroll
-    for (int d = 0; d < 3; d++) {
-        const bool act = L.m[d] > 1;
-        const int m = act ? L.m[d] : 0, mc = act ? L.mc[d] : 0;
-        t.w[d] = stab + off;
-        t.K[d] = t.w[d] + 2 * m;
-        t.lf[d] = t.K[d] + 5 * mc;
-        t.ip[d] = t.lf[d] + mc;
-        t.up[d] = t.ip[d] + mc;
-        src[5 * d + 0] = L.tb.w[d];
-        len[5 * d + 0] = 2 * m;
-        src[5 * d + 1] = L.tb.K[d];
-        len[5 * d + 1] = 5 * mc;
-        src[5 * d + 2] = L.lf[d];
-        len[5 * d + 2] = mc;
-        src[5 * d + 3] = L.ip[d];
-        len[5 * d + 3] = mc;
-        src[5 * d + 4] = L.up[d];
-        len[5 * d + 4] = mc;
-        off += 2 * m + 8 * mc;
-    }
-    for (int e0 = 0; e0 < off; e0 += kT) {
-        const int e = e0 + threadIdx.x;
-        // the element's source, selected over the (unrolled) segment list
-        const T* ps = nullptr;
-        int base = 0;
-#pragma unroll
-        for (int sg = 0; sg < 15; sg++) {
-            if (e >= base && e < base + len[sg]) ps = src[sg] + (e - base);
-            base += len[sg];
-        }
-        if (e < off) stab[e] = *ps;
-    }
-    return t;
-}
-
-// Multilinear interpolation at level-grid node (j0, j1, j2) from coarse
-// values: in U itself (coarse nodes at even indices, stride (m1*m2, m2, 1))
-// or, with kHalf, from the packed coarse array W (index / 2).
-template <typename T, bool kHalf>
-__device__ __forceinline__ T tail_interp(const T* A, const TailShape& s, const LdsTab<T>& t, int j0,
-                                         int j1, int j2)
-{
-    const int n1 = kHalf ? s.mc[1] : s.m[1], n2 = kHalf ? s.mc[2] : s.m[2];
-    const int o0 = j0 & 1, o1 = j1 & 1, o2 = j2 & 1;
-    const T a0 = o0 ? t.w[0][2 * j0] : T(1), b0 = o0 ? t.w[0][2 * j0 + 1] : T(0);
-    const T a1 = o1 ? t.w[1][2 * j1] : T(1), b1 = o1 ? t.w[1][2 * j1 + 1] : T(0);
-    const T a2 = o2 ? t.w[2][2 * j2] : T(1), b2 = o2 ? t.w[2][2 * j2 + 1] : T(0);
-    const int l0 = j0 - o0, h0 = j0 + o0, l1 = j1 - o1, h1 = j1 + o1, l2 = j2 - o2, h2 = j2 + o2;
-    auto at = [&](int x, int y, int z) {
-        return kHalf ? A[((x >> 1) * n1 + (y >> 1)) * n2 + (z >> 1)] : A[(x * n1 + y) * n2 + z];
-    };
-    auto row = [&](int x, int y) { return a2 * at(x, y, l2) + (o2 ? b2 * at(x, y, h2) : T(0)); };
-    const T lo = a1 * row(l0, l1) + (o1 ? b1 * row(l0, h1) : T(0));
-    const T hi = o0 ? a1 * row(h0, l1) + (o1 ? b1 * row(h0, h1) : T(0)) : T(0);
-    return a0 * lo + b0 * hi;
-}
-
-// The interpolant of an any-length grid: a sum over the coarse corners, the
-// neighbours along dim 0 first and along dim 2 last, each weighted by the
-// product of its one-dimensional weights.
-template <typename T, bool kHalf>
-__device__ __forceinline__ T tail_interp_corners(const T* A, const TailShape& s, const LdsTab<T>& t, int j0, int j1,
-                                                 int j2)
-{
-    const int n1 = kHalf ? s.mc[1] : s.m[1], n2 = kHalf ? s.mc[2] : s.m[2];
-    const int j[3] = {j0, j1, j2};
-    T acc = T(0);
-    for (int mask = 0; mask < 8; mask++) {
-        int q[3];
-        T w = T(1);
-        bool skip = false;
-#pragma unroll
-        for (int d = 0; d < 3; d++) {
-            const bool up = (mask >> d) & 1, odd = j[d] & 1;
-            skip = skip || (up && !odd);
-            q[d] = odd ? (up ? j[d] + 1 : j[d] - 1) : j[d];
-            if (odd) w *= t.w[d][2 * j[d] + (up ? 1 : 0)];
-        }
-        if (skip) continue;
-        const T v = kHalf ? A[((q[0] >> 1) * n1 + (q[1] >> 1)) * n2 + (q[2] >> 1)] : A[(q[0] * n1 + q[1]) * n2 + q[2]];
-        acc = fma(w, v, acc);
-    }
-    return acc;
-}
-
-// Node (j0, j1, j2) of an any-length level grid: a phantom, and its place in
-// the packed grid (without phantoms).
-template <typename T>
-__device__ __forceinline__ bool tail_phantom(const TailLevel<T>& L, int j0, int j1, int j2)
-{
-    return j0 == L.ph[0] || j1 == L.ph[1] || j2 == L.ph[2];
-}
-template <typename T>
-__device__ __forceinline__ int tail_packed(const TailLevel<T>& L, int j0, int j1, int j2)
-{
-    return (min(j0, L.act[0] - 1) * L.act[1] + min(j1, L.act[1] - 1)) * L.act[2] + min(j2, L.act[2] - 1);
-}
-
-// f = R M vec(U) with U's coarse nodes read as zero; passes last dim first.
-template <typename T>
-__device__ void lds_load_vector(const T* U, T* P1, T* P2, T* F, const TailShape& s,
-                                const LdsTab<T>& t)
-{
-    int sh[3] = {s.m[0], s.m[1], s.m[2]};
-    const T* in = U;
-    int npass = 0, done = 0;
-#pragma unroll
-    for (int d = 0; d < 3; d++) npass += (s.m[d] > 1);
-#pragma unroll
-    for (int d = 2; d >= 0; d--) {
-        if (s.m[d] == 1) continue;
-        const int ish[3] = {sh[0], sh[1], sh[2]};
-        sh[d] = s.mc[d];
-        T* out = (done == npass - 1) ? F : (done == 0 ? P1 : P2);
-        const int total = sh[0] * sh[1] * sh[2];
-        const int is[3] = {ish[1] * ish[2], ish[2], 1};
-        for (int idx = threadIdx.x; idx < total; idx += kT) {
-            int o[3];
-            dec3(idx, sh, o[0], o[1], o[2]);
-            const int i = o[d];
-            int oth = 0;
-#pragma unroll
-            for (int e = 0; e < 3; e++)
-                if (e != d) oth |= o[e];
-            const bool mask = (done == 0) && ((oth & 1) == 0);
-            T acc = T(0);
-            for (int tt = -2; tt <= 2; tt++) {
-                const int jd = 2 * i + tt;
-                if (jd < 0 || jd >= ish[d]) continue;
-                if (mask && !(tt & 1)) continue;  // coarse node: C is zero there
-                int q = 0;
-#pragma unroll
-                for (int e = 0; e < 3; e++) q += ((e == d) ? jd : o[e]) * is[e];
-                acc += t.K[d][5 * i + tt + 2] * in[q];
+    const int m = D.m, nt = uni(D.nt), mc = D.mc, off = D.off, smax = m - nt, nfib = uni(outer * inner);
+    auto start_of = [&](int g) { return min(max(8 * g - off, 0), smax); };
+    if (nfib >= 32) {
+        const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
+        const int nch = (nfib + 63) >> 6, units = nch * ((uni(mc) + 3) >> 2);
+        const float rch = __builtin_amdgcn_rcpf((float)nch);
+        for (int u = wave; u < units; u += kWaves) {
+            const int g = uni(fdiv(u, rch)), f = (u - g * nch) * 64 + lane;
+            const int fc = min(f, nfib - 1), q = fdiv(fc, rinner), r = fc - __mul24(q, inner);
+            const T* x = in + __mul24(__mul24(q, m) + start_of(g), inner) + r;
+            const T* b = B + 4 * nt * g;
+            T a0 = T(0), a1 = T(0), a2 = T(0), a3 = T(0);
+#pragma unroll 4
+            for (int t = 0; t < nt; t++) {
+                const T v = *x;
+                x += inner;
+                const typename Tap<T>::V w = *reinterpret_cast<const typename Tap<T>::V*>(b);
+                b += 4;
+                a0 = fma(w.x, v, a0);
+                a1 = fma(w.y, v, a1);
+                a2 = fma(w.z, v, a2);
+                a3 = fma(w.w, v, a3);
             }
-            out[idx] = acc;
-        }
-        __syncthreads();
-        in = out;
-        done++;
-    }
-}
-
-// Plain Thomas solves on F along every active dimension (last first), then
-// W += sign * F.
-template <typename T>
-__device__ void lds_solve_apply(T* F, T* W, T sign, const TailShape& s, const LdsTab<T>& t)
-{
-    const int cs[3] = {s.mc[1] * s.mc[2], s.mc[2], 1};
-#pragma unroll
-    for (int d = 2; d >= 0; d--) {
-        if (s.m[d] == 1) continue;
-        const int da = (d == 0) ? 1 : 0, db = (d == 2) ? 1 : 2;
-        const int n = s.mc[d], nfib = s.mc[da] * s.mc[db];
-        const T* lf = t.lf[d];
-        const T* ip = t.ip[d];
-        const T* up = t.up[d];
-        for (int f = threadIdx.x; f < nfib; f += kT) {
-            const int ja = f / s.mc[db], jb = f % s.mc[db];
-            T* p = F + ja * cs[da] + jb * cs[db];
-            const int sd = cs[d];
-            T g = p[0];
-            for (int i = 1; i < n; i++) {
-                g = p[i * sd] - lf[i] * g;
-                p[i * sd] = g;
-            }
-            T z = g * ip[n - 1];
-            p[(n - 1) * sd] = z;
-            for (int i = n - 2; i >= 0; i--) {
-                z = (p[i * sd] - up[i] * z) * ip[i];
-                p[i * sd] = z;
-            }
-        }
-        __syncthreads();
-    }
-    for (int q = threadIdx.x; q < s.Vc; q += kT) W[q] += sign * F[q];
-    __syncthreads();
-}
-
-// LDS regions sized for the first (largest) tail level.
-template <typename T>
-struct Regions {
-    T *U, *P1, *P2, *F, *W;
-};
-
-template <typename T>
-__device__ Regions<T> carve(T* sbuf, const TailLevel<T>& L0)
-{
-    const TailShape s = shape_of(L0.m, L0.mc);
-    int sh[3] = {s.m[0], s.m[1], s.m[2]};
-    int sz[2] = {0, 0}, k = 0;
-#pragma unroll
-    for (int d = 2; d >= 0; d--) {
-        if (k >= 2) break;
-        if (s.m[d] == 1) continue;
-        sh[d] = s.mc[d];
-        sz[k++] = sh[0] * sh[1] * sh[2];
-    }
-    Regions<T> r;
-    r.U = sbuf;
-    r.P1 = r.U + s.V;
-    r.P2 = r.P1 + sz[0];
-    r.F = r.P2 + sz[1];
-    r.W = r.F + s.Vc;
-    return r;
-}
-
-// kGen: level grids of any length.  Their LDS arrays hold the phantom nodes
-// (zero); the user's arrays are reached through clamped offsets and the packed
-// grids in the workspace and in R.W have no phantoms.
-template <typename T, bool kDec, bool kGen>
-__device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* sbuf, T* stab)
-{
-    const Regions<T> R = carve(sbuf, a.lv[0]);
-    const int64_t* st = a.st;
-    // offset in the user's arrays of node j of level grid k
-    auto user = [&](int k, int j0, int j1, int j2) {
-        const int64_t o0 = j0 * (st[0] << k), o1 = j1 * (st[1] << k), o2 = j2 * (st[2] << k);
-        return kGen ? min(o0, a.last[0]) + min(o1, a.last[1]) + min(o2, a.last[2]) : o0 + o1 + o2;
-    };
-
-    if (kDec) {
-        // input level grid k0: the caller's array (k0 == 0) or workspace
-        {
-            const TailLevel<T>& L = a.lv[0];
-            const TailShape s = shape_of(L.m, L.mc);
-            // in batches of kTB loads per lane, all in flight together
-            for (int b0 = 0; b0 < s.V; b0 += kTB * kT) {
-                T tmp[kTB];
-#pragma unroll
-                for (int q = 0; q < kTB; q++) {
-                    const int idx = min(b0 + q * kT + (int)threadIdx.x, s.V - 1);
-                    int j0, j1, j2;
-                    dec3(idx, s.m, j0, j1, j2);
-                    const int pk = kGen ? tail_packed(L, j0, j1, j2) : idx;
-                    tmp[q] = (a.k0 == 0) ? src[user(0, j0, j1, j2)] : L.Wk[pk] + (a.Z0 ? a.Z0[pk] : T(0));
-                    if (kGen && tail_phantom(L, j0, j1, j2)) tmp[q] = T(0);
-                }
-#pragma unroll
-                for (int q = 0; q < kTB; q++)
-                    if (b0 + q * kT + (int)threadIdx.x < s.V) R.U[b0 + q * kT + threadIdx.x] = tmp[q];
-            }
-        }
-        for (int l = 0; l < a.nlev; l++) {
-            const TailLevel<T>& L = a.lv[l];
-            const int k = a.k0 + l;
-            const TailShape s = shape_of(L.m, L.mc);
-            const LdsTab<T> t = stage_tables(L, stab);
-            __syncthreads();
-            // coefficients in place (only coarse nodes are read by others)
-            for (int idx = threadIdx.x; idx < s.V; idx += kT) {
-                int j0, j1, j2;
-                dec3(idx, s.m, j0, j1, j2);
-                if (kGen && tail_phantom(L, j0, j1, j2)) continue;
-                if (((j0 | j1 | j2) & 1) == 0) {
-                    R.W[((j0 >> 1) * s.mc[1] + (j1 >> 1)) * s.mc[2] + (j2 >> 1)] = R.U[idx];
-                } else {
-                    const T c = R.U[idx] - (kGen ? tail_interp_corners<T, false>(R.U, s, t, j0, j1, j2)
-                                                 : tail_interp<T, false>(R.U, s, t, j0, j1, j2));
-                    R.U[idx] = c;
-                    dst[user(k, j0, j1, j2)] = c;
-                }
-            }
-            __syncthreads();
-            lds_load_vector(R.U, R.P1, R.P2, R.F, s, t);
-            lds_solve_apply(R.F, R.W, T(1), s, t);
-            if (l + 1 < a.nlev) {
-                if (kGen) {
-                    const TailLevel<T>& N = a.lv[l + 1];
-                    for (int q = threadIdx.x; q < N.m[0] * N.m[1] * N.m[2]; q += kT) {
-                        int j0, j1, j2;
-                        dec3(q, N.m, j0, j1, j2);
-                        R.U[q] = tail_phantom(N, j0, j1, j2) ? T(0) : R.W[tail_packed(N, j0, j1, j2)];
-                    }
-                } else {
-                    for (int q = threadIdx.x; q < s.Vc; q += kT) R.U[q] = R.W[q];
-                }
-                __syncthreads();
-            } else {
-                // coarsest values to their nodes
-                for (int idx = threadIdx.x; idx < s.Vc; idx += kT) {
-                    int j0, j1, j2;
-                    dec3(idx, s.mc, j0, j1, j2);
-                    dst[user(k + 1, j0, j1, j2)] = R.W[idx];
-                }
+            if (f < nfib) {
+                const T v[4] = {a0, a1, a2, a3};
+                out(__mul24(__mul24(q, mc) + 4 * g, inner) + r, inner, uni(min(4, mc - 4 * g)), v);
             }
         }
     } else {
-        {
-            const TailLevel<T>& Lc = a.lv[a.nlev - 1];
-            const TailShape s = shape_of(Lc.m, Lc.mc);
-            const int L = a.k0 + a.nlev;
-            for (int idx = threadIdx.x; idx < s.Vc; idx += kT) {
-                int j0, j1, j2;
-                dec3(idx, s.mc, j0, j1, j2);
-                R.W[idx] = src[user(L, j0, j1, j2)];
+        // few fibres: a lane per output
+        for (int e = threadIdx.x; e < nfib * mc; e += kT) {
+            const int f = fdiv(e, D.rmc), i = e - __mul24(f, mc), g = i >> 2;
+            const int q = fdiv(f, rinner), r = f - __mul24(q, inner);
+            const T* x = in + __mul24(__mul24(q, m) + start_of(g), inner) + r;
+            const T* b = B + 4 * __mul24(nt, g) + (i & 3);
+            T a = T(0);
+#pragma unroll 4
+            for (int t = 0; t < nt; t++) {
+                a = fma(*b, *x, a);
+                b += 4;
+                x += inner;
             }
-        }
-        for (int l = a.nlev - 1; l >= 0; l--) {
-            const TailLevel<T>& L = a.lv[l];
-            const int k = a.k0 + l;
-            const TailShape s = shape_of(L.m, L.mc);
-            const LdsTab<T> t = stage_tables(L, stab);
-            for (int b0 = 0; b0 < s.V; b0 += kTB * kT) {
-                T tmp[kTB];
-#pragma unroll
-                for (int q = 0; q < kTB; q++) {
-                    const int idx = min(b0 + q * kT + (int)threadIdx.x, s.V - 1);
-                    int j0, j1, j2;
-                    dec3(idx, s.m, j0, j1, j2);
-                    tmp[q] = (((j0 | j1 | j2) & 1) == 0 || (kGen && tail_phantom(L, j0, j1, j2)))
-                                 ? T(0)
-                                 : src[user(k, j0, j1, j2)];
-                }
-#pragma unroll
-                for (int q = 0; q < kTB; q++)
-                    if (b0 + q * kT + (int)threadIdx.x < s.V) R.U[b0 + q * kT + threadIdx.x] = tmp[q];
-            }
-            __syncthreads();
-            lds_load_vector(R.U, R.P1, R.P2, R.F, s, t);
-            lds_solve_apply(R.F, R.W, T(-1), s, t);
-            for (int idx = threadIdx.x; idx < s.V; idx += kT) {
-                int j0, j1, j2;
-                dec3(idx, s.m, j0, j1, j2);
-                if (((j0 | j1 | j2) & 1) == 0)
-                    R.U[idx] = R.W[((j0 >> 1) * s.mc[1] + (j1 >> 1)) * s.mc[2] + (j2 >> 1)];
-                else if (!kGen)
-                    R.U[idx] += tail_interp<T, true>(R.W, s, t, j0, j1, j2);
-                else if (!tail_phantom(L, j0, j1, j2))
-                    R.U[idx] += tail_interp_corners<T, true>(R.W, s, t, j0, j1, j2);
-            }
-            __syncthreads();
-            if (l > 0) {
-                if (kGen) {
-                    for (int q = threadIdx.x; q < s.V; q += kT) {
-                        int j0, j1, j2;
-                        dec3(q, s.m, j0, j1, j2);
-                        if (!tail_phantom(L, j0, j1, j2)) R.W[tail_packed(L, j0, j1, j2)] = R.U[q];
-                    }
-                } else {
-                    for (int q = threadIdx.x; q < s.V; q += kT) R.W[q] = R.U[q];
-                }
-                __syncthreads();
-            }
-        }
-        // the level-k0 grid goes to the workspace, or to the output if k0 == 0
-        const TailLevel<T>& L = a.lv[0];
-        const TailShape s = shape_of(L.m, L.mc);
-        for (int idx = threadIdx.x; idx < s.V; idx += kT) {
-            int j0, j1, j2;
-            dec3(idx, s.m, j0, j1, j2);
-            if (kGen && tail_phantom(L, j0, j1, j2)) continue;
-            if (a.k0 == 0)
-                dst[user(0, j0, j1, j2)] = R.U[idx];
-            else
-                L.Wk[kGen ? tail_packed(L, j0, j1, j2) : idx] = R.U[idx];
+            const T v[1] = {a};
+            out(__mul24(__mul24(q, mc) + i, inner) + r, inner, 1, v);
         }
     }
 }
 
-template <typename T, bool kDec, bool kGen>
+// Phase ps (0 .. na - 1) of a level's correction, the active dimensions last
+// first; the last phase gives the z of coarse nodes to fin(c, step, n, z): z[k] is
+// that of node c + k step.  A: the level's arrays.
+template <typename T, class Fin>
+__device__ __forceinline__ void tail_phase(const TailLevel& L, const T* tab, T* A, int ps, Fin fin)
+{
+    const int na = uni(L.na), d = uni((L.dims >> (2 * ps)) & 3);
+    const bool last = ps == na - 1;
+    const T* const in = A + (ps == 0 ? 0 : ps == 1 ? L.p1 : L.p2);
+    T* const o = A + (ps == 0 ? L.p1 : L.p2);
+    const int outer = (d == 2) ? L.d[0].m * L.d[1].m : (d == 1) ? L.d[0].m : 1;
+    const int inner = (d == 2) ? 1 : (d == 1) ? L.d[2].mc : L.d[1].mc * L.d[2].mc;
+    const float rinner = (d == 2) ? 1.0f : (d == 1) ? L.d[2].rmc : L.d[1].rmc * L.d[2].rmc;
+    tail_dots(L.d[d], tab + L.d[d].B, in, outer, inner, rinner, [&](int c, int step, int n, const auto& v) {
+        if (last) {
+            fin(c, step, n, v);
+        } else {
+#pragma unroll
+            for (int k = 0; k < (int)(sizeof(v) / sizeof(T)); k++)
+                if (k < n) o[c + k * step] = v[k];
+        }
+    });
+}
+
+// Cells of a level: for every coarse node i, fn(i, ok, u, p, g): u[e] is the
+// value of U at node 2 i + e of the level grid (e: bit d set, odd along
+// dimension d), p[e] its interpolant from the coarse values G, ok[e] whether
+// e > 0 is a fine node there; g the coarse value.  The interpolant is a sum
+// over the corners, the neighbours along dim 0 first and along dim 2 last,
+// each weighted by the product of its one-dimensional weights.  Every LDS read
+// of a cell is issued before the first is used.
+template <typename T, class Fn>
+__device__ __forceinline__ void tail_cells(const TailLevel& L, const T* tab, const T* U, const T* G, Fn fn)
+{
+    const int Vc = uni(L.Vc), mc1 = L.d[1].mc, mc2 = L.d[2].mc, m2 = L.d[2].m, m12 = __mul24(L.d[1].m, m2);
+    for (int c = threadIdx.x; c < Vc; c += kT) {
+        int i[3];
+        coarse_of(L, c, i[0], i[1], i[2]);
+        bool has[3];
+        T wl[3], wh[3];
+        int up[3], fu[3];
+        const int cs[3] = {__mul24(mc1, mc2), mc2, 1}, fs[3] = {m12, m2, 1};
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            const bool in = i[d] < L.d[d].mc - 1;
+            has[d] = in && 2 * i[d] + 1 != L.d[d].ph;
+            up[d] = in ? cs[d] : 0;
+            fu[d] = in ? fs[d] : 0;
+            // (of an inactive dimension no node is fine: any readable entry)
+            const T* w = tab + (in ? L.d[d].w + 4 * i[d] + 2 : 0);
+            wl[d] = w[0];
+            wh[d] = w[1];
+        }
+        const int u0 = 2 * (__mul24(i[0], m12) + __mul24(i[1], m2) + i[2]);
+        T g[8], u[8], p[8];
+        bool ok[8];
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            g[e] = G[c + ((e & 1) ? up[0] : 0) + ((e & 2) ? up[1] : 0) + ((e & 4) ? up[2] : 0)];
+            u[e] = U[u0 + ((e & 1) ? fu[0] : 0) + ((e & 2) ? fu[1] : 0) + ((e & 4) ? fu[2] : 0)];
+        }
+        p[0] = T(0);
+        ok[0] = false;
+#pragma unroll
+        for (int e = 1; e < 8; e++) {
+            ok[e] = (!(e & 1) || has[0]) && (!(e & 2) || has[1]) && (!(e & 4) || has[2]);
+            T acc = T(0);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                if (k & ~e) continue;
+                T w = T(1);
+#pragma unroll
+                for (int d = 0; d < 3; d++)
+                    if (e >> d & 1) w *= (k >> d & 1) ? wh[d] : wl[d];
+                acc = fma(w, g[k], acc);
+            }
+            p[e] = acc;
+        }
+        fn(i, u0, fs, ok, u, p, g[0]);
+    }
+}
+
+template <typename T, bool kDec, bool kLdsTab>
+__device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* lds)
+{
+    // offsets in the user's arrays of the finest tail level's nodes, per
+    // dimension (node j of l levels on is node min(j 2^l, m - 1) there)
+    __shared__ int64_t off0[kTailOffs], off1[kTailOffs], off2[kTailOffs];
+    // the levels' descriptions (each phase needs a dozen of their fields: from
+    // LDS, since a scalar load that misses its cache waits some 600 cycles)
+    __shared__ TailLevel lv[kMaxTail];
+    const int tid = threadIdx.x, nlev = a.nlev, k0 = a.k0;
+    {
+        const int* q = reinterpret_cast<const int*>(a.lv);
+        int* o = reinterpret_cast<int*>(lv);
+        for (int e = tid; e < nlev * (int)(sizeof(TailLevel) / 4); e += kT) o[e] = q[e];
+    }
+    // the tables are one contiguous range: their loads go out first
+    constexpr int kTT = 4;
+    const int ntab = kLdsTab ? a.tab_elems : 0;
+    T tt[kTT];
+    if (kLdsTab) {
+#pragma unroll
+        for (int q = 0; q < kTT; q++) tt[q] = a.tab[min(q * kT + tid, ntab - 1)];
+    }
+    if (tid < kTailOffs) {
+        off0[tid] = min((int64_t)tid * (a.st[0] << k0), a.last[0]);
+        off1[tid] = min((int64_t)tid * (a.st[1] << k0), a.last[1]);
+        off2[tid] = min((int64_t)tid * (a.st[2] << k0), a.last[2]);
+    }
+    __syncthreads();  // descriptions, offsets
+    const TailLevel L0 = lv[0];
+    const int base = uni(L0.cum), tbase = uni(L0.tab);
+    T* const ltab = lds + a.data_elems;
+    // tables of a level
+    auto tables = [&](const TailLevel& L) -> const T* {
+        return (kLdsTab ? (const T*)ltab : a.tab) + (L.tab - tbase);
+    };
+    const int x0 = L0.d[0].m - 1, x1 = L0.d[1].m - 1, x2 = L0.d[2].m - 1;
+    auto user0 = [&](int l, int j) { return off0[min(j << l, x0)]; };
+    auto user1 = [&](int l, int j) { return off1[min(j << l, x1)]; };
+    auto user2 = [&](int l, int j) { return off2[min(j << l, x2)]; };
+    // offset in the user's arrays of node j of the level l steps after k0
+    auto user = [&](int l, int j0, int j1, int j2) { return user0(l, j0) + user1(l, j1) + user2(l, j2); };
+    // node idx of a level (its value v) to its LDS arrays A
+    auto put = [&](const TailLevel& L, T* A, int idx, int j0, int j1, int j2, T v) {
+        const bool coarse = ((j0 | j1 | j2) & 1) == 0;
+        if (kDec && coarse)
+            A[L.g + __mul24(__mul24(j0 >> 1, L.d[1].mc) + (j1 >> 1), L.d[2].mc) + (j2 >> 1)] = v;
+        A[idx] = (coarse || phantom(L, j0, j1, j2)) ? T(0) : v;
+    };
+    // ---- loads: the finest level grid, then (recomposition) the coarser
+    // levels' coefficients and the coarsest values, all issued before the
+    // first is waited for
+    T tmp[kTB];
+    auto load0 = [&](int b0) {
+#pragma unroll
+        for (int q = 0; q < kTB; q++) {
+            const int idx = min(b0 + q * kT + tid, L0.V - 1);
+            int j0, j1, j2;
+            node_of(L0, idx, j0, j1, j2);
+            if (kDec && k0 > 0) {
+                const int pk = packed_at(L0, j0, j1, j2);
+                tmp[q] = a.Wk[pk] + a.Z0[pk];
+            } else {
+                tmp[q] = src[user(0, j0, j1, j2)];
+            }
+        }
+    };
+    auto put0 = [&](int b0) {
+#pragma unroll
+        for (int q = 0; q < kTB; q++) {
+            const int idx = b0 + q * kT + tid;
+            int j0, j1, j2;
+            node_of(L0, min(idx, L0.V - 1), j0, j1, j2);
+            if (idx < L0.V) put(L0, lds, idx, j0, j1, j2, tmp[q]);
+        }
+    };
+    load0(0);
+    if (kDec) {
+        // the coarser levels' arrays: their coarse nodes and phantoms stay zero
+        for (int e = (nlev > 1 ? lv[1].cum - base : a.data_elems) + tid; e < a.data_elems; e += kT) lds[e] = T(0);
+    } else {
+        // nodes of the levels after the first, level by level, then the
+        // coarsest values: element e of the sequence
+        int rest = 0;
+        for (int l = 1; l < nlev; l++) rest += lv[l].V;
+        const TailLevel& Lt = lv[nlev - 1];
+        const int all = rest + Lt.Vc;
+        constexpr int kTC = 2;
+        for (int b0 = 0; b0 < all; b0 += kTC * kT) {
+            T v[kTC];
+            int at[kTC];
+            bool zero[kTC];
+#pragma unroll
+            for (int q = 0; q < kTC; q++) {
+                int e = min(b0 + q * kT + tid, all - 1);
+                int64_t o = 0;
+                at[q] = 0;
+                zero[q] = false;
+                if (e >= rest) {
+                    int i0, i1, i2;
+                    coarse_of(Lt, e - rest, i0, i1, i2);
+                    o = user(nlev, i0, i1, i2);
+                    at[q] = Lt.cum - base + Lt.g + (e - rest);
+                } else {
+                    for (int l = 1; l < nlev; l++) {
+                        const TailLevel& L = lv[l];
+                        if (e >= 0 && e < L.V) {
+                            int j0, j1, j2;
+                            node_of(L, e, j0, j1, j2);
+                            o = user(l, j0, j1, j2);
+                            at[q] = L.cum - base + e;
+                            zero[q] = ((j0 | j1 | j2) & 1) == 0 || phantom(L, j0, j1, j2);
+                        }
+                        e -= L.V;
+                    }
+                }
+                v[q] = src[o];
+            }
+#pragma unroll
+            for (int q = 0; q < kTC; q++)
+                if (b0 + q * kT + tid < all) lds[at[q]] = zero[q] ? T(0) : v[q];
+        }
+    }
+    put0(0);
+    for (int b0 = kTB * kT; b0 < L0.V; b0 += kTB * kT) {
+        load0(b0);
+        put0(b0);
+    }
+    if (kLdsTab) {
+#pragma unroll
+        for (int q = 0; q < kTT; q++)
+            if (q * kT + tid < ntab) ltab[q * kT + tid] = tt[q];
+        for (int e = kTT * kT + tid; e < ntab; e += kT) ltab[e] = a.tab[e];
+    }
+    __syncthreads();
+
+    if (kDec) {
+        for (int l = 0; l < nlev; l++) {
+            const TailLevel& L = lv[l];
+            const T* const tab = tables(L);
+            T* const A = lds + (L.cum - base);
+            const T* const G = A + L.g;
+            tail_cells(L, tab, A, G,
+                       [&](const int (&i)[3], int u0, const int (&fs)[3], const bool (&ok)[8], const T (&u)[8],
+                           const T (&p)[8], T) {
+                           int64_t o[3][2];
+#pragma unroll
+                           for (int b = 0; b < 2; b++) {
+                               o[0][b] = user0(l, 2 * i[0] + b);
+                               o[1][b] = user1(l, 2 * i[1] + b);
+                               o[2][b] = user2(l, 2 * i[2] + b);
+                           }
+#pragma unroll
+                           for (int e = 1; e < 8; e++) {
+                               const T v = u[e] - p[e];
+                               if (ok[e]) {
+                                   A[u0 + ((e & 1) ? fs[0] : 0) + ((e & 2) ? fs[1] : 0) + ((e & 4) ? fs[2] : 0)] = v;
+                                   dst[o[0][e & 1] + o[1][e >> 1 & 1] + o[2][e >> 2]] = v;
+                               }
+                           }
+                       });
+            __syncthreads();
+            // z added to the coarse values, which are the next level's grid
+            const bool lastl = l + 1 == nlev;
+            const TailLevel& N = lv[lastl ? l : l + 1];
+            T* const An = lds + (N.cum - base);
+            const int e0 = L.d[0].mc - 1, e1 = L.d[1].mc - 1, e2 = L.d[2].mc - 1;
+            const int f0 = N.d[0].m - 1, f1 = N.d[1].m - 1, f2 = N.d[2].m - 1;
+            const int g1 = N.d[1].mc, g2 = N.d[2].mc, gn = N.g;
+            auto fin = [&](int c, int step, int n, const auto& z) {
+                constexpr int NZ = (int)(sizeof(z) / sizeof(T));
+                T v[NZ];
+#pragma unroll
+                for (int k = 0; k < NZ; k++) v[k] = G[c + (k < n ? k * step : 0)] + z[k];
+#pragma unroll
+                for (int k = 0; k < NZ; k++) {
+                    if (k >= n) break;
+                    int i0, i1, i2;
+                    coarse_of(L, c + k * step, i0, i1, i2);
+                    if (lastl) {
+                        dst[user(l + 1, i0, i1, i2)] = v[k];
+                        continue;
+                    }
+                    // index in the next level grid with its phantom
+                    const int j0 = (i0 == e0) ? f0 : i0, j1 = (i1 == e1) ? f1 : i1, j2 = (i2 == e2) ? f2 : i2;
+                    const int s = ((j0 | j1 | j2) & 1) ? 0 : 1;
+                    An[(s ? gn : 0) + __mul24(__mul24(j0 >> s, s ? g1 : f1 + 1) + (j1 >> s), s ? g2 : f2 + 1) + (j2 >> s)] = v[k];
+                }
+            };
+            const int na = uni(L.na);
+            for (int ps = 0; ps < na; ps++) {
+                tail_phase(L, tab, A, ps, fin);
+                __syncthreads();
+            }
+        }
+    } else {
+        // every level's correction, then the chain; z_l goes to the level's
+        // own G, except the coarsest level's, which is subtracted at once
+        // from the coarsest values there
+        const int na = uni(L0.na);
+        for (int ps = 0; ps < na; ps++) {
+            for (int l = 0; l < nlev; l++) {
+                const TailLevel& L = lv[l];
+                T* const A = lds + (L.cum - base);
+                T* const G = A + L.g;
+                const bool top = l + 1 == nlev;
+                tail_phase(L, tables(L), A, ps, [&](int c, int step, int n, const auto& z) {
+                    constexpr int NZ = (int)(sizeof(z) / sizeof(T));
+                    T v[NZ];
+#pragma unroll
+                    for (int k = 0; k < NZ; k++) v[k] = top ? G[c + (k < n ? k * step : 0)] - z[k] : z[k];
+#pragma unroll
+                    for (int k = 0; k < NZ; k++)
+                        if (k < n) G[c + k * step] = v[k];
+                });
+            }
+            __syncthreads();
+        }
+        for (int l = nlev - 1; l >= 0; l--) {
+            const TailLevel& L = lv[l];
+            const T* const A = lds + (L.cum - base);
+            // node (j0, j1, j2) of this level's grid: subtract the next finer
+            // level's z (it is that level's coarse node), or write it out
+            const bool last = l == 0;
+            const TailLevel& N = lv[last ? 0 : l - 1];
+            T* const Gn = lds + (N.cum - base) + N.g;
+            tail_cells(L, tables(L), A, A + L.g,
+                       [&](const int (&i)[3], int, const int (&)[3], const bool (&ok)[8], const T (&u)[8], const T (&p)[8],
+                           T g) {
+                           // places in the packed grid, or in the user's array
+                           int k[3][2];
+                           int64_t o[3][2];
+#pragma unroll
+                           for (int b = 0; b < 2; b++) {
+                               k[0][b] = __mul24(__mul24(min(2 * i[0] + b, L.d[0].act - 1), L.d[1].act), L.d[2].act);
+                               k[1][b] = __mul24(min(2 * i[1] + b, L.d[1].act - 1), L.d[2].act);
+                               k[2][b] = min(2 * i[2] + b, L.d[2].act - 1);
+                               if (last && k0 == 0) {
+                                   o[0][b] = user0(0, 2 * i[0] + b);
+                                   o[1][b] = user1(0, 2 * i[1] + b);
+                                   o[2][b] = user2(0, 2 * i[2] + b);
+                               }
+                           }
+                           T z[8];
+#pragma unroll
+                           for (int e = 0; e < 8; e++)
+                               z[e] = last ? T(0) : Gn[k[0][e & 1] + k[1][e >> 1 & 1] + k[2][e >> 2]];
+#pragma unroll
+                           for (int e = 0; e < 8; e++) {
+                               const T v = (e == 0) ? g : u[e] + p[e];
+                               if (e > 0 && !ok[e]) continue;
+                               const int pk = k[0][e & 1] + k[1][e >> 1 & 1] + k[2][e >> 2];
+                               if (!last)
+                                   Gn[pk] = v - z[e];
+                               else if (k0 == 0)
+                                   dst[o[0][e & 1] + o[1][e >> 1 & 1] + o[2][e >> 2]] = v;
+                               else
+                                   a.Wk[pk] = v;
+                           }
+                       });
+            __syncthreads();
+        }
+    }
+}
+
+extern __shared__ __align__(16) unsigned char tail_lds[];
+
+template <typename T, bool kDec, bool kLdsTab>
 __global__ void __launch_bounds__(kT) k_tail(TailArgs<T> a)
 {
-    __shared__ T sbuf[kTailDataElems];
-    __shared__ T stab[kTailTabElems];
-    tail_body<T, kDec, kGen>(a, a.src, a.dst, sbuf, stab);
+    tail_body<T, kDec, kLdsTab>(a, a.src, a.dst, reinterpret_cast<T*>(tail_lds));
 }
 
 // One workgroup per entry of a batch; arguments in device memory.
-template <typename T, bool kDec>
+template <typename T, bool kLdsTab>
 __global__ void __launch_bounds__(kT) k_tail_batch(const TailArgs<T>* __restrict__ args, const int* __restrict__ field,
                                                    const T* const* __restrict__ src, T* const* __restrict__ dst)
 {
-    __shared__ T sbuf[kTailDataElems];
-    __shared__ T stab[kTailTabElems];
     const int f = field[blockIdx.x];
-    tail_body<T, kDec, false>(args[blockIdx.x], src[f], dst[f], sbuf, stab);
+    tail_body<T, true, kLdsTab>(args[blockIdx.x], src[f], dst[f], reinterpret_cast<T*>(tail_lds));
+}
+
+// LDS beyond 64 KB has to be asked for once per kernel and device.
+template <typename K>
+hipError_t allow_lds(K kern, size_t bytes, bool (&done)[64])
+{
+    if (bytes <= 65536) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (done[dev]) return hipSuccess;
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kTailLdsElems * 8);
+    if (e == hipSuccess) done[dev] = true;
+    return e;
+}
+
+template <typename T, bool kDec, bool kLdsTab>
+hipError_t launch_tail_cfg(const TailArgs<T>& a, size_t bytes, hipStream_t st)
+{
+    static bool done[64] = {};
+    const hipError_t e = allow_lds(k_tail<T, kDec, kLdsTab>, bytes, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_tail<T, kDec, kLdsTab>), dim3(1), dim3(kT), bytes, st, a);
+    return hipGetLastError();
+}
+
+template <typename T, bool kLdsTab>
+hipError_t launch_tail_batch_cfg(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst,
+                                 int n, size_t bytes, hipStream_t st)
+{
+    static bool done[64] = {};
+    const hipError_t e = allow_lds(k_tail_batch<T, kLdsTab>, bytes, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_tail_batch<T, kLdsTab>), dim3((unsigned)n), dim3(kT), bytes, st, dev_args, field, src, dst);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 template <typename T>
-hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst,
-                             int n, bool decompose, hipStream_t st)
+hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst, int n,
+                             int data_elems, int tab_elems, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (decompose)
-        hipLaunchKernelGGL((k_tail_batch<T, true>), dim3((unsigned)n), dim3(kT), 0, st, dev_args, field, src, dst);
-    else
-        hipLaunchKernelGGL((k_tail_batch<T, false>), dim3((unsigned)n), dim3(kT), 0, st, dev_args, field, src, dst);
-    return hipGetLastError();
+    if (data_elems + tab_elems <= kTailLdsElems)
+        return launch_tail_batch_cfg<T, true>(dev_args, field, src, dst, n, sizeof(T) * (size_t)(data_elems + tab_elems), st);
+    return launch_tail_batch_cfg<T, false>(dev_args, field, src, dst, n, sizeof(T) * (size_t)data_elems, st);
 }
-
-template hipError_t launch_tail_batch<float>(const TailArgs<float>*, const int*, const float* const*, float* const*,
-                                             int, bool, hipStream_t);
-template hipError_t launch_tail_batch<double>(const TailArgs<double>*, const int*, const double* const*,
-                                              double* const*, int, bool, hipStream_t);
 
 template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st)
 {
-    if (a.gen) {
-        if (decompose)
-            hipLaunchKernelGGL((k_tail<T, true, true>), dim3(1), dim3(kT), 0, st, a);
-        else
-            hipLaunchKernelGGL((k_tail<T, false, true>), dim3(1), dim3(kT), 0, st, a);
-    } else if (decompose) {
-        hipLaunchKernelGGL((k_tail<T, true, false>), dim3(1), dim3(kT), 0, st, a);
-    } else {
-        hipLaunchKernelGGL((k_tail<T, false, false>), dim3(1), dim3(kT), 0, st, a);
+    if (a.data_elems + a.tab_elems <= kTailLdsElems) {
+        const size_t bytes = sizeof(T) * (size_t)(a.data_elems + a.tab_elems);
+        return decompose ? launch_tail_cfg<T, true, true>(a, bytes, st) : launch_tail_cfg<T, false, true>(a, bytes, st);
     }
-    return hipGetLastError();
+    const size_t bytes = sizeof(T) * (size_t)a.data_elems;
+    return decompose ? launch_tail_cfg<T, true, false>(a, bytes, st) : launch_tail_cfg<T, false, false>(a, bytes, st);
 }
 
 template hipError_t launch_tail<float>(const TailArgs<float>&, bool, hipStream_t);
 template hipError_t launch_tail<double>(const TailArgs<double>&, bool, hipStream_t);
+template hipError_t launch_tail_batch<float>(const TailArgs<float>*, const int*, const float* const*, float* const*,
+                                             int, int, int, hipStream_t);
+template hipError_t launch_tail_batch<double>(const TailArgs<double>*, const int*, const double* const*,
+                                              double* const*, int, int, int, hipStream_t);
 
 }  // namespace mgr
