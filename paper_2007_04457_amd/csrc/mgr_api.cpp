@@ -1830,7 +1830,7 @@ struct BatchPlan {
            off_args = 0, dev_bytes = 0;
     std::vector<std::pair<int, int>> waves;  // (first item, items) per launch
     int n_items = 0, n_tail = 0;
-    int tail_data = 0, tail_tab = 0;  // LDS elements of the tail launch
+    int tail_lds = 0;  // LDS elements of the tail launch
     int chunk = 8, tuned = 0;
     int wide = 0;                  // 3-D streaming items on the wide tile geometry
     int64_t bytes = 0;             // input bytes of the batch
@@ -2201,11 +2201,8 @@ int batch_upload(BatchPlan& b, int chunk)
     b.waves = t.waves;
     b.n_items = (int)t.items.size();
     b.n_tail = (int)t.tail.size();
-    b.tail_data = b.tail_tab = 0;
-    for (const TailArgs<T>& ta : t.tail) {
-        b.tail_data = std::max(b.tail_data, ta.data_elems);
-        b.tail_tab = std::max(b.tail_tab, ta.tab_elems);
-    }
+    b.tail_lds = 0;
+    for (const TailArgs<T>& ta : t.tail) b.tail_lds = std::max(b.tail_lds, tail_lds_elems(ta));
     b.chunk = chunk;
     b.ran_persistent = 0;
     return MGR_OK;
@@ -2266,7 +2263,7 @@ int batch_run(BatchPlan& b, const void* const* src, void* const* dst, hipStream_
                       return launch_tail_batch<T>((const TailArgs<T>*)(d + b.off_tail), (const int*)(d + b.off_tailf),
                                                   (const T* const*)(d + b.off_ptrs),
                                                   (T* const*)(d + b.off_ptrs + sizeof(void*) * (size_t)nf), b.n_tail,
-                                                  b.tail_data, b.tail_tab, st);
+                                                  b.tail_lds, st);
                   }),
             "batch tail launch");
     return MGR_OK;

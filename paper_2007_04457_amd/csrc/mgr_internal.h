@@ -145,13 +145,13 @@ hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const So
 // Single-workgroup kernel for the small coarse levels (mgr_tail.hip): all
 // level steps k0 .. k0 + nlev - 1 in one launch, in LDS.  The levels' arrays
 // (tail_data_elems) must fit kTailDataElems elements; the tables share the LDS
-// when both fit kTailLdsElems, else they are read from global memory.
+// when both fit kTailLdsBytes, else they are read from global memory.
 constexpr int kTailThreads = 1024;
 constexpr int kMaxTail = 16;
 constexpr int64_t kTailMaxNodes = 5000;
 constexpr int kTailMaxSide = 513;  // longest dimension of a level grid (its tables' rows)
 constexpr int kTailDataElems = 17000;
-constexpr int kTailLdsElems = 18400;
+constexpr int kTailLdsBytes = 18400 * 8;
 
 // A level's description, in device memory beside its tables (kernel arguments
 // lie in host memory: every first touch of a level's line there costs the
@@ -198,10 +198,22 @@ template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st);
 // Decompositions, one workgroup per entry: dev_args[i] in device memory,
 // applied to field field[i] of the per-field pointer tables src / dst (device
-// memory).  data_elems, tab_elems: the largest over the entries.
+// memory).  lds_elems: the largest LDS need over the entries
+// (tail_lds_elems).
 template <typename T>
 hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst, int n,
-                             int data_elems, int tab_elems, hipStream_t st);
+                             int lds_elems, hipStream_t st);
+// LDS elements of a tail, and whether its tables are among them.
+template <typename T>
+__host__ __device__ inline bool tail_tab_in_lds(const TailArgs<T>& a)
+{
+    return (size_t)(a.data_elems + a.tab_elems) * sizeof(T) <= (size_t)kTailLdsBytes;
+}
+template <typename T>
+inline int tail_lds_elems(const TailArgs<T>& a)
+{
+    return a.data_elems + (tail_tab_in_lds(a) ? a.tab_elems : 0);
+}
 
 template <typename T>
 hipError_t launch_stream_level(StreamArgs<T> a, bool dec, hipStream_t st);

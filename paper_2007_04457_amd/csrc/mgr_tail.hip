@@ -227,15 +227,21 @@ __device__ __forceinline__ void tail_cells(const TailLevel& L, const T* tab, con
     }
 }
 
-template <typename T, bool kDec, bool kLdsTab>
-__device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* lds)
-{
+struct TailStatic {
     // offsets in the user's arrays of the finest tail level's nodes, per
     // dimension (node j of l levels on is node min(j 2^l, m - 1) there)
-    __shared__ int64_t off0[kTailOffs], off1[kTailOffs], off2[kTailOffs];
+    int64_t off0[kTailOffs], off1[kTailOffs], off2[kTailOffs];
     // the levels' descriptions (each phase needs a dozen of their fields: from
     // LDS, since a scalar load that misses its cache waits some 600 cycles)
-    __shared__ TailLevel lv[kMaxTail];
+    TailLevel lv[kMaxTail];
+};
+static_assert(sizeof(TailStatic) + kTailLdsBytes <= 163840, "fits a CU's LDS");
+
+template <typename T, bool kDec, bool kLdsTab>
+__device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* lds, TailStatic& sm)
+{
+    int64_t *const off0 = sm.off0, *const off1 = sm.off1, *const off2 = sm.off2;
+    TailLevel* const lv = sm.lv;
     const int tid = threadIdx.x, nlev = a.nlev, k0 = a.k0;
     {
         const int* q = reinterpret_cast<const int*>(a.lv);
@@ -497,16 +503,22 @@ extern __shared__ __align__(16) unsigned char tail_lds[];
 template <typename T, bool kDec, bool kLdsTab>
 __global__ void __launch_bounds__(kT) k_tail(TailArgs<T> a)
 {
-    tail_body<T, kDec, kLdsTab>(a, a.src, a.dst, reinterpret_cast<T*>(tail_lds));
+    __shared__ TailStatic sm;
+    tail_body<T, kDec, kLdsTab>(a, a.src, a.dst, reinterpret_cast<T*>(tail_lds), sm);
 }
 
 // One workgroup per entry of a batch; arguments in device memory.
-template <typename T, bool kLdsTab>
+template <typename T>
 __global__ void __launch_bounds__(kT) k_tail_batch(const TailArgs<T>* __restrict__ args, const int* __restrict__ field,
                                                    const T* const* __restrict__ src, T* const* __restrict__ dst)
 {
+    __shared__ TailStatic sm;
     const int f = field[blockIdx.x];
-    tail_body<T, true, kLdsTab>(args[blockIdx.x], src[f], dst[f], reinterpret_cast<T*>(tail_lds));
+    const TailArgs<T>& a = args[blockIdx.x];
+    if (tail_tab_in_lds(a))
+        tail_body<T, true, true>(a, src[f], dst[f], reinterpret_cast<T*>(tail_lds), sm);
+    else
+        tail_body<T, true, false>(a, src[f], dst[f], reinterpret_cast<T*>(tail_lds), sm);
 }
 
 // LDS beyond 64 KB has to be asked for once per kernel and device.
@@ -519,7 +531,7 @@ hipError_t allow_lds(K kern, size_t bytes, bool (&done)[64])
     if (e != hipSuccess) return e;
     if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
     if (done[dev]) return hipSuccess;
-    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kTailLdsElems * 8);
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kTailLdsBytes);
     if (e == hipSuccess) done[dev] = true;
     return e;
 }
@@ -534,45 +546,35 @@ hipError_t launch_tail_cfg(const TailArgs<T>& a, size_t bytes, hipStream_t st)
     return hipGetLastError();
 }
 
-template <typename T, bool kLdsTab>
-hipError_t launch_tail_batch_cfg(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst,
-                                 int n, size_t bytes, hipStream_t st)
-{
-    static bool done[64] = {};
-    const hipError_t e = allow_lds(k_tail_batch<T, kLdsTab>, bytes, done);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_tail_batch<T, kLdsTab>), dim3((unsigned)n), dim3(kT), bytes, st, dev_args, field, src, dst);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 template <typename T>
 hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst, int n,
-                             int data_elems, int tab_elems, hipStream_t st)
+                             int lds_elems, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    if (data_elems + tab_elems <= kTailLdsElems)
-        return launch_tail_batch_cfg<T, true>(dev_args, field, src, dst, n, sizeof(T) * (size_t)(data_elems + tab_elems), st);
-    return launch_tail_batch_cfg<T, false>(dev_args, field, src, dst, n, sizeof(T) * (size_t)data_elems, st);
+    static bool done[64] = {};
+    const size_t bytes = sizeof(T) * (size_t)lds_elems;
+    const hipError_t e = allow_lds(k_tail_batch<T>, bytes, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_tail_batch<T>), dim3((unsigned)n), dim3(kT), bytes, st, dev_args, field, src, dst);
+    return hipGetLastError();
 }
 
 template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st)
 {
-    if (a.data_elems + a.tab_elems <= kTailLdsElems) {
-        const size_t bytes = sizeof(T) * (size_t)(a.data_elems + a.tab_elems);
+    const size_t bytes = sizeof(T) * (size_t)tail_lds_elems(a);
+    if (tail_tab_in_lds(a))
         return decompose ? launch_tail_cfg<T, true, true>(a, bytes, st) : launch_tail_cfg<T, false, true>(a, bytes, st);
-    }
-    const size_t bytes = sizeof(T) * (size_t)a.data_elems;
     return decompose ? launch_tail_cfg<T, true, false>(a, bytes, st) : launch_tail_cfg<T, false, false>(a, bytes, st);
 }
 
 template hipError_t launch_tail<float>(const TailArgs<float>&, bool, hipStream_t);
 template hipError_t launch_tail<double>(const TailArgs<double>&, bool, hipStream_t);
 template hipError_t launch_tail_batch<float>(const TailArgs<float>*, const int*, const float* const*, float* const*,
-                                             int, int, int, hipStream_t);
+                                             int, int, hipStream_t);
 template hipError_t launch_tail_batch<double>(const TailArgs<double>*, const int*, const double* const*,
-                                              double* const*, int, int, int, hipStream_t);
+                                              double* const*, int, int, hipStream_t);
 
 }  // namespace mgr
