@@ -5,19 +5,31 @@
 // class L, each a contiguous segment with its nodes in C order of their
 // grid indices.
 //
-// Each thread handles one node of the in-place layout: its class c is read
-// off the 2-adic valuations of its indices, and its rank inside the class
-// segment has a closed form.  Class c >= 1 holds the nodes of level grid c
-// (stride 2^(L-c)) that are not on level grid c - 1, i.e. whose level-c
-// indices j are not all even; C order of the full grid restricted to them is
-// C order of j, so
+// Class c >= 1 holds the nodes of level grid c (stride 2^v, v = L - c) that are
+// not on level grid c - 1, i.e. whose level indices j = i >> v are not all even;
+// C order of the full grid restricted to them is C order of j, so
 //     rank = lex(j) - #{all-even j' before j in C order},
 // and the all-even count of a box (m0, m1, m2) before j is
 //     E(j0) e1 e2 + [j0 even] (E(j1) e2 + [j1 even] E(j2)),
 // with E(x) = (x + 1) / 2 even values in [0, x) and e_d = (m_d + 1) / 2.
-// Class 0 is the coarsest grid itself: rank = lex(j).  Reads of the in-place
-// array are coalesced; writes are sequential within a class segment (every
-// other lane on even rows of the finest class).
+// Class 0 is the coarsest grid itself: rank = lex(j).
+//
+// The work goes by rows (i0, i1).  With w the smaller 2-adic valuation of i0
+// and i1, a row holds the classes of v = 0 .. w: at the columns of valuation v
+// < w, every second node of the row's level-v grid, and at the remaining ones
+// its whole level-w grid.  Each is a contiguous piece of its class segment, so
+// a row needs one start per class and no division per node, and the three
+// rows of four with w = 0 are plain copies.  A group of lanes walks
+// consecutive row pieces, stepping (i0, i1) instead of dividing.
+//
+// Bound by memory: 513^3 FP32 (1.08 GB moved) packed in 231 us, 4.7 TB/s,
+// against 552 us with a thread per node and two 64-bit divisions each; it
+// moves no byte twice (534 MB written to HBM).  The rest of the way to a
+// linear copy's 6.1 TB/s is the rows' arbitrary alignment: 16-byte stores
+// aligned to the destination measured the same, and so did an XCD-contiguous
+// order of workgroups.
+#include <algorithm>
+
 #include "mgr_internal.h"
 
 namespace mgr {
@@ -30,38 +42,126 @@ __device__ __forceinline__ int v2(int64_t i, int cap)
     return (i == 0) ? cap : min(cap, (int)__builtin_ctzll((unsigned long long)i));
 }
 
-// Packed position of node (i0, i1, i2) of a grid of sizes n (internal 3-D
-// form, inactive dims of size 1) decomposed with L level steps.
-__device__ __forceinline__ int64_t packed_index(int64_t i0, int64_t i1, int64_t i2, const PackArgs& a)
+// Start of the piece of row (i0, i1) that belongs to the class of valuation v
+// (v <= w): packed position of its level-v node 0, with the piece's nodes
+// counted as j2 >> 1 (v < w) or j2 (v = w).
+__device__ __forceinline__ int64_t piece_start(int64_t i0, int64_t i1, int v, int w, const PackArgs& a)
 {
-    const int L = a.L;
-    const int v = min(v2(i0, L), min(v2(i1, L), v2(i2, L)));
-    const int64_t m0 = ((a.n[0] - 1) >> v) + 1, m1 = ((a.n[1] - 1) >> v) + 1, m2 = ((a.n[2] - 1) >> v) + 1;
-    const int64_t j0 = i0 >> v, j1 = i1 >> v, j2 = i2 >> v;
-    const int64_t lex = (j0 * m1 + j1) * m2 + j2;
-    if (v >= L) return lex;  // class 0: the coarsest grid in C order
+    const int64_t m1 = ((a.n[1] - 1) >> v) + 1, m2 = ((a.n[2] - 1) >> v) + 1;
+    const int64_t j0 = i0 >> v, j1 = i1 >> v;
+    const int64_t lex = (j0 * m1 + j1) * m2;
+    if (v >= a.L) return lex;  // class 0: the coarsest grid in C order
     const int64_t e1 = (m1 + 1) >> 1, e2 = (m2 + 1) >> 1;
-    const int64_t ev = ((j0 + 1) >> 1) * e1 * e2 +
-                       ((j0 & 1) ? 0 : (((j1 + 1) >> 1) * e2 + ((j1 & 1) ? 0 : ((j2 + 1) >> 1))));
-    (void)m0;
-    return a.off[L - v] + lex - ev;
+    // (v < w: j0 and j1 are even and the piece's j2 odd, so j2 - E(j2) = j2 >> 1)
+    const int64_t ev = ((j0 + 1) >> 1) * e1 * e2 + ((j0 & 1) ? 0 : ((j1 + 1) >> 1) * e2);
+    return a.off[a.L - v] + lex - ev;
 }
 
-template <typename T, bool kPack>
-__global__ void __launch_bounds__(kPackBlock) k_pack(const T* __restrict__ src, T* __restrict__ dst, PackArgs a)
+// A group of kLanes lanes takes `per` consecutive units (row, piece of seg
+// columns), pieces fastest; kPackBatch elements in flight per lane.  Pos: the type
+// of packed positions (32 bits where the array has fewer elements than that).
+template <typename T, bool kPack, int kLanes, int kPackBatch, typename Pos>
+__global__ void __launch_bounds__(kPackBlock)
+    k_pack(const T* __restrict__ src, T* __restrict__ dst, PackArgs a, int64_t seg, int64_t nseg, int64_t per)
 {
-    const int64_t total = a.n[0] * a.n[1] * a.n[2];
-    const int64_t stride = (int64_t)gridDim.x * kPackBlock;
-    for (int64_t idx = (int64_t)blockIdx.x * kPackBlock + threadIdx.x; idx < total; idx += stride) {
-        const int64_t i2 = idx % a.n[2];
-        const int64_t t = idx / a.n[2];
-        const int64_t i1 = t % a.n[1], i0 = t / a.n[1];
-        const int64_t p = packed_index(i0, i1, i2, a);
-        if (kPack)
-            dst[p] = src[idx];
-        else
-            dst[idx] = src[p];
+    const int lane = threadIdx.x % kLanes;
+    const int64_t group = (int64_t)blockIdx.x * (kPackBlock / kLanes) +
+                          (kLanes == 64 ? uni((int)(threadIdx.x / kLanes)) : (int)(threadIdx.x / kLanes));
+    const int64_t n1 = a.n[1], n2 = a.n[2];
+    const int64_t units = a.n[0] * n1 * nseg;
+    int64_t u = group * per;
+    const int64_t end = min(u + per, units);
+    if (u >= end) return;
+    int64_t row = u / nseg, s = u - row * nseg;
+    int64_t i0 = row / n1, i1 = row - i0 * n1;
+    for (; u < end; u++) {
+        const int w = min(v2(i0, a.L), v2(i1, a.L));
+        // (a piece's columns count from its first, in 32 bits)
+        const int64_t c0 = s * seg;
+        const int n = (int)min(seg, n2 - c0);
+        const int64_t rb = row * n2 + c0;
+        if (w == 0) {
+            const int64_t b0 = piece_start(i0, i1, 0, 0, a) + c0;
+            const T* const x = src + (kPack ? rb : b0);
+            T* const y = dst + (kPack ? b0 : rb);
+            for (int i = lane; i < n; i += kLanes * kPackBatch) {
+                T v[kPackBatch];
+#pragma unroll
+                for (int q = 0; q < kPackBatch; q++) v[q] = x[min(i + q * kLanes, n - 1)];
+#pragma unroll
+                for (int q = 0; q < kPackBatch; q++)
+                    if (i + q * kLanes < n) y[i + q * kLanes] = v[q];
+            }
+        } else {
+            // column c belongs to the class of valuation min(v2(c), w): its
+            // packed position, the row's classes one after the other, then one
+            // load and one store
+            const T* const x = src + rb;
+            T* const y = dst + rb;
+            for (int i = lane; i < n; i += kLanes * kPackBatch) {
+                Pos p[kPackBatch];
+                int cv[kPackBatch];
+                T t[kPackBatch];
+#pragma unroll
+                for (int q = 0; q < kPackBatch; q++) {
+                    const int e = min(i + q * kLanes, n - 1);
+                    cv[q] = min(v2(c0 + e, a.L), w);
+                    if (kPack) t[q] = x[e];
+                    p[q] = 0;
+                }
+                for (int v = 0; v <= w; v++) {
+                    const int sh = v < w ? v + 1 : v;
+                    const Pos b = (Pos)(piece_start(i0, i1, v, w, a) + (c0 >> sh));
+                    const int low = (int)(c0 & (((int64_t)1 << sh) - 1));
+#pragma unroll
+                    for (int q = 0; q < kPackBatch; q++) {
+                        const Pos o = b + (Pos)((low + min(i + q * kLanes, n - 1)) >> sh);
+                        p[q] = (cv[q] == v) ? o : p[q];
+                    }
+                }
+                if constexpr (!kPack) {
+#pragma unroll
+                    for (int q = 0; q < kPackBatch; q++) t[q] = src[p[q]];
+                }
+#pragma unroll
+                for (int q = 0; q < kPackBatch; q++)
+                    if (i + q * kLanes < n) {
+                        if (kPack)
+                            dst[p[q]] = t[q];
+                        else
+                            y[i + q * kLanes] = t[q];
+                    }
+            }
+        }
+        if (++s == nseg) {
+            s = 0;
+            row++;
+            if (++i1 == n1) {
+                i1 = 0;
+                i0++;
+            }
+        }
     }
+}
+
+template <typename T, int kLanes, int kPackBatch>
+hipError_t launch_pack_cfg(const T* src, T* dst, const PackArgs& a, bool pack, hipStream_t st)
+{
+    // row pieces of a few thousand columns, and enough groups for several
+    // rounds of the chip's wave slots where there are rows for them
+    const int64_t rows = a.n[0] * a.n[1];
+    const int64_t seg = std::min<int64_t>(a.n[2], 2304), nseg = (a.n[2] + seg - 1) / seg;
+    const int64_t units = rows * nseg;
+    const int64_t groups = (int64_t)device_cu_count() * 128 * (64 / kLanes);
+    const int64_t per = std::max<int64_t>(1, (units + groups - 1) / groups);
+    const int64_t blocks = ((units + per - 1) / per + kPackBlock / kLanes - 1) / (kPackBlock / kLanes);
+    auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kPackBlock), 0, st, src, dst, a, seg, nseg, per); };
+    const bool small = rows * a.n[2] < ((int64_t)1 << 32);
+    if (pack)
+        small ? launch(k_pack<T, true, kLanes, kPackBatch, unsigned>) : launch(k_pack<T, true, kLanes, kPackBatch, int64_t>);
+    else
+        small ? launch(k_pack<T, false, kLanes, kPackBatch, unsigned>) : launch(k_pack<T, false, kLanes, kPackBatch, int64_t>);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -69,14 +169,15 @@ __global__ void __launch_bounds__(kPackBlock) k_pack(const T* __restrict__ src, 
 template <typename T>
 hipError_t launch_pack(const T* src, T* dst, const PackArgs& a, bool pack, hipStream_t st)
 {
-    const int64_t total = a.n[0] * a.n[1] * a.n[2];
-    int64_t b = (total + kPackBlock - 1) / kPackBlock;
-    b = std::max<int64_t>(1, std::min<int64_t>(b, (int64_t)1 << 20));
-    if (pack)
-        hipLaunchKernelGGL((k_pack<T, true>), dim3((unsigned)b), dim3(kPackBlock), 0, st, src, dst, a);
-    else
-        hipLaunchKernelGGL((k_pack<T, false>), dim3((unsigned)b), dim3(kPackBlock), 0, st, src, dst, a);
-    return hipGetLastError();
+    // a wave per row piece, or 16 lanes where a row would leave most of a
+    // wave's lanes idle; as many elements in flight as a row of 2^k + 1 takes
+    // whole (its odd last element in a batch of its own cost a second memory
+    // latency per row: 292 against 257 us at 513^3, other things equal)
+    const int64_t n = a.n[2];
+    if (n <= 33) return launch_pack_cfg<T, 16, 3>(src, dst, a, pack, st);
+    if (n <= 192) return launch_pack_cfg<T, 64, 3>(src, dst, a, pack, st);
+    if (n <= 320) return launch_pack_cfg<T, 64, 5>(src, dst, a, pack, st);
+    return launch_pack_cfg<T, 64, 9>(src, dst, a, pack, st);
 }
 
 template hipError_t launch_pack<float>(const float*, float*, const PackArgs&, bool, hipStream_t);
