@@ -95,6 +95,10 @@ constexpr int stream_ring()
 {
     return (sizeof(T) == 4 && kDec && !kZ) ? 4 : 2;
 }
+// Rows walked one by one (2-D problems as (m0, 1, m2)): a buffer is a single
+// value per lane there, so the ring is as deep as memory latency asks for
+// (8193^2 level 0: FP32 157 -> 143 us, FP64 295 -> 278, chunks cut too).
+constexpr int kRowRing = 8;
 // Minimum waves per SIMD the streaming kernel is compiled for: the deep ring
 // is held at five (at most 96 registers, a few spilled), which measured
 // faster than four waves without spills.
@@ -506,7 +510,7 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
 
     // plane buffers: a ring of D, so that D - 1 planes are in flight while
     // one is consumed
-    constexpr int D = stream_ring<T, kDec, kZ>();
+    constexpr int D = kAct1 ? stream_ring<T, kDec, kZ>() : kRowRing;
     Cols B0[NRW], B1[NRW], B2[NRW], B3[NRW];  // B2, B3 unused (and dropped) when D = 2
     Cols Z0[NRW], Z1[NRW];                    // unused (and dropped) without the correction
     Cols cur[NRW], Pp[NRW], Pn[NRW];
@@ -536,9 +540,15 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
     // wait for the load); planes past F1 re-read F1.
     auto seq = [&](int j) { return min(j == 0 ? F0 : ((j & 1) ? F0 + j + 1 : F0 + j - 1), F1); };
     const int K = (F1 - F0) / 2;
-    load_plane(seq(0), B0, Z0);
-    load_plane(seq(1), B1, Z1);
-    if constexpr (D > 2) {
+    Cols R[kAct1 ? 1 : D][NRW], RZ[kAct1 ? 1 : D][NRW];  // the rows' ring
+    if constexpr (!kAct1) {
+#pragma unroll
+        for (int j = 0; j < D; j++) load_plane(seq(j), R[j], RZ[j]);
+    } else {
+        load_plane(seq(0), B0, Z0);
+        load_plane(seq(1), B1, Z1);
+    }
+    if constexpr (kAct1 && D > 2) {
         load_plane(seq(2), B2, Z0);
         load_plane(seq(3), B3, Z0);
     }
@@ -572,7 +582,10 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
             load_plane(seq(j + D), B, BZ);
         }
     };
-    consume(0, B0, Z0);
+    if constexpr (kAct1)
+        consume(0, B0, Z0);
+    else
+        consume(0, R[0], RZ[0]);
     reduce_plane(g);
 #pragma unroll
     for (int q = 0; q < NOUT; q++) {
@@ -610,7 +623,18 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
             accC[q] = T(0);
         }
     };
-    if constexpr (D > 2) {
+    if constexpr (!kAct1) {
+        constexpr int HS = D / 2;  // steps per turn of the ring
+        int k = 0;
+        for (; k + HS <= K; k += HS) {
+#pragma unroll
+            for (int h = 0; h < HS; h++)
+                step(k + h, R[2 * h + 1], RZ[2 * h + 1], R[(2 * h + 2) % D], RZ[(2 * h + 2) % D]);
+        }
+#pragma unroll
+        for (int h = 0; h < HS - 1; h++)
+            if (k + h < K) step(k + h, R[2 * h + 1], RZ[2 * h + 1], R[(2 * h + 2) % D], RZ[(2 * h + 2) % D]);
+    } else if constexpr (D > 2) {
         int k = 0;
         for (; k + 1 < K; k += 2) {
             step(k, B1, Z1, B2, Z0);
