@@ -535,6 +535,34 @@ template <typename T>
 hipError_t launch_gen_interp(const T* y, const T* Wn, T* dst, T* Wk, const GenLevel<T>& a, int k, hipStream_t st);
 template <typename T>
 hipError_t launch_gen_scatter(T* full, T* W, const T* Z, const GenLevel<T>& a, int k, bool to_full, hipStream_t st);
+// A level step of a 4-D grid by planes of its last two dimensions
+// (mgr_plane4.hip), for planes that fit kPlane4Lds bytes of LDS.
+constexpr int kPlane4Lds = 150 * 1024;
+template <typename T>
+struct Plane4 {
+    int m[4], mc[4];     // level-grid and coarse sizes
+    int k;               // level step
+    int64_t n[4], st[4]; // sizes and strides of the user's array
+    const T* wl[4];      // interpolation weights of fine-only nodes, load-vector rows (GenLevel)
+    const T* wh[4];
+    const T* K[4];
+    const T* in;   // user's array: field (decomposition, k = 0) or coefficients
+    const T* Wk;   // decomposition, k > 0: packed level grid, read as Wk + Z
+    const T* Z;    // correction: of the level grid (decomposition, k > 0), or of Wn (recomposition, read as Wn - Z)
+    T* Wn;         // packed coarse values (written by the decomposition)
+    T* out;        // user's array; recomposition, k > 0: packed level grid
+    T* F;          // stencils along dims 3 and 2, packed (m0, m1, mc2, mc3)
+};
+template <typename T>
+bool plane4_fits(const Plane4<T>& a);
+// mode 0: decomposition, 1: load vector of stored coefficients, 2:
+// recomposition.
+template <typename T>
+hipError_t launch_plane4(const Plane4<T>& a, int mode, hipStream_t st);
+// Stencils along dims 1 and 0 of F: out packed (mc0, mc1, mc2, mc3).
+template <typename T>
+hipError_t launch_mass01(const T* in, T* out, const Plane4<T>& a, hipStream_t st);
+
 // Partitioned solve of every fibre of length n along the middle index of a
 // packed (outer, n, inner) box, in place; Yb as for launch_solve_partitioned.
 template <typename T>
