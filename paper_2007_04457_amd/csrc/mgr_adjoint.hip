@@ -52,6 +52,7 @@ struct AdjArgs {
     T* O;        // output, level grid
     View3 ov;
     DimTables<T> tb;
+    T sign;      // of the expanded y: 1, or -1 (t subtracted)
     int chunk, nt1, nt2, nch;
 };
 
@@ -159,6 +160,9 @@ __global__ void __launch_bounds__(kThreads) k_stream_adjoint(AdjArgs<T> a)
         } else if (!kAct1) {
             qb[k] = T(1);
         }
+        qa[k] *= a.sign;
+        qb[k] *= a.sign;
+        qc[k] *= a.sign;
         vg[k] = (rin && cin) ? (unsigned)((gr - RB) * as1 + gc * as2) * S : kOut;
         vo[k] = (rown && cown) ? (unsigned)((gr - RB) * os1 + gc * os2) * S : kOut;
     }
@@ -345,12 +349,14 @@ hipError_t launch_adj_cfg(AdjArgs<T> a, hipStream_t st)
 
 // One adjoint level step: g / gv the input at the level grid's fine nodes, y
 // the solved corrections and G the coarse-node input (packed coarse grid
-// yv), O / ov the level-grid output.  O must not overlap g.
+// yv), O / ov the level-grid output.  O must not overlap g.  minus: t is
+// subtracted.
 template <typename T>
 hipError_t launch_stream_adjoint(const T* g, View3 gv, const T* y, const T* G, View3 yv, T* O, View3 ov,
-                                 DimTables<T> tb, hipStream_t st)
+                                 DimTables<T> tb, hipStream_t st, bool minus)
 {
     AdjArgs<T> a;
+    a.sign = minus ? T(-1) : T(1);
     a.g = g;
     a.gv = gv;
     a.y = y;
@@ -368,8 +374,8 @@ hipError_t launch_stream_adjoint(const T* g, View3 gv, const T* y, const T* G, V
 }
 
 template hipError_t launch_stream_adjoint<float>(const float*, View3, const float*, const float*, View3, float*,
-                                                 View3, DimTables<float>, hipStream_t);
+                                                 View3, DimTables<float>, hipStream_t, bool);
 template hipError_t launch_stream_adjoint<double>(const double*, View3, const double*, const double*, View3,
-                                                  double*, View3, DimTables<double>, hipStream_t);
+                                                  double*, View3, DimTables<double>, hipStream_t, bool);
 
 }  // namespace mgr

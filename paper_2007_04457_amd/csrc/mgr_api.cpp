@@ -78,7 +78,8 @@ struct Plan {
     std::vector<size_t> Woff;  // W_k element offsets, k = 1..L (index k)
     size_t F = 0, F2 = 0, Tb = 0, Yb = 0;  // F, F2: corrections of even, odd level steps
     size_t tail_lv = 0, tail_tab = 0;  // the tail's level descriptions (TailLevel, from level step 0 on) and tables
-    std::vector<TailLevel> tails;      // host copy of the descriptions
+    size_t adj_lv = 0, adj_tab = 0;    // the same for the adjoints' tail
+    std::vector<TailLevel> tails, adj_tails;  // host copies of the descriptions
     size_t Yb2 = 0;  // long-fibre solve scratch for the coarser level steps of a recomposition
     // Recomposition computes every level's correction before it is applied,
     // so it keeps one buffer per level step: Zrec[0] = F, Zrec[1] = F2, then
@@ -437,16 +438,8 @@ SolveTab build_solve(const std::vector<double>& yc)
     return t;
 }
 
-// Rows of B = M_{l-1}^{-1} R M_l of a level dimension in the layout of TailDim.
-// A row decays by about 0.27 a coarse node on either side of its own, so the
-// inputs whose weights together stay below 2^-58 (FP64) or 2^-30 (FP32) of a
-// row's sum are left out, over the whole dimension at the distance its worst
-// row needs.
-struct TailTabHost {
-    std::vector<double> B;
-    int nt = 0, off = 0;
-};
-TailTabHost build_tail_rows(const std::vector<double>& K, const SolveTab& sv, int64_t mc, size_t esize)
+// B = M_{l-1}^{-1} R M_l of a level dimension, mc x m.
+std::vector<double> tail_matrix(const std::vector<double>& K, const SolveTab& sv, int64_t mc)
 {
     const int64_t m = 2 * mc - 1;
     std::vector<double> lf((size_t)mc, 0.0), ip((size_t)mc, 0.0), x((size_t)mc), R((size_t)(mc * m), 0.0);
@@ -457,8 +450,6 @@ TailTabHost build_tail_rows(const std::vector<double>& K, const SolveTab& sv, in
         den = diag - (i > 0 ? lf[(size_t)i] * sv.sup[(size_t)(i - 1)] : 0.0);
         ip[(size_t)i] = 1.0 / den;
     }
-    const double tol = (esize == 8) ? 0x1p-58 : 0x1p-30;
-    int64_t h = 0;
     for (int64_t i = 0; i < mc; i++) {
         // M x = e_i (M is symmetric: x is also row i of its inverse)
         std::fill(x.begin(), x.end(), 0.0);
@@ -467,17 +458,42 @@ TailTabHost build_tail_rows(const std::vector<double>& K, const SolveTab& sv, in
         for (int64_t k = mc - 1; k >= 0; k--)
             x[(size_t)k] = (x[(size_t)k] - (k < mc - 1 ? sv.sup[(size_t)k] * x[(size_t)(k + 1)] : 0.0)) * ip[(size_t)k];
         double* row = &R[(size_t)(i * m)];
-        double sum = 0.0;
         for (int64_t k = 0; k < mc; k++)
             for (int t = -2; t <= 2; t++) {
                 const int64_t j = 2 * k + t;
                 if (j >= 0 && j < m) row[j] += x[(size_t)k] * K[(size_t)(5 * k + t + 2)];
             }
-        for (int64_t j = 0; j < m; j++) sum += std::fabs(row[j]);
-        double out = 0.0;
+    }
+    return R;
+}
+
+// Rows (columns: the adjoints) of B in the layout of TailDim.  B decays by about
+// 0.27 a coarse node on either side of its diagonal j = 2 i, so the entries
+// whose weights together stay below 2^-58 (FP64) or 2^-30 (FP32) of a row's
+// (column's) sum are left out, over the whole dimension at the distance |2 i -
+// j| that its worst row (column) needs.
+struct TailTabHost {
+    std::vector<double> B;
+    int nt = 0, off = 0;
+};
+TailTabHost pack_tail(const std::vector<double>& R, int64_t mc, size_t esize, bool columns)
+{
+    const int64_t m = 2 * mc - 1;
+    const double tol = (esize == 8) ? 0x1p-58 : 0x1p-30;
+    auto at = [&](int64_t i, int64_t j) { return R[(size_t)(i * m + j)]; };
+    int64_t h = 0;
+    for (int64_t q = 0; q < (columns ? m : mc); q++) {
+        double sum = 0.0, out = 0.0;
+        for (int64_t r = 0; r < (columns ? mc : m); r++) sum += std::fabs(columns ? at(r, q) : at(q, r));
         int64_t d = m;
         while (d > h) {  // distance d and beyond left out
-            const double w = (2 * i - d >= 0 ? std::fabs(row[2 * i - d]) : 0.0) + (2 * i + d < m ? std::fabs(row[2 * i + d]) : 0.0);
+            double w = 0.0;
+            if (!columns) {
+                w = (2 * q - d >= 0 ? std::fabs(at(q, 2 * q - d)) : 0.0) + (2 * q + d < m ? std::fabs(at(q, 2 * q + d)) : 0.0);
+            } else if (((q - d) & 1) == 0) {
+                const int64_t lo = (q - d) / 2, hi = (q + d) / 2;
+                w = (q - d >= 0 ? std::fabs(at(lo, q)) : 0.0) + (hi < mc ? std::fabs(at(hi, q)) : 0.0);
+            }
             if (out + w > tol * sum) break;
             out += w;
             d--;
@@ -485,13 +501,16 @@ TailTabHost build_tail_rows(const std::vector<double>& K, const SolveTab& sv, in
         h = std::max(h, d);
     }
     TailTabHost t;
-    t.nt = (int)std::min<int64_t>(m, 7 + 2 * h);
-    t.off = (int)h;
-    const int64_t ng = (mc + 3) / 4;
+    const int64_t no = columns ? m : mc, ni = columns ? mc : m, step = columns ? 2 : 8;
+    // inputs within h of the first and of the last output of a group
+    t.off = (int)(columns ? h / 2 : h);
+    t.nt = (int)std::min<int64_t>(ni, columns ? h / 2 + (h + 3) / 2 + 1 : 7 + 2 * h);
+    const int64_t ng = (no + 3) / 4;
     t.B.assign((size_t)(4 * ng * t.nt), 0.0);
-    for (int64_t i = 0; i < mc; i++) {
-        const int64_t g = i / 4, start = std::min(std::max<int64_t>(8 * g - h, 0), m - t.nt);
-        for (int q = 0; q < t.nt; q++) t.B[(size_t)((g * t.nt + q) * 4 + i % 4)] = R[(size_t)(i * m + start + q)];
+    for (int64_t o = 0; o < no; o++) {
+        const int64_t g = o / 4, start = std::min(std::max<int64_t>(step * g - t.off, 0), ni - t.nt);
+        for (int q = 0; q < t.nt; q++)
+            t.B[(size_t)((g * t.nt + q) * 4 + o % 4)] = columns ? at(start + q, o) : at(o, start + q);
     }
     return t;
 }
@@ -568,7 +587,7 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
         ly.tail = ly.tail && (k == L - 1 || p.lv[(size_t)(k + 1)].tail) &&
                   (small += tail_data_elems(ly)) <= kTailDataElems;
     }
-    std::vector<double> tail_tab;
+    std::vector<double> tail_tab, adj_tab;
     p.tails.assign((size_t)L, TailLevel{});
     for (int k = 0, cum = 0; k < L; k++) {
         const LevelLayout& ly = p.lv[(size_t)k];
@@ -595,6 +614,9 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
         t.tab = -1;
         cum += (int)tail_data_elems(ly);
     }
+    const bool adjoints = !dec_only && !p.gen;
+    p.adj_tails.clear();
+    if (adjoints) p.adj_tails = p.tails;
     for (int k = 0; k < L; k++) {
         LevelLayout& ly = p.lv[(size_t)k];
         for (int d = 0; d < 3; d++) {
@@ -614,17 +636,22 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             for (int64_t i = 0; i < ly.mc[d]; i++) yc[(size_t)i] = y[(size_t)std::min(2 * i, act - 1)];
             SolveTab sv = build_solve(yc);
             if (ly.tail) {
-                // weight pairs and rows of B of the level's tail tables
-                TailDim& td = p.tails[(size_t)k].d[d];
-                const TailTabHost tt = build_tail_rows(t.K, sv, ly.mc[d], sizeof(T));
-                td.nt = tt.nt;
-                td.off = tt.off;
-                if (p.tails[(size_t)k].tab < 0) p.tails[(size_t)k].tab = (int)tail_tab.size();
-                td.w = (int)tail_tab.size() - p.tails[(size_t)k].tab;
-                tail_tab.insert(tail_tab.end(), t.w.begin(), t.w.end());
-                while (tail_tab.size() % 4) tail_tab.push_back(0.0);
-                td.B = (int)tail_tab.size() - p.tails[(size_t)k].tab;
-                tail_tab.insert(tail_tab.end(), tt.B.begin(), tt.B.end());
+                // weight pairs and B of the level's tail tables
+                const std::vector<double> R = tail_matrix(t.K, sv, ly.mc[d]);
+                auto add = [&](TailLevel& tl, std::vector<double>& tab, bool columns) {
+                    TailDim& td = tl.d[d];
+                    const TailTabHost tt = pack_tail(R, ly.mc[d], sizeof(T), columns);
+                    td.nt = tt.nt;
+                    td.off = tt.off;
+                    if (tl.tab < 0) tl.tab = (int)tab.size();
+                    td.w = (int)tab.size() - tl.tab;
+                    tab.insert(tab.end(), t.w.begin(), t.w.end());
+                    while (tab.size() % 4) tab.push_back(0.0);
+                    td.B = (int)tab.size() - tl.tab;
+                    tab.insert(tab.end(), tt.B.begin(), tt.B.end());
+                };
+                add(p.tails[(size_t)k], tail_tab, false);
+                if (adjoints) add(p.adj_tails[(size_t)k], adj_tab, true);
             }
             ly.S[d] = sv.S;
             ly.dec[d] = separators_apart(sv.couple, sizeof(T));
@@ -640,14 +667,18 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             push_table(host, sv.su, &ly.su[d]);
         }
     }
+    // the descriptions as they are (4-byte words) among the tables
+    auto push_levels = [&](const std::vector<TailLevel>& lv, size_t* off) {
+        *off = host.size();
+        const size_t bytes = sizeof(TailLevel) * lv.size();
+        if (bytes == 0) return;
+        host.resize(align_up(*off + (bytes + sizeof(T) - 1) / sizeof(T), 64), T(0));
+        std::memcpy((void*)(host.data() + *off), lv.data(), bytes);
+    };
     push_table(host, tail_tab, &p.tail_tab);
-    p.tail_lv = host.size();
-    if (L > 0) {
-        // the descriptions as they are (4-byte words) among the tables
-        const size_t bytes = sizeof(TailLevel) * p.tails.size();
-        host.resize(align_up(p.tail_lv + (bytes + sizeof(T) - 1) / sizeof(T), 64), T(0));
-        std::memcpy((void*)(host.data() + p.tail_lv), p.tails.data(), bytes);
-    }
+    push_levels(p.tails, &p.tail_lv);
+    push_table(host, adj_tab, &p.adj_tab);
+    push_levels(p.adj_tails, &p.adj_lv);
     // workspace: W_1..W_L, corrections F, F2 (and per level for
     // recomposition), adjoint buffer Tb, long-fibre solve scratch Yb
     const size_t al = 256 / sizeof(T);
@@ -896,6 +927,7 @@ void set_gen(const Plan& p, int k, StreamArgs<T>& a)
 {
     a.gen = p.gen ? 1 : 0;
     for (int d = 0; d < 3; d++) a.ph[d] = p.lv[(size_t)k].ph[d];
+    a.keep_coarse = 0;
 }
 
 // Streaming level kernel of level step k: coefficients + load vector (dec,
@@ -926,14 +958,16 @@ int stream_level(const Plan& p, int k, bool dec, const T* A, const T* Z, View3 a
     return MGR_OK;
 }
 
-// Correction solves of level step k on F along every dimension, in place.
+// Correction solves of level step k along every dimension, in place or of src
+// into F.
 // whole_cu: a small grid may be solved by one workgroup that needs a whole
 // CU (all dimensions in one launch); a caller whose launches share the
 // device with long-running kernels on another stream passes false, since
 // such a workgroup waits until one CU has drained completely (the
 // per-dimension launches give the same values).
 template <typename T>
-int solve_all(const Plan& p, int k, bool reverse, T* F, hipStream_t st, T* Yb = nullptr, bool whole_cu = true)
+int solve_all(const Plan& p, int k, bool reverse, T* F, hipStream_t st, T* Yb = nullptr, bool whole_cu = true,
+              const T* src = nullptr)
 {
     T* ws = (T*)p.ws;
     View3 fv = packed(p.lv[(size_t)k].mc);
@@ -948,21 +982,26 @@ int solve_all(const Plan& p, int k, bool reverse, T* F, hipStream_t st, T* Yb = 
             tbs[nd++] = solve_tables_of<T>(p, k, d);
         }
         if (solve_small_fits<T>(fv, dims, nd, tbs)) {
-            MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_small<T>(F, fv, dims, nd, tbs, st); }),
+            MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_small<T>(F, fv, dims, nd, tbs, st, src); }),
                     "small solve launch");
             return MGR_OK;
         }
-        // planes that fit in LDS: dimensions 2 and 1 in one launch, then 0
-        if (!reverse && p.active[1] && p.active[2]) {
+        // planes that fit in LDS: dimensions 2 and 1 in one launch, after 0 or
+        // before it
+        if (p.active[1] && p.active[2] && (reverse || !src)) {
             const SolveTables<T> t2 = solve_tables_of<T>(p, k, 2), t1 = solve_tables_of<T>(p, k, 1);
             if (solve_plane_fits<T>(fv, t2, t1)) {
-                MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_plane<T>(F, fv, t2, t1, st); }),
-                        "plane solve launch");
-                if (p.active[0]) {
-                    SolveTables<T> t0 = solve_tables_of<T>(p, k, 0);
-                    MGR_TRY(timed(KC_SOLVE, k, st,
-                                  [&] { return launch_solve_partitioned<T>(F, fv, 0, t0, Yb ? Yb : ws + p.Yb, st); }),
-                            "solve launch");
+                for (int s = 0; s < 2; s++) {
+                    if ((s == 0) == reverse) {
+                        if (!p.active[0]) continue;
+                        const SolveTables<T> t0 = solve_tables_of<T>(p, k, 0);
+                        MGR_TRY(timed(KC_SOLVE, k, st,
+                                      [&] { return launch_solve_partitioned<T>(F, fv, 0, t0, Yb ? Yb : ws + p.Yb, st, src); }),
+                                "solve launch");
+                    } else {
+                        MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_plane<T>(F, fv, t2, t1, st); }),
+                                "plane solve launch");
+                    }
                 }
                 return MGR_OK;
             }
@@ -973,8 +1012,9 @@ int solve_all(const Plan& p, int k, bool reverse, T* F, hipStream_t st, T* Yb = 
         if (!p.active[d]) continue;
         SolveTables<T> tb = solve_tables_of<T>(p, k, d);
         MGR_TRY(timed(KC_SOLVE, k, st,
-                      [&] { return launch_solve_partitioned<T>(F, fv, d, tb, Yb ? Yb : ws + p.Yb, st); }),
+                      [&] { return launch_solve_partitioned<T>(F, fv, d, tb, Yb ? Yb : ws + p.Yb, st, src); }),
                 "solve launch");
+        src = nullptr;
     }
     return MGR_OK;
 }
@@ -1011,7 +1051,7 @@ int tail_start(const Plan& p)
 }
 
 template <typename T>
-TailArgs<T> tail_args(const Plan& p, int k0, const T* src, T* dst, void* wsp = nullptr)
+TailArgs<T> tail_args(const Plan& p, int k0, const T* src, T* dst, void* wsp = nullptr, bool adjoint = false)
 {
     TailArgs<T> a;
     std::memset(&a, 0, sizeof(a));
@@ -1026,14 +1066,15 @@ TailArgs<T> tail_args(const Plan& p, int k0, const T* src, T* dst, void* wsp = n
     a.src = src;
     a.dst = dst;
     a.Wk = (k0 == 0) ? nullptr : ws + p.Woff[(size_t)k0];
-    a.lv = (const TailLevel*)(base + p.tail_lv) + k0;
-    const TailLevel &t0 = p.tails[(size_t)k0], &t1 = p.tails.back();
-    a.tab = base + p.tail_tab + t0.tab;
+    const std::vector<TailLevel>& tails = adjoint ? p.adj_tails : p.tails;
+    a.lv = (const TailLevel*)(base + (adjoint ? p.adj_lv : p.tail_lv)) + k0;
+    const TailLevel &t0 = tails[(size_t)k0], &t1 = tails.back();
+    a.tab = base + (adjoint ? p.adj_tab : p.tail_tab) + t0.tab;
     // (the tables after the arrays start at a multiple of four elements)
     a.data_elems = (int)align_up((size_t)(t1.cum - t0.cum) + (size_t)tail_data_elems(p.lv.back()), 4);
     a.tab_elems = t1.tab - t0.tab;
     for (int d = 0; d < 3; d++)
-        if (t1.d[d].m > 1) a.tab_elems += tail_tab_len(t1.d[d].m, t1.d[d].mc, t1.d[d].nt);
+        if (t1.d[d].m > 1) a.tab_elems += tail_tab_len(t1.d[d].m, adjoint ? t1.d[d].m : t1.d[d].mc, t1.d[d].nt);
     return a;
 }
 
@@ -1304,18 +1345,23 @@ int run_adjoint(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     const T* src = (const T*)src_;
     T* dst = (T*)dst_;
     T* ws = (T*)p.ws;
-    View3 cl = level_view(p, L);
-    MGR_TRY(timed(KC_COPY_VIEW, L, st,
-                  [&] { return launch_copy_view<T>(src, nullptr, cl, ws + p.Woff[(size_t)L], packed(cl.n), st); }),
-            "coarsest gather");
-    for (int k = L - 1; k >= 0; k--) {
+    const int kt = tail_start(p);
+    if (kt < L) {
+        // the small level steps in one workgroup (which has read its input
+        // before it writes: in place too)
+        const TailArgs<T> a = tail_args<T>(p, kt, src, dst, nullptr, true);
+        MGR_TRY(timed(KC_ADJOINT, kt, st, [&] { return launch_tail_adjoint<T>(a, false, st); }), "adjoint tail launch");
+    } else {
+        View3 cl = level_view(p, L);
+        MGR_TRY(timed(KC_COPY_VIEW, L, st,
+                      [&] { return launch_copy_view<T>(src, nullptr, cl, ws + p.Woff[(size_t)L], packed(cl.n), st); }),
+                "coarsest gather");
+    }
+    for (int k = kt - 1; k >= 0; k--) {
         const LevelLayout& ly = p.lv[(size_t)k];
         T* G = ws + p.Woff[(size_t)k + 1];
         View3 gv = packed(ly.mc);
-        int64_t nc = ly.mc[0] * ly.mc[1] * ly.mc[2];
-        MGR_TRY(hipMemcpyAsync(ws + p.F, G, (size_t)nc * sizeof(T), hipMemcpyDeviceToDevice, st),
-                "adjoint copy");
-        int rc = solve_all<T>(p, k, true, ws + p.F, st);
+        int rc = solve_all<T>(p, k, true, ws + p.F, st, nullptr, true, G);
         if (rc) return rc;
         // the level-grid output: fine nodes g + (M P) y, coarse nodes G minus
         // the transposed interpolation of the fine outputs; in place, the
@@ -1340,18 +1386,17 @@ int run_adjoint(const Plan& p, const void* src_, void* dst_, hipStream_t st)
 
 // Transpose of the recomposition (D^{-T}), fine to coarse.  Per level step,
 // with g the level grid (the input at k = 0, else W_k):
-//   Ft = P^T g_f (load-vector pass with P^T as its stencil; coarse positions
-//        read as zero),
-//   G = g_c + Ft -> W_{k+1} (the next step's grid), and -G into the solve
-//        buffer,
-//   y = M_c^{-1} (-G) (solves, dimensions first to last),
-//   out_f = g_f + (M P) y at the level grid's fine-only nodes, written to their
+//   G = g_c + P^T g_f -> W_{k+1} (the next step's grid): the load-vector pass
+//        with P^T as its stencil, whose centre is 1, over the whole level grid,
+//   y = M_c^{-1} G (solves, dimension 0 first),
+//   out_f = g_f - (M P) y at the level grid's fine-only nodes, written to their
 //        final places in dst (the adjoint kernel; the values it also writes at
 //        coarse positions are overwritten by the coarser steps),
 // and finally the coarsest grid W_L to its nodes.  In place, each step reads
 // the input's coarse values (into W_{k+1}) before the expansion overwrites
 // them; the finest step's expansion, whose tiles also read halo inputs of
-// their neighbours, writes to the workspace and is copied back.
+// their neighbours, writes to the workspace and is copied back.  The small
+// level steps run in one workgroup.
 template <typename T>
 int run_recompose_adjoint(const Plan& p, const void* src_, void* dst_, hipStream_t st)
 {
@@ -1360,11 +1405,13 @@ int run_recompose_adjoint(const Plan& p, const void* src_, void* dst_, hipStream
     const T* src = (const T*)src_;
     T* dst = (T*)dst_;
     T* ws = (T*)p.ws;
-    for (int k = 0; k < L; k++) {
+    const int kt = tail_start(p);
+    for (int k = 0; k < kt; k++) {
         const LevelLayout& ly = p.lv[(size_t)k];
         const T* g = (k == 0) ? src : ws + p.Woff[(size_t)k];
         const View3 gv = grid_view(p, k);
         T* F = corr<T>(p, k);
+        T* W = ws + p.Woff[(size_t)k + 1];
         const View3 cv = packed(ly.mc);
         {
             StreamArgs<T> a;
@@ -1375,23 +1422,17 @@ int run_recompose_adjoint(const Plan& p, const void* src_, void* dst_, hipStream
             a.cv = gv;
             a.W = nullptr;
             a.wv = cv;
-            a.F = F;
+            a.F = W;
             a.fv = cv;
             a.tb = pt_tables_of<T>(p, k);
             a.write_coarse = 0;
             a.chunk = a.nt1 = a.nt2 = a.nch = 0;
             set_gen(p, k, a);
+            a.keep_coarse = 1;
             MGR_TRY(timed(KC_STREAM_LOAD, k, st, [&] { return launch_stream_level<T>(a, false, st); }),
                     "transposed interpolation launch");
         }
-        View3 gc = gv;  // the coarse nodes of the level grid
-        for (int d = 0; d < 3; d++) {
-            gc.n[d] = ly.mc[d];
-            gc.s[d] = p.active[d] ? 2 * gv.s[d] : gv.s[d];
-        }
-        T* W = ws + p.Woff[(size_t)k + 1];
-        MGR_TRY(launch_add_split<T>(g, gc, F, W, F, st), "combine launch");
-        int rc = solve_all<T>(p, k, true, F, st);
+        int rc = solve_all<T>(p, k, true, F, st, nullptr, true, W);
         if (rc) return rc;
         // in place, the finest step's tiles would re-read halo inputs that a
         // neighbouring tile has already overwritten: it goes through the
@@ -1401,12 +1442,18 @@ int run_recompose_adjoint(const Plan& p, const void* src_, void* dst_, hipStream
         T* out = via_tb ? ws + p.Tb : dst;
         const View3 ov = via_tb ? full_view(p) : level_view(p, k);
         MGR_TRY(timed(KC_ADJOINT, k, st,
-                      [&] { return launch_stream_adjoint<T>(g, gv, F, W, cv, out, ov, tables_of<T>(p, k), st); }),
+                      [&] { return launch_stream_adjoint<T>(g, gv, F, W, cv, out, ov, tables_of<T>(p, k), st, true); }),
                 "recomposition adjoint level launch");
         if (via_tb) {
             const size_t bytes = (size_t)(p.n[0] * p.n[1] * p.n[2]) * sizeof(T);
             MGR_TRY(hipMemcpyAsync(dst, ws + p.Tb, bytes, hipMemcpyDeviceToDevice, st), "adjoint copy-out");
         }
+    }
+    if (kt < L) {
+        const TailArgs<T> a = tail_args<T>(p, kt, src, dst, nullptr, true);
+        MGR_TRY(timed(KC_ADJOINT, kt, st, [&] { return launch_tail_adjoint<T>(a, true, st); }),
+                "recomposition adjoint tail launch");
+        return MGR_OK;
     }
     View3 cl = level_view(p, L);
     MGR_TRY(timed(KC_COPY_VIEW, L, st,

@@ -111,7 +111,7 @@ __device__ __attribute__((noinline)) void exec_strided(const BatchKernelArgs<T>*
     const BatchItem it = load_uniform(itp);
     const BatchSolve<T> b = load_uniform(A->solves + it.args);
     const int tid = threadIdx.x;
-    solve_strided_tile<T, 16, false>(b.F, fibre_map(b), b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads,
+    solve_strided_tile<T, 16, false>(b.F, b.F, fibre_map(b), b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads,
                                      tid, *reinterpret_cast<StridedSmem<T>*>(batch_lds), 0, b.tb.S, nullptr);
 }
 
@@ -156,7 +156,7 @@ __device__ __attribute__((noinline)) void exec_chunk_strided(const BatchKernelAr
     const FibreMap m = fibre_map(b);
     const int ns = solve_chunk_segs(m.S, m.inner, m.nfib), s0 = it.by * ns;
     const int tid = threadIdx.x;
-    solve_strided_tile<T, 16, false>(b.F, m, b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads, tid,
+    solve_strided_tile<T, 16, false>(b.F, b.F, m, b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads, tid,
                                      *reinterpret_cast<StridedSmem<T>*>(batch_lds), s0, min(ns, m.S - s0),
                                      b.Yb + ((int64_t)it.by - 1) * m.nfib);
 }

@@ -69,6 +69,7 @@ struct StreamArgs {
     int write_coarse;  // also write u at coarse positions of C
     int gen;           // any-length level grid: offsets through View3::last, phantoms
     int ph[3];         // index of the phantom node of A (and C) along each dimension, or -1
+    int keep_coarse;   // load-vector pass: coarse positions count as they are, not as zero
     int chunk, nt1, nt2, nch;  // filled in by the launcher
 };
 
@@ -121,16 +122,18 @@ __host__ __device__ inline int solve_chunk_segs(int S, int64_t inner, int64_t nf
     return 16;
 }
 
-// In-place correction solve of F along dimension d.
+// Correction solve of F along dimension d, in place, or of src into F.
 template <typename T>
-hipError_t launch_solve_partitioned(T* F, View3 fv, int d, SolveTables<T> tb, T* Yb, hipStream_t st);
+hipError_t launch_solve_partitioned(T* F, View3 fv, int d, SolveTables<T> tb, T* Yb, hipStream_t st,
+                                    const T* src = nullptr);
 // All active dimensions of a small coarse grid in one workgroup (order:
 // dimensions dims[0], dims[1], ... of the nd listed), each fibre by the same
 // segment arithmetic as launch_solve_partitioned; returns hipErrorNotSupported
 // (launching nothing) unless every listed dimension is one segment long and
-// the grid fits in the workgroup's LDS.
+// the grid fits in the workgroup's LDS.  In place, or of src into F.
 template <typename T>
-hipError_t launch_solve_small(T* F, View3 fv, const int* dims, int nd, const SolveTables<T>* tb, hipStream_t st);
+hipError_t launch_solve_small(T* F, View3 fv, const int* dims, int nd, const SolveTables<T>* tb, hipStream_t st,
+                              const T* src = nullptr);
 template <typename T>
 bool solve_small_fits(View3 fv, const int* dims, int nd, const SolveTables<T>* tb);
 // Dimensions 2 and then 1 of the packed array F (sizes fv, 3-D) in one
@@ -160,7 +163,9 @@ constexpr int kTailLdsBytes = 18400 * 8;
 // One dimension: interpolation weight pairs w (as DimTables) and the rows of
 // B = M_{l-1}^{-1} R M_l, four outputs to a group: group g (outputs 4 g .. 4 g +
 // 3) reads the nt inputs from clamp(8 g - off, 0, m - nt) on, and
-// B[(g nt + t) 4 + o] weights input t for output 4 g + o.
+// B[(g nt + t) 4 + o] weights input t for output 4 g + o.  The adjoints have
+// descriptions of their own, with the columns of B: outputs are the level
+// grid's nodes, inputs the coarse ones from clamp(2 g - off, 0, mc - nt) on.
 struct TailDim {
     int m, mc;      // level grid (with its phantom) and coarse nodes (1 for inactive dims)
     int act, ph;    // nodes without the phantom, the phantom's index (or -1)
@@ -196,6 +201,11 @@ struct TailArgs {
 
 template <typename T>
 hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st);
+// The adjoint of the same steps of the decomposition (in: the classes in src;
+// out: Wk, or dst for k0 = 0) or of the recomposition (in: Wk, or src for k0 =
+// 0; out: dst), with the adjoints' descriptions and tables.
+template <typename T>
+hipError_t launch_tail_adjoint(const TailArgs<T>& a, bool recompose, hipStream_t st);
 // Decompositions, one workgroup per entry: dev_args[i] in device memory,
 // applied to field field[i] of the per-field pointer tables src / dst (device
 // memory).  lds_elems: the largest LDS need over the entries
@@ -240,9 +250,10 @@ hipError_t launch_solve_multi(T* const* F, const View3* fv, int d, const SolveTa
 // One adjoint level step (mgr_adjoint.hip): g / gv the input at the level
 // grid's fine nodes, y the solved corrections and G the coarse-node input
 // (packed coarse grid yv), O / ov the level-grid output (not overlapping g).
+// minus: the expanded y is subtracted.
 template <typename T>
 hipError_t launch_stream_adjoint(const T* g, View3 gv, const T* y, const T* G, View3 yv, T* O, View3 ov,
-                                 DimTables<T> tb, hipStream_t st);
+                                 DimTables<T> tb, hipStream_t st, bool minus = false);
 // Coarse rows and columns per decomposition tile (act1: the problem has a
 // second active dimension; elem_bytes: 4 or 8; wide: the two-wave-wide 3-D
 // geometry); workgroup id = (chunk * nt1 + t1) * nt2 + t2.
@@ -466,10 +477,6 @@ template <typename T>
 hipError_t launch_copy_view(const T* X, const T* Z, View3 xv, T* Y, View3 yv, hipStream_t st);
 
 hipError_t launch_bench_copy(const void* src, void* dst, size_t nbytes, hipStream_t st);
-// Y[i] = X(view xv)[i] + Z[i] and N[i] = -Y[i] for every node i of xv, with
-// Z, Y, N packed (N may alias Z).
-template <typename T>
-hipError_t launch_add_split(const T* X, View3 xv, const T* Z, T* Y, T* N, hipStream_t st);
 
 // Class-packed layout (mgr_packed.hip): grid sizes in the internal 3-D form,
 // level count L and the start of every class segment off[0..L+1].
@@ -564,9 +571,9 @@ template <typename T>
 hipError_t launch_mass01(const T* in, T* out, const Plane4<T>& a, hipStream_t st);
 
 // Partitioned solve of every fibre of length n along the middle index of a
-// packed (outer, n, inner) box, in place; Yb as for launch_solve_partitioned.
+// packed (outer, n, inner) box; src and Yb as for launch_solve_partitioned.
 template <typename T>
 hipError_t launch_solve_fibres(T* F, int64_t n, int64_t inner, int64_t outer, SolveTables<T> tb, T* Yb,
-                               hipStream_t st);
+                               hipStream_t st, const T* src = nullptr);
 
 }  // namespace mgr

@@ -36,14 +36,14 @@ namespace {
 
 template <typename T>
 __global__ void __launch_bounds__(64 * kMaxSegWG)
-k_solve_strided_wg(T* __restrict__ F, FibreMap m, SolveTables<T> tb)
+k_solve_strided_wg(const T* in, T* F, FibreMap m, SolveTables<T> tb)
 {
     __shared__ StridedSmem<T> sm;
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.y);
     // neighbouring fibre groups split cache lines of every segment row they
     // write: keep them on one XCD (one L2)
     const int bx = remap_xcd((int)blockIdx.x, (int)gridDim.x);
-    solve_strided_tile<T, 64, true>(F, m, tb, (int64_t)bx * 64, s, (int)threadIdx.x, 64 * m.S,
+    solve_strided_tile<T, 64, true>(in, F, m, tb, (int64_t)bx * 64, s, (int)threadIdx.x, 64 * m.S,
                                     (int)(threadIdx.y * 64 + threadIdx.x), sm, 0, m.S, nullptr);
 }
 
@@ -52,13 +52,13 @@ k_solve_strided_wg(T* __restrict__ F, FibreMap m, SolveTables<T> tb)
 // barriers.
 template <typename T>
 __global__ void __launch_bounds__(64 * kMaxSegWG)
-k_solve_strided_chunk(T* __restrict__ F, const T* __restrict__ zb, FibreMap m, SolveTables<T> tb, int ns, int nfb)
+k_solve_strided_chunk(const T* in, T* F, const T* __restrict__ zb, FibreMap m, SolveTables<T> tb, int ns, int nfb)
 {
     __shared__ StridedSmem<T> sm;
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.y);
     const int b = remap_xcd((int)blockIdx.x, (int)gridDim.x);
     const int c = b / nfb, bx = b - c * nfb, s0 = c * ns;
-    solve_strided_tile<T, 64, false>(F, m, tb, (int64_t)bx * 64, s, (int)threadIdx.x, 64 * (int)blockDim.y,
+    solve_strided_tile<T, 64, false>(in, F, m, tb, (int64_t)bx * 64, s, (int)threadIdx.x, 64 * (int)blockDim.y,
                                      (int)(threadIdx.y * 64 + threadIdx.x), sm, s0, min(ns, m.S - s0),
                                      zb + ((int64_t)c - 1) * m.nfib);
 }
@@ -175,6 +175,7 @@ constexpr int kSmallThreads = 1024;
 
 template <typename T>
 struct SmallSolveArgs {
+    const T* in;
     T* F;
     int n[3];
     int nd, dims[3];
@@ -200,7 +201,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(SmallSolveArgs<T>
     for (int b0 = 0; b0 < V; b0 += NB * kSmallThreads) {
         T tmp[NB];
 #pragma unroll
-        for (int q = 0; q < NB; q++) tmp[q] = a.F[min(b0 + q * kSmallThreads + tid, V - 1)];
+        for (int q = 0; q < NB; q++) tmp[q] = a.in[min(b0 + q * kSmallThreads + tid, V - 1)];
         if (b0 == 0)
             for (int e = tid; e < a.nd * 3 * kSlot; e += kSmallThreads) {
                 const int dd = e / (3 * kSlot), w = (e / kSlot) % 3, q = e % kSlot;
@@ -412,7 +413,7 @@ __global__ void __launch_bounds__(kMaxThr) k_solve_strided_multi(MultiSolve<T> a
     const int b = remap_xcd((int)blockIdx.x, (int)gridDim.x);
     const int l = multi_entry(a, b);
     const int s = __builtin_amdgcn_readfirstlane(threadIdx.y);
-    solve_strided_tile<T, 64, false>(a.F[l], a.m[l], a.tb[l], (int64_t)(b - a.start[l]) * 64, s, (int)threadIdx.x,
+    solve_strided_tile<T, 64, false>(a.F[l], a.F[l], a.m[l], a.tb[l], (int64_t)(b - a.start[l]) * 64, s, (int)threadIdx.x,
                                      (int)(64 * blockDim.y), (int)(threadIdx.y * 64 + threadIdx.x), sm, 0, a.m[l].S,
                                      nullptr);
 }
@@ -486,17 +487,17 @@ template hipError_t launch_solve_multi<double>(double* const*, const View3*, int
 // Solve along dimension d of the packed array F (shape fv.n), in place.  Yb
 // is scratch of at least 2 * S * (number of fibres) elements.
 template <typename T>
-hipError_t launch_solve_partitioned(T* F, View3 fv, int d, SolveTables<T> tb, T* Yb, hipStream_t st)
+hipError_t launch_solve_partitioned(T* F, View3 fv, int d, SolveTables<T> tb, T* Yb, hipStream_t st, const T* src)
 {
     int64_t inner = 1, outer = 1;
     for (int e = d + 1; e < 3; e++) inner *= fv.n[e];
     for (int e = 0; e < d; e++) outer *= fv.n[e];
-    return launch_solve_fibres<T>(F, fv.n[d], inner, outer, tb, Yb, st);
+    return launch_solve_fibres<T>(F, fv.n[d], inner, outer, tb, Yb, st, src);
 }
 
 template <typename T>
 hipError_t launch_solve_fibres(T* F, int64_t n, int64_t inner, int64_t outer, SolveTables<T> tb, T* Yb,
-                               hipStream_t st)
+                               hipStream_t st, const T* src)
 {
     FibreMap m;
     m.n = n;
@@ -505,7 +506,15 @@ hipError_t launch_solve_fibres(T* F, int64_t n, int64_t inner, int64_t outer, So
     m.nfib = m.inner * m.outer;
     m.S = tb.S;
     const int ns = solve_chunk_segs(m.S, m.inner, m.nfib);
-    if (tb.dec && ns < m.S) {
+    const bool chunks = tb.dec && ns < m.S;
+    if (src && src != F && !(m.inner > 1 && (chunks || m.S <= kMaxSegWG))) {
+        // only the strided kernels of one pass read another array
+        const hipError_t e = hipMemcpyAsync(F, src, (size_t)(m.nfib * n) * sizeof(T), hipMemcpyDeviceToDevice, st);
+        if (e != hipSuccess) return e;
+        src = nullptr;
+    }
+    if (!src) src = F;
+    if (chunks) {
         // chunks of ns segments: the separators between them first, from the
         // rows around each, then every chunk by itself in one pass.  4097 x
         // 4097 FP64 nodes (134 MB): rows 112 us, against 266 us with a whole
@@ -515,11 +524,11 @@ hipError_t launch_solve_fibres(T* F, int64_t n, int64_t inner, int64_t outer, So
         // through global memory).  Bound by memory: 3.2 TB/s.
         const int nch = (m.S + ns - 1) / ns;
         if (m.inner > 1) {
-            hipLaunchKernelGGL(k_sep_bounds_strided<T>, dim3(blocks(m.nfib) * (unsigned)(nch - 1)), dim3(kBlk), 0, st, F,
+            hipLaunchKernelGGL(k_sep_bounds_strided<T>, dim3(blocks(m.nfib) * (unsigned)(nch - 1)), dim3(kBlk), 0, st, src,
                                Yb, m, tb, ns);
             const int nfb = (int)((m.nfib + 63) / 64);
-            hipLaunchKernelGGL(k_solve_strided_chunk<T>, dim3((unsigned)(nfb * nch)), dim3(64, (unsigned)ns), 0, st, F,
-                               Yb, m, tb, ns, nfb);
+            hipLaunchKernelGGL(k_solve_strided_chunk<T>, dim3((unsigned)(nfb * nch)), dim3(64, (unsigned)ns), 0, st, src,
+                               F, Yb, m, tb, ns, nfb);
         } else {
             const int64_t units = m.nfib * (nch - 1);
             hipLaunchKernelGGL(k_sep_bounds_rows<T>, dim3((unsigned)((units + 3) / 4)), dim3(kBlk), 0, st, F, Yb, m, tb,
@@ -539,7 +548,7 @@ hipError_t launch_solve_fibres(T* F, int64_t n, int64_t inner, int64_t outer, So
     }
     if (m.inner > 1 && m.S <= kMaxSegWG) {
         hipLaunchKernelGGL(k_solve_strided_wg<T>, dim3((unsigned)((m.nfib + 63) / 64)), dim3(64, m.S), 0, st,
-                           F, m, tb);
+                           src, F, m, tb);
         return hipGetLastError();
     }
     const dim3 grid = (m.inner > 1) ? dim3(blocks(m.nfib), (unsigned)m.S) : dim3(blocks(m.nfib * m.S));
@@ -587,10 +596,12 @@ bool solve_small_fits(View3 fv, const int* dims, int nd, const SolveTables<T>* t
 }
 
 template <typename T>
-hipError_t launch_solve_small(T* F, View3 fv, const int* dims, int nd, const SolveTables<T>* tb, hipStream_t st)
+hipError_t launch_solve_small(T* F, View3 fv, const int* dims, int nd, const SolveTables<T>* tb, hipStream_t st,
+                              const T* src)
 {
     if (!solve_small_fits(fv, dims, nd, tb)) return hipErrorNotSupported;
     SmallSolveArgs<T> a;
+    a.in = src ? src : F;
     a.F = F;
     for (int d = 0; d < 3; d++) a.n[d] = (int)fv.n[d];
     a.nd = nd;
@@ -666,16 +677,17 @@ template hipError_t launch_solve_plane<double>(double*, View3, const SolveTables
 
 template bool solve_small_fits<float>(View3, const int*, int, const SolveTables<float>*);
 template bool solve_small_fits<double>(View3, const int*, int, const SolveTables<double>*);
-template hipError_t launch_solve_small<float>(float*, View3, const int*, int, const SolveTables<float>*, hipStream_t);
+template hipError_t launch_solve_small<float>(float*, View3, const int*, int, const SolveTables<float>*, hipStream_t,
+                                              const float*);
 template hipError_t launch_solve_small<double>(double*, View3, const int*, int, const SolveTables<double>*,
-                                               hipStream_t);
+                                               hipStream_t, const double*);
 template hipError_t launch_solve_fibres<float>(float*, int64_t, int64_t, int64_t, SolveTables<float>, float*,
-                                               hipStream_t);
+                                               hipStream_t, const float*);
 template hipError_t launch_solve_fibres<double>(double*, int64_t, int64_t, int64_t, SolveTables<double>, double*,
-                                               hipStream_t);
+                                               hipStream_t, const double*);
 template hipError_t launch_solve_partitioned<float>(float*, View3, int, SolveTables<float>, float*,
-                                                    hipStream_t);
+                                                    hipStream_t, const float*);
 template hipError_t launch_solve_partitioned<double>(double*, View3, int, SolveTables<double>, double*,
-                                                    hipStream_t);
+                                                    hipStream_t, const double*);
 
 }  // namespace mgr

@@ -124,7 +124,7 @@ __device__ __forceinline__ T sep_alone(T f, T sub, T ylast, T sup, T yfirst, T i
 // its two outer separators are then in zb, the chunk's own at zb[fib], the
 // next one's at zb[nfib + fib]).  kAllSeg: every s < ns.
 template <typename T, int FB, bool kAllSeg>
-__device__ __forceinline__ void solve_strided_tile(T* __restrict__ F, const FibreMap& m,
+__device__ __forceinline__ void solve_strided_tile(const T* in, T* F, const FibreMap& m,
                                                    const SolveTables<T>& tb, int64_t fib0, int s,
                                                    int j, int nthr, int tid, StridedSmem<T>& sm,
                                                    int s0, int ns, const T* __restrict__ zb)
@@ -144,8 +144,8 @@ __device__ __forceinline__ void solve_strided_tile(T* __restrict__ F, const Fibr
     // for their loads before the fibre loads were issued)
     T v[kSlot];
 #pragma unroll
-    for (int q = 0; q < kSlot; q++) v[q] = F[base + (int64_t)(lo + min(q, len - 1)) * m.inner];
-    const T fsep = F[base + (int64_t)((s0 + sc) * kSeg) * m.inner];  // f at the segment's left separator
+    for (int q = 0; q < kSlot; q++) v[q] = in[base + (int64_t)(lo + min(q, len - 1)) * m.inner];
+    const T fsep = in[base + (int64_t)((s0 + sc) * kSeg) * m.inner];  // f at the segment's left separator
     T zol = T(0), zor = T(0);
     if (outer_l) zol = zb[fc];
     if (outer_r) zor = zb[m.nfib + fc];

@@ -392,7 +392,8 @@ __device__ __forceinline__ void stream_level_tile(const StreamArgs<T>& a, int bi
 #pragma unroll
                 for (int j = 0; j < CPL; j++) {
                     // coarse positions hold other classes: read them as zero
-                    const bool ce = !((cb + j) & 1);
+                    // (not so where the pass restricts a whole level grid)
+                    const bool ce = !((cb + j) & 1) && !a.keep_coarse;
                     sC_at(k, j) = (even && !RP && ce) ? T(0) : cur[k][j];
                 }
             }

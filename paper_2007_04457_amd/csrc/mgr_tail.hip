@@ -90,15 +90,20 @@ struct Tap {
     typedef T V __attribute__((ext_vector_type(4), aligned(16)));
 };
 
-// Dot products of one dimension: the array `in` is (outer, D.m, inner); n
-// results at a time go to out(o, inner, n, v): v[k] is element o + k inner of
-// (outer, D.mc, inner).
-template <typename T, class Out>
+// Dot products of one dimension: the array `in` is (outer, m, inner); n results
+// at a time go to out(o, inner, n, v): v[k] is element o + k inner of (outer,
+// mc, inner).  m and mc are the level grid and its coarse nodes with the rows
+// of B (kStep 8: input nodes per group of four outputs), the other way round
+// with its columns (the adjoints: kStep 2).
+template <int kStep, typename T, class Out>
 __device__ __forceinline__ void tail_dots(const TailDim& D, const T* B, const T* in, int outer, int inner, float rinner,
                                           Out out)
 {
-    const int m = D.m, nt = uni(D.nt), mc = D.mc, off = D.off, smax = m - nt, nfib = uni(outer * inner);
-    auto start_of = [&](int g) { return min(max(8 * g - off, 0), smax); };
+    constexpr bool kRows = kStep == 8;
+    const int m = kRows ? D.m : D.mc, mc = kRows ? D.mc : D.m;
+    const float rmc = kRows ? D.rmc : D.rm;
+    const int nt = uni(D.nt), off = D.off, smax = m - nt, nfib = uni(outer * inner);
+    auto start_of = [&](int g) { return min(max(kStep * g - off, 0), smax); };
     if (nfib >= 32) {
         const int lane = threadIdx.x & 63, wave = uni((int)(threadIdx.x >> 6));
         const int nch = (nfib + 63) >> 6, units = nch * ((uni(mc) + 3) >> 2);
@@ -128,7 +133,7 @@ __device__ __forceinline__ void tail_dots(const TailDim& D, const T* B, const T*
     } else {
         // few fibres: a lane per output
         for (int e = threadIdx.x; e < nfib * mc; e += kT) {
-            const int f = fdiv(e, D.rmc), i = e - __mul24(f, mc), g = i >> 2;
+            const int f = fdiv(e, rmc), i = e - __mul24(f, mc), g = i >> 2;
             const int q = fdiv(f, rinner), r = f - __mul24(q, inner);
             const T* x = in + __mul24(__mul24(q, m) + start_of(g), inner) + r;
             const T* b = B + 4 * __mul24(nt, g) + (i & 3);
@@ -158,7 +163,7 @@ __device__ __forceinline__ void tail_phase(const TailLevel& L, const T* tab, T* 
     const int outer = (d == 2) ? L.d[0].m * L.d[1].m : (d == 1) ? L.d[0].m : 1;
     const int inner = (d == 2) ? 1 : (d == 1) ? L.d[2].mc : L.d[1].mc * L.d[2].mc;
     const float rinner = (d == 2) ? 1.0f : (d == 1) ? L.d[2].rmc : L.d[1].rmc * L.d[2].rmc;
-    tail_dots(L.d[d], tab + L.d[d].B, in, outer, inner, rinner, [&](int c, int step, int n, const auto& v) {
+    tail_dots<8>(L.d[d], tab + L.d[d].B, in, outer, inner, rinner, [&](int c, int step, int n, const auto& v) {
         if (last) {
             fin(c, step, n, v);
         } else {
@@ -237,9 +242,30 @@ struct TailStatic {
 };
 static_assert(sizeof(TailStatic) + kTailLdsBytes <= 163840, "fits a CU's LDS");
 
-template <typename T, bool kDec, bool kLdsTab>
-__device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* lds, TailStatic& sm)
+// Offsets in the user's arrays of node (j0, j1, j2) of the level l steps after
+// the tail's first.
+struct TailUser {
+    const int64_t *off0, *off1, *off2;
+    int x0, x1, x2;
+    __device__ __forceinline__ int64_t at0(int l, int j) const { return off0[min(j << l, x0)]; }
+    __device__ __forceinline__ int64_t at1(int l, int j) const { return off1[min(j << l, x1)]; }
+    __device__ __forceinline__ int64_t at2(int l, int j) const { return off2[min(j << l, x2)]; }
+    __device__ __forceinline__ int64_t operator()(int l, int j0, int j1, int j2) const
+    {
+        return at0(l, j0) + at1(l, j1) + at2(l, j2);
+    }
+};
+
+// What the input is: the finest level grid (the next ones are formed by the
+// kernel), in the user's array or the workspace, there plus its correction or
+// alone; or the classes, in the user's array.
+enum TailIn { kTailGridZ, kTailGrid, kTailClasses };
+
+// Descriptions, offsets, tables and input to LDS.
+template <typename T, TailIn kIn, bool kLdsTab>
+__device__ __forceinline__ TailUser tail_load(const TailArgs<T>& a, const T* src, T* lds, TailStatic& sm)
 {
+    constexpr bool kDec = kIn != kTailClasses;
     int64_t *const off0 = sm.off0, *const off1 = sm.off1, *const off2 = sm.off2;
     TailLevel* const lv = sm.lv;
     const int tid = threadIdx.x, nlev = a.nlev, k0 = a.k0;
@@ -263,18 +289,9 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
     }
     __syncthreads();  // descriptions, offsets
     const TailLevel L0 = lv[0];
-    const int base = uni(L0.cum), tbase = uni(L0.tab);
+    const int base = uni(L0.cum);
     T* const ltab = lds + a.data_elems;
-    // tables of a level
-    auto tables = [&](const TailLevel& L) -> const T* {
-        return (kLdsTab ? (const T*)ltab : a.tab) + (L.tab - tbase);
-    };
-    const int x0 = L0.d[0].m - 1, x1 = L0.d[1].m - 1, x2 = L0.d[2].m - 1;
-    auto user0 = [&](int l, int j) { return off0[min(j << l, x0)]; };
-    auto user1 = [&](int l, int j) { return off1[min(j << l, x1)]; };
-    auto user2 = [&](int l, int j) { return off2[min(j << l, x2)]; };
-    // offset in the user's arrays of node j of the level l steps after k0
-    auto user = [&](int l, int j0, int j1, int j2) { return user0(l, j0) + user1(l, j1) + user2(l, j2); };
+    const TailUser user = {off0, off1, off2, L0.d[0].m - 1, L0.d[1].m - 1, L0.d[2].m - 1};
     // node idx of a level (its value v) to its LDS arrays A
     auto put = [&](const TailLevel& L, T* A, int idx, int j0, int j1, int j2, T v) {
         const bool coarse = ((j0 | j1 | j2) & 1) == 0;
@@ -294,7 +311,7 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
             node_of(L0, idx, j0, j1, j2);
             if (kDec && k0 > 0) {
                 const int pk = packed_at(L0, j0, j1, j2);
-                tmp[q] = a.Wk[pk] + a.Z0[pk];
+                tmp[q] = (kIn == kTailGridZ) ? a.Wk[pk] + a.Z0[pk] : a.Wk[pk];
             } else {
                 tmp[q] = src[user(0, j0, j1, j2)];
             }
@@ -368,6 +385,22 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
         for (int e = kTT * kT + tid; e < ntab; e += kT) ltab[e] = a.tab[e];
     }
     __syncthreads();
+    return user;
+}
+
+template <typename T, bool kDec, bool kLdsTab>
+__device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T* dst, T* lds, TailStatic& sm)
+{
+    const TailUser user = tail_load<T, kDec ? kTailGridZ : kTailClasses, kLdsTab>(a, src, lds, sm);
+    TailLevel* const lv = sm.lv;
+    const int nlev = a.nlev, k0 = a.k0;
+    const TailLevel& L0 = lv[0];
+    const int base = uni(L0.cum), tbase = uni(L0.tab);
+    T* const ltab = lds + a.data_elems;
+    // tables of a level
+    auto tables = [&](const TailLevel& L) -> const T* {
+        return (kLdsTab ? (const T*)ltab : a.tab) + (L.tab - tbase);
+    };
 
     if (kDec) {
         for (int l = 0; l < nlev; l++) {
@@ -381,9 +414,9 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
                            int64_t o[3][2];
 #pragma unroll
                            for (int b = 0; b < 2; b++) {
-                               o[0][b] = user0(l, 2 * i[0] + b);
-                               o[1][b] = user1(l, 2 * i[1] + b);
-                               o[2][b] = user2(l, 2 * i[2] + b);
+                               o[0][b] = user.at0(l, 2 * i[0] + b);
+                               o[1][b] = user.at1(l, 2 * i[1] + b);
+                               o[2][b] = user.at2(l, 2 * i[2] + b);
                            }
 #pragma unroll
                            for (int e = 1; e < 8; e++) {
@@ -471,9 +504,9 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
                                k[1][b] = __mul24(min(2 * i[1] + b, L.d[1].act - 1), L.d[2].act);
                                k[2][b] = min(2 * i[2] + b, L.d[2].act - 1);
                                if (last && k0 == 0) {
-                                   o[0][b] = user0(0, 2 * i[0] + b);
-                                   o[1][b] = user1(0, 2 * i[1] + b);
-                                   o[2][b] = user2(0, 2 * i[2] + b);
+                                   o[0][b] = user.at0(0, 2 * i[0] + b);
+                                   o[1][b] = user.at1(0, 2 * i[1] + b);
+                                   o[2][b] = user.at2(0, 2 * i[2] + b);
                                }
                            }
                            T z[8];
@@ -498,6 +531,170 @@ __device__ __forceinline__ void tail_body(const TailArgs<T>& a, const T* src, T*
     }
 }
 
+// ---- adjoints ---------------------------------------------------------------
+// The transposes of the same steps, with the columns of B (t = B^T y, expanded
+// dimension by dimension, 0 first, through the arrays that the reductions use
+// in reverse).  Adjoint of the decomposition, coarse to fine:
+//   O = g + B^T G at the fine nodes, O = G - P^T O at the coarse ones,
+// which is the next finer level's G; of the recomposition, fine to coarse:
+//   G' = G + P^T g (the next level grid), out = g - B^T G' at the fine nodes,
+// where the expansions of all levels follow the chain of the G and share three
+// phases.  The last steps of a 257^3 FP32 adjoint, from 17^3 nodes on, took seven
+// launches (58 us in the kernels) and a copy per step; 23 us here.
+
+// P^T U at coarse node (i0, i1, i2): its up to 26 fine neighbours (U is zero at
+// coarse nodes).
+template <typename T>
+__device__ __forceinline__ T tail_restrict(const TailLevel& L, const T* tab, const T* U, const int (&i)[3])
+{
+    const int m2 = L.d[2].m, m12 = __mul24(L.d[1].m, m2);
+    const int fs[3] = {m12, m2, 1};
+    T w[3][2];
+    int o[3][2];
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        const bool lo = i[d] > 0, hi = i[d] < L.d[d].mc - 1;
+        const T* q = tab + L.d[d].w + 4 * i[d];
+        w[d][0] = lo ? q[-1] : T(0);
+        w[d][1] = hi ? q[2] : T(0);
+        o[d][0] = lo ? -fs[d] : 0;
+        o[d][1] = hi ? fs[d] : 0;
+    }
+    const T* const u = U + 2 * (__mul24(i[0], m12) + __mul24(i[1], m2) + i[2]);
+    T r[3];
+#pragma unroll
+    for (int b0 = 0; b0 < 3; b0++) {
+        T q[3];
+#pragma unroll
+        for (int b1 = 0; b1 < 3; b1++) {
+            const T* x = u + (b0 == 0 ? o[0][0] : b0 == 2 ? o[0][1] : 0) + (b1 == 0 ? o[1][0] : b1 == 2 ? o[1][1] : 0);
+            q[b1] = fma(w[2][1], x[o[2][1]], fma(w[2][0], x[o[2][0]], x[0]));
+        }
+        r[b0] = fma(w[1][1], q[2], fma(w[1][0], q[0], q[1]));
+    }
+    return fma(w[0][1], r[2], fma(w[0][0], r[0], r[1]));
+}
+
+// Phase ps (0 .. na - 1) of B^T G; the last one gives the t of the level's nodes
+// to fin(idx, step, n, t).
+template <typename T, class Fin>
+__device__ __forceinline__ void tail_adj_phase(const TailLevel& L, const T* tab, T* A, int ps, Fin fin)
+{
+    const int na = uni(L.na), q = na - 1 - ps, d = uni((L.dims >> (2 * q)) & 3);
+    const T* const in = A + (ps == 0 ? L.g : q == 0 ? L.p1 : L.p2);
+    T* const o = A + (q == 1 ? L.p1 : L.p2);
+    const int outer = (d == 2) ? L.d[0].m * L.d[1].m : (d == 1) ? L.d[0].m : 1;
+    const int inner = (d == 2) ? 1 : (d == 1) ? L.d[2].mc : L.d[1].mc * L.d[2].mc;
+    const float rinner = (d == 2) ? 1.0f : (d == 1) ? L.d[2].rmc : L.d[1].rmc * L.d[2].rmc;
+    tail_dots<2>(L.d[d], tab + L.d[d].B, in, outer, inner, rinner, [&](int c, int step, int n, const auto& v) {
+        if (q == 0) {
+            fin(c, step, n, v);
+        } else {
+#pragma unroll
+            for (int k = 0; k < (int)(sizeof(v) / sizeof(T)); k++)
+                if (k < n) o[c + k * step] = v[k];
+        }
+    });
+}
+
+template <typename T, bool kRec, bool kLdsTab>
+__device__ __forceinline__ void tail_adj_body(const TailArgs<T>& a, T* lds, TailStatic& sm)
+{
+    const TailUser user = tail_load<T, kRec ? kTailGrid : kTailClasses, kLdsTab>(a, a.src, lds, sm);
+    TailLevel* const lv = sm.lv;
+    const int nlev = a.nlev, k0 = a.k0;
+    const TailLevel& L0 = lv[0];
+    const int base = uni(L0.cum), tbase = uni(L0.tab), na = uni(L0.na);
+    T* const ltab = lds + a.data_elems;
+    auto tables = [&](const TailLevel& L) -> const T* {
+        return (kLdsTab ? (const T*)ltab : a.tab) + (L.tab - tbase);
+    };
+    T* const dst = a.dst;
+    if (!kRec) {
+        for (int l = nlev - 1; l >= 0; l--) {
+            const TailLevel& L = lv[l];
+            const T* const tab = tables(L);
+            T* const A = lds + (L.cum - base);
+            T* const G = A + L.g;
+            // O at node idx: the next finer level's G, or out
+            const TailLevel& N = lv[max(l - 1, 0)];
+            T* const Gn = lds + (N.cum - base) + N.g;
+            auto put = [&](int idx, int j0, int j1, int j2, T v) {
+                if (l > 0)
+                    Gn[idx] = v;
+                else if (k0 == 0)
+                    dst[user(0, j0, j1, j2)] = v;
+                else
+                    a.Wk[idx] = v;
+            };
+            for (int ps = 0; ps < na; ps++) {
+                tail_adj_phase(L, tab, A, ps, [&](int c, int step, int n, const auto& t) {
+#pragma unroll
+                    for (int k = 0; k < (int)(sizeof(t) / sizeof(T)); k++) {
+                        if (k >= n) break;
+                        const int idx = c + k * step;
+                        int j0, j1, j2;
+                        node_of(L, idx, j0, j1, j2);
+                        if (((j0 | j1 | j2) & 1) == 0) continue;
+                        const T v = A[idx] + t[k];
+                        A[idx] = v;
+                        put(idx, j0, j1, j2, v);
+                    }
+                });
+                __syncthreads();
+            }
+            for (int c = threadIdx.x; c < L.Vc; c += kT) {
+                int i[3];
+                coarse_of(L, c, i[0], i[1], i[2]);
+                const T v = G[c] - tail_restrict(L, tab, A, i);
+                const int idx = 2 * (__mul24(__mul24(i[0], L.d[1].m) + i[1], L.d[2].m) + i[2]);
+                put(idx, 2 * i[0], 2 * i[1], 2 * i[2], v);
+            }
+            __syncthreads();
+        }
+    } else {
+        for (int l = 0; l < nlev; l++) {
+            const TailLevel& L = lv[l];
+            const T* const tab = tables(L);
+            T* const A = lds + (L.cum - base);
+            T* const G = A + L.g;
+            const bool last = l + 1 == nlev;
+            const TailLevel& N = lv[last ? l : l + 1];
+            T* const An = lds + (N.cum - base);
+            for (int c = threadIdx.x; c < L.Vc; c += kT) {
+                int i[3];
+                coarse_of(L, c, i[0], i[1], i[2]);
+                const T h = G[c] + tail_restrict(L, tab, A, i);
+                G[c] = h;
+                if (last)
+                    dst[user(nlev, i[0], i[1], i[2])] = h;
+                else if (((i[0] | i[1] | i[2]) & 1) == 0)
+                    An[N.g + __mul24(__mul24(i[0] >> 1, N.d[1].mc) + (i[1] >> 1), N.d[2].mc) + (i[2] >> 1)] = h;
+                else
+                    An[c] = h;
+            }
+            __syncthreads();
+        }
+        for (int ps = 0; ps < na; ps++) {
+            for (int l = 0; l < nlev; l++) {
+                const TailLevel& L = lv[l];
+                T* const A = lds + (L.cum - base);
+                tail_adj_phase(L, tables(L), A, ps, [&](int c, int step, int n, const auto& t) {
+#pragma unroll
+                    for (int k = 0; k < (int)(sizeof(t) / sizeof(T)); k++) {
+                        if (k >= n) break;
+                        const int idx = c + k * step;
+                        int j0, j1, j2;
+                        node_of(L, idx, j0, j1, j2);
+                        if ((j0 | j1 | j2) & 1) dst[user(l, j0, j1, j2)] = A[idx] - t[k];
+                    }
+                });
+            }
+            __syncthreads();
+        }
+    }
+}
+
 extern __shared__ __align__(16) unsigned char tail_lds[];
 
 template <typename T, bool kDec, bool kLdsTab>
@@ -505,6 +702,13 @@ __global__ void __launch_bounds__(kT) k_tail(TailArgs<T> a)
 {
     __shared__ TailStatic sm;
     tail_body<T, kDec, kLdsTab>(a, a.src, a.dst, reinterpret_cast<T*>(tail_lds), sm);
+}
+
+template <typename T, bool kRec, bool kLdsTab>
+__global__ void __launch_bounds__(kT) k_tail_adj(TailArgs<T> a)
+{
+    __shared__ TailStatic sm;
+    tail_adj_body<T, kRec, kLdsTab>(a, reinterpret_cast<T*>(tail_lds), sm);
 }
 
 // One workgroup per entry of a batch; arguments in device memory.
@@ -546,7 +750,26 @@ hipError_t launch_tail_cfg(const TailArgs<T>& a, size_t bytes, hipStream_t st)
     return hipGetLastError();
 }
 
+template <typename T, bool kRec, bool kLdsTab>
+hipError_t launch_adj_cfg(const TailArgs<T>& a, size_t bytes, hipStream_t st)
+{
+    static bool done[64] = {};
+    const hipError_t e = allow_lds(k_tail_adj<T, kRec, kLdsTab>, bytes, done);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((k_tail_adj<T, kRec, kLdsTab>), dim3(1), dim3(kT), bytes, st, a);
+    return hipGetLastError();
+}
+
 }  // namespace
+
+template <typename T>
+hipError_t launch_tail_adjoint(const TailArgs<T>& a, bool recompose, hipStream_t st)
+{
+    const size_t bytes = sizeof(T) * (size_t)tail_lds_elems(a);
+    if (tail_tab_in_lds(a))
+        return recompose ? launch_adj_cfg<T, true, true>(a, bytes, st) : launch_adj_cfg<T, false, true>(a, bytes, st);
+    return recompose ? launch_adj_cfg<T, true, false>(a, bytes, st) : launch_adj_cfg<T, false, false>(a, bytes, st);
+}
 
 template <typename T>
 hipError_t launch_tail_batch(const TailArgs<T>* dev_args, const int* field, const T* const* src, T* const* dst, int n,
@@ -570,6 +793,8 @@ hipError_t launch_tail(const TailArgs<T>& a, bool decompose, hipStream_t st)
     return decompose ? launch_tail_cfg<T, true, false>(a, bytes, st) : launch_tail_cfg<T, false, false>(a, bytes, st);
 }
 
+template hipError_t launch_tail_adjoint<float>(const TailArgs<float>&, bool, hipStream_t);
+template hipError_t launch_tail_adjoint<double>(const TailArgs<double>&, bool, hipStream_t);
 template hipError_t launch_tail<float>(const TailArgs<float>&, bool, hipStream_t);
 template hipError_t launch_tail<double>(const TailArgs<double>&, bool, hipStream_t);
 template hipError_t launch_tail_batch<float>(const TailArgs<float>*, const int*, const float* const*, float* const*,
