@@ -1183,6 +1183,25 @@ bool aux_ready()
     return g_aux[dev].sr != nullptr;
 }
 
+// Whether the finest level step's correction shares launches with the coarser
+// ones instead of running beside them on a stream of its own.  It does while
+// the problem is bound by the chain of launches (shared: four launches for the
+// corrections of all steps, and one stream less to wait for); from about 20 MB
+// on its bandwidth-bound passes are worth overlapping with that chain.
+// Recomposition, own stream -> shared: 65^3 FP32 71 -> 56 us, FP64 86 -> 66; 129^3
+// 80 -> 78, 100 -> 92 (17 MB); 257 x 129^2 FP64 (34 MB) 116 -> 119; 257^3 147 -> 154,
+// 210 -> 228; 513^2 FP32 77 -> 61, 1025^2 83 -> 67.  A finest step whose solves
+// cannot share (more than 16 segments) keeps its stream.
+constexpr int64_t kSharedBytes = 20 << 20;
+template <typename T>
+bool recompose_shared(const Plan& p, int kt)
+{
+    if (kt < 1 || p.n[0] * p.n[1] * p.n[2] * (int64_t)sizeof(T) > kSharedBytes) return false;
+    for (int d = 0; d < 3; d++)
+        if (p.active[d] && !solve_multi_fits<T>(packed(p.lv[0].mc), d, solve_tables_of<T>(p, 0, d))) return false;
+    return true;
+}
+
 // Recomposition, coarsest level step first: u_k = c_k + Pi (W_{k+1} - z_k).
 // The correction z_k of every level step depends on the stored coefficients
 // alone (its load vector is formed from them), so they are all independent
@@ -1215,6 +1234,7 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     // A captured recomposition of an any-length grid keeps to the caller's
     // stream: it needs no auxiliary stream to exist.
     hipStream_t sc = st;  // the stream of the tail
+    const bool shared = recompose_shared<T>(p, kt);
     const bool fork = kt > 0 && !(p.gen && capturing(st));
     if (fork) {
         if (!aux_ready() && capturing(st))
@@ -1222,7 +1242,7 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
         MGR_TRY(aux_stream(&aux), "auxiliary stream");
         MGR_TRY(hipEventRecord(aux->start, st), "fork event");
         MGR_TRY(hipStreamWaitEvent(aux->sr, aux->start, 0), "fork wait");
-        MGR_TRY(hipStreamWaitEvent(aux->s0, aux->start, 0), "fork wait");
+        if (!shared) MGR_TRY(hipStreamWaitEvent(aux->s0, aux->start, 0), "fork wait");
         sc = aux->sr;
     }
     if (kt < L) {
@@ -1239,21 +1259,21 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
         if (fork) MGR_TRY(hipEventRecord(aux->rdone, sc), "tail event");
         // one level step's correction on its own launches (the finest on s0)
         auto single = [&](int k) -> int {
-            hipStream_t sk = (k == 0 && fork) ? aux->s0 : st;
+            hipStream_t sk = (k == 0 && fork && !shared) ? aux->s0 : st;
             View3 cv = level_view(p, k);
             T* z = ws + p.Zrec[(size_t)k];
             int rc = stream_level<T>(p, k, false, src, nullptr, cv, nullptr, cv, nullptr, false, sk, z);
             if (rc) return rc;
             rc = solve_all<T>(p, k, false, z, sk, (k == 0) ? ws + p.Yb : ws + p.Yb2, k == 0);
             if (rc) return rc;
-            if (k == 0 && fork) MGR_TRY(hipEventRecord(aux->done[0], sk), "level event");
+            if (k == 0 && fork && !shared) MGR_TRY(hipEventRecord(aux->done[0], sk), "level event");
             return MGR_OK;
         };
-        // the finest step's correction first, so that its launches reach the
-        // device together with the coarser chain's
-        int rc = single(0);
-        if (rc) return rc;
-        // the coarser steps' corrections (coarsest first) share launches
+        // the finest step's correction first (unless it joins the others), so
+        // that its launches reach the device together with the coarser chain's
+        int rc = 0;
+        if (!shared && (rc = single(0))) return rc;
+        // the other steps' corrections (coarsest first) share launches
         // where their solves allow it: one load-vector launch and one launch
         // per dimension for up to kMultiLevels steps, instead of a chain of
         // small launches per step
@@ -1296,7 +1316,7 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
             group.clear();
             return MGR_OK;
         };
-        for (int k = kt - 1; k >= 1; k--) {
+        for (int k = kt - 1; k >= (shared ? 0 : 1); k--) {
             bool fits = true;
             for (int d = 0; d < 3; d++)
                 if (p.active[d])
@@ -1316,7 +1336,7 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
         const LevelLayout& ly = p.lv[(size_t)k];
         View3 cv = level_view(p, k);
         hipStream_t sk = st;
-        if (k == 0 && fork) MGR_TRY(hipStreamWaitEvent(st, aux->done[0], 0), "join wait");  // the finest correction
+        if (k == 0 && fork && !shared) MGR_TRY(hipStreamWaitEvent(st, aux->done[0], 0), "join wait");  // the finest correction
         StreamArgs<T> a;
         a.A = src;
         a.Z = ws + p.Zrec[(size_t)k];
