@@ -198,20 +198,27 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(SmallSolveArgs<T>
     // batch covers every grid that fits the LDS, and the tables are staged
     // after its loads are issued, so one memory latency covers all
     constexpr int NB = (sizeof(T) == 4) ? 40 : 20;
-    for (int b0 = 0; b0 < V; b0 += NB * kSmallThreads) {
-        T tmp[NB];
+    auto stage = [&](auto nb) {
+        constexpr int N = decltype(nb)::value;
+        T tmp[N];
 #pragma unroll
-        for (int q = 0; q < NB; q++) tmp[q] = a.in[min(b0 + q * kSmallThreads + tid, V - 1)];
-        if (b0 == 0)
-            for (int e = tid; e < a.nd * 3 * kSlot; e += kSmallThreads) {
-                const int dd = e / (3 * kSlot), w = (e / kSlot) % 3, q = e % kSlot;
-                const T* src = (w == 0) ? a.L[dd] : (w == 1) ? a.U[dd] : a.IP[dd];
-                tab[e] = src[q];
-            }
+        for (int q = 0; q < N; q++) tmp[q] = a.in[min(q * kSmallThreads + tid, V - 1)];
+        for (int e = tid; e < a.nd * 3 * kSlot; e += kSmallThreads) {
+            const int dd = e / (3 * kSlot), w = (e / kSlot) % 3, q = e % kSlot;
+            const T* src = (w == 0) ? a.L[dd] : (w == 1) ? a.U[dd] : a.IP[dd];
+            tab[e] = src[q];
+        }
 #pragma unroll
-        for (int q = 0; q < NB; q++)
-            if (b0 + q * kSmallThreads + tid < V) g[b0 + q * kSmallThreads + tid] = tmp[q];
-    }
+        for (int q = 0; q < N; q++)
+            if (q * kSmallThreads + tid < V) g[q * kSmallThreads + tid] = tmp[q];
+    };
+    // (the smaller batch: 17^3 and below, whose lanes would issue 35 loads too
+    // many)
+    static_assert(NB * kSmallThreads * sizeof(T) >= 160 * 1024, "covers the LDS");
+    if (V <= 8 * kSmallThreads)
+        stage(std::integral_constant<int, 8>{});
+    else
+        stage(std::integral_constant<int, NB>{});
     __syncthreads();
     const int cs[3] = {n1 * n2, n2, 1};
     for (int dd = 0; dd < a.nd; dd++) {
@@ -224,18 +231,27 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(SmallSolveArgs<T>
         const T* U = tab + (3 * dd + 1) * kSlot;
         const T* IP = tab + (3 * dd + 2) * kSlot;
         for (int f = tid; f < nfib; f += kSmallThreads) {
-            T* p = g + (f / nb) * cs[da] + (f % nb) * cs[db];
+            const int fa = f / nb;
+            T* p = g + __mul24(fa, cs[da]) + __mul24(f - __mul24(fa, nb), cs[db]);
             T v[kSlot];
 #pragma unroll
-            for (int q = 0; q < kSlot; q++) v[q] = p[min(q, n - 1) * sd];
+            for (int q = 0; q < kSlot; q++) v[q] = p[__mul24(min(q, n - 1), sd)];
             seg_solve(v, L, U, IP);
+            // (slots past the fibre: to its last node, before that node's value)
 #pragma unroll
-            for (int q = 0; q < kSlot; q++)
-                if (q < n) p[q * sd] = v[q];
+            for (int q = kSlot - 1; q >= 0; q--) p[__mul24(min(q, n - 1), sd)] = v[q];
         }
         __syncthreads();
     }
-    for (int e = tid; e < V; e += kSmallThreads) a.F[e] = g[e];
+    // (the reads of a batch ahead of its stores)
+    for (int b0 = 0; b0 < V; b0 += 8 * kSmallThreads) {
+        T o[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) o[q] = g[min(b0 + q * kSmallThreads + tid, V - 1)];
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (b0 + q * kSmallThreads + tid < V) a.F[b0 + q * kSmallThreads + tid] = o[q];
+    }
 }
 
 // Largest plane-solve workgroup: ten waves, so that the compiler may give a
@@ -250,6 +266,18 @@ constexpr int kPlaneThreads = 640;
 // instead of two.  One thread per (segment, fibre) task, fibres fastest, so
 // that lanes read LDS at the fibres' stride (odd for 2^k + 1 sizes: no bank
 // conflicts) or contiguously.
+// Bound by the length of a lane's chain, with a wave or three to a CU: 65 planes
+// of 65 x 65 FP32 take 9.8 us, against 13 with the table reads of the final
+// values, the separator reads and every LDS store under conditions of their own
+// (a round trip each); 129 planes of 129 x 129 15 us against 17, FP64 65 x 33 8.8
+// against 12.
+// Loads of the plane in flight per lane; the launch has lanes enough that one
+// batch covers every plane but the largest.
+template <typename T>
+constexpr int plane_batch()
+{
+    return sizeof(T) == 4 ? 32 : 18;
+}
 template <typename T>
 struct PlaneSolveArgs {
     T* F;
@@ -270,49 +298,42 @@ __device__ __forceinline__ void plane_dim(T* P, T* end0, T* end1, const T* tab, 
     m.S = S;
     int lo, len;
     seg_range(m, s, lo, len);
+    // node lo + q, clamped to the segment's last
     T* const p = P + f * sf;
+    T* const p0 = p + __mul24(lo, sd);
     T v[kSlot];
 #pragma unroll
-    for (int q = 0; q < kSlot; q++) v[q] = p[(lo + min(q, len - 1)) * sd];
-    const T ylast = seg_solve(v, tab + 0 * kMaxSegWG * kSlot + s * kSlot, tab + 1 * kMaxSegWG * kSlot + s * kSlot,
-                              tab + 2 * kMaxSegWG * kSlot + s * kSlot);
+    for (int q = 0; q < kSlot; q++) v[q] = p0[__mul24(min(q, len - 1), sd)];
+    seg_solve(v, tab + 0 * kMaxSegWG * kSlot + s * kSlot, tab + 1 * kMaxSegWG * kSlot + s * kSlot,
+              tab + 2 * kMaxSegWG * kSlot + s * kSlot);
     if (active) {
         end0[s * nf + f] = v[0];
-        end1[s * nf + f] = ylast;
+        end1[s * nf + f] = seg_last(v, s);
     }
     __syncthreads();
-    if (dec) {
-        auto sep = [&](int k) {
-            return sep_alone(p[(k * kSeg) * sd], septab[0 * kMaxSegWG + k], end1[(k - 1) * nf + f],
-                             septab[1 * kMaxSegWG + k], end0[k * nf + f], septab[3 * kMaxSegWG + k]);
-        };
-        const T zl = (s > 0) ? sep(s) : T(0);
-        const T zr = (s < S - 1) ? sep(s + 1) : T(0);
-        __syncthreads();  // every task has read its separators
-        if (active) {
-            const T* ta = tab + 3 * kMaxSegWG * kSlot + s * kSlot;
-            const T* tb = tab + 4 * kMaxSegWG * kSlot + s * kSlot;
-#pragma unroll
-            for (int q = 0; q < kSlot; q++)
-                if (q < len) p[(lo + q) * sd] = seg_final(v[q], ta[q], zl, tb[q], zr);
-            if (s > 0) p[(s * kSeg) * sd] = zl;
-        }
+    if (!dec) {
+        if (active && s == 0 && S > 1)
+            sep_solve(S, p, (int64_t)kSeg * sd, end0 + f, end1 + f, nf, septab + 0 * kMaxSegWG,
+                      septab + 1 * kMaxSegWG, septab + 2 * kMaxSegWG, septab + 3 * kMaxSegWG, septab + 4 * kMaxSegWG);
         __syncthreads();
-        return;
     }
-    if (active && s == 0 && S > 1)
-        sep_solve(S, p, (int64_t)kSeg * sd, end0 + f, end1 + f, nf, septab + 0 * kMaxSegWG,
-                  septab + 1 * kMaxSegWG, septab + 2 * kMaxSegWG, septab + 3 * kMaxSegWG, septab + 4 * kMaxSegWG);
-    __syncthreads();
-    const T zl = (s > 0) ? p[(s * kSeg) * sd] : T(0);
-    const T zr = (s < S - 1) ? p[((s + 1) * kSeg) * sd] : T(0);
+    // read without a condition, indices clamped to a separator there is
+    auto sep = [&](int k) {
+        const int kc = min(max(k, S > 1 ? 1 : 0), S - 1), km = max(kc - 1, 0);
+        const T z = p[(kc * kSeg) * sd];
+        const T w = sep_alone(z, septab[0 * kMaxSegWG + kc], end1[km * nf + f], septab[1 * kMaxSegWG + kc],
+                              end0[kc * nf + f], septab[3 * kMaxSegWG + kc]);
+        return dec ? w : z;
+    };
+    const T sl = sep(s), sr = sep(s + 1);
+    const T zl = (s > 0) ? sl : T(0), zr = (s < S - 1) ? sr : T(0);
     __syncthreads();  // every task has read its separators
     if (active) {
-        const T* ta = tab + 3 * kMaxSegWG * kSlot + s * kSlot;
-        const T* tb = tab + 4 * kMaxSegWG * kSlot + s * kSlot;
-#pragma unroll
-        for (int q = 0; q < kSlot; q++)
-            if (q < len) p[(lo + q) * sd] = seg_final(v[q], ta[q], zl, tb[q], zr);
+        // slots past the segment go to its last node, before that node's own
+        // value (a store each, without a condition)
+        seg_finals(v, tab + 3 * kMaxSegWG * kSlot + s * kSlot, zl, tab + 4 * kMaxSegWG * kSlot + s * kSlot, zr,
+                   [&](int q, T x) { p0[__mul24(min(q, len - 1), sd)] = x; });
+        if (s > 0) p[(s * kSeg) * sd] = zl;
     }
     __syncthreads();
 }
@@ -331,41 +352,37 @@ __global__ void __launch_bounds__(kPlaneThreads) k_solve_plane(PlaneSolveArgs<T>
     T* const F = a.F + (int64_t)blockIdx.x * V;
     // the plane's loads first (one batch covers every plane that fits), the
     // tables' after them: one memory latency covers both
-    constexpr int NB = (sizeof(T) == 4) ? 20 : 10;
+    constexpr int NB = plane_batch<T>();
     for (int b0 = 0; b0 < V; b0 += NB * nthr) {
         T tmp[NB];
 #pragma unroll
         for (int q = 0; q < NB; q++) tmp[q] = F[min(b0 + q * nthr + tid, V - 1)];
         if (b0 == 0)
-            for (int d = 0; d < 2; d++) {
-                const SolveTables<T>& t = a.tb[d];
-                for (int e = tid; e < t.S * kSlot; e += nthr) {
-                    T* o = tab + d * TAB + e;
-                    o[0 * kMaxSegWG * kSlot] = t.L[e];
-                    o[1 * kMaxSegWG * kSlot] = t.U[e];
-                    o[2 * kMaxSegWG * kSlot] = t.IP[e];
-                    o[3 * kMaxSegWG * kSlot] = t.A[e];
-                    o[4 * kMaxSegWG * kSlot] = t.B[e];
-                }
-                for (int e = tid; e < t.S; e += nthr) {
-                    T* o = septab + d * SEP + e;
-                    o[0 * kMaxSegWG] = t.ssub[e];
-                    o[1 * kMaxSegWG] = t.ssup[e];
-                    o[2 * kMaxSegWG] = t.sl[e];
-                    o[3 * kMaxSegWG] = t.sip[e];
-                    o[4 * kMaxSegWG] = t.su[e];
-                }
-            }
+            for (int d = 0; d < 2; d++)
+                stage_tables(a.tb[d], 0, a.tb[d].S, tid, nthr, *reinterpret_cast<T(*)[5][kMaxSegWG * kSlot]>(tab + d * TAB),
+                             *reinterpret_cast<T(*)[5][kMaxSegWG]>(septab + d * SEP));
 #pragma unroll
         for (int q = 0; q < NB; q++)
             if (b0 + q * nthr + tid < V) P[b0 + q * nthr + tid] = tmp[q];
     }
     __syncthreads();
-    // rows (dimension 2): fibre f = row, node i at f n2 + i
-    plane_dim(P, end, end + kPlaneThreads, tab, septab, n2, a.tb[0].S, n1, 1, n2, tid, a.tb[0].dec);
-    // columns (dimension 1): fibre f = column, node i at i n2 + f
-    plane_dim(P, end, end + kPlaneThreads, tab + TAB, septab + SEP, n1, a.tb[1].S, n2, n2, 1, tid, a.tb[1].dec);
-    for (int e = tid; e < V; e += nthr) F[e] = P[e];
+    // rows (dimension 2): fibre f = row, node i at f n2 + i; then columns
+    // (dimension 1): fibre f = column, node i at i n2 + f.  One copy of the
+    // code for both: straight-line code that a launch runs once is bound by
+    // its instruction fetches.
+#pragma unroll 1
+    for (int d = 0; d < 2; d++)
+        plane_dim(P, end, end + kPlaneThreads, tab + d * TAB, septab + d * SEP, d ? n1 : n2, a.tb[d].S, d ? n2 : n1,
+                  d ? n2 : 1, d ? 1 : n2, tid, a.tb[d].dec);
+    // (the reads of a batch ahead of its stores)
+    for (int b0 = 0; b0 < V; b0 += 8 * nthr) {
+        T o[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) o[q] = P[min(b0 + q * nthr + tid, V - 1)];
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (b0 + q * nthr + tid < V) F[b0 + q * nthr + tid] = o[q];
+    }
 }
 
 // Solves of several level steps along one dimension in one grid: block b
@@ -662,7 +679,8 @@ hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const So
     a.n2 = (int)fv.n[2];
     a.tb[0] = t2;
     a.tb[1] = t1;
-    const int64_t tasks = std::max<int64_t>(t2.S * fv.n[1], t1.S * fv.n[2]);
+    const int64_t tasks = std::max<int64_t>({t2.S * fv.n[1], t1.S * fv.n[2],
+                                             (fv.n[1] * fv.n[2] + plane_batch<T>() - 1) / plane_batch<T>()});
     const unsigned thr = (unsigned)std::min<int64_t>(kPlaneThreads, std::max<int64_t>(64, (tasks + 63) / 64 * 64));
     hipLaunchKernelGGL(k_solve_plane<T>, dim3((unsigned)fv.n[0]), dim3(thr), plane_solve_bytes<T>(fv), st, a);
     return hipGetLastError();

@@ -29,26 +29,27 @@ __device__ __forceinline__ void seg_range(const FibreMap& m, int s, int& lo, int
 // Segment-local Thomas solve in registers with padded tables (L = forward
 // multipliers, U = super-diagonal, IP = inverse pivots; zero past the
 // segment so padded slots come out as 0).
-// Returns y at the segment's last node (slot len - 1); it is picked up during
-// the backward sweep, as the first nonzero-pivot slot from the end, so that
-// the compiler never indexes the register array with a runtime value.
+// The roundings are fixed (explicit FMAs), so that every form gives the same
+// values.
 template <typename T>
-__device__ __forceinline__ T seg_solve(T (&v)[kSlot], const T* L, const T* U, const T* IP)
+__device__ __forceinline__ void seg_solve(T (&v)[kSlot], const T* L, const T* U, const T* IP)
 {
 #pragma unroll
-    for (int q = 1; q < kSlot; q++) v[q] -= L[q] * v[q - 1];
-    T z = T(0), last = T(0);
-    bool found = false;
+    for (int q = 1; q < kSlot; q++) v[q] = fma(-L[q], v[q - 1], v[q]);
+    T z = T(0);
 #pragma unroll
     for (int q = kSlot - 1; q >= 0; q--) {
-        const T ip = IP[q];
-        z = (v[q] - U[q] * z) * ip;
+        z = fma(-U[q], z, v[q]) * IP[q];
         v[q] = z;
-        const bool here = !found && ip != T(0);
-        last = here ? z : last;
-        found = found || here;
     }
-    return last;
+}
+
+// y at the last node of segment s (the fibre's first has kSeg nodes, the
+// others one fewer; the last segment's end is next to no separator).
+template <typename T>
+__device__ __forceinline__ T seg_last(const T (&v)[kSlot], int s)
+{
+    return s == 0 ? v[kSeg - 1] : v[kSeg - 2];
 }
 
 // Separator elimination and the segments' final values with one fixed
@@ -75,6 +76,45 @@ template <typename T>
 __device__ __forceinline__ T seg_final(T y, T alpha, T zl, T beta, T zr)
 {
     return fma(beta, zr, fma(alpha, zl, y));
+}
+
+// Tables of segments s0 .. s0 + ns - 1 to LDS: the segment tables (L, U, IP,
+// alpha, beta) and the separators' (sub, sup, sl, sip, su), all loads of a turn
+// ahead of its stores, so that one memory latency covers both.
+template <typename T, int NT, int NS>
+__device__ __forceinline__ void stage_tables(const SolveTables<T>& tb, int s0, int ns, int tid, int nthr,
+                                             T (&tab)[5][NT], T (&septab)[5][NS])
+{
+    for (int e = tid; e < ns * kSlot; e += nthr) {
+        const int g = s0 * kSlot + e, k = s0 + min(e, ns - 1);
+        const T a[5] = {tb.L[g], tb.U[g], tb.IP[g], tb.A[g], tb.B[g]};
+        const T b[5] = {tb.ssub[k], tb.ssup[k], tb.sl[k], tb.sip[k], tb.su[k]};
+#pragma unroll
+        for (int q = 0; q < 5; q++) tab[q][e] = a[q];
+        if (e < ns)
+#pragma unroll
+            for (int q = 0; q < 5; q++) septab[q][e] = b[q];
+    }
+}
+
+// The final values of a whole segment to put(q, value), q descending, in groups:
+// a group's values before the first of them is stored.  Under a store's
+// condition (slot in the segment) the table reads would each wait their own
+// round trip to the LDS (plane solve, 33 slots: 4300 cycles, 2000 so); all
+// reads ahead of all stores would need more registers than there are.
+template <typename T, class Put>
+__device__ __forceinline__ void seg_finals(T (&v)[kSlot], const T* ta, T zl, const T* tb, T zr, Put put)
+{
+    constexpr int G = 11;
+    static_assert(kSlot % G == 0, "whole groups");
+#pragma unroll
+    for (int g = kSlot - G; g >= 0; g -= G) {
+#pragma unroll
+        for (int q = 0; q < G; q++) v[g + q] = seg_final(v[g + q], ta[g + q], zl, tb[g + q], zr);
+#pragma unroll
+        for (int q = G - 1; q >= 0; q--) put(g + q, v[g + q]);
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 // Separator system of one fibre from the separator f values (in sep[], which
@@ -149,52 +189,38 @@ __device__ __forceinline__ void solve_strided_tile(const T* in, T* F, const Fibr
     T zol = T(0), zor = T(0);
     if (outer_l) zol = zb[fc];
     if (outer_r) zor = zb[m.nfib + fc];
-    for (int e = tid; e < ns * kSlot; e += nthr) {
-        const int g = s0 * kSlot + e;
-        sm.tab[0][e] = tb.L[g];
-        sm.tab[1][e] = tb.U[g];
-        sm.tab[2][e] = tb.IP[g];
-        sm.tab[3][e] = tb.A[g];
-        sm.tab[4][e] = tb.B[g];
-    }
-    for (int e = tid; e < ns; e += nthr) {
-        sm.septab[0][e] = tb.ssub[s0 + e];
-        sm.septab[1][e] = tb.ssup[s0 + e];
-        sm.septab[2][e] = tb.sl[s0 + e];
-        sm.septab[3][e] = tb.sip[s0 + e];
-        sm.septab[4][e] = tb.su[s0 + e];
-    }
+    stage_tables(tb, s0, ns, tid, nthr, sm.tab, sm.septab);
     if (inseg) sm.sep[s * FB + j] = (s0 + s > 0) ? fsep : T(0);
     __syncthreads();  // tables staged
-    const T ylast = seg_solve(v, &sm.tab[0][sc * kSlot], &sm.tab[1][sc * kSlot], &sm.tab[2][sc * kSlot]);
+    seg_solve(v, &sm.tab[0][sc * kSlot], &sm.tab[1][sc * kSlot], &sm.tab[2][sc * kSlot]);
     if (inseg) {
         sm.end[0][s * FB + j] = v[0];
-        sm.end[1][s * FB + j] = ylast;
+        sm.end[1][s * FB + j] = seg_last(v, s0 + s);
     }
     __syncthreads();
     T zl, zr;
-    if (tb.dec) {
-        auto sep = [&](int k) {
-            return sep_alone(sm.sep[k * FB + j], sm.septab[0][k], sm.end[1][(k - 1) * FB + j], sm.septab[1][k],
-                             sm.end[0][k * FB + j], sm.septab[3][k]);
-        };
-        if (!active) return;
-        zl = (s > 0) ? sep(s) : zol;
-        zr = (s < ns - 1) ? sep(s + 1) : zor;
-    } else {
+    if (!tb.dec) {
         if (s == 0 && S > 1)
             sep_solve(S, &sm.sep[j], FB, &sm.end[0][j], &sm.end[1][j], FB, sm.septab[0], sm.septab[1],
                       sm.septab[2], sm.septab[3], sm.septab[4]);
         __syncthreads();
-        if (!active) return;
-        zl = (s > 0) ? sm.sep[s * FB + j] : T(0);
-        zr = (s < S - 1) ? sm.sep[(s + 1) * FB + j] : T(0);
     }
-    const T* ta = &sm.tab[3][s * kSlot];
-    const T* tbt = &sm.tab[4][s * kSlot];
-#pragma unroll
-    for (int q = 0; q < kSlot; q++)
-        if (q < len) F[base + (int64_t)(lo + q) * m.inner] = seg_final(v[q], ta[q], zl, tbt[q], zr);
+    if (!active) return;
+    // the separators left and right of the segment, read without a condition
+    // (indices clamped to a separator there is)
+    auto sep = [&](int k) {
+        const int kc = min(max(k, ns > 1 ? 1 : 0), ns - 1), km = max(kc - 1, 0);
+        const T z = sm.sep[kc * FB + j];
+        const T w = sep_alone(z, sm.septab[0][kc], sm.end[1][km * FB + j], sm.septab[1][kc], sm.end[0][kc * FB + j],
+                              sm.septab[3][kc]);
+        return tb.dec ? w : z;
+    };
+    const T sl = sep(s), sr = sep(s + 1);
+    zl = (s > 0) ? sl : zol;
+    zr = (s < ns - 1) ? sr : zor;
+    seg_finals(v, &sm.tab[3][s * kSlot], zl, &sm.tab[4][s * kSlot], zr, [&](int q, T x) {
+        if (q < len) F[base + (int64_t)(lo + q) * m.inner] = x;
+    });
     if (s0 + s > 0) F[base + (int64_t)((s0 + s) * kSeg) * m.inner] = zl;
 }
 
@@ -309,22 +335,23 @@ __device__ __forceinline__ void solve_chunk_rows(T* __restrict__ F, const FibreM
     T v[kSlot];
 #pragma unroll
     for (int q = 0; q < kSlot; q++) v[q] = sm.f[padded(e0 + lo + min(q, len - 1))];
-    const T ylast = seg_solve(v, kLdsTab ? &sm.tab[0][so] : tb.L + so, kLdsTab ? &sm.tab[1][so] : tb.U + so,
-                              kLdsTab ? &sm.tab[2][so] : tb.IP + so);
+    seg_solve(v, kLdsTab ? &sm.tab[0][so] : tb.L + so, kLdsTab ? &sm.tab[1][so] : tb.U + so,
+              kLdsTab ? &sm.tab[2][so] : tb.IP + so);
     sm.end[0][tid] = v[0];
-    sm.end[1][tid] = ylast;
+    sm.end[1][tid] = seg_last(v, s0 + s);
     __syncthreads();
-    auto sep = [&](int k, int t) {  // separator left of local segment k, lane t holding that segment
-        return sep_alone(sm.f[padded(e0 + (s0 + k) * kSeg)], tb.ssub[s0 + k], sm.end[1][t - 1], tb.ssup[s0 + k],
-                         sm.end[0][t], tb.sip[s0 + k]);
+    auto sep = [&](int k) {  // separator left of local segment k, clamped to one there is
+        const int kc = min(max(k, ns > 1 ? 1 : 0), ns - 1), t = min(tid - s + kc, kBlk - 1), tm = max(t - 1, 0);
+        return sep_alone(sm.f[padded(e0 + (s0 + kc) * kSeg)], tb.ssub[s0 + kc], sm.end[1][tm], tb.ssup[s0 + kc],
+                         sm.end[0][t], tb.sip[s0 + kc]);
     };
-    if (active && s > 0) zl = sep(s, tid);
-    if (active && s < ns - 1) zr = sep(s + 1, tid + 1);
+    const T sl = sep(s), sr = sep(s + 1);
+    zl = (s > 0) ? sl : zl;
+    zr = (s < ns - 1) ? sr : zr;
     __syncthreads();  // every lane has read its separators
     if (active) {
-#pragma unroll
-        for (int q = 0; q < kSlot; q++)
-            if (q < len) sm.f[padded(e0 + lo + q)] = seg_final(v[q], tA[q], zl, tB[q], zr);
+        // (slots past the segment: to its last node, before that node's value)
+        seg_finals(v, tA, zl, tB, zr, [&](int q, T x) { sm.f[padded(e0 + lo + min(q, len - 1))] = x; });
         if (s0 + s > 0) sm.f[padded(e0 + (s0 + s) * kSeg)] = zl;
     }
     __syncthreads();
@@ -389,14 +416,10 @@ template <typename T, int kSpan, bool kLdsTab>
 __device__ __forceinline__ void rows_tables(const FibreMap& m, const SolveTables<T>& tb,
                                             RowsSmem<T, kSpan, kLdsTab>& sm)
 {
-    if (kLdsTab)
-        for (int e = threadIdx.x; e < m.S * kSlot; e += kBlk) {
-            sm.tab[0][e] = tb.L[e];
-            sm.tab[1][e] = tb.U[e];
-            sm.tab[2][e] = tb.IP[e];
-            sm.tab[3][e] = tb.A[e];
-            sm.tab[4][e] = tb.B[e];
-        }
+    if constexpr (kLdsTab) {
+        stage_tables(tb, 0, m.S, (int)threadIdx.x, kBlk, sm.tab, sm.septab);
+        return;
+    }
     // separator tables: the separator sweep is serial, so each of its steps
     // must find them in LDS rather than wait on a global load
     for (int e = threadIdx.x; e < m.S; e += kBlk) {
@@ -433,53 +456,46 @@ __device__ __forceinline__ void rows_solve_lds(const FibreMap& m, const SolveTab
     T v[kSlot];
 #pragma unroll
     for (int q = 0; q < kSlot; q++) v[q] = sm.f[padded(rr * n + lo + min(q, len - 1))];
-    const T ylast = seg_solve(v, tL, tU, tI);
+    seg_solve(v, tL, tU, tI);
     sm.end[0][tid] = v[0];
-    sm.end[1][tid] = ylast;
+    sm.end[1][tid] = seg_last(v, s);
     bar();
-    T zl = T(0), zr = T(0);
-    if (tb.dec) {
-        auto sep = [&](int k, int t) {
-            return sep_alone(sm.f[padded(rr * n + k * kSeg)], sm.septab[0][k], sm.end[1][t - 1], sm.septab[1][k],
-                             sm.end[0][t], sm.septab[3][k]);
-        };
-        if (active && s > 0) zl = sep(s, tid);
-        if (active && s < m.S - 1) zr = sep(s + 1, tid + 1);
-        bar();  // every lane has read its separators
-        if (active) {
-#pragma unroll
-            for (int q = 0; q < kSlot; q++)
-                if (q < len) sm.f[padded(r * n + lo + q)] = seg_final(v[q], tA[q], zl, tB[q], zr);
-            if (s > 0) sm.f[padded(r * n + s * kSeg)] = zl;
+    if (!tb.dec) {
+        if (active && s == 0 && m.S > 1) {
+            // row r's separators live in sm.f at r*n + k*kSeg
+            const int t0 = tid;
+            T gg = T(0);
+            for (int k = 1; k < m.S; k++) {
+                const int e = padded(r * n + k * kSeg);
+                const T rhs =
+                    sep_rhs(sm.f[e], sm.septab[0][k], sm.end[1][t0 + k - 1], sm.septab[1][k], sm.end[0][t0 + k]);
+                gg = (k == 1) ? rhs : sep_fwd(rhs, sm.septab[2][k], gg);
+                sm.f[e] = gg;
+            }
+            T z = T(0);
+            for (int k = m.S - 1; k >= 1; k--) {
+                const int e = padded(r * n + k * kSeg);
+                z = (k == m.S - 1) ? sm.f[e] * sm.septab[3][k] : sep_bwd(sm.f[e], sm.septab[4][k], z, sm.septab[3][k]);
+                sm.f[e] = z;
+            }
         }
         bar();
-        return;
     }
-    if (active && s == 0 && m.S > 1) {
-        // row r's separators live in sm.f at r*n + k*kSeg
-        const int t0 = tid;
-        T gg = T(0);
-        for (int k = 1; k < m.S; k++) {
-            const int e = padded(r * n + k * kSeg);
-            const T rhs = sep_rhs(sm.f[e], sm.septab[0][k], sm.end[1][t0 + k - 1], sm.septab[1][k], sm.end[0][t0 + k]);
-            gg = (k == 1) ? rhs : sep_fwd(rhs, sm.septab[2][k], gg);
-            sm.f[e] = gg;
-        }
-        T z = T(0);
-        for (int k = m.S - 1; k >= 1; k--) {
-            const int e = padded(r * n + k * kSeg);
-            z = (k == m.S - 1) ? sm.f[e] * sm.septab[3][k] : sep_bwd(sm.f[e], sm.septab[4][k], z, sm.septab[3][k]);
-            sm.f[e] = z;
-        }
-    }
-    bar();
-    zl = (s > 0) ? sm.f[padded(rr * n + s * kSeg)] : T(0);
-    zr = (s < m.S - 1) ? sm.f[padded(rr * n + (s + 1) * kSeg)] : T(0);
+    // read without a condition, indices clamped to a separator there is
+    auto sep = [&](int k) {
+        const int kc = min(max(k, m.S > 1 ? 1 : 0), m.S - 1), t = min(tid - s + kc, kBlk - 1), tm = max(t - 1, 0);
+        const T z = sm.f[padded(rr * n + kc * kSeg)];
+        const T w = sep_alone(z, sm.septab[0][kc], sm.end[1][tm], sm.septab[1][kc], sm.end[0][t], sm.septab[3][kc]);
+        return tb.dec ? w : z;
+    };
+    const T sl = sep(s), sr = sep(s + 1);
+    const T zl = (s > 0) ? sl : T(0), zr = (s < m.S - 1) ? sr : T(0);
     bar();  // every lane has read its separators
     if (active) {
-#pragma unroll
-        for (int q = 0; q < kSlot; q++)
-            if (q < len) sm.f[padded(r * n + lo + q)] = seg_final(v[q], tA[q], zl, tB[q], zr);
+        // slots past the segment go to its last node, before that node's own
+        // value (a store each, without a condition)
+        seg_finals(v, tA, zl, tB, zr, [&](int q, T x) { sm.f[padded(r * n + lo + min(q, len - 1))] = x; });
+        if (s > 0) sm.f[padded(r * n + s * kSeg)] = zl;
     }
     bar();
 }
@@ -502,9 +518,9 @@ __device__ __forceinline__ void solve_rows_tile(T* __restrict__ F, const FibreMa
     {
         T tmp[(kSpan + kBlk - 1) / kBlk];
         rows_load<T, kSpan>(F, row0, span, n, tmp, (int)threadIdx.x);
+        rows_tables(m, tb, sm);  // (one memory latency covers both)
         rows_stage<T, kSpan, kLdsTab>(tmp, span, sm);
     }
-    rows_tables(m, tb, sm);
     __syncthreads();
     rows_solve_lds<T, kSpan, kLdsTab>(m, tb, nrows, sm, (int)threadIdx.x);
     rows_store(F, row0, span, n, sm);
@@ -601,13 +617,13 @@ __device__ __forceinline__ int64_t yb_index(const FibreMap& m, int64_t fib, int 
 }
 
 template <typename T>
-__device__ __forceinline__ T load_solve(const T* F, const FibreMap& m, int64_t base, int s,
+__device__ __forceinline__ void load_solve(const T* F, const FibreMap& m, int64_t base, int s,
                                         const SolveTables<T>& tb, T (&v)[kSlot], int& lo, int& len)
 {
     seg_range(m, s, lo, len);
 #pragma unroll
     for (int q = 0; q < kSlot; q++) v[q] = F[base + (int64_t)(lo + min(q, len - 1)) * m.inner];
-    return seg_solve(v, tb.L + s * kSlot, tb.U + s * kSlot, tb.IP + s * kSlot);
+    seg_solve(v, tb.L + s * kSlot, tb.U + s * kSlot, tb.IP + s * kSlot);
 }
 
 template <typename T>
@@ -618,10 +634,10 @@ __device__ __forceinline__ void seg_ends_tile(const T* __restrict__ F, T* __rest
     int s, lo, len;
     if (!locate(m, bx, by, base, fib, s)) return;
     T v[kSlot];
-    const T ylast = load_solve(F, m, base, s, tb, v, lo, len);
+    load_solve(F, m, base, s, tb, v, lo, len);
     const int64_t yi = yb_index(m, fib, s);
     Yb[yi] = v[0];
-    Yb[yi + 1] = ylast;
+    Yb[yi + 1] = seg_last(v, s);
 }
 
 template <typename T>
