@@ -62,7 +62,12 @@ int level_cfg(StreamArgs<T>& a)
         // the rows being written close together in memory (8193^2 FP64, level
         // 0: 278 us at 16 coarse rows, 289 at 32, 318 in one round of 66)
         if (!kAct1) chunk = std::min(chunk, 16);
-        chunk = std::min(std::max(chunk, 2), kMaxChunk);
+        // At least two coarse planes (a chunk reads three fine planes more than
+        // it owns), but one where even then every workgroup has a CU to
+        // itself: such a step is bound by one workgroup's planes (33^3 FP32
+        // 10 -> 9 us; at 129 x 65 x 257 one plane each takes 22 us, two 15)
+        const int least = (int64_t)tiles * c0 <= device_cu_count() ? 1 : 2;
+        chunk = std::min(std::max(chunk, least), kMaxChunk);
     }
     a.chunk = chunk;
     a.nch = kAct0 ? (c0 + chunk - 1) / chunk : 1;
