@@ -313,7 +313,8 @@ int mgr_batch_tuning(const mgr_batch_plan* plan, int* persistent, double* model)
  * the pointer upload), work items. */
 int mgr_batch_config(const mgr_batch_plan* plan, int* chunk, int* launches, int64_t* items);
 
-/* Sets the chunk length (1..128) and rebuilds the work items. */
+/* Sets the chunk length of the finest level step (1..128; every coarser step
+ * halves it, down to 2) and rebuilds the work items. */
 int mgr_batch_set_config(mgr_batch_plan* plan, int chunk);
 
 /* Launch form of later mgr_batch_decompose calls on the plan (results are

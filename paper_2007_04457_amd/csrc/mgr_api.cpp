@@ -2007,6 +2007,12 @@ const char* const kKernelNames[KC_COUNT] = {
 constexpr int kStagesPerLevel = 10;  // stream + up to three solves of up to three phases
 constexpr int kMaxBatchChunk = 128;  // coarse planes per streaming item (the kernel's LDS tables)
 
+// Items [first, first + n) of a batch, all of one type, in one launch.
+struct BatchLaunch {
+    int first, n, type;
+    bool z;  // streaming items of a level step after the first
+};
+
 struct BatchPlan {
     int dtype = 0, nfields = 0, device = 0;
     // per-field plans built for the batch alone (tables only; the batch's
@@ -2016,9 +2022,10 @@ struct BatchPlan {
     std::vector<size_t> wsoff;     // byte offset of each field's workspace
     void* ws = nullptr;            // the fields' workspaces (same layout as their plans')
     void* dev = nullptr;           // device tables (one allocation)
-    size_t off_items = 0, off_sargs = 0, off_solves = 0, off_scat = 0, off_tail = 0, off_tailf = 0, off_ptrs = 0,
+    size_t off_items = 0, off_litems = 0, off_sargs = 0, off_solves = 0, off_scat = 0, off_tail = 0, off_tailf = 0, off_ptrs = 0,
            off_args = 0, dev_bytes = 0;
-    std::vector<std::pair<int, int>> waves;  // (first item, items) per launch
+    std::vector<std::pair<int, int>> waves;  // (first item, items) per wave
+    std::vector<BatchLaunch> launches;       // the waves' launches
     int n_items = 0, n_tail = 0;
     int tail_lds = 0;  // LDS elements of the tail launch
     int chunk = 8, tuned = 0;
@@ -2141,6 +2148,8 @@ template <typename T>
 struct BatchTables {
     std::vector<BatchItem> items;
     std::vector<std::pair<int, int>> waves;
+    std::vector<BatchItem> litems;  // the items of the launches
+    std::vector<BatchLaunch> launches;
     std::vector<StreamArgs<T>> sargs;
     std::vector<BatchSolve<T>> solves;
     std::vector<BatchScatter<T>> scatters;
@@ -2150,8 +2159,34 @@ struct BatchTables {
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
+// The launches of a wave, items [first, first + n): one per item type, each with
+// its items as that type's kernel takes them.
+template <typename T>
+void batch_launches(BatchTables<T>& out, int first, int n, bool z)
+{
+    for (int type = 0; type < BI_COUNT; type++) {
+        const int at = (int)out.litems.size();
+        for (int i = first; i < first + n; i++) {
+            BatchItem it = out.items[(size_t)i];
+            if (it.type != type) continue;
+            if (type == BI_STRIDED) {
+                const int g = batch_strided_fibres(out.solves[(size_t)it.args].tb.S) / 16;
+                if (it.bx % g) continue;
+                it.bx /= g;
+            }
+            out.litems.push_back(it);
+        }
+        const int m = (int)out.litems.size() - at;
+        if (m > 0) out.launches.push_back(BatchLaunch{at, m, type, z});
+    }
+}
+
+// Coarse planes per streaming item of a new plan (60 fields FP32: 16 964 us, 8
+// 971; 19 of every 16 fine planes are streamed at 8, 35 of 32 at 16).
+constexpr int kBatchChunk = 16;
+
 // Work items of every field, grouped into waves (level step k, stage s) in
-// that order; within a wave, field by field.
+// that order; within a wave field by field.
 template <typename T>
 int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
 {
@@ -2187,7 +2222,10 @@ int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
             a.nt1 = act1 ? (int)cdiv(a.fv.n[1], kT1) : 1;
             a.nt2 = (int)cdiv(a.fv.n[2], kT2);
             const int c0 = (int)a.fv.n[0];
-            a.chunk = act0 ? std::min(std::max(chunk, 2), c0) : c0;
+            // the finest step's chunk; a coarser step, with an eighth of the
+            // nodes, takes half the chunk of the one before: its items are
+            // fewer than the chip has room for, and it ends with its longest
+            a.chunk = act0 ? std::min(std::max(chunk >> k, 2), c0) : c0;
             a.nch = act0 ? (int)cdiv(c0, a.chunk) : 1;
             const int sidx = (int)out.sargs.size();
             out.sargs.push_back(a);
@@ -2228,18 +2266,20 @@ int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
                         bs.rows = (int)std::max<int64_t>(1, std::min<int64_t>(kThreadsBatch / ns, kBatchRowSpan / (ns * kSeg)));
                         for (int y = 0; y < nch; y++)
                             for (int64_t x = 0; x < cdiv(bs.nfib, bs.rows); x++)
-                                s2.push_back(BatchItem{BI_CHUNK_ROWS, vidx, (int)x, y, f});
+                                s2.push_back(BatchItem{ns > 16 ? BI_CHUNK_ROWS_LONG : BI_CHUNK_ROWS, vidx, (int)x, y, f});
                     }
                     stages.push_back(std::move(s1));
                     stages.push_back(std::move(s2));
                 } else if (bs.inner == 1 && S <= kThreadsBatch && bs.n <= kBatchRowSpan) {
                     bs.rows = (int)std::max<int64_t>(1, std::min<int64_t>(kThreadsBatch / S, kBatchRowSpan / bs.n));
                     std::vector<BatchItem> sg;
-                    for (int64_t x = 0; x < cdiv(bs.nfib, bs.rows); x++) sg.push_back(BatchItem{BI_ROWS, vidx, (int)x, 0, f});
+                    for (int64_t x = 0; x < cdiv(bs.nfib, bs.rows); x++)
+                        sg.push_back(BatchItem{S > 16 ? BI_ROWS_LONG : BI_ROWS, vidx, (int)x, 0, f});
                     stages.push_back(std::move(sg));
                 } else if (bs.inner > 1 && S <= 16) {
                     std::vector<BatchItem> sg;
-                    for (int64_t x = 0; x < cdiv(bs.nfib, 16); x++) sg.push_back(BatchItem{BI_STRIDED, vidx, (int)x, 0, f});
+                    for (int64_t x = 0; x < cdiv(bs.nfib, 16); x++)
+                        sg.push_back(BatchItem{BI_STRIDED, vidx, (int)x, 0, f});
                     stages.push_back(std::move(sg));
                 } else {
                     std::vector<BatchItem> s1, s2, s3;
@@ -2277,7 +2317,9 @@ int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
                 out.items.insert(out.items.end(), stages[(size_t)s].begin(), stages[(size_t)s].end());
             }
             const int n = (int)out.items.size() - first;
-            if (n > 0) out.waves.emplace_back(first, n);
+            if (n <= 0) continue;
+            out.waves.emplace_back(first, n);
+            batch_launches(out, first, n, k > 0);
         }
     // fields whose every level step streamed: coarsest values to their nodes
     {
@@ -2301,7 +2343,10 @@ int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
                 out.items.push_back(BatchItem{BI_SCATTER, idx, (int)x, 0, f});
         }
         const int n = (int)out.items.size() - first;
-        if (n > 0) out.waves.emplace_back(first, n);
+        if (n > 0) {
+            out.waves.emplace_back(first, n);
+            batch_launches(out, first, n, false);
+        }
     }
     if (out.items.size() > (size_t)INT32_MAX) return fail(MGR_ERR_ARG, "too many work items");
     // small level steps: one tail workgroup per field that has them
@@ -2319,6 +2364,20 @@ int batch_tables(BatchPlan& b, int chunk, BatchTables<T>& out)
 }
 
 template <typename T>
+BatchKernelArgs<T> batch_args(const BatchPlan& b)
+{
+    char* d = (char*)b.dev;
+    BatchKernelArgs<T> ka;
+    ka.items = (const BatchItem*)(d + b.off_items);
+    ka.sargs = (const StreamArgs<T>*)(d + b.off_sargs);
+    ka.solves = (const BatchSolve<T>*)(d + b.off_solves);
+    ka.scatters = (const BatchScatter<T>*)(d + b.off_scat);
+    ka.src = (const T* const*)(d + b.off_ptrs);
+    ka.dst = (T* const*)(d + b.off_ptrs + sizeof(void*) * (size_t)b.nfields);
+    return ka;
+}
+
+template <typename T>
 int batch_upload(BatchPlan& b, int chunk)
 {
     BatchTables<T> t;
@@ -2332,6 +2391,7 @@ int batch_upload(BatchPlan& b, int chunk)
         return o;
     };
     b.off_items = take(sizeof(BatchItem) * t.items.size());
+    b.off_litems = take(sizeof(BatchItem) * t.litems.size());
     b.off_sargs = take(sizeof(StreamArgs<T>) * t.sargs.size());
     b.off_solves = take(sizeof(BatchSolve<T>) * t.solves.size());
     b.off_scat = take(sizeof(BatchScatter<T>) * t.scatters.size());
@@ -2355,18 +2415,13 @@ int batch_upload(BatchPlan& b, int chunk)
     }
     b.dev_bytes = off;
     char* d = (char*)b.dev;
-    BatchKernelArgs<T> ka;
-    ka.items = (const BatchItem*)(d + b.off_items);
-    ka.sargs = (const StreamArgs<T>*)(d + b.off_sargs);
-    ka.solves = (const BatchSolve<T>*)(d + b.off_solves);
-    ka.scatters = (const BatchScatter<T>*)(d + b.off_scat);
-    ka.src = (const T* const*)(d + b.off_ptrs);
-    ka.dst = (T* const*)(d + b.off_ptrs + sizeof(void*) * (size_t)b.nfields);
+    const BatchKernelArgs<T> ka = batch_args<T>(b);
     struct Part {
         size_t off;
         const void* src;
         size_t bytes;
     } parts[] = {{b.off_items, t.items.data(), sizeof(BatchItem) * t.items.size()},
+                 {b.off_litems, t.litems.data(), sizeof(BatchItem) * t.litems.size()},
                  {b.off_sargs, t.sargs.data(), sizeof(StreamArgs<T>) * t.sargs.size()},
                  {b.off_solves, t.solves.data(), sizeof(BatchSolve<T>) * t.solves.size()},
                  {b.off_scat, t.scatters.data(), sizeof(BatchScatter<T>) * t.scatters.size()},
@@ -2389,6 +2444,7 @@ int batch_upload(BatchPlan& b, int chunk)
     e = hipMemcpy(d + b.off_qwords, zeros.data(), sizeof(int) * zeros.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "clear queue words");
     b.waves = t.waves;
+    b.launches = t.launches;
     b.n_items = (int)t.items.size();
     b.n_tail = (int)t.tail.size();
     b.tail_lds = 0;
@@ -2442,9 +2498,12 @@ int batch_run(BatchPlan& b, const void* const* src, void* const* dst, hipStream_
                       }),
                 "batch queue launch");
     } else {
-        for (size_t w = 0; w < b.waves.size(); w++) {
-            const int first = b.waves[w].first, n = b.waves[w].second;
-            MGR_TRY(timed(KC_BATCH, (int)w, st, [&] { return launch_batch_wave<T>(dev_args, first, n, st); }),
+        BatchKernelArgs<T> ka = batch_args<T>(b);
+        ka.items = (const BatchItem*)(d + b.off_litems);
+        for (size_t w = 0; w < b.launches.size(); w++) {
+            const BatchLaunch& l = b.launches[w];
+            MGR_TRY(timed(KC_BATCH, (int)w, st,
+                          [&] { return launch_batch_items<T>(ka, l.first, l.n, l.type, l.z, st); }),
                     "batch wave launch");
         }
     }
@@ -2495,7 +2554,7 @@ int batch_create(int nfields, const int* ndim, const int64_t* const* shapes, con
         b->ws = nullptr;
         return fail(MGR_ERR_ALLOC, std::string("hipMalloc batch workspace: ") + hipGetErrorString(e));
     }
-    int rc = (dtype == MGR_F64) ? batch_upload<double>(*b, 8) : batch_upload<float>(*b, 8);
+    int rc = (dtype == MGR_F64) ? batch_upload<double>(*b, kBatchChunk) : batch_upload<float>(*b, kBatchChunk);
     if (rc) return rc;
     *out = b.release();
     return MGR_OK;
@@ -2533,7 +2592,7 @@ BatchTerms batch_terms(const BatchPlan& b, int chunk)
             int kT1, kT2;
             level_tiling(act1, (int)esz, b.wide != 0, &kT1, &kT2);
             const double tiles = (act1 ? std::ceil((double)ly.mc[1] / kT1) : 1.0) * std::ceil((double)ly.mc[2] / kT2);
-            const double ch = act0 ? std::min<double>(std::max(chunk, 2), c0) : c0;
+            const double ch = act0 ? std::min<double>(std::max(chunk >> k, 2), c0) : c0;
             const double nch = act0 ? std::ceil(c0 / ch) : 1.0;
             const double halo = act0 ? (2.0 * ch + 3.0) / (2.0 * ch) : 1.0;
             t.bytes += 2.0 * V * esz * halo;
@@ -3479,9 +3538,9 @@ int mgr_batch_config(const mgr_batch_plan* plan, int* chunk, int* launches, int6
     const BatchPlan* b = reinterpret_cast<const BatchPlan*>(plan);
     if (!b) return fail(MGR_ERR_ARG, "plan is NULL");
     if (chunk) *chunk = b->chunk;
-    // kernel launches per call besides the pointer upload: the waves and the
-    // tail, or the queue reset, the queue and the tail
-    if (launches) *launches = b->persistent ? 3 : (int)b->waves.size() + 1;
+    // kernel launches per call besides the pointer upload: those of the waves
+    // and the tail, or the queue reset, the queue and the tail
+    if (launches) *launches = b->persistent ? 3 : (int)b->launches.size() + 1;
     if (items) *items = b->n_items;
     return MGR_OK;
 }

@@ -4,8 +4,8 @@
 // streaming level tiles and the correction-solve blocks of each level step)
 // as an item, grouped into waves: wave (k, s) holds stage s of level step k
 // of every field that has it (stage 0 the streaming pass, then the solves).
-// One launch runs a wave, one workgroup per item, whatever its field, shape
-// or dimensionality; stream order between the waves carries every
+// One launch runs a wave's items of one type, one workgroup per item,
+// whatever its field or shape; stream order between the waves carries every
 // dependency (stage s of a field needs its stage s - 1, level step k + 1
 // needs the last solve of step k), so no workgroup ever waits for another.
 // The whole sequence (a few dozen launches for any number of fields) is
@@ -29,8 +29,8 @@ union BatchSmem {
     ChunkSmem<T, kBatchRowSpan + 64, false> chunk_g;
 };
 
-// The kernel's LDS (dynamic, sized to BatchSmem<T> at launch).  Each item
-// type runs in a function of its own (not inlined), so that its registers
+// The queue kernel's LDS (dynamic, sized to BatchSmem<T> at launch).  There each
+// item type runs in a function of its own (not inlined), so that its registers
 // are allocated on its own: the kernel's register budget is then set by the
 // largest item, and items above it spill inside themselves only.
 extern __shared__ __align__(16) unsigned char batch_lds[];
@@ -89,20 +89,44 @@ __device__ __forceinline__ FibreMap fibre_map(const BatchSolve<T>& b)
     return m;
 }
 
+template <typename T, bool kLdsTab>
+__device__ __forceinline__ void rows_item(const BatchItem& it, const BatchSolve<T>& b,
+                                          RowsSmem<T, kBatchRowSpan, kLdsTab>& sm)
+{
+    const FibreMap m = fibre_map(b);
+    const int64_t row0 = (int64_t)it.bx * b.rows;
+    const int nrows = (int)min((int64_t)b.rows, m.nfib - row0);
+    solve_rows_tile<T, kBatchRowSpan, kLdsTab>(b.F, m, b.tb, row0, nrows, sm);
+}
+
 template <typename T>
 __device__ __attribute__((noinline)) void exec_rows(const BatchKernelArgs<T>* A, const BatchItem* itp)
 {
     const BatchItem it = load_uniform(itp);
     const BatchSolve<T> b = load_uniform(A->solves + it.args);
-    const FibreMap m = fibre_map(b);
-    const int64_t row0 = (int64_t)it.bx * b.rows;
-    const int nrows = (int)min((int64_t)b.rows, m.nfib - row0);
-    if (m.S <= kMaxSegWG)
-        solve_rows_tile<T, kBatchRowSpan, true>(
-            b.F, m, b.tb, row0, nrows, *reinterpret_cast<RowsSmem<T, kBatchRowSpan, true>*>(batch_lds));
+    if (b.tb.S <= kMaxSegWG)
+        rows_item<T, true>(it, b, *reinterpret_cast<RowsSmem<T, kBatchRowSpan, true>*>(batch_lds));
     else
-        solve_rows_tile<T, kBatchRowSpan, false>(
-            b.F, m, b.tb, row0, nrows, *reinterpret_cast<RowsSmem<T, kBatchRowSpan, false>*>(batch_lds));
+        rows_item<T, false>(it, b, *reinterpret_cast<RowsSmem<T, kBatchRowSpan, false>*>(batch_lds));
+}
+
+template <typename T>
+__device__ __forceinline__ void strided_item(const BatchItem& it, const BatchSolve<T>& b, StridedSmem<T>& sm)
+{
+    const FibreMap m = fibre_map(b);
+    const int tid = threadIdx.x;
+    auto run = [&](auto fb) {
+        constexpr int FB = decltype(fb)::value;
+        solve_strided_tile<T, FB, false>(b.F, b.F, m, b.tb, (int64_t)it.bx * FB, tid / FB, tid % FB, kThreads, tid, sm,
+                                         0, m.S, nullptr);
+    };
+    switch (batch_strided_fibres(m.S)) {
+        case 256: run(std::integral_constant<int, 256>{}); break;
+        case 128: run(std::integral_constant<int, 128>{}); break;
+        case 64: run(std::integral_constant<int, 64>{}); break;
+        case 32: run(std::integral_constant<int, 32>{}); break;
+        default: run(std::integral_constant<int, 16>{}); break;
+    }
 }
 
 template <typename T>
@@ -110,18 +134,17 @@ __device__ __attribute__((noinline)) void exec_strided(const BatchKernelArgs<T>*
 {
     const BatchItem it = load_uniform(itp);
     const BatchSolve<T> b = load_uniform(A->solves + it.args);
+    const FibreMap m = fibre_map(b);
     const int tid = threadIdx.x;
-    solve_strided_tile<T, 16, false>(b.F, b.F, fibre_map(b), b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads,
-                                     tid, *reinterpret_cast<StridedSmem<T>*>(batch_lds), 0, b.tb.S, nullptr);
+    solve_strided_tile<T, 16, false>(b.F, b.F, m, b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads, tid,
+                                     *reinterpret_cast<StridedSmem<T>*>(batch_lds), 0, m.S, nullptr);
 }
 
 // Long fibres whose separators do not couple: the separators between chunks,
 // and the chunks.
 template <typename T>
-__device__ __attribute__((noinline)) void exec_sep_bounds(const BatchKernelArgs<T>* A, const BatchItem* itp)
+__device__ __forceinline__ void sep_bounds_item(const BatchItem& it, const BatchSolve<T>& b)
 {
-    const BatchItem it = load_uniform(itp);
-    const BatchSolve<T> b = load_uniform(A->solves + it.args);
     const FibreMap m = fibre_map(b);
     const int ns = solve_chunk_segs(m.S, m.inner, m.nfib);
     if (m.inner > 1)
@@ -131,21 +154,44 @@ __device__ __attribute__((noinline)) void exec_sep_bounds(const BatchKernelArgs<
 }
 
 template <typename T>
+__device__ __attribute__((noinline)) void exec_sep_bounds(const BatchKernelArgs<T>* A, const BatchItem* itp)
+{
+    const BatchItem it = load_uniform(itp);
+    sep_bounds_item<T>(it, load_uniform(A->solves + it.args));
+}
+
+template <typename T, bool kLdsTab>
+__device__ __forceinline__ void chunk_rows_item(const BatchItem& it, const BatchSolve<T>& b, int ns,
+                                                ChunkSmem<T, kBatchRowSpan + 64, kLdsTab>& sm)
+{
+    const FibreMap m = fibre_map(b);
+    const int s0 = it.by * ns, nsc = min(ns, m.S - s0);
+    const int64_t row0 = (int64_t)it.bx * b.rows;
+    const int nrows = (int)min((int64_t)b.rows, m.nfib - row0);
+    const T* zb = b.Yb + ((int64_t)it.by - 1) * m.nfib;
+    solve_chunk_rows<T, kBatchRowSpan + 64, kLdsTab>(b.F, m, b.tb, row0, nrows, s0, nsc, zb, sm);
+}
+
+template <typename T>
 __device__ __attribute__((noinline)) void exec_chunk_rows(const BatchKernelArgs<T>* A, const BatchItem* itp)
 {
     const BatchItem it = load_uniform(itp);
     const BatchSolve<T> b = load_uniform(A->solves + it.args);
-    const FibreMap m = fibre_map(b);
-    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib), s0 = it.by * ns, nsc = min(ns, m.S - s0);
-    const int64_t row0 = (int64_t)it.bx * b.rows;
-    const int nrows = (int)min((int64_t)b.rows, m.nfib - row0);
-    const T* zb = b.Yb + ((int64_t)it.by - 1) * m.nfib;
+    const int ns = solve_chunk_segs(b.tb.S, b.inner, b.nfib);
     if (ns <= kMaxSegWG)
-        solve_chunk_rows<T, kBatchRowSpan + 64, true>(
-            b.F, m, b.tb, row0, nrows, s0, nsc, zb, *reinterpret_cast<ChunkSmem<T, kBatchRowSpan + 64, true>*>(batch_lds));
+        chunk_rows_item<T, true>(it, b, ns, *reinterpret_cast<ChunkSmem<T, kBatchRowSpan + 64, true>*>(batch_lds));
     else
-        solve_chunk_rows<T, kBatchRowSpan + 64, false>(
-            b.F, m, b.tb, row0, nrows, s0, nsc, zb, *reinterpret_cast<ChunkSmem<T, kBatchRowSpan + 64, false>*>(batch_lds));
+        chunk_rows_item<T, false>(it, b, ns, *reinterpret_cast<ChunkSmem<T, kBatchRowSpan + 64, false>*>(batch_lds));
+}
+
+template <typename T>
+__device__ __forceinline__ void chunk_strided_item(const BatchItem& it, const BatchSolve<T>& b, StridedSmem<T>& sm)
+{
+    const FibreMap m = fibre_map(b);
+    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib), s0 = it.by * ns;
+    const int tid = threadIdx.x;
+    solve_strided_tile<T, 16, false>(b.F, b.F, m, b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads, tid, sm, s0,
+                                     min(ns, m.S - s0), b.Yb + ((int64_t)it.by - 1) * m.nfib);
 }
 
 template <typename T>
@@ -153,19 +199,12 @@ __device__ __attribute__((noinline)) void exec_chunk_strided(const BatchKernelAr
 {
     const BatchItem it = load_uniform(itp);
     const BatchSolve<T> b = load_uniform(A->solves + it.args);
-    const FibreMap m = fibre_map(b);
-    const int ns = solve_chunk_segs(m.S, m.inner, m.nfib), s0 = it.by * ns;
-    const int tid = threadIdx.x;
-    solve_strided_tile<T, 16, false>(b.F, b.F, m, b.tb, (int64_t)it.bx * 16, tid / 16, tid % 16, kThreads, tid,
-                                     *reinterpret_cast<StridedSmem<T>*>(batch_lds), s0, min(ns, m.S - s0),
-                                     b.Yb + ((int64_t)it.by - 1) * m.nfib);
+    chunk_strided_item<T>(it, b, *reinterpret_cast<StridedSmem<T>*>(batch_lds));
 }
 
 template <typename T>
-__device__ __attribute__((noinline)) void exec_phase(const BatchKernelArgs<T>* A, const BatchItem* itp)
+__device__ __forceinline__ void phase_item(const BatchItem& it, const BatchSolve<T>& b)
 {
-    const BatchItem it = load_uniform(itp);
-    const BatchSolve<T> b = load_uniform(A->solves + it.args);
     const FibreMap m = fibre_map(b);
     if (it.type == BI_SEG_ENDS)
         seg_ends_tile(b.F, b.Yb, m, b.tb, it.bx, it.by);
@@ -176,11 +215,15 @@ __device__ __attribute__((noinline)) void exec_phase(const BatchKernelArgs<T>* A
 }
 
 template <typename T>
-__device__ __attribute__((noinline)) void exec_scatter(const BatchKernelArgs<T>* A, const BatchItem* itp)
+__device__ __attribute__((noinline)) void exec_phase(const BatchKernelArgs<T>* A, const BatchItem* itp)
 {
     const BatchItem it = load_uniform(itp);
-    const BatchScatter<T> sc = load_uniform(A->scatters + it.args);
-    T* dst = load_uniform(A->dst + it.field);
+    phase_item<T>(it, load_uniform(A->solves + it.args));
+}
+
+template <typename T>
+__device__ __forceinline__ void scatter_item(const BatchItem& it, const BatchScatter<T>& sc, T* dst)
+{
     const int64_t idx = (int64_t)it.bx * kThreads + threadIdx.x;
     if (idx >= sc.n[0] * sc.n[1] * sc.n[2]) return;
     const int64_t j2 = idx % sc.n[2], j1 = (idx / sc.n[2]) % sc.n[1], j0 = idx / (sc.n[1] * sc.n[2]);
@@ -188,23 +231,86 @@ __device__ __attribute__((noinline)) void exec_scatter(const BatchKernelArgs<T>*
 }
 
 template <typename T>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8)))
-k_batch(const BatchKernelArgs<T>* __restrict__ A, int first)
+__device__ __attribute__((noinline)) void exec_scatter(const BatchKernelArgs<T>* A, const BatchItem* itp)
 {
-    const BatchItem* itp = A->items + first + blockIdx.x;
-    switch (itp->type) {
-        case BI_STREAM3: exec_stream<T, true, true, false>(A, itp); break;
-        case BI_STREAM3W: exec_stream<T, true, true, true>(A, itp); break;
-        case BI_STREAM2: exec_stream<T, true, false, false>(A, itp); break;
-        case BI_STREAM1: exec_stream<T, false, false, false>(A, itp); break;
-        case BI_ROWS: exec_rows<T>(A, itp); break;
-        case BI_STRIDED: exec_strided<T>(A, itp); break;
-        case BI_SCATTER: exec_scatter<T>(A, itp); break;
-        case BI_SEP_BOUNDS: exec_sep_bounds<T>(A, itp); break;
-        case BI_CHUNK_ROWS: exec_chunk_rows<T>(A, itp); break;
-        case BI_CHUNK_STRIDED: exec_chunk_strided<T>(A, itp); break;
-        default: exec_phase<T>(A, itp); break;
-    }
+    const BatchItem it = load_uniform(itp);
+    scatter_item<T>(it, load_uniform(A->scatters + it.args), load_uniform(A->dst + it.field));
+}
+
+// One launch per item type of a wave: its kernel holds that type alone, with
+// its registers and LDS, and deals neighbouring items to one XCD (they share
+// halo lines).  60 fields FP32 (445 MB): 910 us, against 1286 in launches of a
+// kernel that reached every type through function calls (four waves a SIMD and
+// 30 KB of LDS for all of them); 16 fields FP64 650 against 2320 (904 bytes of
+// scratch there).  Types of a wave run one after the other: also with few items
+// that is faster than together (4 fields 168 -> 130 and 620 -> 216 us).
+template <typename T, bool kAct0, bool kAct1, bool kWide, bool kZ>
+__global__ void __launch_bounds__(kThreads)
+    __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && kWide && !kZ ? 4 : stream_min_waves<T, true, kZ>(), 8)))
+k_batch_stream(BatchKernelArgs<T> A, int first)
+{
+    __shared__ LevelSmem<T, kAct0, kAct1, true, kWide> sm;
+    const BatchItem it = A.items[first + remap_xcd((int)blockIdx.x, (int)gridDim.x)];
+    StreamArgs<T> a = A.sargs[it.args];
+    if (!kZ) a.A = A.src[it.field];
+    a.C = A.dst[it.field];
+    stream_level_tile<T, kAct0, kAct1, true, kZ, false, kWide>(a, it.bx, sm);
+}
+
+template <typename T, bool kLong>
+__global__ void __launch_bounds__(kThreads) k_batch_rows(BatchKernelArgs<T> A, int first)
+{
+    __shared__ RowsSmem<T, kBatchRowSpan, !kLong> sm;
+    const BatchItem it = A.items[first + remap_xcd((int)blockIdx.x, (int)gridDim.x)];
+    rows_item<T, !kLong>(it, A.solves[it.args], sm);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_batch_strided(BatchKernelArgs<T> A, int first)
+{
+    __shared__ StridedSmem<T> sm;
+    const BatchItem it = A.items[first + remap_xcd((int)blockIdx.x, (int)gridDim.x)];
+    const BatchSolve<T> b = A.solves[it.args];
+    strided_item<T>(it, b, sm);
+}
+
+template <typename T, bool kLong>
+__global__ void __launch_bounds__(kThreads) k_batch_chunk_rows(BatchKernelArgs<T> A, int first)
+{
+    __shared__ ChunkSmem<T, kBatchRowSpan + 64, !kLong> sm;
+    const BatchItem it = A.items[first + (int)blockIdx.x];
+    const BatchSolve<T> b = A.solves[it.args];
+    chunk_rows_item<T, !kLong>(it, b, solve_chunk_segs(b.tb.S, b.inner, b.nfib), sm);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_batch_chunk_strided(BatchKernelArgs<T> A, int first)
+{
+    __shared__ StridedSmem<T> sm;
+    const BatchItem it = A.items[first + remap_xcd((int)blockIdx.x, (int)gridDim.x)];
+    const BatchSolve<T> b = A.solves[it.args];
+    chunk_strided_item<T>(it, b, sm);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_batch_sep_bounds(BatchKernelArgs<T> A, int first)
+{
+    const BatchItem it = A.items[first + (int)blockIdx.x];
+    sep_bounds_item<T>(it, A.solves[it.args]);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_batch_phase(BatchKernelArgs<T> A, int first)
+{
+    const BatchItem it = A.items[first + (int)blockIdx.x];
+    phase_item<T>(it, A.solves[it.args]);
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kThreads) k_batch_scatter(BatchKernelArgs<T> A, int first)
+{
+    const BatchItem it = A.items[first + (int)blockIdx.x];
+    scatter_item<T>(it, A.scatters[it.args], A.dst[it.field]);
 }
 
 // Device side of the queue protocol (mgr_queue.h), run by a whole wave:
@@ -260,11 +366,13 @@ __device__ __forceinline__ void run_item(const BatchKernelArgs<T>* A, const Batc
         case BI_STREAM3W: exec_stream<T, true, true, true>(A, itp); break;
         case BI_STREAM2: exec_stream<T, true, false, false>(A, itp); break;
         case BI_STREAM1: exec_stream<T, false, false, false>(A, itp); break;
-        case BI_ROWS: exec_rows<T>(A, itp); break;
+        case BI_ROWS:
+        case BI_ROWS_LONG: exec_rows<T>(A, itp); break;
         case BI_STRIDED: exec_strided<T>(A, itp); break;
         case BI_SCATTER: exec_scatter<T>(A, itp); break;
         case BI_SEP_BOUNDS: exec_sep_bounds<T>(A, itp); break;
-        case BI_CHUNK_ROWS: exec_chunk_rows<T>(A, itp); break;
+        case BI_CHUNK_ROWS:
+        case BI_CHUNK_ROWS_LONG: exec_chunk_rows<T>(A, itp); break;
         case BI_CHUNK_STRIDED: exec_chunk_strided<T>(A, itp); break;
         default: exec_phase<T>(A, itp); break;
     }
@@ -330,14 +438,36 @@ int device_cu_count()
     return cache[dev];
 }
 
-// One wave of items: dev_a (device memory) lists them; this launch runs
-// items [first, first + n).
 template <typename T>
-hipError_t launch_batch_wave(const BatchKernelArgs<T>* dev_a, int first, int n, hipStream_t st)
+hipError_t launch_batch_items(const BatchKernelArgs<T>& a, int first, int n, int type, bool z, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_batch<T>, dim3((unsigned)n), dim3(kThreads), sizeof(BatchSmem<T>), st, dev_a, first);
-    return hipGetLastError();
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3((unsigned)n), dim3(kThreads), 0, st, a, first);
+        return hipGetLastError();
+    };
+    switch (type) {
+        case BI_STREAM3:
+            return z ? go(k_batch_stream<T, true, true, false, true>) : go(k_batch_stream<T, true, true, false, false>);
+        case BI_STREAM3W:
+            return z ? go(k_batch_stream<T, true, true, true, true>) : go(k_batch_stream<T, true, true, true, false>);
+        case BI_STREAM2:
+            return z ? go(k_batch_stream<T, true, false, false, true>) : go(k_batch_stream<T, true, false, false, false>);
+        case BI_STREAM1:
+            return z ? go(k_batch_stream<T, false, false, false, true>) : go(k_batch_stream<T, false, false, false, false>);
+        case BI_ROWS: return go(k_batch_rows<T, false>);
+        case BI_ROWS_LONG: return go(k_batch_rows<T, true>);
+        case BI_STRIDED: return go(k_batch_strided<T>);
+        case BI_CHUNK_ROWS: return go(k_batch_chunk_rows<T, false>);
+        case BI_CHUNK_ROWS_LONG: return go(k_batch_chunk_rows<T, true>);
+        case BI_CHUNK_STRIDED: return go(k_batch_chunk_strided<T>);
+        case BI_SEP_BOUNDS: return go(k_batch_sep_bounds<T>);
+        case BI_SEG_ENDS:
+        case BI_SEPARATORS:
+        case BI_SEG_FINAL: return go(k_batch_phase<T>);
+        case BI_SCATTER: return go(k_batch_scatter<T>);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 // Writes up to kPtrChunk pointers, passed by value, to dst.  A graph that
@@ -393,7 +523,7 @@ template hipError_t launch_batch_queue<double>(const BatchKernelArgs<double>*, c
                                                int, int, unsigned, hipStream_t);
 template int batch_queue_slots<float>();
 template int batch_queue_slots<double>();
-template hipError_t launch_batch_wave<float>(const BatchKernelArgs<float>*, int, int, hipStream_t);
-template hipError_t launch_batch_wave<double>(const BatchKernelArgs<double>*, int, int, hipStream_t);
+template hipError_t launch_batch_items<float>(const BatchKernelArgs<float>&, int, int, int, bool, hipStream_t);
+template hipError_t launch_batch_items<double>(const BatchKernelArgs<double>&, int, int, int, bool, hipStream_t);
 
 }  // namespace mgr

@@ -380,7 +380,8 @@ enum BatchItemType {
     BI_STREAM2,      // 2-D problem (m0, 1, m2)
     BI_STREAM1,      // 1-D problem
     BI_ROWS,         // solve along the contiguous dimension, a block of rows
-    BI_STRIDED,      // solve along a strided dimension, 16 fibres (S <= 16)
+    BI_STRIDED,      // solve along a strided dimension (S <= 16), 16 fibres, or in a
+                     // launch of its own batch_strided_fibres(S)
     BI_SEG_ENDS,     // long fibres, three phases (three waves)
     BI_SEPARATORS,
     BI_SEG_FINAL,
@@ -389,8 +390,19 @@ enum BatchItemType {
     BI_SEP_BOUNDS,   // long fibres whose separators do not couple, two waves:
     BI_CHUNK_ROWS,   // the separators between chunks, then the chunks (by: chunk)
     BI_CHUNK_STRIDED,
+    BI_ROWS_LONG,        // BI_ROWS and BI_CHUNK_ROWS of more than 16 segments
+    BI_CHUNK_ROWS_LONG,
     BI_COUNT
 };
+
+// Fibres of a BI_STRIDED item in a launch of that type: its 256 threads are that
+// many fibres times at least S segments.  As many as fit, so that a row of them
+// covers whole cache lines (60 fields FP32, the finest steps: dimension 1 37 ->
+// 19 us).
+__host__ __device__ inline int batch_strided_fibres(int S)
+{
+    return S == 1 ? 256 : S == 2 ? 128 : S <= 4 ? 64 : S <= 8 ? 32 : 16;
+}
 
 struct BatchItem {
     int type;
@@ -439,10 +451,10 @@ struct PtrChunk {
     int first, n;
 };
 hipError_t launch_set_ptrs(const PtrChunk& c, void** dst, hipStream_t st);
-
-// Runs items [first, first + n) of the table dev_a->items, one workgroup each.
+// Items [first, first + n), all of one type; z: streaming items with a
+// correction to add.
 template <typename T>
-hipError_t launch_batch_wave(const BatchKernelArgs<T>* dev_a, int first, int n, hipStream_t st);
+hipError_t launch_batch_items(const BatchKernelArgs<T>& a, int first, int n, int type, bool z, hipStream_t st);
 // Persistent form: all items in one launch of `grid` workgroups through the
 // queue of mgr_queue.h (the queue words zeroed first by a small kernel).
 template <typename T>
