@@ -1305,10 +1305,23 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
             }
             MGR_TRY(timed(KC_STREAM_LOAD, group[0], st, [&] { return launch_stream_load_multi<T>(la, n, st); }),
                     "shared load-vector launch");
-            for (int sd = 0; sd < 3; sd++) {
+            // planes that fit in LDS: dimensions 2 and 1 in one launch (only
+            // where no long-running launch shares the device: a plane's
+            // workgroup may need a whole CU)
+            bool planes = shared && p.active[1] && p.active[2];
+            SolveTables<T> tb[kMultiLevels], tb1[kMultiLevels];
+            for (int i = 0; planes && i < n; i++) {
+                tb[i] = solve_tables_of<T>(p, group[(size_t)i], 2);
+                tb1[i] = solve_tables_of<T>(p, group[(size_t)i], 1);
+                planes = solve_plane_fits<T>(fv[i], tb[i], tb1[i]);
+            }
+            if (planes)
+                MGR_TRY(timed(KC_SOLVE, group[0], st,
+                              [&] { return launch_solve_plane_multi<T>(Fz, fv, tb, tb1, n, st); }),
+                        "shared plane solve launch");
+            for (int sd = planes ? 2 : 0; sd < 3; sd++) {
                 const int d = 2 - sd;
                 if (!p.active[d]) continue;
-                SolveTables<T> tb[kMultiLevels];
                 for (int i = 0; i < n; i++) tb[i] = solve_tables_of<T>(p, group[(size_t)i], d);
                 MGR_TRY(timed(KC_SOLVE, group[0], st, [&] { return launch_solve_multi<T>(Fz, fv, d, tb, n, st); }),
                         "shared solve launch");

@@ -247,6 +247,11 @@ bool solve_multi_fits(View3 fv, int d, const SolveTables<T>& tb);
 template <typename T>
 hipError_t launch_solve_multi(T* const* F, const View3* fv, int d, const SolveTables<T>* tb, int n,
                               hipStream_t st);
+// Dimensions 2 and 1 of several level steps' planes (each solve_plane_fits) in one
+// launch.
+template <typename T>
+hipError_t launch_solve_plane_multi(T* const* F, const View3* fv, const SolveTables<T>* t2, const SolveTables<T>* t1,
+                                    int n, hipStream_t st);
 // One adjoint level step (mgr_adjoint.hip): g / gv the input at the level
 // grid's fine nodes, y the solved corrections and G the coarse-node input
 // (packed coarse grid yv), O / ov the level-grid output (not overlapping g).

@@ -338,10 +338,11 @@ __device__ __forceinline__ void plane_dim(T* P, T* end0, T* end1, const T* tab, 
     __syncthreads();
 }
 
+extern __shared__ __align__(16) unsigned char plane_lds[];
+
 template <typename T>
-__global__ void __launch_bounds__(kPlaneThreads) k_solve_plane(PlaneSolveArgs<T> a)
+__device__ __forceinline__ void plane_body(const PlaneSolveArgs<T>& a, int plane)
 {
-    extern __shared__ __align__(16) unsigned char plane_lds[];
     constexpr int TAB = 5 * kMaxSegWG * kSlot, SEP = 5 * kMaxSegWG;
     T* const tab = reinterpret_cast<T*>(plane_lds);  // [dim][L, U, IP, A, B][segment][slot]
     T* const septab = tab + 2 * TAB;                  // [dim][sub, sup, sl, sip, su][separator]
@@ -349,7 +350,7 @@ __global__ void __launch_bounds__(kPlaneThreads) k_solve_plane(PlaneSolveArgs<T>
     T* const P = end + 2 * kPlaneThreads;             // the plane, n1 x n2
     const int tid = threadIdx.x, nthr = blockDim.x;
     const int n1 = a.n1, n2 = a.n2, V = n1 * n2;
-    T* const F = a.F + (int64_t)blockIdx.x * V;
+    T* const F = a.F + (int64_t)plane * V;
     // the plane's loads first (one batch covers every plane that fits), the
     // tables' after them: one memory latency covers both
     constexpr int NB = plane_batch<T>();
@@ -383,6 +384,31 @@ __global__ void __launch_bounds__(kPlaneThreads) k_solve_plane(PlaneSolveArgs<T>
         for (int q = 0; q < 8; q++)
             if (b0 + q * nthr + tid < V) F[b0 + q * nthr + tid] = o[q];
     }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kPlaneThreads) k_solve_plane(PlaneSolveArgs<T> a)
+{
+    plane_body(a, (int)blockIdx.x);
+}
+
+// Planes of several level steps in one grid: plane b belongs to the step l with
+// start[l] <= b < start[l + 1].
+template <typename T>
+struct MultiPlane {
+    PlaneSolveArgs<T> a[kMultiLevels];
+    int start[kMultiLevels + 1];
+    int n;
+};
+static_assert(sizeof(MultiPlane<double>) <= 4096, "fits the kernel argument segment");
+
+template <typename T>
+__global__ void __launch_bounds__(kPlaneThreads) k_solve_plane_multi(MultiPlane<T> m)
+{
+    const int b = (int)blockIdx.x;
+    int l = 0;
+    for (int i = 1; i < m.n; i++) l += (b >= m.start[i]) ? 1 : 0;
+    plane_body(m.a[l], b - m.start[l]);
 }
 
 // Solves of several level steps along one dimension in one grid: block b
@@ -645,8 +671,10 @@ int plane_solve_lds()
             v = 65536;
         max_lds[dev] = v;
         if (v > 65536 &&
-            hipFuncSetAttribute((const void*)k_solve_plane<T>, hipFuncAttributeMaxDynamicSharedMemorySize, v) !=
-                hipSuccess) {
+            (hipFuncSetAttribute((const void*)k_solve_plane<T>, hipFuncAttributeMaxDynamicSharedMemorySize, v) !=
+                 hipSuccess ||
+             hipFuncSetAttribute((const void*)k_solve_plane_multi<T>, hipFuncAttributeMaxDynamicSharedMemorySize, v) !=
+                 hipSuccess)) {
             (void)hipGetLastError();  // not sticky: keep it from the next launch check
             max_lds[dev] = 65536;
         }
@@ -669,11 +697,11 @@ bool solve_plane_fits(View3 fv, const SolveTables<T>& t2, const SolveTables<T>& 
     return plane_solve_bytes<T>(fv) <= (size_t)plane_solve_lds<T>();
 }
 
+// Arguments of a plane solve; returns the lanes it wants (a task each, and loads
+// enough in flight).
 template <typename T>
-hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const SolveTables<T>& t1, hipStream_t st)
+unsigned plane_args(T* F, View3 fv, const SolveTables<T>& t2, const SolveTables<T>& t1, PlaneSolveArgs<T>& a)
 {
-    if (!solve_plane_fits<T>(fv, t2, t1)) return hipErrorNotSupported;
-    PlaneSolveArgs<T> a;
     a.F = F;
     a.n1 = (int)fv.n[1];
     a.n2 = (int)fv.n[2];
@@ -681,11 +709,46 @@ hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const So
     a.tb[1] = t1;
     const int64_t tasks = std::max<int64_t>({t2.S * fv.n[1], t1.S * fv.n[2],
                                              (fv.n[1] * fv.n[2] + plane_batch<T>() - 1) / plane_batch<T>()});
-    const unsigned thr = (unsigned)std::min<int64_t>(kPlaneThreads, std::max<int64_t>(64, (tasks + 63) / 64 * 64));
+    return (unsigned)std::min<int64_t>(kPlaneThreads, std::max<int64_t>(64, (tasks + 63) / 64 * 64));
+}
+
+template <typename T>
+hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const SolveTables<T>& t1, hipStream_t st)
+{
+    if (!solve_plane_fits<T>(fv, t2, t1)) return hipErrorNotSupported;
+    PlaneSolveArgs<T> a;
+    const unsigned thr = plane_args<T>(F, fv, t2, t1, a);
     hipLaunchKernelGGL(k_solve_plane<T>, dim3((unsigned)fv.n[0]), dim3(thr), plane_solve_bytes<T>(fv), st, a);
     return hipGetLastError();
 }
 
+template <typename T>
+hipError_t launch_solve_plane_multi(T* const* F, const View3* fv, const SolveTables<T>* t2, const SolveTables<T>* t1,
+                                    int n, hipStream_t st)
+{
+    if (n < 1 || n > kMultiLevels) return hipErrorInvalidValue;
+    MultiPlane<T> m;
+    std::memset(&m, 0, sizeof(m));
+    m.n = n;
+    unsigned thr = 0;
+    size_t bytes = 0;
+    int tot = 0;
+    for (int i = 0; i < n; i++) {
+        if (!solve_plane_fits<T>(fv[i], t2[i], t1[i])) return hipErrorNotSupported;
+        thr = std::max(thr, plane_args<T>(F[i], fv[i], t2[i], t1[i], m.a[i]));
+        bytes = std::max(bytes, plane_solve_bytes<T>(fv[i]));
+        m.start[i] = tot;
+        tot += (int)fv[i].n[0];
+    }
+    for (int i = n; i <= kMultiLevels; i++) m.start[i] = tot;
+    hipLaunchKernelGGL(k_solve_plane_multi<T>, dim3((unsigned)tot), dim3(thr), bytes, st, m);
+    return hipGetLastError();
+}
+
+template hipError_t launch_solve_plane_multi<float>(float* const*, const View3*, const SolveTables<float>*,
+                                                    const SolveTables<float>*, int, hipStream_t);
+template hipError_t launch_solve_plane_multi<double>(double* const*, const View3*, const SolveTables<double>*,
+                                                     const SolveTables<double>*, int, hipStream_t);
 template bool solve_plane_fits<float>(View3, const SolveTables<float>&, const SolveTables<float>&);
 template bool solve_plane_fits<double>(View3, const SolveTables<double>&, const SolveTables<double>&);
 template hipError_t launch_solve_plane<float>(float*, View3, const SolveTables<float>&, const SolveTables<float>&,
