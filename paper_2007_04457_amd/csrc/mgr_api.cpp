@@ -1778,7 +1778,7 @@ int gen_correction(const GenPlan& p, int k, const T* y, hipStream_t st, T** zout
 // Plane form of level step k (4-D); plane4_plan: whether every level step of
 // the plan takes it (the planes only shrink from step to step, so the first
 // decides).  It is faster wherever it fits, so that LDS and index ranges are
-// the only limits: 40 x 50 x 60 x 70 FP64 both ways 529 us against 1925 us in
+// the only limits: 40 x 50 x 60 x 70 FP64 both ways 478 us against 1925 us in
 // the per-stage kernels.
 template <typename T>
 Plane4<T> plane4_level(const GenPlan& p, int k)
@@ -1807,37 +1807,43 @@ bool plane4_plan(const GenPlan& p)
     return p.n[2] * p.n[3] < (1 << 20) && plane4_fits<T>(plane4_level<T>(p, 0));
 }
 
-// Solves of level step k of a 4-D grid on F (packed mc): dims 3 and 2 of a
-// plane in one launch where it fits, then 1 and 0.
+// Load vector and solves of level step k of a 4-D grid from a.F (the stencils
+// along dims 3 and 2 done) to F (packed mc), in two launches where they fit.
 template <typename T>
-int plane4_solves(const GenPlan& p, int k, T* F, hipStream_t st)
+int plane4_correction(const GenPlan& p, int k, const Plane4<T>& a, T* F, hipStream_t st)
 {
     const GenLevelHost& ly = p.lv[(size_t)k];
     const T* tb = (const T*)p.tables;
-    auto tables = [&](int d) {
-        SolveTables<T> t;
-        const T** f[10] = {&t.L, &t.U, &t.IP, &t.A, &t.B, &t.ssub, &t.ssup, &t.sl, &t.sip, &t.su};
+    SolveTables<T> t[4];
+    for (int d = 0; d < 4; d++) {
+        const T** f[10] = {&t[d].L, &t[d].U, &t[d].IP, &t[d].A, &t[d].B, &t[d].ssub, &t[d].ssup, &t[d].sl, &t[d].sip, &t[d].su};
         for (int q = 0; q < 10; q++) *f[q] = tb + ly.solve[d][q];
-        t.S = ly.S[d];
-        t.dec = ly.dec[d];
-        return t;
-    };
-    const int64_t pn[3] = {ly.mc[0] * ly.mc[1], ly.mc[2], ly.mc[3]};
-    const View3 fv = packed(pn);
-    int last = 3;
-    if (solve_plane_fits<T>(fv, tables(3), tables(2))) {
-        MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_plane<T>(F, fv, tables(3), tables(2), st); }),
-                "plane solve launch");
-        last = 1;
+        t[d].S = ly.S[d];
+        t[d].dec = ly.dec[d];
     }
-    for (int d = last; d >= 0; d--) {
+    auto solve = [&](int d) -> int {
         int64_t inner = 1, outer = 1;
         for (int e = d + 1; e < 4; e++) inner *= ly.mc[e];
         for (int e = 0; e < d; e++) outer *= ly.mc[e];
         MGR_TRY(timed(KC_SOLVE, k, st,
-                      [&] { return launch_solve_fibres<T>(F, ly.mc[d], inner, outer, tables(d), (T*)p.ws + p.Yb, st); }),
+                      [&] { return launch_solve_fibres<T>(F, ly.mc[d], inner, outer, t[d], (T*)p.ws + p.Yb, st); }),
                 "solve launch");
+        return MGR_OK;
+    };
+    bool done = false;
+    int rc = MGR_OK;
+    MGR_TRY(timed(KC_STREAM_LOAD, k, st, [&] { return launch_mass_plane<T>(a.F, F, a, t[3], t[2], st, &done); }),
+            "load-vector launch");
+    if (!done) {
+        const int64_t pn[3] = {ly.mc[0] * ly.mc[1], ly.mc[2], ly.mc[3]};
+        if (solve_plane_fits<T>(packed(pn), t[3], t[2]))
+            MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_plane<T>(F, packed(pn), t[3], t[2], st); }),
+                    "plane solve launch");
+        else if ((rc = solve(3)) || (rc = solve(2)))
+            return rc;
     }
+    MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_cols<T>(F, a, t[1], t[0], st, &done); }), "solve launch");
+    if (!done && ((rc = solve(1)) || (rc = solve(0)))) return rc;
     return MGR_OK;
 }
 
@@ -1857,9 +1863,7 @@ int run_plane4_decompose(const GenPlan& p, const T* src, T* dst, hipStream_t st)
         a.out = dst;
         a.F = ws + p.A;
         MGR_TRY(timed(KC_COEF, k, st, [&] { return launch_plane4<T>(a, 0, st); }), "coefficient launch");
-        MGR_TRY(timed(KC_STREAM_LOAD, k, st, [&] { return launch_mass01<T>(a.F, ws + p.B, a, st); }),
-                "load-vector launch");
-        int rc = plane4_solves<T>(p, k, ws + p.B, st);
+        const int rc = plane4_correction<T>(p, k, a, ws + p.B, st);
         if (rc) return rc;
     }
     const GenLevel<T> aL = gen_level<T>(p, L);
@@ -1887,9 +1891,7 @@ int run_plane4_recompose(const GenPlan& p, const T* src, T* dst, hipStream_t st)
         a.out = (k == 0) ? dst : ws + p.Woff[(size_t)k];
         a.F = ws + p.A;
         MGR_TRY(timed(KC_STREAM_LOAD, k, st, [&] { return launch_plane4<T>(a, 1, st); }), "load-vector launch");
-        MGR_TRY(timed(KC_STREAM_LOAD, k, st, [&] { return launch_mass01<T>(a.F, ws + p.B, a, st); }),
-                "load-vector launch");
-        int rc = plane4_solves<T>(p, k, ws + p.B, st);
+        const int rc = plane4_correction<T>(p, k, a, ws + p.B, st);
         if (rc) return rc;
         MGR_TRY(timed(KC_INTERP, k, st, [&] { return launch_plane4<T>(a, 2, st); }), "interpolation launch");
     }

@@ -583,9 +583,16 @@ bool plane4_fits(const Plane4<T>& a);
 // recomposition.
 template <typename T>
 hipError_t launch_plane4(const Plane4<T>& a, int mode, hipStream_t st);
-// Stencils along dims 1 and 0 of F: out packed (mc0, mc1, mc2, mc3).
+// Stencils along dims 1 and 0 of F (out packed (mc0, mc1, mc2, mc3)) and, where a
+// plane's tasks and nodes fit a workgroup (*done), the solves along dims 3 and 2.
 template <typename T>
-hipError_t launch_mass01(const T* in, T* out, const Plane4<T>& a, hipStream_t st);
+hipError_t launch_mass_plane(const T* in, T* out, const Plane4<T>& a, const SolveTables<T>& t3, const SolveTables<T>& t2,
+                             hipStream_t st, bool* done);
+// Solves along dims 1 and 0 of F, where their tasks fit a workgroup (*done; else
+// nothing is launched).
+template <typename T>
+hipError_t launch_solve_cols(T* F, const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0, hipStream_t st,
+                             bool* done);
 
 // Partitioned solve of every fibre of length n along the middle index of a
 // packed (outer, n, inner) box; src and Yb as for launch_solve_partitioned.

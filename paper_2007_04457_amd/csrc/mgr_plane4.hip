@@ -12,18 +12,21 @@
 //                   packed (m0, m1, mc2, mc3);
 //   load vector     the same stencils on stored coefficients;
 //   recomposition   coefficients plus Pi Q, Q from the corrected coarse values.
-// The stencils along dims 1 and 0 follow in one pass over that quarter
-// (k_mass01: 25 inputs per output, all but the first read of each from the
-// caches), then the solves.  A correction is never added in a pass of its own:
-// the next level step reads W + Z.
+// The stencils along dims 1 and 0 follow on that quarter (25 inputs per output,
+// all but the first read of each from the caches), a workgroup per coarse plane,
+// which solves dims 3 and 2 of its plane in LDS before it stores it
+// (k_mass_plane); the solves along dims 1 and 0 run on column tiles in LDS
+// (k_solve_cols).  Sizes that do not fit those take the stencils and the solves
+// one by one.  A correction is never added in a pass of its own: the next level
+// step reads W + Z.
 //
-// Bound by memory at the finest step, by launches below it: five per level
-// step.  40 x 50 x 60 x 70 FP64 nonuniform decomposed and recomposed in
-// 529 us (61, 34 and 41 us the plane passes of the finest step), against 1925 us with a thread per node, 64-bit index divisions, up to
+// Bound by memory at the finest step, by launches below it: three per level
+// step of a decomposition.  40 x 50 x 60 x 70 FP64 nonuniform decomposed and recomposed in
+// 478 us (62, 33 and 40 us the plane passes of the finest step), against 1925 us with a thread per node, 64-bit index divisions, up to
 // sixteen corner reads per node and ten launches per level step.
 #include <algorithm>
 
-#include "mgr_internal.h"
+#include "mgr_solve_dev.h"
 
 namespace mgr {
 namespace {
@@ -232,31 +235,135 @@ __global__ void __launch_bounds__(kPlane4Threads) k_plane4(Plane4<T> a)
     }
 }
 
-// Stencils along dims 1 and 0: out (mc0, mc1, R) from in (m0, m1, R), R
-// contiguous; workgroup (x, i0 mc1 + i1).
+// Stencils along dims 1 and 0 of in (m0, m1, R) at coarse (i0, i1), element r.
+template <typename T>
+__device__ __forceinline__ T mass01_at(const T* __restrict__ in, const Plane4<T>& a, int R, int i0, int i1, int r)
+{
+    const int m0 = a.m[0], m1 = a.m[1];
+    const int f0 = level_of(i0, m0, a.mc[0]), f1 = level_of(i1, m1, a.mc[1]);
+    // (all 25 loads at once, at clamped indices; outside the grid K is zero)
+    T v[5][5];
+#pragma unroll
+    for (int s = 0; s < 5; s++)
+#pragma unroll
+        for (int t = 0; t < 5; t++) {
+            const int c0 = min(max(f0 - 2 + s, 0), m0 - 1), c1 = min(max(f1 - 2 + t, 0), m1 - 1);
+            v[s][t] = in[((int64_t)c0 * m1 + c1) * R + r];
+        }
+    T acc = T(0);
+#pragma unroll
+    for (int s = 0; s < 5; s++) {
+        T t5 = T(0);
+#pragma unroll
+        for (int t = 0; t < 5; t++) {
+            const bool in1 = f1 - 2 + t >= 0 && f1 - 2 + t < m1;
+            t5 = fma(in1 ? a.K[1][5 * i1 + t] : T(0), v[s][t], t5);
+        }
+        const bool in0 = f0 - 2 + s >= 0 && f0 - 2 + s < m0;
+        acc = fma(in0 ? a.K[0][5 * i0 + s] : T(0), t5, acc);
+    }
+    return acc;
+}
+
+// out (mc0, mc1, R), R contiguous; workgroup (x, i0 mc1 + i1).
 template <typename T>
 __global__ void __launch_bounds__(256) k_mass01(const T* __restrict__ in, T* __restrict__ out, Plane4<T> a, int R, int nx)
 {
     const int b = (int)blockIdx.x / nx, r = ((int)blockIdx.x - b * nx) * 256 + (int)threadIdx.x;
-    const int m0 = a.m[0], m1 = a.m[1], mc0 = a.mc[0], mc1 = a.mc[1];
-    const int i0 = b / mc1, i1 = b - i0 * mc1;
     if (r >= R) return;
-    const int f0 = level_of(i0, m0, mc0), f1 = level_of(i1, m1, mc1);
-    T acc = T(0);
-    for (int s = 0; s < 5; s++) {
-        const int c0 = f0 - 2 + s;
-        if (c0 < 0 || c0 >= m0) continue;
-        T t5 = T(0);
+    const int i0 = b / a.mc[1], i1 = b - i0 * a.mc[1];
+    out[(int64_t)b * R + r] = mass01_at(in, a, R, i0, i1, r);
+}
+
+// LDS of the plane solves: tables of two dimensions, segment ends, the nodes.
+constexpr int kTab4 = 5 * kMaxSegWG * kSlot, kSep4 = 5 * kMaxSegWG;
+template <typename T>
+size_t solve4_bytes(int64_t nodes)
+{
+    return sizeof(T) * (size_t)(2 * kTab4 + 2 * kSep4 + 2 * kPlaneThreads + nodes);
+}
+template <typename T>
+__device__ __forceinline__ void stage4(T* lds, const SolveTables<T> (&tb)[2], int tid, int nthr)
+{
 #pragma unroll
-        for (int t = 0; t < 5; t++) {
-            const int c1 = f1 - 2 + t;
-            const bool ok = c1 >= 0 && c1 < m1;
-            const T v = in[((int64_t)c0 * m1 + (ok ? c1 : f1)) * R + r];
-            t5 = fma(ok ? a.K[1][5 * i1 + t] : T(0), v, t5);
+    for (int d = 0; d < 2; d++)
+        stage_tables(tb[d], 0, tb[d].S, tid, nthr, *reinterpret_cast<T(*)[5][kMaxSegWG * kSlot]>(lds + d * kTab4),
+                     *reinterpret_cast<T(*)[5][kMaxSegWG]>(lds + 2 * kTab4 + d * kSep4));
+}
+
+template <typename T>
+struct Tables2 {
+    SolveTables<T> tb[2];
+};
+
+// Stencils along dims 1 and 0 of one coarse plane, then the solves of its dims 3
+// and 2 (tb[0], tb[1]): workgroup i0 mc1 + i1.
+template <typename T>
+__global__ void __launch_bounds__(kPlaneThreads)
+k_mass_plane(const T* __restrict__ in, T* __restrict__ out, Plane4<T> a, Tables2<T> t)
+{
+    T* const lds = reinterpret_cast<T*>(plane4_lds);
+    T* const sep = lds + 2 * kTab4;
+    T* const end = sep + 2 * kSep4;
+    T* const P = end + 2 * kPlaneThreads;
+    const int tid = threadIdx.x, nthr = blockDim.x, b = (int)blockIdx.x;
+    const int n2 = a.mc[2], n3 = a.mc[3], R = n2 * n3, i0 = b / a.mc[1], i1 = b - i0 * a.mc[1];
+    stage4(lds, t.tb, tid, nthr);
+    for (int r = tid; r < R; r += nthr) P[r] = mass01_at(in, a, R, i0, i1, r);
+    __syncthreads();
+#pragma unroll 1
+    for (int d = 0; d < 2; d++)
+        plane_dim<false>(P, end, end + kPlaneThreads, lds + d * kTab4, sep + d * kSep4, d ? n2 : n3, t.tb[d].S, d ? n3 : n2,
+                         d ? n3 : 1, d ? 1 : n3, 1, 0, tid, t.tb[d].dec);
+    for (int r = tid; r < R; r += nthr) out[(int64_t)b * R + r] = P[r];
+}
+
+// Solves along dims 1 and 0 (tb[0], tb[1]) of F (n0, n1, R): a workgroup takes
+// kCols elements of R.
+template <typename T>
+constexpr int kCols = 64 / (int)sizeof(T);
+template <typename T>
+__global__ void __launch_bounds__(kPlaneThreads) k_solve_cols(T* F, int n0, int n1, int R, Tables2<T> t)
+{
+    constexpr int C = kCols<T>;
+    T* const lds = reinterpret_cast<T*>(plane4_lds);
+    T* const sep = lds + 2 * kTab4;
+    T* const end = sep + 2 * kSep4;
+    T* const P = end + 2 * kPlaneThreads;
+    const int tid = threadIdx.x, nthr = blockDim.x, r0 = (int)blockIdx.x * C, V = n0 * n1 * C;
+    // node (i0, i1, r) at P[(i0 n1 + i1) C + r]; columns past R repeat its last one
+    // and are not stored
+    for (int b0 = 0; b0 < V; b0 += 8 * nthr) {
+        T v[8];
+#pragma unroll
+        for (int q = 0; q < 8; q++) {
+            const int e = min(b0 + q * nthr + tid, V - 1);
+            v[q] = F[(int64_t)(e / C) * R + min(r0 + e % C, R - 1)];
         }
-        acc = fma(a.K[0][5 * i0 + s], t5, acc);
+        if (b0 == 0) stage4(lds, t.tb, tid, nthr);
+#pragma unroll
+        for (int q = 0; q < 8; q++)
+            if (b0 + q * nthr + tid < V) P[b0 + q * nthr + tid] = v[q];
     }
-    out[(int64_t)b * R + r] = acc;
+    __syncthreads();
+#pragma unroll 1
+    for (int d = 0; d < 2; d++)
+        plane_dim<true>(P, end, end + kPlaneThreads, lds + d * kTab4, sep + d * kSep4, d ? n0 : n1, t.tb[d].S,
+                        (d ? n1 : n0) * C, d ? n1 * C : C, 1, d ? n1 * C : C, d ? 0 : n1 * C, tid, t.tb[d].dec);
+    for (int e = tid; e < V; e += nthr)
+        if (r0 + e % C < R) F[(int64_t)(e / C) * R + r0 + e % C] = P[e];
+}
+
+// Two solves of n nodes each, of nfa and nfb fibres, as plane_dim's tasks: their
+// lanes, or 0 where they do not fit.
+template <typename T>
+int solve4_lanes(const SolveTables<T>& ta, int64_t na, int64_t nfa, const SolveTables<T>& tb, int64_t nb, int64_t nfb,
+                 int64_t nodes)
+{
+    if (ta.S < 1 || tb.S < 1 || ta.S > kMaxSegWG || tb.S > kMaxSegWG || na < 2 || nb < 2) return 0;
+    const int64_t tasks = std::max<int64_t>(ta.S * nfa, tb.S * nfb);
+    if (tasks > kPlaneThreads || solve4_bytes<T>(nodes) > (size_t)kPlane4Lds) return 0;
+    return (int)((tasks + 63) / 64 * 64);
 }
 
 template <typename T>
@@ -265,23 +372,28 @@ size_t plane4_bytes(const Plane4<T>& a)
     return sizeof(T) * ((size_t)a.m[2] * a.m[3] + 2 * ((size_t)a.m[2] + a.m[3]) + (size_t)a.m[2] * a.mc[3]);
 }
 
+// LDS beyond 64 KB has to be asked for once per kernel and device.
+template <typename K>
+hipError_t allow_lds4(K kern, size_t bytes, bool (&done)[64])
+{
+    if (bytes <= 65536) return hipSuccess;
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
+    if (done[dev]) return hipSuccess;
+    e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kPlane4Lds);
+    if (e == hipSuccess) done[dev] = true;
+    return e;
+}
+
 template <typename T, int kMode>
 hipError_t launch_mode(const Plane4<T>& a, hipStream_t st)
 {
     const size_t bytes = plane4_bytes(a);
     static bool done[64] = {};
-    if (bytes > 65536) {
-        int dev = 0;
-        hipError_t e = hipGetDevice(&dev);
-        if (e != hipSuccess) return e;
-        if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-        if (!done[dev]) {
-            e = hipFuncSetAttribute((const void*)k_plane4<T, kMode>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    kPlane4Lds);
-            if (e != hipSuccess) return e;
-            done[dev] = true;
-        }
-    }
+    const hipError_t e = allow_lds4(k_plane4<T, kMode>, bytes, done);
+    if (e != hipSuccess) return e;
     // a few nodes a lane, so that the loads of a plane are in flight together
     const int V = a.m[2] * a.m[3];
     const unsigned thr = V <= 128 ? 64 : V <= 1024 ? 256 : kPlane4Threads;
@@ -306,11 +418,61 @@ hipError_t launch_plane4(const Plane4<T>& a, int mode, hipStream_t st)
     return mode == 0 ? launch_mode<T, 0>(a, st) : mode == 1 ? launch_mode<T, 1>(a, st) : launch_mode<T, 2>(a, st);
 }
 
+// Stencils along dims 1 and 0 alone.
 template <typename T>
-hipError_t launch_mass01(const T* in, T* out, const Plane4<T>& a, hipStream_t st)
+static hipError_t launch_mass01(const T* in, T* out, const Plane4<T>& a, hipStream_t st)
 {
     const int R = a.mc[2] * a.mc[3], nx = (R + 255) / 256;
     hipLaunchKernelGGL(k_mass01<T>, dim3((unsigned)((int64_t)a.mc[0] * a.mc[1] * nx)), dim3(256), 0, st, in, out, a, R, nx);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_mass_plane(const T* in, T* out, const Plane4<T>& a, const SolveTables<T>& t3, const SolveTables<T>& t2,
+                             hipStream_t st, bool* done_)
+{
+    const int64_t n2 = a.mc[2], n3 = a.mc[3];
+    // (with more planes than CUs the stencils' own launch, of many more waves, is
+    // faster: 546 planes of 31 x 36 FP64 16 + 20 us against 42 together; 12 of 8 x 9
+    // 13 against 10)
+    const int lanes = a.mc[0] * a.mc[1] > device_cu_count() ? 0 : solve4_lanes<T>(t3, n3, n2, t2, n2, n3, n2 * n3);
+    *done_ = lanes > 0;
+    if (lanes == 0) return launch_mass01<T>(in, out, a, st);
+    static bool done[64] = {};
+    const size_t bytes = solve4_bytes<T>(n2 * n3);
+    const hipError_t e = allow_lds4(k_mass_plane<T>, bytes, done);
+    if (e != hipSuccess) return e;
+    // (two or three stencils a lane)
+    const int64_t want = (n2 * n3 / 3 + 63) / 64 * 64;
+    const unsigned thr = (unsigned)std::min<int64_t>(kPlaneThreads, std::max<int64_t>(lanes, want));
+    Tables2<T> t;
+    t.tb[0] = t3;
+    t.tb[1] = t2;
+    hipLaunchKernelGGL(k_mass_plane<T>, dim3((unsigned)(a.mc[0] * a.mc[1])), dim3(thr), bytes, st, in, out, a, t);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_solve_cols(T* F, const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0, hipStream_t st,
+                             bool* done_)
+{
+    const int64_t n0 = a.mc[0], n1 = a.mc[1], nodes = n0 * n1 * kCols<T>;
+    const int lanes = a.mc[0] * a.mc[1] > device_cu_count()
+                          ? 0
+                          : solve4_lanes<T>(t1, n1, n0 * kCols<T>, t0, n0, n1 * kCols<T>, nodes);
+    *done_ = lanes > 0;
+    if (lanes == 0) return hipSuccess;
+    static bool done[64] = {};
+    const size_t bytes = solve4_bytes<T>(nodes);
+    const hipError_t e = allow_lds4(k_solve_cols<T>, bytes, done);
+    if (e != hipSuccess) return e;
+    const int R = a.mc[2] * a.mc[3];
+    const unsigned thr = (unsigned)std::min<int64_t>(kPlaneThreads, std::max<int64_t>(lanes, (nodes / 8 + 63) / 64 * 64));
+    Tables2<T> t;
+    t.tb[0] = t1;
+    t.tb[1] = t0;
+    hipLaunchKernelGGL(k_solve_cols<T>, dim3((unsigned)((R + kCols<T> - 1) / kCols<T>)), dim3(thr), bytes, st, F, (int)n0,
+                       (int)n1, R, t);
     return hipGetLastError();
 }
 
@@ -318,7 +480,13 @@ template bool plane4_fits<float>(const Plane4<float>&);
 template bool plane4_fits<double>(const Plane4<double>&);
 template hipError_t launch_plane4<float>(const Plane4<float>&, int, hipStream_t);
 template hipError_t launch_plane4<double>(const Plane4<double>&, int, hipStream_t);
-template hipError_t launch_mass01<float>(const float*, float*, const Plane4<float>&, hipStream_t);
-template hipError_t launch_mass01<double>(const double*, double*, const Plane4<double>&, hipStream_t);
+template hipError_t launch_mass_plane<float>(const float*, float*, const Plane4<float>&, const SolveTables<float>&,
+                                             const SolveTables<float>&, hipStream_t, bool*);
+template hipError_t launch_mass_plane<double>(const double*, double*, const Plane4<double>&, const SolveTables<double>&,
+                                              const SolveTables<double>&, hipStream_t, bool*);
+template hipError_t launch_solve_cols<float>(float*, const Plane4<float>&, const SolveTables<float>&,
+                                             const SolveTables<float>&, hipStream_t, bool*);
+template hipError_t launch_solve_cols<double>(double*, const Plane4<double>&, const SolveTables<double>&,
+                                              const SolveTables<double>&, hipStream_t, bool*);
 
 }  // namespace mgr

@@ -254,10 +254,6 @@ __global__ void __launch_bounds__(kSmallThreads) k_solve_small(SmallSolveArgs<T>
     }
 }
 
-// Largest plane-solve workgroup: ten waves, so that the compiler may give a
-// lane up to 168 registers (the FP64 kernel spilled at the 128 of 16 waves).
-constexpr int kPlaneThreads = 640;
-
 // Dimensions 2 and then 1 of a coarse grid whose planes (a fixed index along
 // dim 0) fit in LDS: one workgroup per plane stages it, solves every row and
 // then every column in LDS with the partitioned arithmetic of the
@@ -284,59 +280,6 @@ struct PlaneSolveArgs {
     int n1, n2;
     SolveTables<T> tb[2];  // dimension 2, dimension 1
 };
-
-template <typename T>
-__device__ __forceinline__ void plane_dim(T* P, T* end0, T* end1, const T* tab, const T* septab, int n, int S,
-                                          int nf, int sd, int sf, int tid, int dec)
-{
-    // task tid: segment s of fibre f; fibre f starts at P[f sf], node i of it
-    // is at P[f sf + i sd]
-    const bool active = tid < S * nf;
-    const int s = active ? tid / nf : 0, f = active ? tid % nf : 0;
-    FibreMap m;
-    m.n = n;
-    m.S = S;
-    int lo, len;
-    seg_range(m, s, lo, len);
-    // node lo + q, clamped to the segment's last
-    T* const p = P + f * sf;
-    T* const p0 = p + __mul24(lo, sd);
-    T v[kSlot];
-#pragma unroll
-    for (int q = 0; q < kSlot; q++) v[q] = p0[__mul24(min(q, len - 1), sd)];
-    seg_solve(v, tab + 0 * kMaxSegWG * kSlot + s * kSlot, tab + 1 * kMaxSegWG * kSlot + s * kSlot,
-              tab + 2 * kMaxSegWG * kSlot + s * kSlot);
-    if (active) {
-        end0[s * nf + f] = v[0];
-        end1[s * nf + f] = seg_last(v, s);
-    }
-    __syncthreads();
-    if (!dec) {
-        if (active && s == 0 && S > 1)
-            sep_solve(S, p, (int64_t)kSeg * sd, end0 + f, end1 + f, nf, septab + 0 * kMaxSegWG,
-                      septab + 1 * kMaxSegWG, septab + 2 * kMaxSegWG, septab + 3 * kMaxSegWG, septab + 4 * kMaxSegWG);
-        __syncthreads();
-    }
-    // read without a condition, indices clamped to a separator there is
-    auto sep = [&](int k) {
-        const int kc = min(max(k, S > 1 ? 1 : 0), S - 1), km = max(kc - 1, 0);
-        const T z = p[(kc * kSeg) * sd];
-        const T w = sep_alone(z, septab[0 * kMaxSegWG + kc], end1[km * nf + f], septab[1 * kMaxSegWG + kc],
-                              end0[kc * nf + f], septab[3 * kMaxSegWG + kc]);
-        return dec ? w : z;
-    };
-    const T sl = sep(s), sr = sep(s + 1);
-    const T zl = (s > 0) ? sl : T(0), zr = (s < S - 1) ? sr : T(0);
-    __syncthreads();  // every task has read its separators
-    if (active) {
-        // slots past the segment go to its last node, before that node's own
-        // value (a store each, without a condition)
-        seg_finals(v, tab + 3 * kMaxSegWG * kSlot + s * kSlot, zl, tab + 4 * kMaxSegWG * kSlot + s * kSlot, zr,
-                   [&](int q, T x) { p0[__mul24(min(q, len - 1), sd)] = x; });
-        if (s > 0) p[(s * kSeg) * sd] = zl;
-    }
-    __syncthreads();
-}
 
 extern __shared__ __align__(16) unsigned char plane_lds[];
 
@@ -373,8 +316,8 @@ __device__ __forceinline__ void plane_body(const PlaneSolveArgs<T>& a, int plane
     // its instruction fetches.
 #pragma unroll 1
     for (int d = 0; d < 2; d++)
-        plane_dim(P, end, end + kPlaneThreads, tab + d * TAB, septab + d * SEP, d ? n1 : n2, a.tb[d].S, d ? n2 : n1,
-                  d ? n2 : 1, d ? 1 : n2, tid, a.tb[d].dec);
+        plane_dim<false>(P, end, end + kPlaneThreads, tab + d * TAB, septab + d * SEP, d ? n1 : n2, a.tb[d].S,
+                         d ? n2 : n1, d ? n2 : 1, d ? 1 : n2, 1, 0, tid, a.tb[d].dec);
     // (the reads of a batch ahead of its stores)
     for (int b0 = 0; b0 < V; b0 += 8 * nthr) {
         T o[8];
