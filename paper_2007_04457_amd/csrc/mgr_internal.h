@@ -114,10 +114,13 @@ struct SolveTables {
 // strided) whose separators do not couple; S: the fibre is not split.  Up to
 // 16 segments share a workgroup's LDS tables; a longer fibre is cut into
 // chunks of 16, or of 128 where there are too few contiguous fibres to fill a
-// workgroup with 16-segment pieces (1-D problems).
+// workgroup with 16-segment pieces (1-D problems).  Up to 256 rows of up to 64
+// segments stay whole: a workgroup each on a CU of its own, in one launch
+// instead of two (65 x 4097 FP32, three steps decomposed: split 70 us, whole 59).
 __host__ __device__ inline int solve_chunk_segs(int S, int64_t inner, int64_t nfib)
 {
     if (S <= 16) return S;
+    if (inner == 1 && nfib <= 256 && S <= 64) return S;
     if (inner == 1 && nfib < 16) return S < 128 ? S : 128;
     return 16;
 }
