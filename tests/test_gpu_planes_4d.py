@@ -1,7 +1,8 @@
 """Four-dimensional grids by planes of the last two dimensions against the CPU
 FP64 oracle: even and odd lengths in every dimension, planes of one wave and
 of several, long last dimensions (chunked solves), planes above 64 KB of LDS,
-a plane too large for LDS (a thread per node), each number of levels.
+a plane too large for LDS (a thread per node), more planes than CUs, each
+number of levels.
 
 Tolerances (max |gpu - oracle| / max |input|): 1e-12 in float64, 2e-5 in
 float32, as for the other grids.
@@ -20,7 +21,7 @@ TOL = {torch.float64: 1e-12, torch.float32: 2e-5}
 
 SHAPES = [(3, 3, 3, 3), (4, 3, 4, 3), (3, 4, 3, 4), (4, 4, 4, 4), (5, 6, 7, 8), (8, 7, 6, 5), (9, 10, 12, 11),
           (10, 9, 11, 12), (3, 20, 4, 33), (17, 4, 40, 5), (6, 5, 8, 16), (5, 6, 3, 700), (4, 5, 90, 91),
-          (3, 4, 150, 140)]
+          (3, 4, 150, 140), (33, 34, 5, 6)]
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])
