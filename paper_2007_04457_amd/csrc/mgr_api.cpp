@@ -53,6 +53,7 @@ struct LevelLayout {
     size_t w[3], K[3];
     size_t PT[3];  // P^T as a 5-point row per coarse node (transposed interpolation)
     bool tail;  // the level may join the tail
+    bool few;   // a dimension has fewer than 32 fibres in the tail's reductions
     size_t L[3], U[3], IP[3], A[3], B[3], ssub[3], ssup[3], sl[3], sip[3], su[3];
     int S[3], dec[3];
 };
@@ -583,9 +584,15 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             ly.ph[d] = (ly.m[d] != act) ? (int)act - 1 : -1;
             ly.tail = ly.tail && ly.m[d] <= kTailMaxSide;
         }
+        ly.few = false;
+        for (int d = 0; d < 3; d++) {
+            int64_t fibres = 1;
+            for (int e = 0; e < 3; e++) fibres *= (e < d) ? ly.m[e] : (e > d) ? ly.mc[e] : 1;
+            ly.few = ly.few || (ly.m[d] > 1 && fibres < 32);
+        }
         // every coarser level is in it too
         ly.tail = ly.tail && (k == L - 1 || p.lv[(size_t)(k + 1)].tail) &&
-                  (small += tail_data_elems(ly)) <= kTailDataElems;
+                  (small += tail_data_elems(ly)) * (int64_t)sizeof(T) <= kTailDataBytes;
     }
     std::vector<double> tail_tab, adj_tab;
     p.tails.assign((size_t)L, TailLevel{});
@@ -1036,7 +1043,12 @@ int identity_copy(const Plan& p, const void* src, void* dst, hipStream_t st)
 std::atomic<int64_t> g_tail_nodes{kTailMaxNodes};
 
 // First level step handled by the tail kernel: the finest step such that it
-// and every coarser step are small, at most kMaxTail steps.
+// and every coarser step are small, at most kMaxTail steps.  Up to 10000 nodes
+// (and the LDS) one workgroup is faster than the launches it replaces, and a
+// recomposition that it holds whole forks no stream: 17 x 17 x 33 FP32 decomposed
+// in 27 -> 22 us, recomposed in 48 -> 22, 18 x 18 x 17 28 -> 19 and 47 -> 20.  A
+// dimension of fewer than 32 fibres takes its dot products one output a lane,
+// so such grids stop at half of it (257 x 33: 32 us in launches, 63 so).
 int tail_start(const Plan& p)
 {
     const int L = p.nlevels;
@@ -1044,7 +1056,7 @@ int tail_start(const Plan& p)
     int k = L;
     while (k > 0) {
         const LevelLayout& ly = p.lv[(size_t)(k - 1)];
-        if (!ly.tail || ly.m[0] * ly.m[1] * ly.m[2] > limit) break;
+        if (!ly.tail || ly.m[0] * ly.m[1] * ly.m[2] > (ly.few ? limit / 2 : limit)) break;
         k--;
     }
     return k;

@@ -150,13 +150,13 @@ hipError_t launch_solve_plane(T* F, View3 fv, const SolveTables<T>& t2, const So
 
 // Single-workgroup kernel for the small coarse levels (mgr_tail.hip): all
 // level steps k0 .. k0 + nlev - 1 in one launch, in LDS.  The levels' arrays
-// (tail_data_elems) must fit kTailDataElems elements; the tables share the LDS
+// (tail_data_elems) must fit kTailDataBytes bytes; the tables share the LDS
 // when both fit kTailLdsBytes, else they are read from global memory.
 constexpr int kTailThreads = 1024;
 constexpr int kMaxTail = 16;
-constexpr int64_t kTailMaxNodes = 5000;
+constexpr int64_t kTailMaxNodes = 10000;
 constexpr int kTailMaxSide = 513;  // longest dimension of a level grid (its tables' rows)
-constexpr int kTailDataElems = 17000;
+constexpr int kTailDataBytes = 17000 * 8;
 constexpr int kTailLdsBytes = 18400 * 8;
 
 // A level's description, in device memory beside its tables (kernel arguments

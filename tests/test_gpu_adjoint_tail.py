@@ -22,7 +22,8 @@ TOL = {torch.float64: 1e-12, torch.float32: 2e-5}
 
 SHAPES = [(3,), (5,), (9,), (33,), (257,), (513,), (1025,), (3, 3), (3, 5), (5, 3), (9, 33), (33, 9), (65, 65), (3, 513),
           (513, 3), (257, 17), (2049, 5), (5, 2049), (3, 3, 3), (5, 3, 9), (3, 65, 3), (9, 9, 9), (17, 17, 17),
-          (5, 129, 5), (65, 5, 9), (9, 17, 33), (33, 33, 33), (129, 9, 17), (17, 65, 129), (1025, 5, 9)]
+          (5, 129, 5), (65, 5, 9), (9, 17, 33), (33, 33, 33), (129, 9, 17), (17, 65, 129), (1025, 5, 9), (17, 17, 33), (129, 65),
+          (257, 33)]
 
 
 @pytest.mark.parametrize("dt", [torch.float32, torch.float64], ids=["f32", "f64"])

@@ -24,6 +24,7 @@ TOL = {torch.float64: 1e-12, torch.float32: 2e-5}
 SHAPES = [
     (4, 4, 4), (3, 4, 6), (6, 3, 4), (4, 6, 3), (7, 8, 9), (16, 16, 16), (17, 18, 62), (18, 17, 61), (34, 32, 64),
     (33, 34, 66), (5, 16, 124), (12, 48, 126), (40, 66, 65), (66, 33, 254), (20, 130, 70), (130, 6, 10),
+    (18, 18, 17), (19, 19, 19), (21, 21, 21),
     (4, 4), (3, 6), (6, 3), (17, 252), (40, 254), (130, 256), (257, 258), (600, 50), (50, 600),
     (4,), (6,), (7,), (64,), (254,), (255,), (1030,), (5000,),
 ]
