@@ -117,6 +117,14 @@ __device__ __forceinline__ void seg_finals(T (&v)[kSlot], const T* ta, T zl, con
     }
 }
 
+// A separator whose neighbours' terms are below the working precision
+// (SolveTables::dec).
+template <typename T>
+__device__ __forceinline__ T sep_alone(T f, T sub, T ylast, T sup, T yfirst, T ip)
+{
+    return sep_rhs(f, sub, ylast, sup, yfirst) * ip;
+}
+
 // Separator system of one fibre from the separator f values (in sep[], which
 // receives z) and the segment-end values; coefficient tables per separator.
 template <typename T>
@@ -150,14 +158,6 @@ struct StridedSmem {
     T end[2][kMaxSegWG * 64];     // y at the two ends of each segment [s][j]
     T sep[kMaxSegWG * 64];        // f, then z, at each separator [s][j]
 };
-
-// A separator whose neighbours' terms are below the working precision
-// (SolveTables::dec).
-template <typename T>
-__device__ __forceinline__ T sep_alone(T f, T sub, T ylast, T sup, T yfirst, T ip)
-{
-    return sep_rhs(f, sub, ylast, sup, yfirst) * ip;
-}
 
 // s: the lane's segment within the workgroup, of the ns segments s0 .. s0 +
 // ns - 1 (a whole fibre, or a chunk of one whose separators do not couple:
@@ -650,6 +650,14 @@ __device__ __forceinline__ void separators_tile(T* __restrict__ F, const T* __re
     T* p = F + o * m.n * m.inner + in;
     const int64_t ys = (m.inner > 1) ? 2 * m.nfib : 2;
     const T* y0 = Yb + yb_index(m, fib, 0);
+    if (tb.dec) {
+        // (the batch's rows that are too long for its staging and too few for
+        // chunks: the values of the kernels that keep such a row whole)
+        const int64_t ps = (int64_t)kSeg * m.inner;
+        for (int k = 1; k < m.S; k++)
+            p[k * ps] = sep_alone(p[k * ps], tb.ssub[k], y0[1 + (k - 1) * ys], tb.ssup[k], y0[k * ys], tb.sip[k]);
+        return;
+    }
     sep_solve(m.S, p, (int64_t)kSeg * m.inner, y0, y0 + 1, ys, tb.ssub, tb.ssup, tb.sl, tb.sip, tb.su);
 }
 
