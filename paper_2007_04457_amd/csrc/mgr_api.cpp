@@ -1247,15 +1247,20 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     // stream: it needs no auxiliary stream to exist.
     hipStream_t sc = st;  // the stream of the tail
     const bool shared = recompose_shared<T>(p, kt);
-    const bool fork = kt > 0 && !(p.gen && capturing(st));
-    if (fork) {
-        if (!aux_ready() && capturing(st))
-            return fail(MGR_ERR_CAPTURE, "auxiliary streams not created and the stream is capturing; call mgr_prepare first");
+    const bool aux_use = kt > 0 && !(p.gen && capturing(st));
+    if (aux_use && !aux_ready() && capturing(st))
+        return fail(MGR_ERR_CAPTURE, "auxiliary streams not created and the stream is capturing; call mgr_prepare first");
+    // A fork costs the host two events and two waits: where there is no tail
+    // (the coarsest values are one short gather) and a single correction there
+    // is nothing to run beside the caller's chain (1000 nodes, one level step:
+    // 49 us with both streams, 21 without).
+    const bool fork = aux_use && kt < L, fork0 = aux_use && !shared && (kt > 1 || fork);
+    if (fork || fork0) {
         MGR_TRY(aux_stream(&aux), "auxiliary stream");
         MGR_TRY(hipEventRecord(aux->start, st), "fork event");
-        if (!shared) MGR_TRY(hipStreamWaitEvent(aux->sr, aux->start, 0), "fork wait");
-        if (!shared) MGR_TRY(hipStreamWaitEvent(aux->s0, aux->start, 0), "fork wait");
-        sc = aux->sr;
+        if (fork && !shared) MGR_TRY(hipStreamWaitEvent(aux->sr, aux->start, 0), "fork wait");
+        if (fork0) MGR_TRY(hipStreamWaitEvent(aux->s0, aux->start, 0), "fork wait");
+        if (fork) sc = aux->sr;
     }
     // the coarsest values, up to the streamed steps' coarsest grid
     auto run_tail = [&]() -> int {
@@ -1275,21 +1280,22 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     };
     // (shared: the corrections are the longer chain and go first, so that they
     // start while the host is still forking: 65^3 FP64 63 -> 58 us)
-    if (!shared) {
+    const bool tail_first = kt == 0 || (fork && !shared);
+    if (tail_first) {
         const int rc = run_tail();
         if (rc) return rc;
     }
     if (kt > 0) {
         // one level step's correction on its own launches (the finest on s0)
         auto single = [&](int k) -> int {
-            hipStream_t sk = (k == 0 && fork && !shared) ? aux->s0 : st;
+            hipStream_t sk = (k == 0 && fork0) ? aux->s0 : st;
             View3 cv = level_view(p, k);
             T* z = ws + p.Zrec[(size_t)k];
             int rc = stream_level<T>(p, k, false, src, nullptr, cv, nullptr, cv, nullptr, false, sk, z);
             if (rc) return rc;
             rc = solve_all<T>(p, k, false, z, sk, (k == 0) ? ws + p.Yb : ws + p.Yb2, k == 0);
             if (rc) return rc;
-            if (k == 0 && fork && !shared) MGR_TRY(hipEventRecord(aux->done[0], sk), "level event");
+            if (k == 0 && fork0) MGR_TRY(hipEventRecord(aux->done[0], sk), "level event");
             return MGR_OK;
         };
         // the finest step's correction first (unless it joins the others), so
@@ -1365,7 +1371,7 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
             }
         }
         if ((rc = flush())) return rc;
-        if (shared && (rc = run_tail())) return rc;
+        if (!tail_first && (rc = run_tail())) return rc;
         // the coarsest values (tail) before the first interpolation
         if (fork) MGR_TRY(hipStreamWaitEvent(st, aux->rdone, 0), "tail wait");
     }
@@ -1373,7 +1379,7 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
         const LevelLayout& ly = p.lv[(size_t)k];
         View3 cv = level_view(p, k);
         hipStream_t sk = st;
-        if (k == 0 && fork && !shared) MGR_TRY(hipStreamWaitEvent(st, aux->done[0], 0), "join wait");  // the finest correction
+        if (k == 0 && fork0) MGR_TRY(hipStreamWaitEvent(st, aux->done[0], 0), "join wait");  // the finest correction
         StreamArgs<T> a;
         a.A = src;
         a.Z = ws + p.Zrec[(size_t)k];
