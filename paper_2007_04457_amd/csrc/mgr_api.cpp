@@ -1195,6 +1195,16 @@ bool aux_ready()
     return g_aux[dev].sr != nullptr;
 }
 
+// Whether they are part of a capture under way (on another thread's stream;
+// caller holds g_aux_mu): work launched on them now would be recorded there.
+bool aux_captured()
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return false;
+    const AuxStream& a = g_aux[dev];
+    return a.sr && (capturing(a.sr) || capturing(a.s0));
+}
+
 // Whether the finest level step's correction shares launches with the coarser
 // ones instead of running beside them on a stream of its own.  It does while
 // the problem is bound by the chain of launches (shared: four launches for the
@@ -1244,10 +1254,11 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     // another stream's event costs the waiting stream several microseconds
     // even when the event has long completed.
     // A captured recomposition of an any-length grid keeps to the caller's
-    // stream: it needs no auxiliary stream to exist.
+    // stream: it needs no auxiliary stream to exist.  So does one that is
+    // enqueued while another thread's capture holds those streams.
     hipStream_t sc = st;  // the stream of the tail
     const bool shared = recompose_shared<T>(p, kt);
-    const bool aux_use = kt > 0 && !(p.gen && capturing(st));
+    const bool aux_use = kt > 0 && !(p.gen && (capturing(st) || aux_captured()));
     if (aux_use && !aux_ready() && capturing(st))
         return fail(MGR_ERR_CAPTURE, "auxiliary streams not created and the stream is capturing; call mgr_prepare first");
     // A fork costs the host two events and two waits: where there is no tail

@@ -7,6 +7,8 @@ eager and replayed from a capture.
 Tolerances (max |gpu - oracle| / max |input|): 1e-12 in float64, 2e-5 in
 float32, as for the other grids.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -60,3 +62,47 @@ def test_streams(case):
     finally:
         if prev is not None:
             mgr.mgr_set_tail_max_nodes(prev)
+
+
+def test_any_length_while_another_thread_captures():
+    """A recomposition of a 2^k + 1 grid being captured holds the library's
+    streams until the capture ends; one of an any-length grid that another
+    thread enqueues meanwhile keeps to its own stream: it runs at once, and
+    the captured graph holds the captured call alone."""
+    dt = torch.float64
+    cap_shape, shape = (65, 65, 65), (40, 50, 44)
+    yc = torch.from_numpy(synth.sinusoid_field(cap_shape, 92)[0]).to(dt).to(DEV)
+    y = torch.from_numpy(synth.sinusoid_field(shape, 93)[0]).to(dt).to(DEV)
+    mgr.mgr_prepare(dt, cap_shape)
+    mgr.mgr_prepare(dt, shape)
+    want_c, want = mgr.recompose(yc), mgr.recompose(y)
+    out_c, out = torch.zeros_like(yc), torch.zeros_like(y)
+    other, st = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    errors = []
+
+    def eager():
+        try:
+            with torch.cuda.stream(other):
+                mgr.mgr_recompose(y, out)
+        except Exception as e:  # reported by the test's own thread
+            errors.append(e)
+
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(st):
+        with torch.cuda.graph(g, stream=st, capture_error_mode="thread_local"):
+            mgr.mgr_recompose(yc, out_c)
+            t = threading.Thread(target=eager)
+            t.start()
+            t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    assert torch.equal(out, want)
+    for _ in range(3):
+        out.zero_()
+        out_c.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out_c, want_c)
+        assert not bool(out.any())
+        assert torch.equal(mgr.recompose(y), want)
