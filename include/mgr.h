@@ -244,12 +244,11 @@ const char* mgr_last_error(void);
 void mgr_finalize(void);
 
 /* Level steps whose level grid has at most `max_nodes` nodes run together in
- * one single-workgroup launch (the small coarse levels are launch-bound);
- * larger steps use one streaming launch plus one solve launch per
- * dimension.  Default 10000; half of the number holds for level grids with
- * fewer than 32 fibres along a dimension, and the workgroup's LDS bounds it
- * too.  0 disables the combined launch.  Returns the previous value.
- * Process-wide; affects calls enqueued afterwards. */
+ * one single-workgroup launch (the small coarse levels are launch-bound) where
+ * they fit its LDS and are not slower there than in launches of their own;
+ * the other steps use one streaming launch plus one solve launch per
+ * dimension.  Default 10000; 0 disables the combined launch.  Returns the
+ * previous value.  Process-wide; affects calls enqueued afterwards. */
 int64_t mgr_set_tail_max_nodes(int64_t max_nodes);
 
 /* ---- batched decomposition ----------------------------------------------

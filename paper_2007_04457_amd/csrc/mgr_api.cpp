@@ -53,6 +53,7 @@ struct LevelLayout {
     size_t w[3], K[3];
     size_t PT[3];  // P^T as a 5-point row per coarse node (transposed interpolation)
     bool tail;  // the level may join the tail
+    int taps;   // taps that a lane of the tail takes one after the other (tail_taps)
     bool few;   // a dimension has fewer than 32 fibres in the tail's reductions
     size_t L[3], U[3], IP[3], A[3], B[3], ssub[3], ssup[3], sl[3], sip[3], su[3];
     int S[3], dec[3];
@@ -525,6 +526,20 @@ int64_t tail_data_elems(const LevelLayout& ly)
     return V + Vc + (na > 1 ? ly.m[0] * ly.m[1] * ly.mc[2] : 0) + (na > 2 ? ly.m[0] * ly.mc[1] * ly.mc[2] : 0);
 }
 
+// Taps that a lane of the tail takes one after the other in the dot products of
+// dimension d, nt each (tail_dots: a wave takes 64 fibres and four outputs at
+// once, or a lane takes one output where there are fewer than 32 fibres: *few).
+int tail_taps(const LevelLayout& ly, int d, int nt, bool* few)
+{
+    int64_t fibres = 1;
+    for (int e = 0; e < 3; e++) fibres *= (e < d) ? ly.m[e] : (e > d) ? ly.mc[e] : 1;
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    *few = *few || fibres < 32;
+    const int64_t rounds = (fibres >= 32) ? up(up(fibres, 64) * up(ly.mc[d], 4), kTailThreads / 64)
+                                          : up(fibres * ly.mc[d], kTailThreads);
+    return (int)rounds * nt;
+}
+
 std::string plan_key(int device, int dtype, int ndim, const int64_t* shape,
                      const double* const* coords, int nlevels)
 {
@@ -584,12 +599,8 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             ly.ph[d] = (ly.m[d] != act) ? (int)act - 1 : -1;
             ly.tail = ly.tail && ly.m[d] <= kTailMaxSide;
         }
+        ly.taps = 0;
         ly.few = false;
-        for (int d = 0; d < 3; d++) {
-            int64_t fibres = 1;
-            for (int e = 0; e < 3; e++) fibres *= (e < d) ? ly.m[e] : (e > d) ? ly.mc[e] : 1;
-            ly.few = ly.few || (ly.m[d] > 1 && fibres < 32);
-        }
         // every coarser level is in it too
         ly.tail = ly.tail && (k == L - 1 || p.lv[(size_t)(k + 1)].tail) &&
                   (small += tail_data_elems(ly)) * (int64_t)sizeof(T) <= kTailDataBytes;
@@ -659,6 +670,7 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
                 };
                 add(p.tails[(size_t)k], tail_tab, false);
                 if (adjoints) add(p.adj_tails[(size_t)k], adj_tab, true);
+                ly.taps += tail_taps(ly, d, p.tails[(size_t)k].d[d].nt, &ly.few);
             }
             ly.S[d] = sv.S;
             ly.dec[d] = separators_apart(sv.couple, sizeof(T));
@@ -1042,21 +1054,45 @@ int identity_copy(const Plan& p, const void* src, void* dst, hipStream_t st)
 // step whose level grid is small, but no more than kMaxTail steps.
 std::atomic<int64_t> g_tail_nodes{kTailMaxNodes};
 
+// LDS elements of the arrays and of the tables of a tail that starts at level
+// step k0.
+void tail_elems(const Plan& p, int k0, bool adjoint, int* data, int* tab)
+{
+    const std::vector<TailLevel>& tails = adjoint ? p.adj_tails : p.tails;
+    const TailLevel &t0 = tails[(size_t)k0], &t1 = tails.back();
+    // (the tables after the arrays start at a multiple of four elements)
+    *data = (int)align_up((size_t)(t1.cum - t0.cum) + (size_t)tail_data_elems(p.lv.back()), 4);
+    *tab = t1.tab - t0.tab;
+    for (int d = 0; d < 3; d++)
+        if (t1.d[d].m > 1) *tab += tail_tab_len(t1.d[d].m, adjoint ? t1.d[d].m : t1.d[d].mc, t1.d[d].nt);
+}
+
 // First level step handled by the tail kernel: the finest step such that it
-// and every coarser step are small, at most kMaxTail steps.  Up to 10000 nodes
-// (and the LDS) one workgroup is faster than the launches it replaces, and a
-// recomposition that it holds whole forks no stream: 17 x 17 x 33 FP32 decomposed
-// in 27 -> 22 us, recomposed in 48 -> 22, 18 x 18 x 17 28 -> 19 and 47 -> 20.  A
-// dimension of fewer than 32 fibres takes its dot products one output a lane,
-// so such grids stop at half of it (257 x 33: 32 us in launches, 63 so).
-int tail_start(const Plan& p)
+// and every coarser step are small, at most kMaxTail steps, and not slower there
+// than in launches of their own.  Up to 10000 nodes that is so while the tables
+// share the LDS (17 x 17 x 33 FP32 decomposed in 27 -> 22 us, recomposed in
+// 48 -> 22) and a lane's chain of taps stays below some 300 (one step, FP32: 154
+// taps 25.6 us in launches, 20.2 here; 241 20.5, 20.4; 337 19.0, 21.0; 362 19.4,
+// 26.4).  Tables in global memory cost each tap a trip there: up to 150 taps are
+// still no slower (513 x 5 FP64, 134: 23.3, 19.6; 148: 29.9, 28.4), more are
+// (9 x 257, 267: 19.0, 26.2; 33 x 257, 420: 21, 74; 65 x 129, 517: 21, 85).  A
+// recomposition takes more taps, since without streamed steps it forks no stream,
+// and its tables come from global memory at less cost unless fibres are few (9 x
+// 5 x 129 FP64, 272: 31.8, 19.1; 33 x 129, 291: 52 with a fork, 29).
+enum TailUse { TAIL_DEC, TAIL_REC, TAIL_ADJ };
+int tail_start(const Plan& p, TailUse use)
 {
     const int L = p.nlevels;
     const int64_t limit = g_tail_nodes.load();
     int k = L;
     while (k > 0) {
         const LevelLayout& ly = p.lv[(size_t)(k - 1)];
-        if (!ly.tail || ly.m[0] * ly.m[1] * ly.m[2] > (ly.few ? limit / 2 : limit)) break;
+        if (!ly.tail || ly.m[0] * ly.m[1] * ly.m[2] > limit) break;
+        int data, tab;
+        tail_elems(p, k - 1, use == TAIL_ADJ, &data, &tab);
+        const bool lds = (size_t)(data + tab) * p.esize <= (size_t)kTailLdsBytes;
+        const int most = (use == TAIL_REC && (lds || !ly.few)) ? 400 : lds ? 300 : 150;
+        if (ly.taps > most) break;
         k--;
     }
     return k;
@@ -1080,13 +1116,8 @@ TailArgs<T> tail_args(const Plan& p, int k0, const T* src, T* dst, void* wsp = n
     a.Wk = (k0 == 0) ? nullptr : ws + p.Woff[(size_t)k0];
     const std::vector<TailLevel>& tails = adjoint ? p.adj_tails : p.tails;
     a.lv = (const TailLevel*)(base + (adjoint ? p.adj_lv : p.tail_lv)) + k0;
-    const TailLevel &t0 = tails[(size_t)k0], &t1 = tails.back();
-    a.tab = base + (adjoint ? p.adj_tab : p.tail_tab) + t0.tab;
-    // (the tables after the arrays start at a multiple of four elements)
-    a.data_elems = (int)align_up((size_t)(t1.cum - t0.cum) + (size_t)tail_data_elems(p.lv.back()), 4);
-    a.tab_elems = t1.tab - t0.tab;
-    for (int d = 0; d < 3; d++)
-        if (t1.d[d].m > 1) a.tab_elems += tail_tab_len(t1.d[d].m, adjoint ? t1.d[d].m : t1.d[d].mc, t1.d[d].nt);
+    a.tab = base + (adjoint ? p.adj_tab : p.tail_tab) + tails[(size_t)k0].tab;
+    tail_elems(p, k0, adjoint, &a.data_elems, &a.tab_elems);
     return a;
 }
 
@@ -1098,7 +1129,7 @@ int run_decompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     const T* src = (const T*)src_;
     T* dst = (T*)dst_;
     T* ws = (T*)p.ws;
-    const int kt = tail_start(p);
+    const int kt = tail_start(p, TAIL_DEC);
     for (int k = 0; k < kt; k++) {
         const LevelLayout& ly = p.lv[(size_t)k];
         // level grid k: the input, or the previous step's coarse values plus its correction
@@ -1242,7 +1273,11 @@ int run_recompose(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     const T* src = (const T*)src_;
     T* dst = (T*)dst_;
     T* ws = (T*)p.ws;
-    const int kt = tail_start(p);
+    int kt = tail_start(p, TAIL_REC);
+    // up to three steps that share their launches are faster without a tail than
+    // with a fork for it (9 x 257 FP64, two steps: 51 -> 27 us; 17 x 513 FP32,
+    // three: 55 -> 29)
+    if (kt > 0 && L <= 3 && recompose_shared<T>(p, L)) kt = L;
     std::unique_lock<std::mutex> lk(g_aux_mu);
     AuxStream* aux = nullptr;
     // Streams: the caller's (the coarser corrections and interpolations,
@@ -1419,7 +1454,7 @@ int run_adjoint(const Plan& p, const void* src_, void* dst_, hipStream_t st)
     const T* src = (const T*)src_;
     T* dst = (T*)dst_;
     T* ws = (T*)p.ws;
-    const int kt = tail_start(p);
+    const int kt = tail_start(p, TAIL_ADJ);
     if (kt < L) {
         // the small level steps in one workgroup (which has read its input
         // before it writes: in place too)
@@ -1479,7 +1514,7 @@ int run_recompose_adjoint(const Plan& p, const void* src_, void* dst_, hipStream
     const T* src = (const T*)src_;
     T* dst = (T*)dst_;
     T* ws = (T*)p.ws;
-    const int kt = tail_start(p);
+    const int kt = tail_start(p, TAIL_ADJ);
     for (int k = 0; k < kt; k++) {
         const LevelLayout& ly = p.lv[(size_t)k];
         const T* g = (k == 0) ? src : ws + p.Woff[(size_t)k];
@@ -2598,7 +2633,7 @@ int batch_create(int nfields, const int* ndim, const int64_t* const* shapes, con
         Plan* p = pp.get();
         b->plans.push_back(std::move(pp));
         if (p->nlevels == 0) return fail(MGR_ERR_LEVELS, "field " + std::to_string(f) + ": batches need nlevels >= 1");
-        const int kt = tail_start(*p);  // as the per-field path, so results agree bit for bit
+        const int kt = tail_start(*p, TAIL_DEC);  // as the per-field path, so results agree bit for bit
         b->kt.push_back(kt);
         b->wsoff.push_back(ws_total);
         ws_total = align_up(ws_total + p->ws_bytes, 256);
@@ -2993,7 +3028,7 @@ int batch_host_items_t(int nfields, const int* ndim, const int64_t* const* shape
         std::vector<T> host;
         plan_layout<T>(*p, nullptr, false, host);
         p->tables = base;
-        b.kt.push_back(tail_start(*p));
+        b.kt.push_back(tail_start(*p, TAIL_DEC));
         b.wsoff.push_back(ws_total);
         ws_total = align_up(ws_total + p->ws_bytes, 256);
         b.plans.push_back(std::move(p));
