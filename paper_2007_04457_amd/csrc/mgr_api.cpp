@@ -1853,9 +1853,13 @@ int gen_correction(const GenPlan& p, int k, const T* y, hipStream_t st, T** zout
 
 // Plane form of level step k (4-D); plane4_plan: whether every level step of
 // the plan takes it (the planes only shrink from step to step, so the first
-// decides).  It is faster wherever it fits, so that LDS and index ranges are
-// the only limits: 40 x 50 x 60 x 70 FP64 both ways 478 us against 1925 us in
-// the per-stage kernels.
+// decides).  It is faster wherever it fits (40 x 50 x 60 x 70 FP64 both ways 478 us
+// against 1925 us in the per-stage kernels), except over very many tiny planes: a
+// plane is a workgroup and costs some 2.6 ns of the whole chip (FP64 4.5) however
+// few nodes it has, the per-stage kernels 0.07 ns a node (0.077) and some 36 us
+// more in launches.  One step decomposed, per stage and by planes: 400 x 400
+// planes of 3 x 3 nodes FP32 157, 431 us, 5 x 5 333, 438, 6 x 8 613, 440; FP64 5 x 5
+// 354, 752, 9 x 9 1059, 773; 150 x 150 of 4 x 4 FP32 84, 84; 60 x 60 of 3 x 3 64, 33.
 template <typename T>
 Plane4<T> plane4_level(const GenPlan& p, int k)
 {
@@ -1880,7 +1884,9 @@ bool plane4_plan(const GenPlan& p)
     if (p.nd != 4 || p.nlevels < 1) return false;
     for (int d = 0; d < 4; d++)
         if (p.n[d] > (1 << 20)) return false;  // index divisions through floats
-    return p.n[2] * p.n[3] < (1 << 20) && plane4_fits<T>(plane4_level<T>(p, 0));
+    const int64_t nodes = p.n[2] * p.n[3], even = sizeof(T) == 4 ? 38 : 58;
+    if (nodes < even && p.n[0] * p.n[1] * (even - nodes) > 500000) return false;
+    return nodes < (1 << 20) && plane4_fits<T>(plane4_level<T>(p, 0));
 }
 
 // Load vector and solves of level step k of a 4-D grid from a.F (the stencils
