@@ -15,6 +15,7 @@
 // wave-uniform and no per-element division is needed.  Class-packed: the
 // class of an element is the segment its position falls in.
 #include <algorithm>
+#include <type_traits>
 
 #include "mgr_internal.h"
 
@@ -100,8 +101,11 @@ __global__ void __launch_bounds__(kQuantBlock)
 //
 // Class-packed: a workgroup takes kSpan consecutive elements.  Nearly every
 // span lies inside one class, whose bin is then uniform; a span across a
-// boundary looks every element's class up.  kVec elements move per access (one
-// where the pointers are not 16-byte aligned), kBatch accesses in flight.
+// boundary steps every lane's class up from the first.  kVec elements move per access (one
+// where the pointers are not 16-byte aligned), kBatch accesses in flight: four,
+// or one where spans of four would leave the chip a single round of workgroups,
+// all loading and then all storing (dequantised FP32, four and one: 2^23 + 1
+// elements 19.6, 12.9 us, 2^24 + 1 25.4, 20.7; quantised FP64, 2^23 + 1: 18.7, 19.8).
 template <typename T>
 constexpr int quant_vec()
 {
@@ -120,27 +124,28 @@ struct QuantVec<E, 1> {
     };
 };
 
-template <typename T, bool kQuant, int kVec>
+template <typename T, bool kQuant, int kVec, int kBatch>
 __global__ void __launch_bounds__(kQuantBlock)
     k_quant_packed(const T* __restrict__ y, int* __restrict__ q, T* __restrict__ out, QuantArgs a,
                    unsigned long long* counter)
 {
     using VT = typename QuantVec<T, kVec>::V;
     using VI = typename QuantVec<int, kVec>::V;
-    constexpr int64_t kSpan = (int64_t)kQuantBlock * kVec * kQuantBatch;
+    constexpr int64_t kSpan = (int64_t)kQuantBlock * kVec * kBatch;
     const int64_t total = a.off[a.L + 1];
     int clamped = 0;
     for (int64_t e0 = (int64_t)blockIdx.x * kSpan; e0 < total; e0 += (int64_t)gridDim.x * kSpan) {
-        int cls = a.L;  // the finest class holds most elements: scan downwards
-        while (e0 < a.off[cls]) cls--;
+        // class of the span's first element: the starts at or below it, one a lane
+        const int lane = (int)threadIdx.x & 63;
+        const int cls = uni((int)__popcll(__ballot(lane <= a.L && e0 >= a.off[min(lane, a.L)])) - 1);
         const int64_t e1 = min(e0 + kSpan, total);
         if (e1 <= a.off[cls + 1] && e1 - e0 == kSpan) {
             const T b = (T)a.bins[cls];
             const int64_t i0 = e0 + (int64_t)threadIdx.x * kVec;
-            VT v[kQuantBatch];
-            VI c[kQuantBatch];
+            VT v[kBatch];
+            VI c[kBatch];
 #pragma unroll
-            for (int k = 0; k < kQuantBatch; k++) {
+            for (int k = 0; k < kBatch; k++) {
                 const int64_t i = i0 + (int64_t)k * kQuantBlock * kVec;
                 if (kQuant)
                     v[k] = *reinterpret_cast<const VT*>(y + i);
@@ -148,7 +153,7 @@ __global__ void __launch_bounds__(kQuantBlock)
                     c[k] = *reinterpret_cast<const VI*>(q + i);
             }
 #pragma unroll
-            for (int k = 0; k < kQuantBatch; k++) {
+            for (int k = 0; k < kBatch; k++) {
                 const int64_t i = i0 + (int64_t)k * kQuantBlock * kVec;
 #pragma unroll
                 for (int j = 0; j < kVec; j++) {
@@ -163,9 +168,9 @@ __global__ void __launch_bounds__(kQuantBlock)
                     *reinterpret_cast<VT*>(out + i) = v[k];
             }
         } else {
+            int ci = cls;  // (a lane's elements ascend)
             for (int64_t i = e0 + threadIdx.x; i < e1; i += kQuantBlock) {
-                int ci = a.L;
-                while (i < a.off[ci]) ci--;
+                while (i >= a.off[ci + 1]) ci++;
                 const T b = (T)a.bins[ci];
                 if (kQuant)
                     q[i] = code_of(y[i], b, &clamped);
@@ -213,13 +218,23 @@ hipError_t launch_quant(const T* y, int* q, T* out, QuantArgs a, bool quant, uns
         constexpr int kV = quant_vec<T>();
         const uintptr_t where = (uintptr_t)q | (uintptr_t)(quant ? (const void*)y : (const void*)out);
         const bool wide = where % 16 == 0;
-        const int64_t span = (int64_t)kQuantBlock * kQuantBatch * (wide ? kV : 1);
-        const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>((a.off[a.L + 1] + span - 1) / span, (int64_t)1 << 22)));
-        auto launch = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(kQuantBlock), 0, st, y, q, out, a, counter); };
-        if (quant)
-            wide ? launch(k_quant_packed<T, true, kV>) : launch(k_quant_packed<T, true, 1>);
+        auto spans = [&](int batch) {
+            const int64_t span = (int64_t)kQuantBlock * batch * (wide ? kV : 1);
+            return (a.off[a.L + 1] + span - 1) / span;
+        };
+        auto launch = [&](auto batch) {
+            constexpr int B = decltype(batch)::value;
+            const dim3 grid((unsigned)std::max<int64_t>(1, std::min<int64_t>(spans(B), (int64_t)1 << 22)));
+            auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, dim3(kQuantBlock), 0, st, y, q, out, a, counter); };
+            if (quant)
+                wide ? go(k_quant_packed<T, true, kV, B>) : go(k_quant_packed<T, true, 1, B>);
+            else
+                wide ? go(k_quant_packed<T, false, kV, B>) : go(k_quant_packed<T, false, 1, B>);
+        };
+        if (spans(kQuantBatch) < 2048 * kV)
+            launch(std::integral_constant<int, 1>{});
         else
-            wide ? launch(k_quant_packed<T, false, kV>) : launch(k_quant_packed<T, false, 1>);
+            launch(std::integral_constant<int, kQuantBatch>{});
     } else {
         if (quant)
             hipLaunchKernelGGL((k_quant_inplace<T, true>), dim3(blocks), dim3(kQuantBlock), 0, st, y, q, out, a,
