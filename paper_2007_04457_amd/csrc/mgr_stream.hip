@@ -32,20 +32,20 @@
 namespace mgr {
 namespace {
 
-template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen>
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen, bool kWide>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(stream_min_waves<T, kDec, kZ>(), 8)))
 k_stream_level(StreamArgs<T> a)
 {
-    __shared__ LevelSmem<T, kAct0, kAct1, kDec> sm;
-    stream_level_tile<T, kAct0, kAct1, kDec, kZ, kU, wide_tile<T, kDec>(), kGen>(a, remap_xcd((int)blockIdx.x, (int)gridDim.x), sm);
+    __shared__ LevelSmem<T, kAct0, kAct1, kDec, kWide> sm;
+    stream_level_tile<T, kAct0, kAct1, kDec, kZ, kU, kWide, kGen>(a, remap_xcd((int)blockIdx.x, (int)gridDim.x), sm);
 }
 
 // Tiles and plane chunks of one level step (filled into a); returns its
 // workgroup count.
-template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen>
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen, bool kWide = wide_tile<T, kDec>()>
 int level_cfg(StreamArgs<T>& a)
 {
-    using G = LevelGeom<kAct1, cols_per_lane<T>(), wide_tile<T, kDec>()>;
+    using G = LevelGeom<kAct1, cols_per_lane<T>(), kWide>;
     const int c0 = (int)a.fv.n[0], c1 = (int)a.fv.n[1], c2 = (int)a.fv.n[2];
     a.nt1 = kAct1 ? (c1 + G::kT1 - 1) / G::kT1 : 1;
     a.nt2 = (c2 + G::kT2 - 1) / G::kT2;
@@ -55,7 +55,7 @@ int level_cfg(StreamArgs<T>& a)
         // One round of resident workgroups: a second, partial round would
         // run latency-bound on a mostly idle chip.
         static int occ = 0;
-        const int slots = resident_per_cu(k_stream_level<T, kAct0, kAct1, kDec, kZ, kU, kGen>, occ) * device_cu_count();
+        const int slots = resident_per_cu(k_stream_level<T, kAct0, kAct1, kDec, kZ, kU, kGen, kWide>, occ) * device_cu_count();
         const int nch = std::max(1, slots / tiles);
         chunk = (c0 + nch - 1) / nch;
         // Single rows (2-D): short chunks, several rounds of workgroups, keep
@@ -74,13 +74,25 @@ int level_cfg(StreamArgs<T>& a)
     return tiles * a.nch;
 }
 
+template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen, bool kWide>
+hipError_t launch_level_tile(StreamArgs<T> a, hipStream_t st)
+{
+    const int blocks = level_cfg<T, kAct0, kAct1, kDec, kZ, kU, kGen, kWide>(a);
+    hipLaunchKernelGGL((k_stream_level<T, kAct0, kAct1, kDec, kZ, kU, kGen, kWide>), dim3((unsigned)blocks), dim3(kThreads),
+                       0, st, a);
+    return hipGetLastError();
+}
+
 template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool kGen>
 hipError_t launch_level_cfg(StreamArgs<T> a, hipStream_t st)
 {
-    const int blocks = level_cfg<T, kAct0, kAct1, kDec, kZ, kU, kGen>(a);
-    hipLaunchKernelGGL((k_stream_level<T, kAct0, kAct1, kDec, kZ, kU, kGen>), dim3((unsigned)blocks), dim3(kThreads), 0,
-                       st, a);
-    return hipGetLastError();
+    // any-length grids of short rows: a narrow tile holds them in half the rows
+    // a wave (one step FP64, wide, narrow, per stage before: 30000 x 3 x 4 342, 273,
+    // 267 us; 100000 x 20 x 6 1707, 1178, 1491)
+    if constexpr (kAct0 && kAct1 && kGen && wide_tile<T, kDec>())
+        if (a.fv.n[2] <= LevelGeom<kAct1, cols_per_lane<T>(), false>::kT2)
+            return launch_level_tile<T, kAct0, kAct1, kDec, kZ, kU, kGen, false>(a, st);
+    return launch_level_tile<T, kAct0, kAct1, kDec, kZ, kU, kGen, wide_tile<T, kDec>()>(a, st);
 }
 
 // Load-vector passes of several level steps in one grid: block b belongs to
