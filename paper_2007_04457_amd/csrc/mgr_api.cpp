@@ -196,8 +196,11 @@ std::vector<double> axis_positions(int64_t n, const double* x)
     if (!x) {
         for (int64_t i = 0; i < n; i++) X[(size_t)i] = (double)i;
     } else {
-        const double sc = std::exp2(std::round(std::log2((double)(n - 1) / (x[n - 1] - x[0]))));
-        for (int64_t i = 0; i < n; i++) X[(size_t)i] = (x[i] - x[0]) * sc;
+        // (through the exponent: for spacings near the smallest double the factor
+        // itself would overflow)
+        const double span = x[n - 1] - x[0];
+        const int e = std::isfinite(span) ? (int)std::lround(std::log2((double)(n - 1)) - std::log2(span)) : 0;
+        for (int64_t i = 0; i < n; i++) X[(size_t)i] = std::ldexp(x[i] - x[0], e);
     }
     return X;
 }
