@@ -1927,8 +1927,10 @@ int plane4_correction(const GenPlan& p, int k, const Plane4<T>& a, T* F, hipStre
         else if ((rc = solve(3)) || (rc = solve(2)))
             return rc;
     }
-    MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_cols<T>(F, a, t[1], t[0], st, &done); }), "solve launch");
-    if (!done && ((rc = solve(1)) || (rc = solve(0)))) return rc;
+    if (solve_cols_fits<T>(a, t[1], t[0]))
+        MGR_TRY(timed(KC_SOLVE, k, st, [&] { return launch_solve_cols<T>(F, a, t[1], t[0], st); }), "solve launch");
+    else if ((rc = solve(1)) || (rc = solve(0)))
+        return rc;
     return MGR_OK;
 }
 

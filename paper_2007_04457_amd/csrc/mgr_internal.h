@@ -591,11 +591,12 @@ hipError_t launch_plane4(const Plane4<T>& a, int mode, hipStream_t st);
 template <typename T>
 hipError_t launch_mass_plane(const T* in, T* out, const Plane4<T>& a, const SolveTables<T>& t3, const SolveTables<T>& t2,
                              hipStream_t st, bool* done);
-// Solves along dims 1 and 0 of F, where their tasks fit a workgroup (*done; else
-// nothing is launched).
+// Solves along dims 1 and 0 of F, and whether their tasks fit a workgroup
+// (launch_solve_cols launches nothing where they do not).
 template <typename T>
-hipError_t launch_solve_cols(T* F, const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0, hipStream_t st,
-                             bool* done);
+bool solve_cols_fits(const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0);
+template <typename T>
+hipError_t launch_solve_cols(T* F, const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0, hipStream_t st);
 
 // Partitioned solve of every fibre of length n along the middle index of a
 // packed (outer, n, inner) box; src and Yb as for launch_solve_partitioned.

@@ -453,15 +453,24 @@ hipError_t launch_mass_plane(const T* in, T* out, const Plane4<T>& a, const Solv
 }
 
 template <typename T>
-hipError_t launch_solve_cols(T* F, const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0, hipStream_t st,
-                             bool* done_)
+int solve_cols_lanes(const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0)
+{
+    const int64_t n0 = a.mc[0], n1 = a.mc[1];
+    if (n0 * n1 > device_cu_count()) return 0;
+    return solve4_lanes<T>(t1, n1, n0 * kCols<T>, t0, n0, n1 * kCols<T>, n0 * n1 * kCols<T>);
+}
+template <typename T>
+bool solve_cols_fits(const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0)
+{
+    return solve_cols_lanes<T>(a, t1, t0) > 0;
+}
+
+template <typename T>
+hipError_t launch_solve_cols(T* F, const Plane4<T>& a, const SolveTables<T>& t1, const SolveTables<T>& t0, hipStream_t st)
 {
     const int64_t n0 = a.mc[0], n1 = a.mc[1], nodes = n0 * n1 * kCols<T>;
-    const int lanes = a.mc[0] * a.mc[1] > device_cu_count()
-                          ? 0
-                          : solve4_lanes<T>(t1, n1, n0 * kCols<T>, t0, n0, n1 * kCols<T>, nodes);
-    *done_ = lanes > 0;
-    if (lanes == 0) return hipSuccess;
+    const int lanes = solve_cols_lanes<T>(a, t1, t0);
+    if (lanes == 0) return hipErrorNotSupported;
     static bool done[64] = {};
     const size_t bytes = solve4_bytes<T>(nodes);
     const hipError_t e = allow_lds4(k_solve_cols<T>, bytes, done);
@@ -485,8 +494,10 @@ template hipError_t launch_mass_plane<float>(const float*, float*, const Plane4<
 template hipError_t launch_mass_plane<double>(const double*, double*, const Plane4<double>&, const SolveTables<double>&,
                                               const SolveTables<double>&, hipStream_t, bool*);
 template hipError_t launch_solve_cols<float>(float*, const Plane4<float>&, const SolveTables<float>&,
-                                             const SolveTables<float>&, hipStream_t, bool*);
+                                             const SolveTables<float>&, hipStream_t);
+template bool solve_cols_fits<float>(const Plane4<float>&, const SolveTables<float>&, const SolveTables<float>&);
 template hipError_t launch_solve_cols<double>(double*, const Plane4<double>&, const SolveTables<double>&,
-                                              const SolveTables<double>&, hipStream_t, bool*);
+                                              const SolveTables<double>&, hipStream_t);
+template bool solve_cols_fits<double>(const Plane4<double>&, const SolveTables<double>&, const SolveTables<double>&);
 
 }  // namespace mgr

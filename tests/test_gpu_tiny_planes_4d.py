@@ -40,3 +40,17 @@ def test_matches_oracle(shape, dt):
     z = yr.to(DEV)
     mgr.mgr_recompose(z, z, coords, 1)
     assert torch.equal(z, r)
+
+
+@pytest.mark.parametrize("shape,launches", [((40, 50, 5, 5), 3), ((20, 20, 5, 5), 1)], ids=["planes-alone", "together"])
+def test_timing_counts_launches_made(shape, launches):
+    """Solve launches of the finest step: the planes' and one for each of dims 1
+    and 0 where there are more planes than CUs; otherwise the planes are solved
+    with their load vector and dims 1 and 0 in one launch."""
+    x = torch.from_numpy(synth.sinusoid_field(shape, 101)[0]).to(DEV)
+    mgr.decompose(x, None, 1)
+    mgr.mgr_timing_enable("solve", 0)
+    mgr.decompose(x, None, 1)
+    n = mgr.mgr_timing_read()[1]
+    mgr.mgr_timing_disable()
+    assert n == launches
