@@ -443,27 +443,41 @@ SolveTab build_solve(const std::vector<double>& yc)
     return t;
 }
 
-// B = M_{l-1}^{-1} R M_l of a level dimension, mc x m.
-std::vector<double> tail_matrix(const std::vector<double>& K, const SolveTab& sv, int64_t mc)
+// B = M_{l-1}^{-1} R M_l of a level dimension, mc x m; zero further than *band
+// coarse nodes from the diagonal j = 2 i, where its entries stay below 2^-90 of
+// their row's.
+std::vector<double> tail_matrix(const std::vector<double>& K, const SolveTab& sv, int64_t mc, int64_t* band)
 {
     const int64_t m = 2 * mc - 1;
-    std::vector<double> lf((size_t)mc, 0.0), ip((size_t)mc, 0.0), x((size_t)mc), R((size_t)(mc * m), 0.0);
+    std::vector<double> lf((size_t)mc, 0.0), ip((size_t)mc, 0.0), x((size_t)mc), w((size_t)mc, 0.0),
+        R((size_t)(mc * m), 0.0);
     double den = 0.0;
     for (int64_t i = 0; i < mc; i++) {
         const double diag = 2.0 * (sv.sub[(size_t)i] + sv.sup[(size_t)i]);
         if (i > 0) lf[(size_t)i] = sv.sub[(size_t)i] / den;
         den = diag - (i > 0 ? lf[(size_t)i] * sv.sup[(size_t)(i - 1)] : 0.0);
         ip[(size_t)i] = 1.0 / den;
+        for (int t = 0; t < 5; t++) w[(size_t)i] += std::fabs(K[(size_t)(5 * i + t)]);
     }
+    *band = 0;
     for (int64_t i = 0; i < mc; i++) {
         // M x = e_i (M is symmetric: x is also row i of its inverse)
-        std::fill(x.begin(), x.end(), 0.0);
+        const double least = 0x1p-90 * ip[(size_t)i] * w[(size_t)i];
         x[(size_t)i] = 1.0;
-        for (int64_t k = i + 1; k < mc; k++) x[(size_t)k] = -lf[(size_t)k] * x[(size_t)(k - 1)];
-        for (int64_t k = mc - 1; k >= 0; k--)
-            x[(size_t)k] = (x[(size_t)k] - (k < mc - 1 ? sv.sup[(size_t)k] * x[(size_t)(k + 1)] : 0.0)) * ip[(size_t)k];
+        int64_t hi = i, lo = i;
+        while (hi + 1 < mc) {
+            x[(size_t)(hi + 1)] = -lf[(size_t)(hi + 1)] * x[(size_t)hi];
+            hi++;
+            if (std::fabs(x[(size_t)hi]) * ip[(size_t)hi] * w[(size_t)hi] < least) break;
+        }
+        for (int64_t k = hi; k >= 0; k--) {
+            x[(size_t)k] = ((k >= i ? x[(size_t)k] : 0.0) - (k < hi ? sv.sup[(size_t)k] * x[(size_t)(k + 1)] : 0.0)) * ip[(size_t)k];
+            lo = std::min(lo, k);
+            if (k < i && std::fabs(x[(size_t)k]) * w[(size_t)k] < least) break;
+        }
+        *band = std::max({*band, hi - i, i - lo});
         double* row = &R[(size_t)(i * m)];
-        for (int64_t k = 0; k < mc; k++)
+        for (int64_t k = lo; k <= hi; k++)
             for (int t = -2; t <= 2; t++) {
                 const int64_t j = 2 * k + t;
                 if (j >= 0 && j < m) row[j] += x[(size_t)k] * K[(size_t)(5 * k + t + 2)];
@@ -481,16 +495,19 @@ struct TailTabHost {
     std::vector<double> B;
     int nt = 0, off = 0;
 };
-TailTabHost pack_tail(const std::vector<double>& R, int64_t mc, size_t esize, bool columns)
+TailTabHost pack_tail(const std::vector<double>& R, int64_t mc, int64_t band, size_t esize, bool columns)
 {
     const int64_t m = 2 * mc - 1;
     const double tol = (esize == 8) ? 0x1p-58 : 0x1p-30;
     auto at = [&](int64_t i, int64_t j) { return R[(size_t)(i * m + j)]; };
+    const int64_t far = 2 * band + 2;  // |2 i - j| of the furthest entries
     int64_t h = 0;
     for (int64_t q = 0; q < (columns ? m : mc); q++) {
         double sum = 0.0, out = 0.0;
-        for (int64_t r = 0; r < (columns ? mc : m); r++) sum += std::fabs(columns ? at(r, q) : at(q, r));
-        int64_t d = m;
+        const int64_t r0 = columns ? (q - far) / 2 : 2 * q - far, r1 = columns ? (q + far) / 2 : 2 * q + far;
+        for (int64_t r = std::max<int64_t>(r0, 0); r <= std::min(r1, (columns ? mc : m) - 1); r++)
+            sum += std::fabs(columns ? at(r, q) : at(q, r));
+        int64_t d = std::min(m, far);
         while (d > h) {  // distance d and beyond left out
             double w = 0.0;
             if (!columns) {
@@ -658,10 +675,11 @@ void plan_layout(Plan& p, const double* const* coords, bool dec_only, std::vecto
             SolveTab sv = build_solve(yc);
             if (ly.tail) {
                 // weight pairs and B of the level's tail tables
-                const std::vector<double> R = tail_matrix(t.K, sv, ly.mc[d]);
+                int64_t band = 0;
+                const std::vector<double> R = tail_matrix(t.K, sv, ly.mc[d], &band);
                 auto add = [&](TailLevel& tl, std::vector<double>& tab, bool columns) {
                     TailDim& td = tl.d[d];
-                    const TailTabHost tt = pack_tail(R, ly.mc[d], sizeof(T), columns);
+                    const TailTabHost tt = pack_tail(R, ly.mc[d], band, sizeof(T), columns);
                     td.nt = tt.nt;
                     td.off = tt.off;
                     if (tl.tab < 0) tl.tab = (int)tab.size();
