@@ -20,10 +20,11 @@
  *    coarse nodes.  The full decomposition stops when the shortest level grid
  *    has 3 nodes (L = min_d ceil(log2(n_d - 1)) - 1), and 0..L+1 level steps
  *    are accepted.  A node's class is L minus the finest level k <= L whose
- *    grid holds it in every dimension.  (4-D shapes and planes of 2 GiB or
- *    more run per-stage kernels without the per-plane addressing limit, the
- *    others the fused kernels of the 2^k + 1 grids.)  The other entry points
- *    refuse these shapes with MGR_ERR_SHAPE.
+ *    grid holds it in every dimension.  (Shapes of up to three dimensions and
+ *    planes below 2 GiB run the fused kernels of the 2^k + 1 grids, most 4-D
+ *    shapes whose planes of the last two dimensions fit a workgroup's LDS kernels
+ *    of their own, the others per-stage kernels without an addressing limit.)  The
+ *    other entry points refuse these shapes with MGR_ERR_SHAPE.
  *  - `coords` describes node positions (nonuniform structured grids,
  *    Sec. II-A): NULL, or coords[d] == NULL, means uniform spacing along d;
  *    otherwise coords[d] is a HOST array of shape[d] strictly increasing
@@ -250,6 +251,11 @@ void mgr_finalize(void);
  * dimension.  Default 10000; 0 disables the combined launch.  Returns the
  * previous value.  Process-wide; affects calls enqueued afterwards. */
 int64_t mgr_set_tail_max_nodes(int64_t max_nodes);
+
+/* For tests: while on, the calling thread's decompositions and recompositions
+ * of general grids run the per-stage kernels whatever their shape.  Off by
+ * default; returns the previous setting. */
+int mgr_set_per_stage(int on);
 
 /* ---- batched decomposition ----------------------------------------------
  * Many independent fields (any mix of shapes, dimensionalities, coordinates

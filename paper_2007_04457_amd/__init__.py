@@ -293,6 +293,12 @@ def mgr_set_tail_max_nodes(max_nodes):
     return _lib.load().mgr_set_tail_max_nodes(int(max_nodes))
 
 
+def mgr_set_per_stage(on):
+    """For tests: this thread's calls on general grids run the per-stage
+    kernels whatever their shape; returns the previous setting."""
+    return bool(_lib.load().mgr_set_per_stage(int(bool(on))))
+
+
 def mgr_finalize():
     _lib.load().mgr_finalize()
 

@@ -1597,8 +1597,7 @@ int run_recompose_adjoint(const Plan& p, const void* src_, void* dst_, hipStream
 // node: the level-k grid of a dimension of n nodes has ceil((n - 1) / 2^k) + 1
 // nodes, and a level grid of m nodes has m / 2 + 1 coarse nodes (its even
 // positions and its last one).  For 2^k + 1 sizes this is the usual nested
-// grid, which the fused path handles; the general path (mgr_general.hip)
-// runs any other shape, and every shape of four dimensions.
+// grid.  Which kernels run a shape: fused_general, plane4_plan.
 // Level steps after which a dimension of n >= 3 nodes is down to two nodes.
 int gen_steps_to_two(int64_t n)
 {
@@ -1648,15 +1647,20 @@ int validate_general(int dtype, int ndim, const int64_t* shape, const double* co
     return MGR_OK;
 }
 
+// Calls of this thread on general grids run the per-stage kernels
+// (mgr_set_per_stage).
+thread_local bool t_per_stage = false;
+
 // General shapes that run the fused kernels (phantom nodes, View3): one to
 // three dimensions within the kernels' 32-bit offsets (a plane below 2 GiB, a
-// plane stride of the coarsest level grid below 2^32 elements).  The rest,
-// every 4-D shape among them, run the per-stage kernels.  One pass per level
-// step instead of a pass per stage and dimension, and no index divisions:
-// 500^3 FP32 decomposed and recomposed 12.00 -> 1.40 ms.
+// plane stride of the coarsest level grid below 2^32 elements).  Of the rest,
+// 4-D shapes run the plane kernels where plane4_plan holds, all others the
+// per-stage kernels.  One pass per level step instead of a pass per stage and
+// dimension, and no index divisions: 500^3 FP32 decomposed and recomposed
+// 12.00 -> 1.40 ms.
 bool fused_general(int dtype, int ndim, const int64_t* shape, int nlevels)
 {
-    if (ndim > kMaxDim) return false;
+    if (ndim > kMaxDim || t_per_stage) return false;
     const int64_t esz = (dtype == MGR_F64) ? 8 : 4;
     const int64_t plane = (ndim == 3) ? shape[1] * shape[2] : shape[ndim - 1];
     if (plane > ((int64_t)1 << 31) / esz - 1) return false;
@@ -1902,7 +1906,7 @@ Plane4<T> plane4_level(const GenPlan& p, int k)
 template <typename T>
 bool plane4_plan(const GenPlan& p)
 {
-    if (p.nd != 4 || p.nlevels < 1) return false;
+    if (p.nd != 4 || p.nlevels < 1 || t_per_stage) return false;
     for (int d = 0; d < 4; d++)
         if (p.n[d] > (1 << 20)) return false;  // index divisions through floats
     const int64_t nodes = p.n[2] * p.n[3], even = sizeof(T) == 4 ? 38 : 58;
@@ -3443,6 +3447,13 @@ void mgr_finalize(void)
     }
     g_tm.ev.clear();
     g_tm.on = false;
+}
+
+int mgr_set_per_stage(int on)
+{
+    const int prev = t_per_stage ? 1 : 0;
+    t_per_stage = on != 0;
+    return prev;
 }
 
 int64_t mgr_set_tail_max_nodes(int64_t max_nodes)
