@@ -105,7 +105,7 @@ __global__ void __launch_bounds__(kQuantBlock)
 // where the pointers are not 16-byte aligned), kBatch accesses in flight: four,
 // or one where spans of four would leave the chip a single round of workgroups,
 // all loading and then all storing (dequantised FP32, four and one: 2^23 + 1
-// elements 19.6, 12.9 us, 2^24 + 1 25.4, 20.7; quantised FP64, 2^23 + 1: 18.7, 19.8).
+// elements 19.6, 12.9 us, 2^24 + 1 25.4, 20.7).
 template <typename T>
 constexpr int quant_vec()
 {
@@ -135,9 +135,12 @@ __global__ void __launch_bounds__(kQuantBlock)
     const int64_t total = a.off[a.L + 1];
     int clamped = 0;
     for (int64_t e0 = (int64_t)blockIdx.x * kSpan; e0 < total; e0 += (int64_t)gridDim.x * kSpan) {
-        // class of the span's first element: the starts at or below it, one a lane
+        // class of the span's first element: among the finest, which hold most; else
+        // from the starts at or below it, one a lane
         const int lane = (int)threadIdx.x & 63;
-        const int cls = uni((int)__popcll(__ballot(lane <= a.L && e0 >= a.off[min(lane, a.L)])) - 1);
+        int cls = a.L;
+        for (int k = 0; k < 4 && e0 < a.off[cls]; k++) cls--;
+        if (e0 < a.off[cls]) cls = uni((int)__popcll(__ballot(lane < a.L && e0 >= a.off[min(lane, a.L)])) - 1);
         const int64_t e1 = min(e0 + kSpan, total);
         if (e1 <= a.off[cls + 1] && e1 - e0 == kSpan) {
             const T b = (T)a.bins[cls];
@@ -231,7 +234,7 @@ hipError_t launch_quant(const T* y, int* q, T* out, QuantArgs a, bool quant, uns
             else
                 wide ? go(k_quant_packed<T, false, kV, B>) : go(k_quant_packed<T, false, 1, B>);
         };
-        if (spans(kQuantBatch) < 2048 * kV)
+        if (spans(kQuantBatch) < 8192)
             launch(std::integral_constant<int, 1>{});
         else
             launch(std::integral_constant<int, kQuantBatch>{});

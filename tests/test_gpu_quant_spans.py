@@ -13,7 +13,7 @@ import paper_2007_04457_amd as mgr
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
-CASES = [((65, 513, 1025), torch.float32, 0), ((4097, 2049), torch.float64, 0), ((2049, 2049), torch.float64, 0),
+CASES = [((65, 513, 1025), torch.float32, 0), ((4097, 4097), torch.float64, 0), ((4097, 2049), torch.float64, 0), ((2049, 2049), torch.float64, 0),
          ((2049, 2049), torch.float32, 1), ((2**20 + 1,), torch.float32, 0), ((2**20 + 1,), torch.float64, 1)]
 
 
