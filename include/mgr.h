@@ -6,9 +6,9 @@
  * Data model (shared by every entry point)
  * -----------------------------------------
  *  - A field is a C-order array of `prod(shape)` elements of type `dtype`
- *    in device memory (HBM), `ndim` in 1..3, `shape[d] = 2^k_d + 1` with
- *    k_d >= 1 (the structured grids of Sec. II-A; shape[ndim-1] is the
- *    contiguous dimension).  One plane of the array (the contiguous row in
+ *    in device memory (HBM), `ndim` in 1..3 (general grids, below: 1..4),
+ *    `shape[d] = 2^k_d + 1` with k_d >= 1 (the structured grids of
+ *    Sec. II-A; shape[ndim-1] is the contiguous dimension).  One plane of the array (the contiguous row in
  *    1-D and 2-D, shape[1] * shape[2] elements in 3-D) must stay below 2 GiB:
  *    the kernels address within a plane with 32-bit byte offsets.
  *  - General grids: mgr_decompose, mgr_recompose, mgr_prepare,
@@ -43,6 +43,9 @@
  *  - `stream` is a hipStream_t (NULL = the default stream).  Every GPU
  *    entry point only enqueues work on it and returns; results are ready
  *    when the stream reaches that point.
+ *  - Values that are not finite make the outputs that depend on them beyond the
+ *    working precision not finite; where a solve's response to them has decayed
+ *    below it (some 60 nodes on uniform grids) outputs may stay finite.
  *  - `src` and `dst` are caller-owned device pointers of the same size;
  *    dst == src is allowed (in place); other overlaps are not.
  *  - The library owns its tables and workspace (device memory, cached per

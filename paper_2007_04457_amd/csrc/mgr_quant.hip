@@ -101,11 +101,11 @@ __global__ void __launch_bounds__(kQuantBlock)
 //
 // Class-packed: a workgroup takes kSpan consecutive elements.  Nearly every
 // span lies inside one class, whose bin is then uniform; a span across a
-// boundary steps every lane's class up from the first.  kVec elements move per access (one
-// where the pointers are not 16-byte aligned), kBatch accesses in flight: four,
-// or one where spans of four would leave the chip a single round of workgroups,
-// all loading and then all storing (dequantised FP32, four and one: 2^23 + 1
-// elements 19.6, 12.9 us, 2^24 + 1 25.4, 20.7).
+// boundary steps every lane's class up from the first.  kVec elements move per
+// access (one where the pointers are not 16-byte aligned), kBatch accesses in
+// flight: four, or one where spans of four would leave the chip a single round
+// of workgroups, all loading and then all storing (dequantised FP32, four and
+// one: 2^23 + 1 elements 19.6, 12.9 us, 2^24 + 1 25.4, 20.7).
 template <typename T>
 constexpr int quant_vec()
 {
