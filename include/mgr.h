@@ -20,8 +20,8 @@
  *    coarse nodes.  The full decomposition stops when the shortest level grid
  *    has 3 nodes (L = min_d ceil(log2(n_d - 1)) - 1), and 0..L+1 level steps
  *    are accepted.  A node's class is L minus the finest level k <= L whose
- *    grid holds it in every dimension.  (Shapes of up to three dimensions and
- *    planes below 2 GiB run the fused kernels of the 2^k + 1 grids, most 4-D
+ *    grid holds it in every dimension.  (Most shapes of up to three dimensions
+ *    with planes below 2 GiB run the fused kernels of the 2^k + 1 grids, most 4-D
  *    shapes whose planes of the last two dimensions fit a workgroup's LDS kernels
  *    of their own, the others per-stage kernels without an addressing limit.)  The
  *    other entry points refuse these shapes with MGR_ERR_SHAPE.

@@ -1658,12 +1658,22 @@ thread_local bool t_per_stage = false;
 // per-stage kernels.  One pass per level step instead of a pass per stage and
 // dimension, and no index divisions: 500^3 FP32 decomposed and recomposed
 // 12.00 -> 1.40 ms.
+//
+// Except over very many tiny planes (3-D): the streaming tile takes a plane in
+// some 8 ns of the whole chip (FP32 3.7) however few nodes it has, the per-stage
+// kernels 0.055 ns a node (0.045) and some 22 us more in launches a level step.
+// One step decomposed, fused and per stage: 30000 planes of 3 x 4 nodes FP64 273,
+// 75 us, of 3 x 30 278, 192, 300000 of 9 x 10 2538, 1519, 1000 of 3 x 4 36, 56, 5000 of
+// 9 x 10 76, 76; FP32 30000 of 3 x 4 144, 68, of 3 x 30 158, 170, 10000 of 6 x 8 71, 70;
+// two steps, 7000 of 9 x 10 FP64 recomposed 130, 151.
 bool fused_general(int dtype, int ndim, const int64_t* shape, int nlevels)
 {
     if (ndim > kMaxDim || t_per_stage) return false;
     const int64_t esz = (dtype == MGR_F64) ? 8 : 4;
     const int64_t plane = (ndim == 3) ? shape[1] * shape[2] : shape[ndim - 1];
     if (plane > ((int64_t)1 << 31) / esz - 1) return false;
+    const int64_t even = (dtype == MGR_F64) ? 100 : 70;
+    if (ndim == 3 && nlevels > 0 && plane < even && shape[0] * (even - plane) > (int64_t)400000 * nlevels) return false;
     return ndim == 1 || (nlevels < 32 && (plane << nlevels) < ((int64_t)1 << 32));
 }
 

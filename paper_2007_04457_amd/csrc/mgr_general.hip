@@ -1,8 +1,8 @@
 // General tensor grids: 1 to 4 dimensions of any size >= 3 per dimension, one
 // stage per kernel.  Runs the 4-D shapes whose planes of the last two
-// dimensions exceed the LDS or are tiny and very many (the others:
-// mgr_plane4.hip) and the shapes past the fused kernels' 32-bit offsets; other
-// any-length grids of 1 to 3 dimensions run the fused kernels (View3 in
+// dimensions exceed the LDS (the others: mgr_plane4.hip), 3-D and 4-D shapes of
+// very many tiny planes, and the shapes past the fused kernels' 32-bit offsets;
+// other any-length grids of 1 to 3 dimensions run the fused kernels (View3 in
 // mgr_internal.h).
 //
 // The paper's grids have 2^k + 1 nodes per dimension; for other sizes the

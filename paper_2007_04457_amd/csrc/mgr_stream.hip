@@ -87,8 +87,7 @@ template <typename T, bool kAct0, bool kAct1, bool kDec, bool kZ, bool kU, bool 
 hipError_t launch_level_cfg(StreamArgs<T> a, hipStream_t st)
 {
     // any-length grids of short rows: a narrow tile holds them in half the rows
-    // a wave (one step FP64, wide, narrow, per stage before: 30000 x 3 x 4 342, 273,
-    // 267 us; 100000 x 20 x 6 1707, 1178, 1491)
+    // a wave (one step FP64, wide, narrow: 100000 x 20 x 6 1707, 1178 us)
     if constexpr (kAct0 && kAct1 && kGen && wide_tile<T, kDec>())
         if (a.fv.n[2] <= LevelGeom<kAct1, cols_per_lane<T>(), false>::kT2)
             return launch_level_tile<T, kAct0, kAct1, kDec, kZ, kU, kGen, false>(a, st);
